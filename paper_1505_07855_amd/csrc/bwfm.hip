@@ -1464,8 +1464,20 @@ __device__ __forceinline__ void persistent_body(const DevIndex &ix, const Params
     uint4 *const own_cand = c.cand;
     uint8_t *const own_pd = c.pd;
 
+    // A batch of fewer reads than the grid has lanes is spread evenly: each
+    // wave takes `cap` reads at once, at its first refill, and its other lanes
+    // help from the start (the endgame's sharing), so that every wave of the
+    // device works on it.  With 64 reads to a wave, 60 k reads ran on 940 of
+    // 4096 waves, each 1.7 k iterations long.  (25 k reads of 36 bases, every
+    // placement within 2 mismatches: 9.6 -> 2.3 ms; 30 k pairs of 100 bases,
+    // aligned, paired and rescued: 16.0 -> 8.4 ms; batches of more reads than
+    // lanes take 64 at a time as before and keep their time.)  Long reads
+    // (DP) keep 64 to a wave: their trees are far larger than a wave and the
+    // split rounds spread them over the device.
+    const uint32_t n_waves = gridDim.x * (blockDim.x >> 6);
+    const uint32_t cap = DP ? 64u : min((n_reads + n_waves - 1) / n_waves, 64u);
     int phase = PZ_IDLE;
-    bool exhausted = false;
+    bool exhausted = (uint32_t)lane >= cap;
     bool endgame = false;  // wave-uniform: the batch's reads are all taken
     int ow = lane;         // owner lane of the read this lane works on
     uint32_t r = 0;
@@ -1554,6 +1566,7 @@ __device__ __forceinline__ void persistent_body(const DevIndex &ix, const Params
                     }
                 }
             }
+            if (cap < 64) exhausted = true;
         }
         if (__ballot(phase != PZ_IDLE) == 0) {
             if (__ballot(!exhausted) == 0) break;
@@ -2811,6 +2824,14 @@ uint32_t persistent_lanes(uint32_t bs, size_t lds, int waves_per_simd, bool dp =
     return (uint32_t)cus * (uint32_t)per_cu * bs;
 }
 
+// Lanes of the batched form for n reads: the lanes that fit, but no more
+// than a wave per read (a wave's other lanes help its reads), or one per read
+// for long reads (dpre), which are not spread.
+inline uint32_t batched_lanes(uint32_t fit, uint32_t n, uint32_t bs, bool dpre) {
+    const uint64_t want = ((std::max<uint64_t>(n, 1) * (dpre ? 1 : 64) + bs - 1) / bs) * bs;
+    return (uint32_t)std::min<uint64_t>(fit, want);
+}
+
 // LDS bytes per lane for reads up to mlen bases (an odd number of dwords,
 // which spreads the lanes' rows over the banks) and the largest block that
 // keeps a block's LDS (rows plus the per-wave sharing blocks) within 64 KB.
@@ -2935,7 +2956,7 @@ int align_impl(bwfm_index *ix, bwfm::Workspace &ws, const bwfm_reads *rd, const 
     const size_t lds = (size_t)bs * lstride + (plain ? 0 : (bs / 64) * sizeof(WaveShare));
     const uint32_t nr_up = ((std::max<uint32_t>(n, 1) + bs - 1) / bs) * bs;
     const uint32_t lanes =
-        plain ? nr_up : std::min<uint32_t>(persistent_lanes<LW>(bs, lds, p->waves_per_simd, dpre), nr_up);
+        plain ? nr_up : batched_lanes(persistent_lanes<LW>(bs, lds, p->waves_per_simd, dpre), n, bs, dpre);
     const uint32_t stack_cap = plain ? std::min<uint32_t>(worst_stack, PLAIN_STACK) : worst_stack;
     // the task rounds' grid shares the lane buffers: room for the larger one
     const uint32_t tlanes = sbud ? task_lanes<LW>(nr_up, lanes) : 0u;
@@ -3754,12 +3775,12 @@ extern "C" int bwfm_pipeline_create(const bwfm_index *cix, const bwfm_aln_params
     pl->lds = (size_t)pl->bs * pl->lstride + (plain ? 0 : (pl->bs / 64) * sizeof(WaveShare));
     const uint32_t nr_up = ((nmax + pl->bs - 1) / pl->bs) * pl->bs;
     pl->lanes = plain ? nr_up
-                      : std::min<uint32_t>(by_layout(ix,
-                                                     [&](auto lw) {
-                                                         return persistent_lanes<decltype(lw)::value>(
-                                                             pl->bs, pl->lds, ap->waves_per_simd, dpre);
-                                                     }),
-                                           nr_up);
+                      : batched_lanes(by_layout(ix,
+                                                [&](auto lw) {
+                                                    return persistent_lanes<decltype(lw)::value>(
+                                                        pl->bs, pl->lds, ap->waves_per_simd, dpre);
+                                                }),
+                                      nmax, pl->bs, dpre);
     pl->stack_cap = plain ? std::min<uint32_t>(pl->worst_stack, PLAIN_STACK) : pl->worst_stack;
     pl->tlanes = sbud ? by_layout(ix, [&](auto lw) { return task_lanes<decltype(lw)::value>(nr_up, pl->lanes); }) : 0u;
     const uint32_t blanes = std::max(pl->lanes, pl->tlanes);
