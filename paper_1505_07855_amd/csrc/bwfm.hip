@@ -101,15 +101,6 @@ constexpr uint32_t PLAIN_STACK = 320;  // stack entries per lane, plain form fir
 // on 250 bp reads the pre-pass and a loop that only searches take 5-6% less
 // time than the loop's own scans, on 100 bp reads 7% more.
 constexpr uint32_t DPRE_MIN_LEN = 200;
-//   TWOSTATE: a searching lane expands one state per iteration (0), or two
-//             (1): besides its current state it keeps a second one, taken
-//             from the top of its stack, whose rank query is issued with
-//             the first, so two expansions share one round trip (before the
-//             batch runs dry; in the endgame the second state goes back on
-//             the stack for the sharing).
-#ifndef BWFM_GENE_TWOSTATE
-#define BWFM_GENE_TWOSTATE 0
-#endif
 //   SUBLOAD:  a 128-byte sub-counted query loads the line's first 16 bytes
 //             and, past row 128, its next 16 (0), or 12 bytes of counts and
 //             the one boundary word its row needs (1, shipped: fewer
@@ -117,15 +108,6 @@ constexpr uint32_t DPRE_MIN_LEN = 200;
 #ifndef BWFM_GENE_SUBLOAD
 #define BWFM_GENE_SUBLOAD 1
 #endif
-//   KTLOOP:   the batched form's persistent loop ignores the short-string
-//             table (0), or reads it, like the plain form, for states and
-//             D-array steps whose string is shorter than its levels (1):
-//             with a few levels the table sits in L2, where those rank
-//             queries' line fills from the Infinity Cache do not.
-#ifndef BWFM_GENE_KTLOOP
-#define BWFM_GENE_KTLOOP 0
-#endif
-constexpr bool KT_LOOP = BWFM_GENE_KTLOOP == 1;
 constexpr uint32_t FAST_CAND = BWFM_FAST_CAND;  // hit slots per lane, first pass
 constexpr int BLOCK = 256;
 constexpr int POPS_PER_STEP = BWFM_POPS_PER_STEP;  // stack pops per lane per persistent iteration (more costs the
@@ -222,20 +204,21 @@ constexpr int LW_SUB128 = 33;
 template <int LW> constexpr int line_words() { return LW == LW_SUB ? 16 : (LW == LW_SUB128 ? 32 : LW); }
 constexpr uint32_t SUB128_ROWS = 384;
 
-// The four (k, l) pairs of a string's one-base extensions, read from the
-// short-string table as two 16-byte words (p: A and C, q: G and T), in the
-// rank-query form the search consumes: o1[a] = k_a - C[a],
-// o2[a] = l_a + 1 - C[a].
-__device__ __forceinline__ void kt_pick(const DevDir &d, uint4 p, uint4 q, uint32_t o1[4], uint32_t o2[4]) {
-    o1[0] = p.x - d.C[0];
-    o2[0] = p.y + 1 - d.C[0];
-    o1[1] = p.z - d.C[1];
-    o2[1] = p.w + 1 - d.C[1];
-    o1[2] = q.x - d.C[2];
-    o2[2] = q.y + 1 - d.C[2];
-    o1[3] = q.z - d.C[3];
-    o2[3] = q.w + 1 - d.C[3];
+// The four intervals of a string's one-base extensions, read from the
+// interval table as two 16-byte words (p: A and C, q: G and T), as [lo, hi):
+// lo = k, hi = l + 1.  An extension that does not occur has lo >= hi.
+__device__ __forceinline__ void kt_pick(uint4 p, uint4 q, uint32_t lo[4], uint32_t hi[4]) {
+    lo[0] = p.x;
+    hi[0] = p.y + 1;
+    lo[1] = p.z;
+    hi[1] = p.w + 1;
+    lo[2] = q.x;
+    hi[2] = q.y + 1;
+    lo[3] = q.z;
+    hi[3] = q.w + 1;
 }
+// first entry of level d <= 15, which fits 32 bits
+__device__ __forceinline__ uint32_t kt_start32(int d) { return d == 0 ? 0u : ((1u << (2 * d)) + 8u) / 3u; }
 // entry of the first child of the string of d < 15 bases with code c:
 // level d + 1 starts at (4^(d+1) + 8) / 3, and every entry below level 16
 // has an index under 2^32
@@ -519,6 +502,24 @@ __device__ __forceinline__ void occ4_pair(const DevIndex &ix, const DevDir &d, u
     count(B, i2, l2, o2);
 }
 
+// The intervals [lo, hi) of a string's four extensions from the rank counts
+// at its k (i1) and l + 1 (i2); pair: rows in one line fetch it once.
+template <int LW>
+__device__ __forceinline__ void rank_children(const DevIndex &ix, const DevDir &d, uint32_t i1, uint32_t i2,
+                                              uint32_t lo[4], uint32_t hi[4], bool pair) {
+    if (pair) {
+        occ4_pair<LW>(ix, d, i1, i2, lo, hi);
+    } else {
+        occ4<LW>(ix, d, i1, lo);
+        occ4<LW>(ix, d, i2, hi);
+    }
+#pragma unroll
+    for (int a = 0; a < 4; a++) {
+        lo[a] += d.C[a];
+        hi[a] += d.C[a];
+    }
+}
+
 // Occ(a, i) for one base a.
 template <int LW>
 __device__ __forceinline__ uint32_t occ1(const DevIndex &ix, const DevDir &d, int a, uint32_t i) {
@@ -665,23 +666,17 @@ __device__ int record(LaneCtx &c, const Params &P, uint4 h, int phase) {
     return R_OK;
 }
 
-// pattern base w[i] of the strand: strand + reads the read backwards,
-// strand - reads its complement backwards
-__device__ __forceinline__ int pat(const uint8_t *W, int m, int strand, int i) {
-    int b = W[m - 1 - i];
-    return (strand == 0 || b > 3) ? b : 3 - b;
-}
-
 // Copy read W (m bases) into an LDS row reversed, row[i] = W[m - 1 - i]:
 // the strand + pattern, whose D-array scan then rewrites each byte in place
 // as base | D << 3 (strand -: the complement of the same low bits).  Whole
 // aligned dwords are loaded 8 at a time, so a read costs a few memory round
 // trips instead of one per D-array step; only dwords holding read bases are
-// touched.
-__device__ __forceinline__ void stage_read(uint8_t *row, const uint8_t *W, int m) {
+// touched.  Returns whether the read holds an N.
+__device__ __forceinline__ bool stage_read(uint8_t *row, const uint8_t *W, int m) {
     const uint32_t *A = reinterpret_cast<const uint32_t *>(reinterpret_cast<uintptr_t>(W) & ~uintptr_t(3));
     const int off = (int)(reinterpret_cast<uintptr_t>(W) & 3);
     const int ndw = (off + m + 3) >> 2;
+    uint32_t n_any = 0;
     for (int k0 = 0; k0 < ndw; k0 += 8) {
         uint32_t v[8];
 #pragma unroll
@@ -691,9 +686,13 @@ __device__ __forceinline__ void stage_read(uint8_t *row, const uint8_t *W, int m
 #pragma unroll
             for (int q = 0; q < 4; q++) {
                 const int i = 4 * (k0 + j) + q - off;
-                if (i >= 0 && i < m) row[m - 1 - i] = (uint8_t)(v[j] >> (8 * q));
+                if (i >= 0 && i < m) {
+                    row[m - 1 - i] = (uint8_t)(v[j] >> (8 * q));
+                    n_any |= (v[j] >> (8 * q)) & 4u;
+                }
             }
     }
+    return n_any != 0;
 }
 
 // seed window of the strand pattern: the read's 5' end, consumed first
@@ -718,14 +717,86 @@ __device__ __forceinline__ int s_sd(uint4 s) { return (s.z >> 24) & 15; }
 __device__ __forceinline__ int s_score(uint4 s) { return s.w & 1023; }
 __device__ __forceinline__ int s_len(uint4 s) { return (s.w >> 10) & 1023; }
 
-// k of a state: x itself, or, for a state whose X is shorter than the
-// short-string levels (x holds the code of X), k from X's table entry on
-// the strand's search index.  Only completed hits need it.
-__device__ __forceinline__ uint32_t state_k(const DevIndex &ix, int strand, uint4 s) {
+// Interval of a completed state: (x, y) itself, or, while X is shorter than
+// the interval table's levels (x holds the code of X), X's table entry on
+// the strand's search index.
+__device__ __forceinline__ uint2 state_kl(const DevIndex &ix, int strand, uint4 s) {
     const int len = s_len(s);
-    if (len >= (int)ix.kt_levels) return s.x;
-    const uint32_t *kt = strand == 0 ? ix.dir[1].kt : ix.dir[0].kt;
-    return kt[2 * (kt_level_start(len) + s.x)];
+    if (len >= (int)ix.kt_levels) return make_uint2(s.x, s.y);
+    const uint2 *kt = reinterpret_cast<const uint2 *>(strand == 0 ? ix.dir[1].kt : ix.dir[0].kt);
+    return kt[kt_start32(len) + s.x];
+}
+
+// ---- runs of exact matches through the interval table
+//
+// Most states of a search may take no further difference: the next one
+// would pass the budget, the bound or the seed's.  Such a state only follows
+// the pattern until its string stops occurring, which for strings shorter
+// than the table's levels one table entry decides: the entry of the whole
+// run at the deepest level holds its interval, or how many of its bases
+// occur.  On the benchmark batch three quarters of the expansions are steps
+// of such runs, 4 of them to a run.
+
+// Two bits per base of row[at, at + q), q <= 15, base j in bits 2 j: the row
+// is read as whole dwords (it starts dword-aligned; at most 3 bytes past its
+// last base are touched, inside the row's last dword).
+__device__ __forceinline__ uint32_t row_code(const uint8_t *row, int at, int q) {
+    const uint32_t *A = reinterpret_cast<const uint32_t *>(row) + (at >> 2);
+    const int sh = at & 3, nd = (sh + q + 3) >> 2;
+    uint32_t v[5];
+#pragma unroll
+    for (int t = 0; t < 5; t++) v[t] = t < nd ? A[t] : 0u;
+#pragma unroll
+    for (int t = 0; t < 5; t++) {
+        uint32_t u = v[t] & 0x03030303u;
+        u |= u >> 6;
+        v[t] = (u & 0x0fu) | ((u >> 12) & 0xf0u);
+    }
+    const uint32_t lo = v[0] | (v[1] << 8) | (v[2] << 16) | (v[3] << 24);
+    const uint64_t w = ((uint64_t)v[4] << 32) | lo;
+    return (uint32_t)(w >> (2 * sh)) & ((1u << (2 * q)) - 1u);
+}
+// the q two-bit digits of c in the opposite order
+__device__ __forceinline__ uint32_t rev_digits(uint32_t c, int q) {
+    const uint32_t r = __brev(c);
+    return q ? (((r >> 1) & 0x55555555u) | ((r & 0x55555555u) << 1)) >> (32 - 2 * q) : 0u;
+}
+
+// Steps of the exact run from state cur (i >= 0, |X| < the table's levels)
+// to the deepest level, or 0 when a difference may still be taken on the
+// way: D falls towards the pattern's start, so no difference fits anywhere
+// in the run when none fits with the D of its end.
+__device__ __forceinline__ int run_steps(const DevIndex &ix, uint4 cur, const uint8_t *pd, int maxd, int bound,
+                                         bool has_n, const Seed &S, const Params &P) {
+    const int q = (int)ix.kt_levels - s_len(cur);
+    const int e = s_i(cur) - q;
+    if (e < -1) return 0;
+    const int De = e >= 0 ? pd[e] >> 3 : 0;
+    const int diffs = s_nmm(cur) + s_ngo(cur) + s_nge(cur);
+    const bool none = diffs + 1 + De > maxd || s_score(cur) + P.minc + P.minc * De > bound ||
+                      (S.sl != 0 && !has_n && s_sd(cur) >= P.seed_diff && e + 1 >= S.lo);
+    return none ? q : 0;
+}
+// Table entry of the run of q steps from cur.
+__device__ __forceinline__ uint32_t run_entry(const DevIndex &ix, uint4 cur, const uint8_t *pd, int q) {
+    return kt_start32((int)ix.kt_levels) + ((cur.x << (2 * q)) | row_code(pd, s_i(cur) + 1 - q, q));
+}
+// cur after its run: the state q steps on, or dropped (valid cleared) when
+// its string stops occurring.  Returns the states the run expanded.
+__device__ __forceinline__ uint32_t run_take(uint4 &cur, bool &valid, uint2 kl, const uint8_t *pd, int q,
+                                             const Params &P) {
+    if (kl.y == 0) {  // absent: kl.x - 1 of the bases occur
+        valid = false;
+        return kl.x - (uint32_t)s_len(cur);
+    }
+    const int e = s_i(cur) - q;
+    const int De = e >= 0 ? pd[e] >> 3 : 0;
+    cur.x = kl.x;
+    cur.y = kl.y;
+    cur.z = (cur.z & ~(3u << 10)) - (uint32_t)q;
+    cur.w = (cur.w & 0xfffffu) + ((uint32_t)q << 10);
+    cur.w |= (uint32_t)(s_score(cur) + P.minc * De) << 20;
+    return (uint32_t)q;
 }
 
 // the empty string's interval, nothing consumed, lower bound minc * D[m - 1]
@@ -740,7 +811,6 @@ __device__ __forceinline__ uint4 root_state(const DevIndex &ix, int m, int lb) {
 // the pop limit was reached first, 3 when cur is a completed hit left for
 // the caller to record (only with defer), or -R_CAND when the hit buffer
 // overflowed.
-template <bool KT = true>
 __device__ int resolve(uint4 &cur, bool &valid, int strand, const Params &P, LaneCtx &c, int phase, int max_pops,
                        const DevIndex &ix, bool defer = false) {
     for (int pops = 0;;) {
@@ -761,9 +831,8 @@ __device__ int resolve(uint4 &cur, bool &valid, int strand, const Params &P, Lan
             if (defer) return 3;
             const int score = s_score(cur);
             if (score < c.best) c.best = score;
-            int rc = record(c, P,
-                            make_hit(strand, KT ? state_k(ix, strand, cur) : cur.x, cur.y, s_len(cur), score,
-                                     s_nmm(cur), s_ngo(cur), s_nge(cur)),
+            const uint2 kl = state_kl(ix, strand, cur);
+            int rc = record(c, P, make_hit(strand, kl.x, kl.y, s_len(cur), score, s_nmm(cur), s_ngo(cur), s_nge(cur)),
                             phase);
             if (rc) return -rc;
             valid = false;
@@ -773,14 +842,13 @@ __device__ int resolve(uint4 &cur, bool &valid, int strand, const Params &P, Lan
     }
 }
 
-// Children of an expanded state, from the rank counts at k (ok) and l + 1
-// (ol) on the search index, built directly in packed form: each differs
+// Children of an expanded state, from the intervals [lo, hi) of its
+// string's four extensions, built directly in packed form: each differs
 // from the parent by a few field increments.  They are taken in reverse of
 // the fixed order (match, mismatches by base, insertion, deletions by base);
 // the first surviving one becomes cur, the others are pushed with their
 // lower bounds.  Returns R_OK or R_STACK.
-__device__ int expand_children(uint4 &cur, bool &valid, const uint32_t (&ok)[4], const uint32_t (&ol)[4],
-                               const DevDir &sd_, int b, int m, int maxd, int Di, int Dn, const Seed &S,
+__device__ int expand_children(uint4 &cur, bool &valid, const uint32_t (&lo)[4], const uint32_t (&hi)[4], int b, int m, int maxd, int Di, int Dn, const Seed &S,
                                const Params &P, LaneCtx &c, uint32_t K) {
     const int i = s_i(cur), gs = s_gs(cur), ngo = s_ngo(cur), nge = s_nge(cur), sd = s_sd(cur);
     const int score = s_score(cur), len = s_len(cur);
@@ -789,7 +857,7 @@ __device__ int expand_children(uint4 &cur, bool &valid, const uint32_t (&ok)[4],
     const bool coded = (uint32_t)(len + 1) < K;
     uint32_t kx[4];
 #pragma unroll
-    for (int a = 0; a < 4; a++) kx[a] = coded ? (cur.x << 2) | (uint32_t)a : sd_.C[a] + ok[a];
+    for (int a = 0; a < 4; a++) kx[a] = coded ? (cur.x << 2) | (uint32_t)a : lo[a];
     const int diffs = s_nmm(cur) + ngo + nge;
     const int bound = (P.mode == BWFM_MODE_BEST && c.best != INF_SCORE) ? c.best + P.s_mm : INF_SCORE;
     const uint32_t z0 = cur.z & ~(3u << 10);  // gap state cleared
@@ -831,7 +899,7 @@ __device__ int expand_children(uint4 &cur, bool &valid, const uint32_t (&ok)[4],
             const uint32_t w = (uint32_t)nsc | ((uint32_t)(len + 1) << 10) | ((uint32_t)lb << 20);
 #pragma unroll
             for (int a = 3; a >= 0; a--)
-                if (ok[a] < ol[a]) offer(kx[a], sd_.C[a] + ol[a] - 1, z, w);
+                if (lo[a] < hi[a]) offer(kx[a], hi[a] - 1, z, w);
         }
     }
     const int in_i = (i >= S.lo && i < S.hi) ? 1 : 0;
@@ -857,11 +925,11 @@ __device__ int expand_children(uint4 &cur, bool &valid, const uint32_t (&ok)[4],
             const uint32_t w = (uint32_t)nsc | ((uint32_t)(len + 1) << 10) | ((uint32_t)lb << 20);
 #pragma unroll
             for (int a = 3; a >= 0; a--)
-                if (a != b && ok[a] < ol[a]) offer(kx[a], sd_.C[a] + ol[a] - 1, z, w);
+                if (a != b && lo[a] < hi[a]) offer(kx[a], hi[a] - 1, z, w);
         }
         const int lbm = score + P.minc * Dn;
-        if (b < 4 && sel4(ok, b) < sel4(ol, b) && diffs + Dn <= maxd && lbm <= bound)
-            offer(sel4(kx, b), sel4(sd_.C, b) + sel4(ol, b) - 1, z0 - 1u,
+        if (b < 4 && sel4(lo, b) < sel4(hi, b) && diffs + Dn <= maxd && lbm <= bound)
+            offer(sel4(kx, b), sel4(hi, b) - 1, z0 - 1u,
                   (uint32_t)score | ((uint32_t)(len + 1) << 10) | ((uint32_t)lbm << 20));
     }
     if (have) cur = pend;
@@ -869,45 +937,84 @@ __device__ int expand_children(uint4 &cur, bool &valid, const uint32_t (&ok)[4],
     return rc;
 }
 
-// D-array of one strand on the other index.  Returns false when the bound
-// already exceeds the budget at the root (the strand cannot match).
+// Rewrite cnt bytes of the row from `at` on as base | z << 3, for strand -
+// complementing the staged strand + bases (none of them N): whole dwords,
+// loaded before any is stored.
+__device__ __forceinline__ void row_fill(uint8_t *row, int at, int cnt, int z, int flip) {
+    uint32_t *A = reinterpret_cast<uint32_t *>(row) + (at >> 2);
+    const int sh = at & 3, nd = (sh + cnt + 3) >> 2;  // cnt <= 16: at most 5 dwords
+    uint32_t v[5];
+#pragma unroll
+    for (int t = 0; t < 5; t++) v[t] = t < nd ? A[t] : 0u;
+#pragma unroll
+    for (int t = 0; t < 5; t++) {
+        const int b0 = max(sh - 4 * t, 0), b1 = min(sh + cnt - 4 * t, 4);  // bytes [b0, b1) of this dword
+        if (t < nd && b0 < b1) {
+            const uint32_t mk = (b1 >= 4 ? 0xffffffffu : (1u << (8 * b1)) - 1u) & ~((1u << (8 * b0)) - 1u);
+            const uint32_t nv = ((v[t] ^ (flip ? 0x03030303u : 0u)) & 0x07070707u) | (0x08080808u * (uint32_t)z);
+            A[t] = (v[t] & ~mk) | (nv & mk);
+        }
+    }
+}
+
+// D-array of one strand on the other index, in place over the staged
+// pattern (strand 0: row holds reverse(read), strand 1: its complement is
+// taken here).  Returns false when the bound already exceeds the budget at
+// the root (the strand cannot match).
 template <int LW>
-__device__ bool build_d(const DevIndex &ix, const DevDir &od, const uint8_t *W, int m, int strand, int maxd,
-                        LaneCtx &c) {
+__device__ bool build_d(const DevIndex &ix, const DevDir &od, int m, int strand, int maxd, bool has_n, LaneCtx &c) {
     uint32_t k = 0, l = ix.n;
-    uint32_t code = 0, len = 0;  // the current segment, while shorter than the short-string levels
+    bool fresh = true;  // at the start of a segment
     int z = 0;
-    for (int i = 0; i < m; i++) {
-        int a = pat(W, m, strand, i);
+    for (int i = 0; i < m;) {
+        if (fresh && ix.kt_levels && !has_n) {
+            // the segment's first bases in one table entry
+            const int r = min((int)ix.kt_levels, m - i);
+            uint32_t code = rev_digits(row_code(c.pd, i, r), r);
+            if (strand) code ^= (1u << (2 * r)) - 1u;
+            const uint2 kl = reinterpret_cast<const uint2 *>(od.kt)[kt_start32(r) + code];
+            if (kl.y) {
+                row_fill(c.pd, i, r, z, strand);
+                k = kl.x;
+                l = kl.y;
+                i += r;
+                fresh = false;
+            } else {
+                const int d = (int)kl.x - 1;  // bases that occur; the next one ends the segment
+                row_fill(c.pd, i, d, z, strand);
+                if (++z > maxd) return false;
+                row_fill(c.pd, i + d, 1, z, strand);
+                i += d + 1;
+                k = 0;
+                l = ix.n;
+            }
+            continue;
+        }
+        const int b = c.pd[i] & 7;
+        const int a = (strand == 0 || b > 3) ? b : 3 - b;
         bool empty = true;
-        if (a < 4 && len < ix.kt_levels) {
-            const uint2 e = reinterpret_cast<const uint2 *>(od.kt)[kt_children((int)len, code) + a];
-            empty = e.x > e.y;
-            k = e.x;
-            l = e.y;
-            code = (code << 2) | (uint32_t)a;
-            len++;
-        } else if (a < 4) {
+        if (a < 4) {
             uint32_t ok = occ1<LW>(ix, od, a, k), ol = occ1<LW>(ix, od, a, l + 1);
             empty = ok >= ol;
             k = sel4(od.C, a) + ok;
             l = sel4(od.C, a) + ol - 1;
         }
+        fresh = empty;
         if (empty) {
             z++;
             k = 0;
             l = ix.n;
-            code = len = 0;
             if (z > maxd) return false;
         }
         c.pd[i] = (uint8_t)(a | (z << 3));
+        i++;
     }
     return true;
 }
 
 // Depth-first search of one strand, one lane, start to end.
 template <int LW>
-__device__ int search_strand(const DevIndex &ix, const DevDir &sd_, const uint8_t *W, int m, int strand, int maxd,
+__device__ int search_strand(const DevIndex &ix, const DevDir &sd_, int m, int strand, int maxd, bool has_n,
                              const Params &P, LaneCtx &c, int phase) {
     const Seed S = seed_of(P, m);
     uint4 cur = root_state(ix, m, P.minc * pd_d(c, m - 1));
@@ -917,19 +1024,25 @@ __device__ int search_strand(const DevIndex &ix, const DevDir &sd_, const uint8_
         int rr = resolve(cur, valid, strand, P, c, phase, 0x7fffffff, ix);
         if (rr == 0) return R_OK;
         if (rr < 0) return -rr;
-        c.expand++;
-        uint32_t ok[4], ol[4];
+        uint32_t lo[4], hi[4];
         if ((uint32_t)s_len(cur) < ix.kt_levels) {
-            const uint4 *e = reinterpret_cast<const uint4 *>(sd_.kt + 2 * kt_children(s_len(cur), cur.x));
-            kt_pick(sd_, e[0], e[1], ok, ol);
+            const int bound = (P.mode == BWFM_MODE_BEST && c.best != INF_SCORE) ? c.best + P.s_mm : INF_SCORE;
+            const int q = run_steps(ix, cur, c.pd, maxd, bound, has_n, S, P);
+            if (q) {
+                const uint2 kl = reinterpret_cast<const uint2 *>(sd_.kt)[run_entry(ix, cur, c.pd, q)];
+                c.expand += run_take(cur, valid, kl, c.pd, q, P);
+                continue;
+            }
+            const uint4 *e = reinterpret_cast<const uint4 *>(sd_.kt + 2 * (size_t)kt_children(s_len(cur), cur.x));
+            kt_pick(e[0], e[1], lo, hi);
         } else {
-            occ4<LW>(ix, sd_, cur.x, ok);
-            occ4<LW>(ix, sd_, cur.y + 1, ol);
+            rank_children<LW>(ix, sd_, cur.x, cur.y + 1, lo, hi, false);
         }
+        c.expand++;
         const int i = s_i(cur);
         const int b = pd_base(c, i);
         const int Di = pd_d(c, i), Dn = pd_d(c, i - 1);
-        int rc = expand_children(cur, valid, ok, ol, sd_, b, m, maxd, Di, Dn, S, P, c, ix.kt_levels);
+        int rc = expand_children(cur, valid, lo, hi, b, m, maxd, Di, Dn, S, P, c, ix.kt_levels);
         if (rc) return rc;
     }
 }
@@ -980,15 +1093,18 @@ __device__ uint32_t finish(LaneCtx &c, const Params &P, uint8_t &status, uint32_
     return r;
 }
 
+// Both strands of one read, one lane: the read is staged in the lane's row
+// once per strand (its D-array scan rewrites the row in place).
 template <int LW>
 __device__ int align_read(const DevIndex &ix, const uint8_t *W, int m, int maxd, const Params &P, LaneCtx &c,
                           int phase) {
     c.ncand = 0;
+    const bool has_n = stage_read(c.pd, W, m);
     for (int strand = 0; strand < 2; strand++) {
         const DevDir sdir = pick_dir(ix, strand == 0 ? 1 : 0);
         const DevDir odir = pick_dir(ix, strand == 0 ? 0 : 1);
-        if (!build_d<LW>(ix, odir, W, m, strand, maxd, c)) continue;
-        int rc = search_strand<LW>(ix, sdir, W, m, strand, maxd, P, c, phase);
+        if (!build_d<LW>(ix, odir, m, strand, maxd, has_n, c)) continue;
+        int rc = search_strand<LW>(ix, sdir, m, strand, maxd, has_n, P, c, phase);
         if (rc) return rc;
     }
     return R_OK;
@@ -1101,7 +1217,7 @@ constexpr uint32_t SPLIT_CTL = 2 * (SPLIT_ROUNDS + 1) + 2;
 
 struct SplitBufs {
     uint32_t *slot_read;    // the slot's read
-    uint32_t *slot_meta;    // m | budget << 10
+    uint32_t *slot_meta;    // m | budget << 10 | the read holds an N << 14
     int *slot_best;         // best score found by any part
     uint32_t *slot_nhit;    // hits delivered (above SLOT_HITS: the slot failed)
     uint32_t *slot_fail;    // nonzero: the read goes to the second pass
@@ -1205,8 +1321,8 @@ constexpr int SH_SLOT_SHIFT = 5;
 // the lane that owns the read).  The caller runs one lane of a wave at a
 // time.  False, with the lane's search unchanged, when no slot or task room
 // is left.
-__device__ bool split_part(const SplitBufs &X, uint32_t r, uint32_t owner, int strand, int m, int maxd, int best,
-                           LaneCtx &c, uint4 cur, bool valid, int &fl) {
+__device__ bool split_part(const SplitBufs &X, uint32_t r, uint32_t owner, int strand, int m, int maxd, bool has_n,
+                           int best, LaneCtx &c, uint4 cur, bool valid, int &fl) {
     const uint32_t cnt = (valid ? 1u : 0u) + (c.sp - c.sbase);
     const bool had = (fl >> SH_SLOT_SHIFT) != 0;
     if (!had && ld_agent(&X.ctl[0]) >= X.slot_cap) return false;
@@ -1222,7 +1338,7 @@ __device__ bool split_part(const SplitBufs &X, uint32_t r, uint32_t owner, int s
             return false;
         }
         X.slot_read[s] = r;
-        X.slot_meta[s] = (uint32_t)m | ((uint32_t)maxd << 10);
+        X.slot_meta[s] = (uint32_t)m | ((uint32_t)maxd << 10) | ((uint32_t)has_n << 14);
         X.slot_best[s] = best;
         X.slot_nhit[s] = 0;
         X.slot_fail[s] = 0;
@@ -1324,7 +1440,7 @@ __global__ __launch_bounds__(BLOCK) void k_align_plain(DevIndex ix, ReadsView rd
 }
 
 enum { PZ_IDLE = 0, PZ_DSCAN = 1, PZ_SEARCH = 2, PZ_HELP = 3, PZ_WAIT = 4 };
-enum { ACT_NONE = 0, ACT_DSTEP = 1, ACT_EXPAND = 2 };
+enum { ACT_NONE = 0, ACT_DSTEP = 1, ACT_EXPAND = 2, ACT_RUN = 3, ACT_DRUN = 4 };
 
 // Per-wave block in LDS through which the lanes of a wave share one read's
 // search once the batch's reads are all taken: an idle lane receives the
@@ -1339,7 +1455,7 @@ struct WaveShare {
     int flags[64];      // SH_FAIL: the hit buffer overflowed; SH_HELPED; the read's slot
     int hexp[64];       // states expanded by helpers
     uint4 box[64];      // donated states
-    uint32_t meta[64];  // owner lane | strand << 6 | budget << 7 | m << 11
+    uint32_t meta[64];  // owner lane | strand << 6 | budget << 7 | m << 11 | the read holds an N << 21
 };
 
 __device__ __forceinline__ int sh_ld(const int *p) {
@@ -1373,7 +1489,8 @@ struct PersistentArgs {
     uint32_t *next_read;
     // the D-array pre-pass's output: per read, one row per strand of
     // dstride bytes (base | D << 3 per pattern position) and a byte whose
-    // bit s is set when strand s is pruned at the root
+    // bit s is set when strand s is pruned at the root, bit 2 when the read
+    // holds an N
     const uint8_t *drows;
     const uint8_t *dflag;
     uint32_t dstride;
@@ -1406,10 +1523,11 @@ __global__ __launch_bounds__(BLOCK) void k_dscan(DevIndex ix, ReadsView rd, Para
     const int m = (int)len;
     LaneCtx c;
     c.pd = lds_bytes + (size_t)threadIdx.x * lstride;
-    uint8_t fl = 0;
+    const bool has_n = stage_read(c.pd, rd.bases + o0, m);
+    uint8_t fl = has_n ? 4 : 0;
     for (int strand = 0; strand < 2; strand++) {
         const DevDir odir = pick_dir(ix, strand == 0 ? 0 : 1);
-        if (!build_d<LW>(ix, odir, rd.bases + o0, m, strand, maxd, c)) {
+        if (!build_d<LW>(ix, odir, m, strand, maxd, has_n, c)) {
             fl |= (uint8_t)(1 << strand);
             continue;
         }
@@ -1482,17 +1600,14 @@ __device__ __forceinline__ void persistent_body(const DevIndex &ix, const Params
     int ow = lane;         // owner lane of the read this lane works on
     uint32_t r = 0;
     int m = 0, maxd = 0, strand = 0;
+    bool has_n = false;  // the read holds an N
     // D scan state
     int di = 0, dz = 0;
     uint32_t dk = 0, dl = 0;
-    uint32_t dcode = 0, dlen = 0;  // the current segment while the table covers it (KTLOOP)
+    bool dfresh = true;  // at the start of a segment
     // search state
     uint4 cur = make_uint4(0, 0, 0, 0);
     bool valid = false;
-#if BWFM_GENE_TWOSTATE == 1
-    uint4 cur2 = make_uint4(0, 0, 0, 0);  // the second state (valid2), same read and strand
-    bool valid2 = false;
-#endif
     Seed S{0, 0, 0};
     // work statistics (measurement only)
     uint32_t w_iters = 0, w_busy = 0, w_query = 0;  // per lane: far below 2^32 per launch
@@ -1535,6 +1650,7 @@ __device__ __forceinline__ void persistent_body(const DevIndex &ix, const Params
                             // the first strand the pre-pass left searchable,
                             // or nothing to search
                             const int dfl = A->dflag[r];
+                            has_n = (dfl & 4) != 0;
                             strand = (dfl & 1) ? 1 : 0;
                             if ((dfl & 3) == 3) {
                                 publish(c, P, O, r);
@@ -1547,14 +1663,14 @@ __device__ __forceinline__ void persistent_body(const DevIndex &ix, const Params
                                 c.sp = c.sbase = 0;
                             }
                         } else {
-                            stage_read(own_pd, rd.bases + o0, m);
+                            has_n = stage_read(own_pd, rd.bases + o0, m);
                             strand = 0;
                             phase = PZ_DSCAN;
                             di = 0;
                             dz = 0;
                             dk = 0;
                             dl = ix.n;
-                            dcode = dlen = 0;
+                            dfresh = true;
                         }
                         S = seed_of(P, m);
                         sh_st(&ws.best[lane], INF_SCORE);
@@ -1573,25 +1689,6 @@ __device__ __forceinline__ void persistent_body(const DevIndex &ix, const Params
             continue;
         }
         endgame = endgame || __ballot(exhausted) != 0;
-#if BWFM_GENE_TWOSTATE == 1
-        if (endgame && valid2) {
-            // the sharing below works on single states: the second one goes
-            // back on the stack; with the stack full the read (still this
-            // lane's alone: nothing is shared before the endgame) goes to
-            // the second pass
-            if (c.sp < c.stack_cap) {
-                c.stack[(size_t)c.sp * c.sstride] = cur2;
-                c.sp++;
-            } else {
-                send_to_second_pass(A->O, r);
-                if (A->O.expand) A->O.expand[r] = c.expand;
-                phase = PZ_IDLE;
-                valid = false;
-                c.sp = c.sbase = 0;
-            }
-            valid2 = false;
-        }
-#endif
         if (O.work) {
             w_iters++;
             w_busy += phase != PZ_IDLE && phase != PZ_WAIT;
@@ -1621,7 +1718,8 @@ __device__ __forceinline__ void persistent_body(const DevIndex &ix, const Params
                     const int gi = __popcll(G & lt);
                     if (gi < n) {
                         ws.box[gi] = c.stack[(size_t)c.sbase * c.sstride];
-                        ws.meta[gi] = (uint32_t)ow | ((uint32_t)strand << 6) | ((uint32_t)maxd << 7) | ((uint32_t)m << 11);
+                        ws.meta[gi] = (uint32_t)ow | ((uint32_t)strand << 6) | ((uint32_t)maxd << 7) | ((uint32_t)m << 11) |
+                                      ((uint32_t)has_n << 21);
                         c.sbase++;
                         atomicAdd(&ws.pending[ow], 1);
                         atomicOr(&ws.flags[ow], SH_HELPED);
@@ -1636,7 +1734,8 @@ __device__ __forceinline__ void persistent_body(const DevIndex &ix, const Params
                         ow = (int)(mt & 63);
                         strand = (int)((mt >> 6) & 1);
                         maxd = (int)((mt >> 7) & 15);
-                        m = (int)(mt >> 11);
+                        m = (int)((mt >> 11) & 1023);
+                        has_n = (mt >> 21) != 0;
                         S = seed_of(P, m);
                         valid = true;
                         c.sp = c.sbase = 0;
@@ -1664,7 +1763,7 @@ __device__ __forceinline__ void persistent_body(const DevIndex &ix, const Params
                         int fl = sh_ld(&ws.flags[ow]);
                         const uint32_t og = gl - (uint32_t)lane + (uint32_t)ow;  // the owner's global lane
                         const uint32_t rr = ow == lane ? r : A->lane_read[og];
-                        if (split_part(A->X, rr, og, strand, m, maxd, sh_ld(&ws.best[ow]), c, cur, valid, fl))
+                        if (split_part(A->X, rr, og, strand, m, maxd, has_n, sh_ld(&ws.best[ow]), c, cur, valid, fl))
                             valid = false;  // the lane's part is over
                         else
                             fl |= SH_NOSPLIT;  // no room: the read's parts go on in the wave
@@ -1679,7 +1778,9 @@ __device__ __forceinline__ void persistent_body(const DevIndex &ix, const Params
         // decide this lane's action and rank queries; a lane that changes
         // phase here acts in its new phase from the next iteration on
         int act = ACT_NONE;
-        bool query = false;
+        int q = 0;           // bases the table entry covers: a run's steps, or a D-array segment's start
+        uint32_t tent = 0;   // the entry
+        bool query = false;  // rank query at q1, q2
         bool hit = false;
         int qdir = 0;  // index queried: 0 = T, 1 = reverse(T)
         uint32_t q1 = 0, q2 = 0;
@@ -1687,18 +1788,23 @@ __device__ __forceinline__ void persistent_body(const DevIndex &ix, const Params
         bool part_done = false;  // this lane's part of the strand's search is over
         if (!DP && phase == PZ_DSCAN) {
             act = ACT_DSTEP;
-            {
+            qdir = strand == 0 ? 0 : 1;
+            if (dfresh && ix.kt_levels && !has_n) {
+                // a segment's first bases in one table entry
+                act = ACT_DRUN;
+                q = min((int)ix.kt_levels, m - di);
+                uint32_t code = rev_digits(row_code(own_pd, di, q), q);
+                if (strand) code ^= (1u << (2 * q)) - 1u;
+                tent = kt_start32(q) + code;
+            } else {
                 const int b = own_pd[di] & 7;  // the staged base (strand +)
                 da = (strand == 0 || b > 3) ? b : 3 - b;
-            }
-            if (da < 4) {
-                query = true;
-                qdir = strand == 0 ? 0 : 1;
+                query = da < 4;
                 q1 = dk;
                 q2 = dl + 1;
             }
         } else if (phase == PZ_SEARCH || phase == PZ_HELP) {
-            int rr = resolve<KT_LOOP>(cur, valid, strand, P, c, PH_FAST, POPS_PER_STEP, ix, endgame);
+            int rr = resolve(cur, valid, strand, P, c, PH_FAST, POPS_PER_STEP, ix, endgame);
             if (rr == 2) {
                 // pop limit reached: keep popping next iteration
             } else if (rr == 3) {
@@ -1713,61 +1819,18 @@ __device__ __forceinline__ void persistent_body(const DevIndex &ix, const Params
             }
             if (rr == 1) {
                 act = ACT_EXPAND;
-                query = true;
                 qdir = strand == 0 ? 1 : 0;
-                q1 = cur.x;
-                q2 = cur.y + 1;
-            }
-#if BWFM_GENE_TWOSTATE == 1
-            if (!endgame && phase == PZ_SEARCH) {
-                const int bound = (P.mode == BWFM_MODE_BEST && c.best != INF_SCORE) ? c.best + P.s_mm : INF_SCORE;
-                // the second state: dropped once the bound passes it,
-                // recorded when it is a completed hit
-                if (valid2 && entry_lb(cur2) > bound) valid2 = false;
-                if (valid2 && s_i(cur2) < 0) {
-                    valid2 = false;
-                    const int score = s_score(cur2);
-                    if (score < c.best) c.best = score;
-                    if (record(c, P, make_hit(strand, KT_LOOP ? state_k(ix, strand, cur2) : cur2.x, cur2.y,
-                                              s_len(cur2), score, s_nmm(cur2), s_ngo(cur2), s_nge(cur2)),
-                               PH_FAST)) {
-                        send_to_second_pass(O, r);
-                        if (O.expand) O.expand[r] = c.expand;
-                        phase = PZ_IDLE;
-                        act = ACT_NONE;
-                        query = false;
-                        part_done = false;
-                    }
-                }
-                // else the next state on the stack, unless it is a completed
-                // hit (left for resolve) or already beaten by the bound
-                if (phase == PZ_SEARCH && !valid2 && c.sp > c.sbase) {
-                    const uint4 t = c.stack[(size_t)(c.sp - 1) * c.sstride];
-                    if (entry_lb(t) > bound) {
-                        c.sp--;
-                    } else if (s_i(t) >= 0) {
-                        c.sp--;
-                        cur2 = t;
-                        valid2 = true;
-                    }
-                }
-                // the lane's part is not over while the second state is left:
-                // it becomes the current one (already resolved above)
-                if (part_done && valid2) {
-                    part_done = false;
-                    cur = cur2;
-                    valid = true;
-                    valid2 = false;
-                    act = ACT_EXPAND;
+                if ((uint32_t)s_len(cur) < ix.kt_levels) {
+                    const int bound = (P.mode == BWFM_MODE_BEST && c.best != INF_SCORE) ? c.best + P.s_mm : INF_SCORE;
+                    q = run_steps(ix, cur, c.pd, maxd, bound, has_n, S, P);
+                    if (q) act = ACT_RUN;
+                    tent = q ? run_entry(ix, cur, c.pd, q) : kt_children(s_len(cur), cur.x);
+                } else {
                     query = true;
                     q1 = cur.x;
                     q2 = cur.y + 1;
                 }
-                // a searching lane queries the strand's search index, for
-                // either state
-                qdir = strand == 0 ? 1 : 0;
             }
-#endif
             if (!endgame && phase == PZ_SEARCH) {
                 sh_st(&ws.best[lane], c.best);
                 sh_st(&ws.ncand[lane], (int)c.ncand);
@@ -1786,9 +1849,10 @@ __device__ __forceinline__ void persistent_body(const DevIndex &ix, const Params
                     if (sb < c.best) c.best = sb;
                     const int score = s_score(cur);
                     if (score < c.best) c.best = score;
+                    const uint2 kl = state_kl(ix, strand, cur);
                     const int rc = record(c, P,
-                                          make_hit(strand, KT_LOOP ? state_k(ix, strand, cur) : cur.x, cur.y,
-                                                   s_len(cur), score, s_nmm(cur), s_ngo(cur), s_nge(cur)),
+                                          make_hit(strand, kl.x, kl.y, s_len(cur), score, s_nmm(cur), s_ngo(cur),
+                                                   s_nge(cur)),
                                           PH_FAST);
                     sh_st(&ws.best[ow], c.best);
                     sh_st(&ws.ncand[ow], (int)c.ncand);
@@ -1842,7 +1906,7 @@ __device__ __forceinline__ void persistent_body(const DevIndex &ix, const Params
                     dz = 0;
                     dk = 0;
                     dl = ix.n;
-                    dcode = dlen = 0;
+                    dfresh = true;
                 }
             } else {
                 c.ncand = (uint32_t)sh_ld(&ws.ncand[lane]);
@@ -1858,59 +1922,51 @@ __device__ __forceinline__ void persistent_body(const DevIndex &ix, const Params
             }
         }
 
-        // the shared part: rank counts at q1 and q2 on one index
-        uint32_t ok[4] = {0, 0, 0, 0}, ol[4] = {0, 0, 0, 0};
+        // the shared part: a table entry (the load issued first, so that its
+        // latency overlaps the rank query's in other lanes), or the rank
+        // counts at q1 and q2, on one index
+        uint32_t lo[4] = {0, 0, 0, 0}, hi[4] = {0, 0, 0, 0};
         const DevDir qd = pick_dir(ix, qdir);
-        if (O.work) w_query += query;
-        if (query) {
-            // a D-array step or an expansion whose string the table covers
-            // reads the children's intervals there
-            const uint32_t qlen = act == ACT_DSTEP ? dlen : (uint32_t)s_len(cur);
-            if (KT_LOOP && qlen < ix.kt_levels) {
-                const uint32_t code = act == ACT_DSTEP ? dcode : cur.x;
-                const uint4 *e = reinterpret_cast<const uint4 *>(qd.kt + 2 * kt_children((int)qlen, code));
-                kt_pick(qd, e[0], e[1], ok, ol);
-            } else {
-                occ4_pair<LW>(ix, qd, q1, q2, ok, ol);
-            }
+        if (O.work) w_query += query || tent;
+        uint4 ta = make_uint4(0, 0, 0, 0), tb = ta;
+        if (tent) {
+            const uint4 *e = reinterpret_cast<const uint4 *>(qd.kt) + (tent >> 1);
+            ta = e[0];
+            if (q == 0) tb = e[1];
         }
-#if BWFM_GENE_TWOSTATE == 1
-        const bool act2 = valid2 && phase == PZ_SEARCH && !endgame;
-        uint32_t ok2[4] = {0, 0, 0, 0}, ol2[4] = {0, 0, 0, 0};
-        if (act2) {
-            if (KT_LOOP && (uint32_t)s_len(cur2) < ix.kt_levels) {
-                const uint4 *e = reinterpret_cast<const uint4 *>(qd.kt + 2 * kt_children(s_len(cur2), cur2.x));
-                kt_pick(qd, e[0], e[1], ok2, ol2);
-            } else {
-                occ4_pair<LW>(ix, qd, cur2.x, cur2.y + 1, ok2, ol2);
-            }
-        }
-        if (O.work) w_query += act2;
-#endif
+        if (query) rank_children<LW>(ix, qd, q1, q2, lo, hi, true);
+        if (tent && q == 0) kt_pick(ta, tb, lo, hi);
+        const uint2 tkl = (tent & 1) ? make_uint2(ta.z, ta.w) : make_uint2(ta.x, ta.y);
 
         // consume
-        if (!DP && act == ACT_DSTEP) {
+        if (!DP && (act == ACT_DSTEP || act == ACT_DRUN)) {
             bool empty = true;
-            if (da < 4) {
-                const uint32_t a1 = sel4(ok, da), a2 = sel4(ol, da);
-                empty = a1 >= a2;
-                dk = sel4(qd.C, da) + a1;
-                dl = sel4(qd.C, da) + a2 - 1;
-                if (KT_LOOP) {
-                    dcode = (dcode << 2) | (uint32_t)da;
-                    dlen++;
-                }
+            if (act == ACT_DSTEP && da < 4) {
+                dk = sel4(lo, da);
+                const uint32_t h = sel4(hi, da);
+                empty = dk >= h;
+                dl = h - 1;
             }
             bool skip = false;
+            if (act == ACT_DRUN) {
+                empty = tkl.y == 0;
+                dk = tkl.x;
+                dl = tkl.y;
+                const int d = empty ? (int)tkl.x - 1 : q;  // bases that occur
+                row_fill(own_pd, di, d, dz, strand);
+                di += d;
+                const int b = own_pd[empty ? di : 0] & 7;
+                da = strand ? 3 - b : b;
+            }
+            dfresh = empty;
             if (empty) {
                 dz++;
                 dk = 0;
                 dl = ix.n;
-                dcode = dlen = 0;
                 skip = dz > maxd;
             }
-            if (!skip) {
-                c.pd[di] = (uint8_t)(da | (dz << 3));
+            if (!skip && (empty || act == ACT_DSTEP)) {
+                own_pd[di] = (uint8_t)(da | (dz << 3));
                 di++;
             }
             if (skip || di == m) {
@@ -1925,7 +1981,7 @@ __device__ __forceinline__ void persistent_body(const DevIndex &ix, const Params
                     dz = 0;
                     dk = 0;
                     dl = ix.n;
-                    dcode = dlen = 0;
+                    dfresh = true;
                 } else {
                     // strand - cannot match; the read's helpers, if any,
                     // were all done before this D scan began
@@ -1941,12 +1997,14 @@ __device__ __forceinline__ void persistent_body(const DevIndex &ix, const Params
                     phase = PZ_IDLE;
                 }
             }
+        } else if (act == ACT_RUN) {
+            c.expand += run_take(cur, valid, tkl, c.pd, q, P);
         } else if (act == ACT_EXPAND) {
             c.expand++;
             const int i = s_i(cur);
             const int b = pd_base(c, i);
             const int Di = pd_d(c, i), Dn = pd_d(c, i - 1);
-            int rc = expand_children(cur, valid, ok, ol, qd, b, m, maxd, Di, Dn, S, P, c, KT_LOOP ? ix.kt_levels : 0);
+            int rc = expand_children(cur, valid, lo, hi, b, m, maxd, Di, Dn, S, P, c, ix.kt_levels);
             if (rc) {
                 // cannot happen with worst-case stacks; kept as a guard
                 if (endgame) {
@@ -1958,23 +2016,6 @@ __device__ __forceinline__ void persistent_body(const DevIndex &ix, const Params
                 }
             }
         }
-#if BWFM_GENE_TWOSTATE == 1
-        if (act2 && phase == PZ_SEARCH) {
-            c.expand++;
-            const int i2 = s_i(cur2);
-            const int b2 = pd_base(c, i2);
-            const int Di2 = pd_d(c, i2), Dn2 = pd_d(c, i2 - 1);
-            // with two states in flight the stack can outgrow its one-path
-            // worst case; the read then goes to the second pass
-            if (expand_children(cur2, valid2, ok2, ol2, qd, b2, m, maxd, Di2, Dn2, S, P, c,
-                                KT_LOOP ? ix.kt_levels : 0)) {
-                send_to_second_pass(O, r);
-                if (O.expand) O.expand[r] = c.expand;
-                phase = PZ_IDLE;
-            }
-        }
-        if (phase == PZ_IDLE) valid2 = false;
-#endif
     }
     if (A->O.work) {
         if (lane == 0) atomicAdd(&A->O.work[0], (unsigned long long)w_iters);
@@ -2047,6 +2088,7 @@ __global__ __launch_bounds__(BLOCK) void k_align_tasks(DevIndex ix, Params P, co
     bool drained = false;  // wave-uniform: the round's tasks are all taken
     uint32_t s = 0, texp = 0, witer = 0;
     int strand = 0, m = 0, maxd = 0;
+    bool has_n = false;
     uint4 cur = make_uint4(0, 0, 0, 0);
     Seed S{0, 0, 0};
     for (;;) {
@@ -2090,7 +2132,8 @@ __global__ __launch_bounds__(BLOCK) void k_align_tasks(DevIndex ix, Params P, co
                 strand = (int)(ref >> 31);
                 const uint32_t meta = X.slot_meta[s];
                 m = (int)(meta & 1023);
-                maxd = (int)(meta >> 10);
+                maxd = (int)((meta >> 10) & 15);
+                has_n = (meta >> 14) != 0;
                 // the slot's row, read in place: the tasks of one read share
                 // it in the caches
                 c.pd = X.slot_rows + ((size_t)s * 2 + (size_t)strand) * X.dstride;
@@ -2112,7 +2155,7 @@ __global__ __launch_bounds__(BLOCK) void k_align_tasks(DevIndex ix, Params P, co
         drained = drained || __ballot(exhausted) != 0;
         bool query = false, done = false;
         if (busy) {
-            const int rr = resolve<KT_LOOP>(cur, valid, strand, P, c, PH_FAST, POPS_PER_STEP, ix, true);
+            const int rr = resolve(cur, valid, strand, P, c, PH_FAST, POPS_PER_STEP, ix, true);
             if (rr == 3) {
                 // a completed hit; a better score is shared with the read's
                 // other parts at once, a full buffer is first delivered
@@ -2121,8 +2164,8 @@ __global__ __launch_bounds__(BLOCK) void k_align_tasks(DevIndex ix, Params P, co
                     c.best = score;
                     atomicMin(&X.slot_best[s], score);
                 }
-                const uint4 h = make_hit(strand, KT_LOOP ? state_k(ix, strand, cur) : cur.x, cur.y, s_len(cur), score,
-                                         s_nmm(cur), s_ngo(cur), s_nge(cur));
+                const uint2 kl = state_kl(ix, strand, cur);
+                const uint4 h = make_hit(strand, kl.x, kl.y, s_len(cur), score, s_nmm(cur), s_ngo(cur), s_nge(cur));
                 if (record(c, P, h, PH_FAST)) {
                     flush_slot(X, P, s, c);
                     if (record(c, P, h, PH_FAST)) {
@@ -2146,20 +2189,32 @@ __global__ __launch_bounds__(BLOCK) void k_align_tasks(DevIndex ix, Params P, co
             }
             // rr == 2: the pop limit; popping goes on next iteration
         }
-        uint32_t ok[4] = {0, 0, 0, 0}, ol[4] = {0, 0, 0, 0};
         const DevDir qd = pick_dir(ix, strand == 0 ? 1 : 0);
-        if (query) {
-            if (KT_LOOP && (uint32_t)s_len(cur) < ix.kt_levels) {
-                const uint4 *e = reinterpret_cast<const uint4 *>(qd.kt + 2 * kt_children(s_len(cur), cur.x));
-                kt_pick(qd, e[0], e[1], ok, ol);
-            } else {
-                occ4_pair<LW>(ix, qd, cur.x, cur.y + 1, ok, ol);
-            }
+        int q = 0;
+        uint32_t tent = 0;
+        uint32_t lo[4] = {0, 0, 0, 0}, hi[4] = {0, 0, 0, 0};
+        uint4 ta = make_uint4(0, 0, 0, 0), tb = ta;
+        if (query && (uint32_t)s_len(cur) < ix.kt_levels) {
+            const int bound = (P.mode == BWFM_MODE_BEST && c.best != INF_SCORE) ? c.best + P.s_mm : INF_SCORE;
+            q = run_steps(ix, cur, c.pd, maxd, bound, has_n, S, P);
+            tent = q ? run_entry(ix, cur, c.pd, q) : kt_children(s_len(cur), cur.x);
+            const uint4 *e = reinterpret_cast<const uint4 *>(qd.kt) + (tent >> 1);
+            ta = e[0];
+            if (q == 0) tb = e[1];
+        }
+        if (query && tent == 0) rank_children<LW>(ix, qd, cur.x, cur.y + 1, lo, hi, true);
+        if (q) {
+            const uint32_t n =
+                run_take(cur, valid, (tent & 1) ? make_uint2(ta.z, ta.w) : make_uint2(ta.x, ta.y), c.pd, q, P);
+            c.expand += n;
+            texp += n;
+        } else if (query) {
+            if (tent) kt_pick(ta, tb, lo, hi);
             c.expand++;
             texp++;
             const int i = s_i(cur);
-            if (expand_children(cur, valid, ok, ol, qd, pd_base(c, i), m, maxd, pd_d(c, i), pd_d(c, i - 1), S, P, c,
-                                KT_LOOP ? ix.kt_levels : 0)) {
+            if (expand_children(cur, valid, lo, hi, pd_base(c, i), m, maxd, pd_d(c, i), pd_d(c, i - 1), S, P, c,
+                                ix.kt_levels)) {
                 atomicOr(&X.slot_fail[s], 1u);  // cannot happen with worst-case stacks; kept as a guard
                 done = true;
             }
@@ -2577,23 +2632,40 @@ __global__ void k_pair(uint32_t n_pairs, EndView e1, EndView e2, int paired, int
 
 // ------------------------------------------------------------------ short-string table
 
-// Level d of direction `which`'s table from level d - 1: one thread per
+// Level d of direction `which`'s table at kt from level d - 1: one thread per
 // string S of d - 1 bases writes the intervals of aS, a = 0..3, from the
-// rank counts at S's k and l + 1 (the same step the search takes).
+// rank counts at S's k and l + 1 (the same step the search takes).  mark:
+// strings that do not occur get (1 + the number of their first-prepended
+// bases that do, 0) instead of the step's crossed pointers (a string that
+// occurs has l >= 1, since row 0 is the empty suffix's).
 template <int LW>
-__global__ __launch_bounds__(256) void k_kt_level(DevIndex ix, int which, int d) {
+__global__ __launch_bounds__(256) void k_kt_level(DevIndex ix, int which, int d, uint32_t *kt, int mark) {
     const uint64_t p = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x;
     if (p >= ((uint64_t)1 << (2 * (d - 1)))) return;
     const DevDir dd = pick_dir(ix, which);
-    uint32_t *kt = const_cast<uint32_t *>(dd.kt);
     const uint64_t pe = kt_level_start(d - 1) + p;
-    const uint32_t k = kt[2 * pe], l = kt[2 * pe + 1];
-    uint32_t ok[4], ol[4];
-    occ4<LW>(ix, dd, k, ok);
-    occ4<LW>(ix, dd, l + 1, ol);
-    uint4 *dst = reinterpret_cast<uint4 *>(kt + 2 * kt_children(d - 1, (uint32_t)p));
-    dst[0] = make_uint4(dd.C[0] + ok[0], dd.C[0] + ol[0] - 1, dd.C[1] + ok[1], dd.C[1] + ol[1] - 1);
-    dst[1] = make_uint4(dd.C[2] + ok[2], dd.C[2] + ol[2] - 1, dd.C[3] + ok[3], dd.C[3] + ol[3] - 1);
+    const uint2 kl = reinterpret_cast<const uint2 *>(kt)[pe];
+    uint32_t lo[4], hi[4];
+    if (mark && kl.y == 0) {
+#pragma unroll
+        for (int a = 0; a < 4; a++) {
+            lo[a] = kl.x;
+            hi[a] = 1;
+        }
+    } else {
+        rank_children<LW>(ix, dd, kl.x, kl.y + 1, lo, hi, false);
+        if (mark) {
+#pragma unroll
+            for (int a = 0; a < 4; a++)
+                if (lo[a] >= hi[a]) {
+                    lo[a] = (uint32_t)d;
+                    hi[a] = 1;
+                }
+        }
+    }
+    uint4 *dst = reinterpret_cast<uint4 *>(kt + 2 * (size_t)kt_children(d - 1, (uint32_t)p));
+    dst[0] = make_uint4(lo[0], hi[0] - 1, lo[1], hi[1] - 1);
+    dst[1] = make_uint4(lo[2], hi[2] - 1, lo[3], hi[3] - 1);
 }
 
 // level 0: the empty string's interval (0, n)
@@ -2706,9 +2778,9 @@ DevIndex dev_index(const bwfm_index *ix) {
         d.dir[k].sa = (const uint32_t *)ix->d_sa[k];
         for (int a = 0; a < 4; a++) d.dir[k].C[a] = (uint32_t)ix->dir[k].C[a];
         d.dir[k].primary = (uint32_t)ix->dir[k].primary;
-        d.dir[k].kt = (const uint32_t *)ix->d_kt[k];
+        d.dir[k].kt = (const uint32_t *)ix->d_jt[k];
     }
-    d.kt_levels = ix->kt_levels;
+    d.kt_levels = ix->jt_levels;
     d.magic = (uint64_t)(((unsigned __int128)1 << 64) / ix->bpl) + 1;
     d.n = (uint32_t)ix->n;
     d.bpl = ix->bpl;
@@ -3115,6 +3187,54 @@ template <class F> auto by_layout(const bwfm_index *ix, F &&f) {
 
 // ===================================================================== C ABI
 
+// table bytes per direction, padded to a multiple of 256 so that a lane's
+// line-sized, line-aligned read around its 32 entry bytes stays inside
+static uint64_t kt_bytes(uint32_t levels) {
+    return levels ? (kt_level_start((int)levels + 1) * 8 + 255) / 256 * 256 : 0;
+}
+
+// Enqueue the levels of direction d's interval table at kt.
+static void fill_table(const bwfm_index *ix, int d, uint32_t *kt, int levels, int mark, hipStream_t st) {
+    const DevIndex D = dev_index(ix);
+    k_kt_root<<<1, 64, 0, st>>>(kt, (uint32_t)ix->n);
+    for (int lv = 1; lv <= levels; lv++) {
+        const uint64_t np = (uint64_t)1 << (2 * (lv - 1));
+        by_layout(ix, [&](auto t) {
+            k_kt_level<decltype(t)::value><<<blocks(np, 256), 256, 0, st>>>(D, d, lv, kt, mark);
+            return 0;
+        });
+    }
+}
+
+// The search's interval table, made once the rank lines are on the device.
+// Depth: the least with 4^depth >= 2 n, at most 15, so that most of the
+// deepest strings are absent or unique and a run of exact matches ends in
+// its one entry: 100 Mbp: 14 levels, 2.9 GB per direction (a level less left
+// twice the rank queries after the runs).  It takes at most a quarter of the
+// free memory (less deep, or not made at all, where that is short: results
+// do not depend on it).
+int bwfm::build_search_tables(bwfm_index *ix, hipStream_t st) {
+    size_t free_b = 0, total_b = 0;
+    HIPCHK(hipMemGetInfo(&free_b, &total_b));
+    int levels = 1;
+    while (levels < 15 && ((uint64_t)1 << (2 * levels)) < 2 * ix->n) levels++;
+    while (levels > 0 && 2 * kt_bytes((uint32_t)levels) > free_b / 4) levels--;
+    if (levels == 0) return BWFM_OK;
+    const uint64_t bytes = kt_bytes((uint32_t)levels);
+    if (hipMalloc(&ix->d_jt[0], bytes) != hipSuccess || hipMalloc(&ix->d_jt[1], bytes) != hipSuccess) {
+        (void)hipGetLastError();
+        if (ix->d_jt[0]) (void)hipFree(ix->d_jt[0]);
+        ix->d_jt[0] = ix->d_jt[1] = nullptr;
+        return BWFM_OK;
+    }
+    for (int d = 0; d < 2; d++) fill_table(ix, d, (uint32_t *)ix->d_jt[d], levels, 1, st);
+    HIPCHK(hipGetLastError());
+    HIPCHK(hipStreamSynchronize(st));
+    ix->jt_levels = (uint32_t)levels;
+    ix->device_bytes += 2 * bytes;
+    return BWFM_OK;
+}
+
 extern "C" int bwfm_index_upload(bwfm_index *ix, void *stream) {
     if (!ix) return fail(BWFM_E_INVAL, "upload: NULL index");
     std::unique_lock<std::shared_mutex> g(ix->mu);
@@ -3138,15 +3258,11 @@ extern "C" int bwfm_index_upload(bwfm_index *ix, void *stream) {
     bytes += pb;
     HIPCHK(hipStreamSynchronize(st));
     ix->device_bytes = bytes;
+    if (int rc = build_search_tables(ix, st)) return rc;
     ix->device = dev;
     return BWFM_OK;
 }
 
-// table bytes per direction, padded to a multiple of 256 so that a lane's
-// line-sized, line-aligned read around its 32 entry bytes stays inside
-static uint64_t kt_bytes(uint32_t levels) {
-    return levels ? (kt_level_start((int)levels + 1) * 8 + 255) / 256 * 256 : 0;
-}
 
 extern "C" int bwfm_index_kmer_table(bwfm_index *ix, int levels, void *stream) {
     if (!ix) return fail(BWFM_E_INVAL, "kmer_table: NULL index");
@@ -3161,7 +3277,6 @@ extern "C" int bwfm_index_kmer_table(bwfm_index *ix, int levels, void *stream) {
     HIPCHK(hipStreamSynchronize(st));
     ix->device_bytes -= 2 * kt_bytes(ix->kt_levels);
     ix->kt_levels = 0;
-    ix->kt_gen++;
     for (int d = 0; d < 2; d++) {
         if (ix->d_kt[d]) (void)hipFree(ix->d_kt[d]);
         ix->d_kt[d] = nullptr;
@@ -3177,17 +3292,7 @@ extern "C" int bwfm_index_kmer_table(bwfm_index *ix, int levels, void *stream) {
             (void)hipGetLastError();
             return fail(BWFM_E_NOMEM, "kmer_table: device allocation failed");
         }
-    const DevIndex D = dev_index(ix);  // kt_levels 0: the builder reads rank lines only
-    for (int d = 0; d < 2; d++) {
-        k_kt_root<<<1, 64, 0, st>>>((uint32_t *)ix->d_kt[d], (uint32_t)ix->n);
-        for (int lv = 1; lv <= levels; lv++) {
-            const uint64_t np = (uint64_t)1 << (2 * (lv - 1));
-            by_layout(ix, [&](auto t) {
-                k_kt_level<decltype(t)::value><<<blocks(np, 256), 256, 0, st>>>(D, d, lv);
-                return 0;
-            });
-        }
-    }
+    for (int d = 0; d < 2; d++) fill_table(ix, d, (uint32_t *)ix->d_kt[d], levels, 0, st);
     HIPCHK(hipGetLastError());
     HIPCHK(hipStreamSynchronize(st));
     ix->kt_levels = (uint32_t)levels;
@@ -3214,6 +3319,7 @@ extern "C" void bwfm_index_free(bwfm_index *ix) {
         if (ix->d_lines[d]) (void)hipFree(ix->d_lines[d]);
         if (ix->d_sa[d]) (void)hipFree(ix->d_sa[d]);
         if (ix->d_kt[d]) (void)hipFree(ix->d_kt[d]);
+        if (ix->d_jt[d]) (void)hipFree(ix->d_jt[d]);
     }
     if (ix->d_pac) (void)hipFree(ix->d_pac);
     for (auto &kv : ix->ws) {
@@ -3652,7 +3758,6 @@ struct bwfm_pipeline {
     hipStream_t cap = nullptr;  // capture only: nothing runs on it
     bool timed_graph = false, timed_last = false;
     bool timing_uncapturable = false;  // a capture with event nodes failed once
-    uint64_t kt_gen = 0;               // the index's table generation the graph was captured with
 };
 
 namespace {
@@ -3918,7 +4023,7 @@ extern "C" int bwfm_pipeline_run(bwfm_pipeline *pl, int graph, void *stream) {
         return pipe_enqueue_any(pl, st, timed, false);
     }
     if (pl->timing_uncapturable) timed = false;
-    if (pl->exec && (pl->timed_graph != timed || pl->kt_gen != pl->ix->kt_gen)) drop_graph(pl);
+    if (pl->exec && pl->timed_graph != timed) drop_graph(pl);
     if (!pl->exec) {
         // recorded on the pipeline's own stream (the caller's may be the
         // null stream, which cannot be captured); launched on the caller's
@@ -3949,7 +4054,6 @@ extern "C" int bwfm_pipeline_run(bwfm_pipeline *pl, int graph, void *stream) {
         pl->graph = gph;
         pl->exec = ex;
         pl->timed_graph = timed;
-        pl->kt_gen = pl->ix->kt_gen;
     }
     pl->timed_last = pl->timed_graph;
     HIPCHK(hipGraphLaunch(pl->exec, st));

@@ -12,6 +12,8 @@
 
 #include "../../include/bwfm.h"
 
+struct ihipStream_t;  // hipStream_t is a pointer to this
+
 namespace bwfm {
 
 // One direction of the index (0: index of T, 1: index of reverse(T)).
@@ -29,7 +31,7 @@ struct DevDir {
     uint32_t C[4];
     uint32_t primary;
     uint32_t pad;
-    const uint32_t *kt;  // short-string interval table, (k, l) word pairs (kt_level_start), or null
+    const uint32_t *kt;  // the search's interval table, (k, l) word pairs (kt_level_start), or null
 };
 
 struct DevIndex {
@@ -39,7 +41,7 @@ struct DevIndex {
     uint32_t bpl;         // rows per rank line
     uint32_t sa_shift;    // log2(sa_sample)
     uint32_t line_words;  // uint32 words per line
-    uint32_t kt_levels;   // levels of the short-string table (0: none)
+    uint32_t kt_levels;   // levels of the search's interval table (0: none)
 };
 
 // First entry of level d of the short-string table: level 0 is entry 0,
@@ -80,6 +82,10 @@ uint8_t bwt_host(const HostDir &d, uint32_t line_words, uint32_t bpl, uint32_t r
 // of word i / 16 (unused high bits of the last word zero)
 void pack_ref(const uint8_t *text, uint64_t n, std::vector<uint32_t> &out);
 
+// Device structures the search derives from the uploaded index (bwfm.hip):
+// 0 or a bwfm_err.  Without room for them the index works without.
+int build_search_tables(bwfm_index *ix, ihipStream_t *st);
+
 }  // namespace bwfm
 
 struct bwfm_index {
@@ -93,9 +99,10 @@ struct bwfm_index {
     void *d_lines[2] = {nullptr, nullptr};
     void *d_sa[2] = {nullptr, nullptr};
     void *d_pac = nullptr;
-    void *d_kt[2] = {nullptr, nullptr};  // short-string interval tables
+    void *d_jt[2] = {nullptr, nullptr};  // the search's interval tables, made at upload
+    uint32_t jt_levels = 0;              // their depth (0: none)
+    void *d_kt[2] = {nullptr, nullptr};  // the caller's short-string tables (bwfm_index_kmer_table)
     uint32_t kt_levels = 0;
-    uint64_t kt_gen = 0;  // bumped whenever the table changes (captured graphs hold its address)
     uint64_t device_bytes = 0;
     // held shared by calls that only read the index's device state (align,
     // locate, pair), exclusively by calls that change it (upload, the

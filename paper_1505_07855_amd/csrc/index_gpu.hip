@@ -382,8 +382,11 @@ extern "C" int bwfm_build_index_device(const uint8_t *ref, uint64_t n, const bwf
     (void)hipStreamSynchronize(st);
     if (t) (void)hipFree(t);
     if (r) (void)hipFree(r);
+    if (!rc) rc = build_search_tables(ix.get(), st);
     if (rc) {
         for (int d = 0; d < 2; d++) {
+            if (ix->d_jt[d]) (void)hipFree(ix->d_jt[d]);
+            ix->d_jt[d] = nullptr;
             if (ix->d_lines[d]) (void)hipFree(ix->d_lines[d]);
             if (ix->d_sa[d]) (void)hipFree(ix->d_sa[d]);
             ix->d_lines[d] = ix->d_sa[d] = nullptr;
@@ -393,7 +396,6 @@ extern "C" int bwfm_build_index_device(const uint8_t *ref, uint64_t n, const bwf
         return rc;
     }
     ix->device = dev;
-    ix->device_bytes = 0;
     for (int d = 0; d < 2; d++) ix->device_bytes += ix->dir[d].lines.size() * 4 + ix->dir[d].sa.size() * 4;
     ix->device_bytes += pac_words * 4;
     *out = ix.release();
