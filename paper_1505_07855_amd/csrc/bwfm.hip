@@ -44,6 +44,14 @@ using namespace bwfm;
 
 namespace {
 
+// 16- and 8-byte words as native vectors: a search state then lives in
+// registers (HIP's vector classes kept the current state of the batched
+// kernel in scratch memory, a store and a load every iteration).
+typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ u4 mk4(uint32_t x, uint32_t y, uint32_t z, uint32_t w) { return u4{x, y, z, w}; }
+__device__ __forceinline__ u2 mk2(uint32_t x, uint32_t y) { return u2{x, y}; }
+
 // ------------------------------------------------------------------ constants
 
 constexpr int GAP_INS = 1, GAP_DEL = 2;  // gap state of a search state (0: not in a gap)
@@ -138,14 +146,26 @@ __device__ __forceinline__ uint64_t count_of(uint64_t n, const uint64_t *n_dev) 
     return n_dev ? min(*n_dev, n) : n;
 }
 
+// A pointer known to be in device memory.  Pointers that a kernel loads from
+// memory (its argument block) have no address space the compiler can see, so
+// accesses through them become flat ones: these count as LDS accesses too,
+// and every wait for an LDS read then waits for all of them.
+// (The empty asm keeps the two casts from folding away.)
+template <class T> __device__ __forceinline__ T *as_global(T *p) {
+    auto g = (__attribute__((address_space(1))) T *)p;
+    asm("" : "+v"(g));
+    return (T *)g;
+}
+
 // start and length of read r
 __device__ __forceinline__ void read_span(const ReadsView &rd, uint32_t r, uint64_t &o0, uint64_t &len, bool &bad) {
-    o0 = rd.off[r];
+    const uint64_t *off = as_global(rd.off);
+    o0 = off[r];
     if (rd.len) {
-        len = rd.len[r];
+        len = as_global(rd.len)[r];
         bad = false;
     } else {
-        const uint64_t o1 = rd.off[r + 1];
+        const uint64_t o1 = off[r + 1];
         bad = o1 < o0;
         len = bad ? 0 : o1 - o0;
     }
@@ -157,8 +177,8 @@ __device__ __forceinline__ void read_span(const ReadsView &rd, uint32_t r, uint6
 // when they do not.  Each lane's strand pattern and D-array live in LDS,
 // lds_stride bytes per lane.
 struct LaneBufs {
-    uint4 *stack;
-    uint4 *cand;
+    u4 *stack;
+    u4 *cand;
     uint32_t stack_lane_step, stack_stride, stack_cap;
     uint32_t cand_lane_step, cand_stride, cand_cap;
     uint32_t lds_stride;
@@ -207,7 +227,7 @@ constexpr uint32_t SUB128_ROWS = 384;
 // The four intervals of a string's one-base extensions, read from the
 // interval table as two 16-byte words (p: A and C, q: G and T), as [lo, hi):
 // lo = k, hi = l + 1.  An extension that does not occur has lo >= hi.
-__device__ __forceinline__ void kt_pick(uint4 p, uint4 q, uint32_t lo[4], uint32_t hi[4]) {
+__device__ __forceinline__ void kt_pick(u4 p, u4 q, uint32_t lo[4], uint32_t hi[4]) {
     lo[0] = p.x;
     hi[0] = p.y + 1;
     lo[1] = p.z;
@@ -233,9 +253,9 @@ __device__ __forceinline__ void occ4_sub(const DevIndex &ix, const DevDir &d, ui
     const uint32_t line = line_of(ix, i);
     const uint32_t r = i - line * 160u, g = r >> 5;
     const uint32_t *L = d.lines + (size_t)line * 16;
-    const uint4 h = *reinterpret_cast<const uint4 *>(L);       // C, G, T before the line; C boundaries
-    const uint2 b = *reinterpret_cast<const uint2 *>(L + 4);   // G, T boundaries
-    const uint2 w = *reinterpret_cast<const uint2 *>(L + 6 + 2 * g);
+    const u4 h = *reinterpret_cast<const u4 *>(L);       // C, G, T before the line; C boundaries
+    const u2 b = *reinterpret_cast<const u2 *>(L + 4);   // G, T boundaries
+    const u2 w = *reinterpret_cast<const u2 *>(L + 6 + 2 * g);
     const uint32_t m = (1u << (r & 31)) - 1u;
     uint32_t cC = __popc(~w.x & w.y & m), cG = __popc(w.x & ~w.y & m), cT = __popc(w.x & w.y & m);
     if (g) {
@@ -257,9 +277,9 @@ __device__ __forceinline__ void occ4_sub(const DevIndex &ix, const DevDir &d, ui
 __device__ __forceinline__ void occ4_sub_pair(const DevIndex &ix, const DevDir &d, uint32_t i1, uint32_t i2,
                                               uint32_t o1[4], uint32_t o2[4]) {
     const uint32_t l1 = line_of(ix, i1), l2 = line_of(ix, i2);
-    const uint4 *L1 = reinterpret_cast<const uint4 *>(d.lines) + (size_t)l1 * 4;
-    const uint4 *L2 = reinterpret_cast<const uint4 *>(d.lines) + (size_t)l2 * 4;
-    uint4 a[4], b[4];
+    const u4 *L1 = reinterpret_cast<const u4 *>(d.lines) + (size_t)l1 * 4;
+    const u4 *L2 = reinterpret_cast<const u4 *>(d.lines) + (size_t)l2 * 4;
+    u4 a[4], b[4];
 #pragma unroll
     for (int q = 0; q < 4; q++) a[q] = L1[q];
     if (l1 != l2) {
@@ -269,7 +289,7 @@ __device__ __forceinline__ void occ4_sub_pair(const DevIndex &ix, const DevDir &
 #pragma unroll
         for (int q = 0; q < 4; q++) b[q] = a[q];
     }
-    auto count = [&](const uint4(&v)[4], uint32_t i, uint32_t line, uint32_t o[4]) {
+    auto count = [&](const u4(&v)[4], uint32_t i, uint32_t line, uint32_t o[4]) {
         const uint32_t r = i - line * 160u, g = r >> 5;
         // the group's two plane words: words 6 + 2 g and 7 + 2 g of the line
         const uint32_t hi = g == 0 ? v[1].z : g == 1 ? v[2].x : g == 2 ? v[2].z : g == 3 ? v[3].x : v[3].z;
@@ -296,7 +316,7 @@ __device__ __forceinline__ void occ4_sub_pair(const DevIndex &ix, const DevDir &
 // of row 64), b = words 4-7 (boundary words of rows 128 .. 320; read only
 // when the row's group needs one of them), p = the four plane words of the
 // row's 64-row group; r = i's row within the line.
-__device__ __forceinline__ void sub128_count(uint4 h, uint4 b, uint4 p, uint32_t r, uint32_t i, uint32_t primary,
+__device__ __forceinline__ void sub128_count(u4 h, u4 b, u4 p, uint32_t r, uint32_t i, uint32_t primary,
                                              uint32_t o[4]) {
     const uint32_t g = r >> 6, t = r & 63;
     const uint32_t m0 = t >= 32 ? 0xffffffffu : (1u << t) - 1u;
@@ -314,7 +334,7 @@ __device__ __forceinline__ void sub128_count(uint4 h, uint4 b, uint4 p, uint32_t
 
 // The same count from the counts before the line (C, G, T), the row's
 // boundary word (0 for the first 64 rows) and its group's plane words.
-__device__ __forceinline__ void sub128_count3(uint3 h, uint32_t bw, uint4 p, uint32_t r, uint32_t i,
+__device__ __forceinline__ void sub128_count3(uint3 h, uint32_t bw, u4 p, uint32_t r, uint32_t i,
                                               uint32_t primary, uint32_t o[4]) {
     const uint32_t t = r & 63;
     const uint32_t m0 = t >= 32 ? 0xffffffffu : (1u << t) - 1u;
@@ -329,12 +349,12 @@ __device__ __forceinline__ void sub128_count3(uint3 h, uint32_t bw, uint4 p, uin
 }
 
 // One row's pieces of its line: counts, boundary word, group planes.
-__device__ __forceinline__ void sub128_load(const uint32_t *L, uint32_t r, uint3 &h, uint32_t &bw, uint4 &p) {
+__device__ __forceinline__ void sub128_load(const uint32_t *L, uint32_t r, uint3 &h, uint32_t &bw, u4 &p) {
     h = *reinterpret_cast<const uint3 *>(L);
     const uint32_t g = r >> 6;
     bw = 0;
     if (g) bw = L[2 + g];
-    p = reinterpret_cast<const uint4 *>(L)[2 + g];
+    p = reinterpret_cast<const u4 *>(L)[2 + g];
 }
 
 __device__ __forceinline__ void occ4_sub128(const DevIndex &ix, const DevDir &d, uint32_t i, uint32_t o[4]) {
@@ -344,7 +364,7 @@ __device__ __forceinline__ void occ4_sub128(const DevIndex &ix, const DevDir &d,
         const uint32_t r = i - line * SUB128_ROWS;
         uint3 h;
         uint32_t bw;
-        uint4 p;
+        u4 p;
         sub128_load(d.lines + (size_t)line * 32, r, h, bw, p);
         sub128_count3(h, bw, p, r, i, d.primary, o);
         return;
@@ -352,11 +372,11 @@ __device__ __forceinline__ void occ4_sub128(const DevIndex &ix, const DevDir &d,
 #endif
     const uint32_t line = line_of(ix, i);
     const uint32_t r = i - line * SUB128_ROWS;
-    const uint4 *L = reinterpret_cast<const uint4 *>(d.lines) + (size_t)line * 8;
-    const uint4 h = L[0];
-    uint4 b = make_uint4(0, 0, 0, 0);
+    const u4 *L = reinterpret_cast<const u4 *>(d.lines) + (size_t)line * 8;
+    const u4 h = L[0];
+    u4 b = mk4(0, 0, 0, 0);
     if (BWFM_GENE_SUBHDR == 1 || r >= 128) b = L[1];
-    const uint4 p = L[2 + (r >> 6)];
+    const u4 p = L[2 + (r >> 6)];
     sub128_count(h, b, p, r, i, d.primary, o);
 }
 
@@ -370,7 +390,7 @@ __device__ __forceinline__ void occ4_sub128_pair(const DevIndex &ix, const DevDi
         const uint32_t r1 = i1 - l1 * SUB128_ROWS, r2 = i2 - l2 * SUB128_ROWS;
         uint3 h1, h2;
         uint32_t b1, b2;
-        uint4 p1, p2;
+        u4 p1, p2;
         sub128_load(d.lines + (size_t)l1 * 32, r1, h1, b1, p1);
         if (l1 != l2 || (r1 >> 6) != (r2 >> 6)) {
             sub128_load(d.lines + (size_t)l2 * 32, r2, h2, b2, p2);
@@ -386,20 +406,20 @@ __device__ __forceinline__ void occ4_sub128_pair(const DevIndex &ix, const DevDi
 #endif
     const uint32_t l1 = line_of(ix, i1), l2 = line_of(ix, i2);
     const uint32_t r1 = i1 - l1 * SUB128_ROWS, r2 = i2 - l2 * SUB128_ROWS;
-    const uint4 *L1 = reinterpret_cast<const uint4 *>(d.lines) + (size_t)l1 * 8;
-    const uint4 *L2 = reinterpret_cast<const uint4 *>(d.lines) + (size_t)l2 * 8;
+    const u4 *L1 = reinterpret_cast<const u4 *>(d.lines) + (size_t)l1 * 8;
+    const u4 *L2 = reinterpret_cast<const u4 *>(d.lines) + (size_t)l2 * 8;
     const bool same = l1 == l2;
-    const uint4 h1 = L1[0];
-    uint4 b1 = make_uint4(0, 0, 0, 0), h2 = h1, b2 = b1;
+    const u4 h1 = L1[0];
+    u4 b1 = mk4(0, 0, 0, 0), h2 = h1, b2 = b1;
     if (BWFM_GENE_SUBHDR == 1 || r1 >= 128 || (same && r2 >= 128)) b1 = L1[1];
-    const uint4 p1 = L1[2 + (r1 >> 6)];
+    const u4 p1 = L1[2 + (r1 >> 6)];
     if (!same) {
         h2 = L2[0];
         if (BWFM_GENE_SUBHDR == 1 || r2 >= 128) b2 = L2[1];
     } else {
         b2 = b1;
     }
-    uint4 p2 = p1;
+    u4 p2 = p1;
     if (!same || (r1 >> 6) != (r2 >> 6)) p2 = L2[2 + (r2 >> 6)];
     sub128_count(h1, b1, p1, r1, i1, d.primary, o1);
     sub128_count(h2, b2, p2, r2, i2, d.primary, o2);
@@ -431,12 +451,12 @@ __device__ __forceinline__ void occ4(const DevIndex &ix, const DevDir &d, uint32
     }
     uint32_t line = line_of(ix, i);
     int r = (int)(i - line * ix.bpl);
-    const uint4 *L = reinterpret_cast<const uint4 *>(d.lines) + (size_t)line * (LW / 4);
-    uint4 h = L[0];
+    const u4 *L = reinterpret_cast<const u4 *>(d.lines) + (size_t)line * (LW / 4);
+    u4 h = L[0];
     uint32_t cC = 0, cG = 0, cT = 0;
 #pragma unroll
     for (int q = 0; q < LW / 4 - 1; q++) {
-        uint4 v = L[1 + q];
+        u4 v = L[1 + q];
         uint32_t m0 = rows_mask(r - q * 64), m1 = rows_mask(r - q * 64 - 32);
         cT += __popc(v.x & v.y & m0) + __popc(v.z & v.w & m1);
         cG += __popc(v.x & ~v.y & m0) + __popc(v.z & ~v.w & m1);
@@ -466,10 +486,10 @@ __device__ __forceinline__ void occ4_pair(const DevIndex &ix, const DevDir &d, u
         return;
     }
     const uint32_t l1 = line_of(ix, i1), l2 = line_of(ix, i2);
-    const uint4 *L1 = reinterpret_cast<const uint4 *>(d.lines) + (size_t)l1 * (LW / 4);
-    const uint4 *L2 = reinterpret_cast<const uint4 *>(d.lines) + (size_t)l2 * (LW / 4);
+    const u4 *L1 = reinterpret_cast<const u4 *>(d.lines) + (size_t)l1 * (LW / 4);
+    const u4 *L2 = reinterpret_cast<const u4 *>(d.lines) + (size_t)l2 * (LW / 4);
     const bool same = BWFM_GENE_PAIRLINE == 0 && l1 == l2;
-    uint4 a[LW / 4], b[LW / 4];
+    u4 a[LW / 4], b[LW / 4];
 #pragma unroll
     for (int q = 0; q < LW / 4; q++) a[q] = L1[q];
     if (!same) {
@@ -479,14 +499,14 @@ __device__ __forceinline__ void occ4_pair(const DevIndex &ix, const DevDir &d, u
 #pragma unroll
         for (int q = 0; q < LW / 4; q++) b[q] = a[q];
     }
-    const uint4(&A)[LW / 4] = a;
-    const uint4(&B)[LW / 4] = b;
-    auto count = [&](const uint4(&v)[LW / 4], uint32_t i, uint32_t line, uint32_t o[4]) {
+    const u4(&A)[LW / 4] = a;
+    const u4(&B)[LW / 4] = b;
+    auto count = [&](const u4(&v)[LW / 4], uint32_t i, uint32_t line, uint32_t o[4]) {
         const int r = (int)(i - line * ix.bpl);
         uint32_t cC = 0, cG = 0, cT = 0;
 #pragma unroll
         for (int q = 0; q < LW / 4 - 1; q++) {
-            const uint4 w = v[1 + q];
+            const u4 w = v[1 + q];
             const uint32_t m0 = rows_mask(r - q * 64), m1 = rows_mask(r - q * 64 - 32);
             cT += __popc(w.x & w.y & m0) + __popc(w.z & w.w & m1);
             cG += __popc(w.x & ~w.y & m0) + __popc(w.z & ~w.w & m1);
@@ -530,14 +550,14 @@ __device__ __forceinline__ uint32_t occ1(const DevIndex &ix, const DevDir &d, in
     }
     uint32_t line = line_of(ix, i);
     int r = (int)(i - line * ix.bpl);
-    const uint4 *L = reinterpret_cast<const uint4 *>(d.lines) + (size_t)line * (LW / 4);
-    uint4 h = L[0];
+    const u4 *L = reinterpret_cast<const u4 *>(d.lines) + (size_t)line * (LW / 4);
+    u4 h = L[0];
     // rows of base a have high bit (a >> 1) and low bit (a & 1)
     const uint32_t fh = (a & 2) ? 0u : 0xffffffffu, fl = (a & 1) ? 0u : 0xffffffffu;
     uint32_t c = 0;
 #pragma unroll
     for (int q = 0; q < LW / 4 - 1; q++) {
-        uint4 v = L[1 + q];
+        u4 v = L[1 + q];
         c += __popc((v.x ^ fh) & (v.y ^ fl) & rows_mask(r - q * 64));
         c += __popc((v.z ^ fh) & (v.w ^ fl) & rows_mask(r - q * 64 - 32));
     }
@@ -551,11 +571,11 @@ __device__ __forceinline__ uint32_t lf_step(const DevIndex &ix, const DevDir &d,
     if constexpr (LW == LW_SUB128) {
         const uint32_t line = line_of(ix, j);
         const uint32_t r = j - line * SUB128_ROWS;
-        const uint4 *L = reinterpret_cast<const uint4 *>(d.lines) + (size_t)line * 8;
-        const uint4 h = L[0];
-        uint4 b = make_uint4(0, 0, 0, 0);
+        const u4 *L = reinterpret_cast<const u4 *>(d.lines) + (size_t)line * 8;
+        const u4 h = L[0];
+        u4 b = mk4(0, 0, 0, 0);
         if (r >= 128) b = L[1];
-        const uint4 p = L[2 + (r >> 6)];
+        const u4 p = L[2 + (r >> 6)];
         const uint32_t hi = (r & 32) ? p.z : p.x, lo = (r & 32) ? p.w : p.y, s = r & 31;
         const int a = (int)((((hi >> s) & 1u) << 1) | ((lo >> s) & 1u));
         uint32_t o[4];
@@ -578,24 +598,24 @@ __device__ __forceinline__ uint32_t lf_step(const DevIndex &ix, const DevDir &d,
 // w = score | |X| << 10 | lb << 20, where lb = score + minc * D[i] is the
 // state's lower bound on its final score, fixed once the D-array is built.
 // Every field fits: diffs <= 15, score <= 15 * 63, |X| <= 512 + 15.
-__device__ __forceinline__ int entry_lb(uint4 v) { return (int)(v.w >> 20); }
+__device__ __forceinline__ int entry_lb(u4 v) { return (int)(v.w >> 20); }
 
 // hit record, same bytes as bwfm_hit
-__device__ __forceinline__ uint4 make_hit(int strand, uint32_t k, uint32_t l, int len, int score, int nmm, int ngo,
+__device__ __forceinline__ u4 make_hit(int strand, uint32_t k, uint32_t l, int len, int score, int nmm, int ngo,
                                           int nge) {
-    return make_uint4(k, l, (uint32_t)len | ((uint32_t)score << 16),
+    return mk4(k, l, (uint32_t)len | ((uint32_t)score << 16),
                       (uint32_t)strand | ((uint32_t)nmm << 8) | ((uint32_t)ngo << 16) | ((uint32_t)nge << 24));
 }
-__device__ __forceinline__ int h_strand(uint4 h) { return h.w & 255; }
-__device__ __forceinline__ int h_score(uint4 h) { return h.z >> 16; }
-__device__ __forceinline__ int h_len(uint4 h) { return h.z & 0xffff; }
-__device__ __forceinline__ int h_nmm(uint4 h) { return (h.w >> 8) & 255; }
-__device__ __forceinline__ int h_ngo(uint4 h) { return (h.w >> 16) & 255; }
-__device__ __forceinline__ int h_nge(uint4 h) { return (h.w >> 24) & 255; }
-__device__ __forceinline__ int h_diffs(uint4 h) { return h_nmm(h) + h_ngo(h) + h_nge(h); }
+__device__ __forceinline__ int h_strand(u4 h) { return h.w & 255; }
+__device__ __forceinline__ int h_score(u4 h) { return h.z >> 16; }
+__device__ __forceinline__ int h_len(u4 h) { return h.z & 0xffff; }
+__device__ __forceinline__ int h_nmm(u4 h) { return (h.w >> 8) & 255; }
+__device__ __forceinline__ int h_ngo(u4 h) { return (h.w >> 16) & 255; }
+__device__ __forceinline__ int h_nge(u4 h) { return (h.w >> 24) & 255; }
+__device__ __forceinline__ int h_diffs(u4 h) { return h_nmm(h) + h_ngo(h) + h_nge(h); }
 
 // (score, diffs, n_gapo, n_mm) of a is smaller than b's
-__device__ __forceinline__ bool better(uint4 a, uint4 b) {
+__device__ __forceinline__ bool better(u4 a, u4 b) {
     if (h_score(a) != h_score(b)) return h_score(a) < h_score(b);
     if (h_diffs(a) != h_diffs(b)) return h_diffs(a) < h_diffs(b);
     if (h_ngo(a) != h_ngo(b)) return h_ngo(a) < h_ngo(b);
@@ -603,7 +623,7 @@ __device__ __forceinline__ bool better(uint4 a, uint4 b) {
 }
 
 // report order (score, strand, k, len)
-__device__ __forceinline__ bool before(uint4 a, uint4 b) {
+__device__ __forceinline__ bool before(u4 a, u4 b) {
     if (h_score(a) != h_score(b)) return h_score(a) < h_score(b);
     if (h_strand(a) != h_strand(b)) return h_strand(a) < h_strand(b);
     if (a.x != b.x) return a.x < b.x;
@@ -611,7 +631,7 @@ __device__ __forceinline__ bool before(uint4 a, uint4 b) {
 }
 
 struct LaneCtx {
-    uint4 *stack, *cand;
+    u4 *stack, *cand;
     uint8_t *pd;  // LDS, per pattern position i: base code | D[i] << 3
     uint32_t sstride, cstride, stack_cap, cand_cap;
     uint32_t sp, sbase;  // stack entries [sbase, sp) are this lane's pending states
@@ -623,8 +643,8 @@ struct LaneCtx {
 extern __shared__ __align__(16) uint8_t lds_bytes[];
 
 __device__ __forceinline__ void init_ctx(LaneCtx &c, const LaneBufs &B, uint32_t lane) {
-    c.stack = B.stack + (size_t)lane * B.stack_lane_step;
-    c.cand = B.cand + (size_t)lane * B.cand_lane_step;
+    c.stack = as_global(B.stack + (size_t)lane * B.stack_lane_step);
+    c.cand = as_global(B.cand + (size_t)lane * B.cand_lane_step);
     c.pd = lds_bytes + (size_t)threadIdx.x * B.lds_stride;
     c.sstride = B.stack_stride;
     c.cstride = B.cand_stride;
@@ -644,10 +664,10 @@ enum { R_OK = 0, R_STACK = 1, R_CAND = 2 };
 
 // Insert a hit: merge with an equal (strand, k, len), else append.  In the
 // first pass a full buffer is first cleared of hits above best + s_mm.
-__device__ int record(LaneCtx &c, const Params &P, uint4 h, int phase) {
+__device__ int record(LaneCtx &c, const Params &P, u4 h, int phase) {
     if (phase == PH_BEST) return R_OK;
     for (uint32_t j = 0; j < c.ncand; j++) {
-        uint4 o = c.cand[(size_t)j * c.cstride];
+        u4 o = c.cand[(size_t)j * c.cstride];
         if (h_strand(o) == h_strand(h) && o.x == h.x && h_len(o) == h_len(h)) {
             if (better(h, o)) c.cand[(size_t)j * c.cstride] = h;
             return R_OK;
@@ -656,7 +676,7 @@ __device__ int record(LaneCtx &c, const Params &P, uint4 h, int phase) {
     if (c.ncand == c.cand_cap && phase == PH_FAST && P.mode == BWFM_MODE_BEST) {
         uint32_t w = 0;
         for (uint32_t j = 0; j < c.ncand; j++) {
-            uint4 o = c.cand[(size_t)j * c.cstride];
+            u4 o = c.cand[(size_t)j * c.cstride];
             if (h_score(o) <= c.best + P.s_mm) c.cand[(size_t)(w++) * c.cstride] = o;
         }
         c.ncand = w;
@@ -673,7 +693,7 @@ __device__ int record(LaneCtx &c, const Params &P, uint4 h, int phase) {
 // trips instead of one per D-array step; only dwords holding read bases are
 // touched.  Returns whether the read holds an N.
 __device__ __forceinline__ bool stage_read(uint8_t *row, const uint8_t *W, int m) {
-    const uint32_t *A = reinterpret_cast<const uint32_t *>(reinterpret_cast<uintptr_t>(W) & ~uintptr_t(3));
+    const uint32_t *A = as_global(reinterpret_cast<const uint32_t *>(reinterpret_cast<uintptr_t>(W) & ~uintptr_t(3)));
     const int off = (int)(reinterpret_cast<uintptr_t>(W) & 3);
     const int ndw = (off + m + 3) >> 2;
     uint32_t n_any = 0;
@@ -708,22 +728,22 @@ __device__ __forceinline__ Seed seed_of(const Params &P, int m) {
 }
 
 // fields of a packed state (see pack)
-__device__ __forceinline__ int s_i(uint4 s) { return (int)(s.z & 1023) - 1; }
-__device__ __forceinline__ int s_gs(uint4 s) { return (s.z >> 10) & 3; }
-__device__ __forceinline__ int s_nmm(uint4 s) { return (s.z >> 12) & 15; }
-__device__ __forceinline__ int s_ngo(uint4 s) { return (s.z >> 16) & 15; }
-__device__ __forceinline__ int s_nge(uint4 s) { return (s.z >> 20) & 15; }
-__device__ __forceinline__ int s_sd(uint4 s) { return (s.z >> 24) & 15; }
-__device__ __forceinline__ int s_score(uint4 s) { return s.w & 1023; }
-__device__ __forceinline__ int s_len(uint4 s) { return (s.w >> 10) & 1023; }
+__device__ __forceinline__ int s_i(u4 s) { return (int)(s.z & 1023) - 1; }
+__device__ __forceinline__ int s_gs(u4 s) { return (s.z >> 10) & 3; }
+__device__ __forceinline__ int s_nmm(u4 s) { return (s.z >> 12) & 15; }
+__device__ __forceinline__ int s_ngo(u4 s) { return (s.z >> 16) & 15; }
+__device__ __forceinline__ int s_nge(u4 s) { return (s.z >> 20) & 15; }
+__device__ __forceinline__ int s_sd(u4 s) { return (s.z >> 24) & 15; }
+__device__ __forceinline__ int s_score(u4 s) { return s.w & 1023; }
+__device__ __forceinline__ int s_len(u4 s) { return (s.w >> 10) & 1023; }
 
 // Interval of a completed state: (x, y) itself, or, while X is shorter than
 // the interval table's levels (x holds the code of X), X's table entry on
 // the strand's search index.
-__device__ __forceinline__ uint2 state_kl(const DevIndex &ix, int strand, uint4 s) {
+__device__ __forceinline__ u2 state_kl(const DevIndex &ix, int strand, u4 s) {
     const int len = s_len(s);
-    if (len >= (int)ix.kt_levels) return make_uint2(s.x, s.y);
-    const uint2 *kt = reinterpret_cast<const uint2 *>(strand == 0 ? ix.dir[1].kt : ix.dir[0].kt);
+    if (len >= (int)ix.kt_levels) return mk2(s.x, s.y);
+    const u2 *kt = reinterpret_cast<const u2 *>(strand == 0 ? ix.dir[1].kt : ix.dir[0].kt);
     return kt[kt_start32(len) + s.x];
 }
 
@@ -766,7 +786,7 @@ __device__ __forceinline__ uint32_t rev_digits(uint32_t c, int q) {
 // to the deepest level, or 0 when a difference may still be taken on the
 // way: D falls towards the pattern's start, so no difference fits anywhere
 // in the run when none fits with the D of its end.
-__device__ __forceinline__ int run_steps(const DevIndex &ix, uint4 cur, const uint8_t *pd, int maxd, int bound,
+__device__ __forceinline__ int run_steps(const DevIndex &ix, u4 cur, const uint8_t *pd, int maxd, int bound,
                                          bool has_n, const Seed &S, const Params &P) {
     const int q = (int)ix.kt_levels - s_len(cur);
     const int e = s_i(cur) - q;
@@ -778,12 +798,12 @@ __device__ __forceinline__ int run_steps(const DevIndex &ix, uint4 cur, const ui
     return none ? q : 0;
 }
 // Table entry of the run of q steps from cur.
-__device__ __forceinline__ uint32_t run_entry(const DevIndex &ix, uint4 cur, const uint8_t *pd, int q) {
+__device__ __forceinline__ uint32_t run_entry(const DevIndex &ix, u4 cur, const uint8_t *pd, int q) {
     return kt_start32((int)ix.kt_levels) + ((cur.x << (2 * q)) | row_code(pd, s_i(cur) + 1 - q, q));
 }
 // cur after its run: the state q steps on, or dropped (valid cleared) when
 // its string stops occurring.  Returns the states the run expanded.
-__device__ __forceinline__ uint32_t run_take(uint4 &cur, bool &valid, uint2 kl, const uint8_t *pd, int q,
+__device__ __forceinline__ uint32_t run_take(u4 &cur, bool &valid, u2 kl, const uint8_t *pd, int q,
                                              const Params &P) {
     if (kl.y == 0) {  // absent: kl.x - 1 of the bases occur
         valid = false;
@@ -800,8 +820,8 @@ __device__ __forceinline__ uint32_t run_take(uint4 &cur, bool &valid, uint2 kl, 
 }
 
 // the empty string's interval, nothing consumed, lower bound minc * D[m - 1]
-__device__ __forceinline__ uint4 root_state(const DevIndex &ix, int m, int lb) {
-    return make_uint4(0u, ix.n, (uint32_t)m, (uint32_t)lb << 20);
+__device__ __forceinline__ u4 root_state(const DevIndex &ix, int m, int lb) {
+    return mk4(0u, ix.n, (uint32_t)m, (uint32_t)lb << 20);
 }
 
 // Advance the search until the current state needs expanding: pop, drop
@@ -811,7 +831,7 @@ __device__ __forceinline__ uint4 root_state(const DevIndex &ix, int m, int lb) {
 // the pop limit was reached first, 3 when cur is a completed hit left for
 // the caller to record (only with defer), or -R_CAND when the hit buffer
 // overflowed.
-__device__ int resolve(uint4 &cur, bool &valid, int strand, const Params &P, LaneCtx &c, int phase, int max_pops,
+__device__ int resolve(u4 &cur, bool &valid, int strand, const Params &P, LaneCtx &c, int phase, int max_pops,
                        const DevIndex &ix, bool defer = false) {
     for (int pops = 0;;) {
         const int bound = (P.mode == BWFM_MODE_BEST && c.best != INF_SCORE) ? c.best + P.s_mm : INF_SCORE;
@@ -831,7 +851,7 @@ __device__ int resolve(uint4 &cur, bool &valid, int strand, const Params &P, Lan
             if (defer) return 3;
             const int score = s_score(cur);
             if (score < c.best) c.best = score;
-            const uint2 kl = state_kl(ix, strand, cur);
+            const u2 kl = state_kl(ix, strand, cur);
             int rc = record(c, P, make_hit(strand, kl.x, kl.y, s_len(cur), score, s_nmm(cur), s_ngo(cur), s_nge(cur)),
                             phase);
             if (rc) return -rc;
@@ -848,7 +868,7 @@ __device__ int resolve(uint4 &cur, bool &valid, int strand, const Params &P, Lan
 // the fixed order (match, mismatches by base, insertion, deletions by base);
 // the first surviving one becomes cur, the others are pushed with their
 // lower bounds.  Returns R_OK or R_STACK.
-__device__ int expand_children(uint4 &cur, bool &valid, const uint32_t (&lo)[4], const uint32_t (&hi)[4], int b, int m, int maxd, int Di, int Dn, const Seed &S,
+__device__ int expand_children(u4 &cur, bool &valid, const uint32_t (&lo)[4], const uint32_t (&hi)[4], int b, int m, int maxd, int Di, int Dn, const Seed &S,
                                const Params &P, LaneCtx &c, uint32_t K) {
     const int i = s_i(cur), gs = s_gs(cur), ngo = s_ngo(cur), nge = s_nge(cur), sd = s_sd(cur);
     const int score = s_score(cur), len = s_len(cur);
@@ -874,7 +894,7 @@ __device__ int expand_children(uint4 &cur, bool &valid, const uint32_t (&lo)[4],
         valid = false;
         return R_STACK;
     }
-    uint4 pend = cur;
+    u4 pend = cur;
     bool have = false;
     const int rc = R_OK;
     auto offer = [&](uint32_t k, uint32_t l, uint32_t z, uint32_t w) {
@@ -882,7 +902,7 @@ __device__ int expand_children(uint4 &cur, bool &valid, const uint32_t (&lo)[4],
             c.stack[(size_t)c.sp * c.sstride] = pend;
             c.sp++;
         }
-        pend = make_uint4(k, l, z, w);
+        pend = mk4(k, l, z, w);
         have = true;
     };
     // deletions: reference base a between read bases i and i + 1 (same i)
@@ -972,7 +992,7 @@ __device__ bool build_d(const DevIndex &ix, const DevDir &od, int m, int strand,
             const int r = min((int)ix.kt_levels, m - i);
             uint32_t code = rev_digits(row_code(c.pd, i, r), r);
             if (strand) code ^= (1u << (2 * r)) - 1u;
-            const uint2 kl = reinterpret_cast<const uint2 *>(od.kt)[kt_start32(r) + code];
+            const u2 kl = reinterpret_cast<const u2 *>(od.kt)[kt_start32(r) + code];
             if (kl.y) {
                 row_fill(c.pd, i, r, z, strand);
                 k = kl.x;
@@ -1017,7 +1037,7 @@ template <int LW>
 __device__ int search_strand(const DevIndex &ix, const DevDir &sd_, int m, int strand, int maxd, bool has_n,
                              const Params &P, LaneCtx &c, int phase) {
     const Seed S = seed_of(P, m);
-    uint4 cur = root_state(ix, m, P.minc * pd_d(c, m - 1));
+    u4 cur = root_state(ix, m, P.minc * pd_d(c, m - 1));
     bool valid = true;
     c.sp = 0;
     for (;;) {
@@ -1029,11 +1049,11 @@ __device__ int search_strand(const DevIndex &ix, const DevDir &sd_, int m, int s
             const int bound = (P.mode == BWFM_MODE_BEST && c.best != INF_SCORE) ? c.best + P.s_mm : INF_SCORE;
             const int q = run_steps(ix, cur, c.pd, maxd, bound, has_n, S, P);
             if (q) {
-                const uint2 kl = reinterpret_cast<const uint2 *>(sd_.kt)[run_entry(ix, cur, c.pd, q)];
+                const u2 kl = reinterpret_cast<const u2 *>(sd_.kt)[run_entry(ix, cur, c.pd, q)];
                 c.expand += run_take(cur, valid, kl, c.pd, q, P);
                 continue;
             }
-            const uint4 *e = reinterpret_cast<const uint4 *>(sd_.kt + 2 * (size_t)kt_children(s_len(cur), cur.x));
+            const u4 *e = reinterpret_cast<const u4 *>(sd_.kt + 2 * (size_t)kt_children(s_len(cur), cur.x));
             kt_pick(e[0], e[1], lo, hi);
         } else {
             rank_children<LW>(ix, sd_, cur.x, cur.y + 1, lo, hi, false);
@@ -1058,7 +1078,7 @@ __device__ uint32_t finish(LaneCtx &c, const Params &P, uint8_t &status, uint32_
     uint32_t n = 0;
     uint64_t c1 = 0, c2 = 0;
     for (uint32_t j = 0; j < c.ncand; j++) {
-        uint4 h = c.cand[(size_t)j * c.cstride];
+        u4 h = c.cand[(size_t)j * c.cstride];
         int sc = h_score(h);
         if (P.mode == BWFM_MODE_ALL || sc <= S + P.s_mm) c.cand[(size_t)(n++) * c.cstride] = h;
         uint64_t w = (uint64_t)h.y - h.x + 1;
@@ -1075,14 +1095,14 @@ __device__ uint32_t finish(LaneCtx &c, const Params &P, uint8_t &status, uint32_
     const bool keep2 = c1 <= (uint64_t)P.max_best;
     uint32_t r = 0;
     for (uint32_t j = 0; j < n; j++) {
-        uint4 h = c.cand[(size_t)j * c.cstride];
+        u4 h = c.cand[(size_t)j * c.cstride];
         if (P.mode == BWFM_MODE_ALL || h_score(h) == S || keep2) c.cand[(size_t)(r++) * c.cstride] = h;
     }
     for (uint32_t j = 1; j < r; j++) {  // insertion sort by (score, strand, k, len)
-        uint4 v = c.cand[(size_t)j * c.cstride];
+        u4 v = c.cand[(size_t)j * c.cstride];
         uint32_t q = j;
         while (q > 0) {
-            uint4 u = c.cand[(size_t)(q - 1) * c.cstride];
+            u4 u = c.cand[(size_t)(q - 1) * c.cstride];
             if (!before(v, u)) break;
             c.cand[(size_t)q * c.cstride] = u;
             q--;
@@ -1115,7 +1135,7 @@ struct ReadOut {
     uint32_t *n_rep, *c1, *c2;
     uint8_t *status;
     uint32_t *slow_list, *n_slow;
-    uint4 *stage;                    // reported hits, a block per read
+    u4 *stage;                    // reported hits, a block per read
     unsigned long long *stage_used;  // staging slots taken
     uint64_t stage_cap;
     uint64_t *stage_off;             // per read: first staging slot
@@ -1125,9 +1145,9 @@ struct ReadOut {
 };
 
 __device__ __forceinline__ void send_to_second_pass(const ReadOut &O, uint32_t r) {
-    O.status[r] = ST_RESEARCH;
-    O.n_rep[r] = 0;
-    O.slow_list[atomicAdd(O.n_slow, 1u)] = r;
+    as_global(O.status)[r] = ST_RESEARCH;
+    as_global(O.n_rep)[r] = 0;
+    as_global(O.slow_list)[atomicAdd(as_global(O.n_slow), 1u)] = r;
 }
 
 // Move a read's nr reported hits (the front of its hit buffer) to the
@@ -1136,10 +1156,11 @@ __device__ __forceinline__ void send_to_second_pass(const ReadOut &O, uint32_t r
 // offsets scan then reports what is needed) and nothing is copied.
 __device__ void stage_hits(const LaneCtx &c, const ReadOut &O, uint32_t r, uint32_t nr) {
     if (!nr) return;
-    const unsigned long long off = atomicAdd(O.stage_used, (unsigned long long)nr);
+    const unsigned long long off = atomicAdd(as_global(O.stage_used), (unsigned long long)nr);
     if (off + nr > O.stage_cap) return;
-    for (uint32_t j = 0; j < nr; j++) O.stage[off + j] = c.cand[(size_t)j * c.cstride];
-    O.stage_off[r] = off;
+    u4 *stage = as_global(O.stage);
+    for (uint32_t j = 0; j < nr; j++) stage[off + j] = c.cand[(size_t)j * c.cstride];
+    as_global(O.stage_off)[r] = off;
 }
 
 // Canonicalise a finished read and move its reported hits to the staging
@@ -1148,12 +1169,12 @@ __device__ void publish(LaneCtx &c, const Params &P, const ReadOut &O, uint32_t 
     uint8_t st;
     uint32_t a, b;
     uint32_t nr = finish(c, P, st, a, b);
-    if (O.expand) O.expand[r] = c.expand;
+    if (O.expand) as_global(O.expand)[r] = c.expand;
     stage_hits(c, O, r, nr);
-    O.n_rep[r] = nr;
-    O.status[r] = st | extra;
-    O.c1[r] = a;
-    O.c2[r] = b;
+    as_global(O.n_rep)[r] = nr;
+    as_global(O.status)[r] = st | extra;
+    as_global(O.c1)[r] = a;
+    as_global(O.c2)[r] = b;
 }
 
 // validity of read r: 0 = search it, 1 = done (empty or invalid, outputs written)
@@ -1163,16 +1184,15 @@ __device__ __forceinline__ int check_read(const ReadsView &rd, const Params &P, 
     bool bad;
     read_span(rd, r, o0, len, bad);
     m = (int)len;
-    maxd = rd.maxd ? rd.maxd[r] : P.max_diff;
-    O.n_rep[r] = 0;
-    O.c1[r] = O.c2[r] = 0;
-    if (O.expand) O.expand[r] = 0;
-    if (bad || len > rd.max_len || len > BWFM_MAX_READ || maxd > BWFM_MAX_DIFF) {
-        O.status[r] = BWFM_ST_INVALID;
-        return 1;
-    }
-    if (m == 0) {
-        O.status[r] = 0;
+    maxd = rd.maxd ? as_global(rd.maxd)[r] : P.max_diff;
+    // (a read that is searched gets its outputs when it is published)
+    const bool invalid = bad || len > rd.max_len || len > BWFM_MAX_READ || maxd > BWFM_MAX_DIFF;
+    if (invalid || m == 0) {
+        as_global(O.n_rep)[r] = 0;
+        as_global(O.c1)[r] = 0;
+        as_global(O.c2)[r] = 0;
+        if (O.expand) as_global(O.expand)[r] = 0;
+        as_global(O.status)[r] = invalid ? BWFM_ST_INVALID : 0;
         return 1;
     }
     return 0;
@@ -1226,18 +1246,18 @@ struct SplitBufs {
     uint32_t *slot_own;     // hits in that buffer when the first pass finished the read
     int *slot_obest;        // and its best score then
     uint8_t *slot_rows;     // per slot and strand: the pattern and D-array row, dstride bytes
-    uint4 *slot_hits;       // per slot: SLOT_HITS hits
-    uint4 *tasks[2];        // task states, by generation parity
+    u4 *slot_hits;       // per slot: SLOT_HITS hits
+    u4 *tasks[2];        // task states, by generation parity
     uint32_t *task_ref[2];  // slot | strand << 31, or TASK_EMPTY
     uint32_t *ctl;          // SPLIT_CTL control words
-    uint4 *lane_cand;       // the first pass's hit buffers, FAST_CAND per lane
+    u4 *lane_cand;       // the first pass's hit buffers, FAST_CAND per lane
     uint32_t slot_cap, task_cap, dstride;
     uint32_t budget;  // expansions of a lane's part of a read before it is split (endgame); 0: off
     uint32_t count;   // nonzero: the parts' expansions are summed (per-read work counters)
 };
 
 __device__ __forceinline__ uint32_t ld_agent(const uint32_t *p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return __hip_atomic_load(as_global(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Reserve cnt task entries of generation g at off.  False when they do not
@@ -1254,10 +1274,10 @@ __device__ bool take_tasks(const SplitBufs &X, uint32_t g, uint32_t cnt, uint32_
 
 // Write cur when has_cur, then the lane's pending stack entries, to the
 // entries reserved at off in generation g; the lane's stack is left empty.
-__device__ void put_tasks(const SplitBufs &X, uint32_t g, uint32_t off, uint32_t ref, LaneCtx &c, uint4 cur,
+__device__ void put_tasks(const SplitBufs &X, uint32_t g, uint32_t off, uint32_t ref, LaneCtx &c, u4 cur,
                           bool has_cur) {
-    uint4 *T = X.tasks[g & 1];
-    uint32_t *R = X.task_ref[g & 1];
+    u4 *T = as_global(X.tasks[g & 1]);
+    uint32_t *R = as_global(X.task_ref[g & 1]);
     if (has_cur) {
         T[off] = cur;
         R[off] = ref;
@@ -1298,9 +1318,9 @@ __device__ void flush_slot(const SplitBufs &X, const Params &P, uint32_t s, Lane
         if (off + keep > SLOT_HITS) {  // the collection left room for FAST_CAND of them
             atomicOr(&X.slot_fail[s], 1u);
         } else {
-            uint4 *dst = X.slot_hits + (size_t)s * SLOT_HITS;
+            u4 *dst = X.slot_hits + (size_t)s * SLOT_HITS;
             for (uint32_t j = 0; j < c.ncand; j++) {
-                const uint4 h = c.cand[(size_t)j * c.cstride];
+                const u4 h = c.cand[(size_t)j * c.cstride];
                 if (h_score(h) <= bound) dst[off++] = h;
             }
         }
@@ -1322,7 +1342,7 @@ constexpr int SH_SLOT_SHIFT = 5;
 // time.  False, with the lane's search unchanged, when no slot or task room
 // is left.
 __device__ bool split_part(const SplitBufs &X, uint32_t r, uint32_t owner, int strand, int m, int maxd, bool has_n,
-                           int best, LaneCtx &c, uint4 cur, bool valid, int &fl) {
+                           int best, LaneCtx &c, u4 cur, bool valid, int &fl) {
     const uint32_t cnt = (valid ? 1u : 0u) + (c.sp - c.sbase);
     const bool had = (fl >> SH_SLOT_SHIFT) != 0;
     if (!had && ld_agent(&X.ctl[0]) >= X.slot_cap) return false;
@@ -1378,8 +1398,8 @@ __global__ void k_split_collect(SplitBufs X) {
     const uint32_t s = blockIdx.x * blockDim.x + threadIdx.x;
     if (s >= min(X.ctl[0], X.slot_cap) || X.slot_fail[s]) return;
     const uint32_t n = X.slot_own[s];
-    const uint4 *src = X.lane_cand + (size_t)X.slot_owner[s] * FAST_CAND;
-    uint4 *dst = X.slot_hits + (size_t)s * SLOT_HITS;
+    const u4 *src = X.lane_cand + (size_t)X.slot_owner[s] * FAST_CAND;
+    u4 *dst = X.slot_hits + (size_t)s * SLOT_HITS;
     for (uint32_t j = 0; j < n; j++) dst[j] = src[j];
     X.slot_nhit[s] = n;
     if (X.slot_obest[s] < X.slot_best[s]) X.slot_best[s] = X.slot_obest[s];
@@ -1404,7 +1424,7 @@ __global__ void k_split_publish(Params P, SplitBufs X, ReadOut O) {
     c.cstride = 1;
     uint32_t w = 0;
     for (uint32_t j = 0; j < nh; j++) {
-        const uint4 h = c.cand[j];
+        const u4 h = c.cand[j];
         uint32_t q = 0;
         while (q < w && !(h_strand(c.cand[q]) == h_strand(h) && c.cand[q].x == h.x && h_len(c.cand[q]) == h_len(h))) q++;
         if (q == w)
@@ -1454,7 +1474,7 @@ struct WaveShare {
     int pending[64];    // helper lanes still searching donated subtrees
     int flags[64];      // SH_FAIL: the hit buffer overflowed; SH_HELPED; the read's slot
     int hexp[64];       // states expanded by helpers
-    uint4 box[64];      // donated states
+    u4 box[64];      // donated states
     uint32_t meta[64];  // owner lane | strand << 6 | budget << 7 | m << 11 | the read holds an N << 21
 };
 
@@ -1543,13 +1563,13 @@ __global__ __launch_bounds__(BLOCK) void k_dscan(DevIndex ix, ReadsView rd, Para
 // round trips (one per dword when each load waits for the store before it,
 // which the compiler must assume may alias it).
 __device__ __forceinline__ void load_drow(uint8_t *pd, const uint8_t *row, int m) {
-    const uint4 *src = reinterpret_cast<const uint4 *>(row);
+    const u4 *src = as_global(reinterpret_cast<const u4 *>(row));
     uint32_t *dst = reinterpret_cast<uint32_t *>(pd);
     const int ndw = (m + 3) >> 2;
     for (int q0 = 0; 4 * q0 < ndw; q0 += 4) {
-        uint4 v[4];
+        u4 v[4];
 #pragma unroll
-        for (int j = 0; j < 4; j++) v[j] = 4 * (q0 + j) < ndw ? src[q0 + j] : make_uint4(0, 0, 0, 0);
+        for (int j = 0; j < 4; j++) v[j] = 4 * (q0 + j) < ndw ? src[q0 + j] : mk4(0, 0, 0, 0);
 #pragma unroll
         for (int j = 0; j < 4; j++) {
             const int k = 4 * (q0 + j);
@@ -1568,7 +1588,11 @@ __global__ void k_set_args(PersistentArgs *dst, PersistentArgs a) {
 // DP: the D-arrays come from the pre-pass (k_dscan); otherwise the loop
 // scans them itself.
 template <int LW, bool DP>
-__device__ __forceinline__ void persistent_body(const DevIndex &ix, const Params &P, const PersistentArgs *A) {
+__device__ __forceinline__ void persistent_body(const DevIndex &ix, const Params &P, const PersistentArgs *Aarg) {
+    // the argument block, through an address space the compiler sees
+    using GlobalArgs = const __attribute__((address_space(1))) PersistentArgs;
+    GlobalArgs *Ag = (GlobalArgs *)Aarg;
+    const PersistentArgs *A = (const PersistentArgs *)Ag;
     const uint32_t gl = blockIdx.x * blockDim.x + threadIdx.x;
     const int lane = threadIdx.x & 63;
     const uint32_t wave0 = threadIdx.x & ~63u;  // the wave's first thread in the block
@@ -1579,7 +1603,7 @@ __device__ __forceinline__ void persistent_body(const DevIndex &ix, const Params
     init_ctx(c, A->B, gl);
     c.sstride = 1;  // persistent lanes own contiguous runs
     c.cstride = 1;
-    uint4 *const own_cand = c.cand;
+    u4 *const own_cand = c.cand;
     uint8_t *const own_pd = c.pd;
 
     // A batch of fewer reads than the grid has lanes is spread evenly: each
@@ -1606,7 +1630,7 @@ __device__ __forceinline__ void persistent_body(const DevIndex &ix, const Params
     uint32_t dk = 0, dl = 0;
     bool dfresh = true;  // at the start of a segment
     // search state
-    uint4 cur = make_uint4(0, 0, 0, 0);
+    u4 cur = mk4(0, 0, 0, 0);
     bool valid = false;
     Seed S{0, 0, 0};
     // work statistics (measurement only)
@@ -1615,7 +1639,8 @@ __device__ __forceinline__ void persistent_body(const DevIndex &ix, const Params
     for (;;) {
         // an opaque step on the pointer keeps the argument loads inside the
         // loop, next to their uses
-        asm volatile("" : "+s"(A));
+        asm volatile("" : "+s"(Ag));
+        A = (const PersistentArgs *)Ag;
         const ReadsView &rd = A->rd;
         const ReadOut &O = A->O;
         uint32_t *const next_read = A->next_read;
@@ -1630,7 +1655,7 @@ __device__ __forceinline__ void persistent_body(const DevIndex &ix, const Params
 #endif
             const int leader = __ffsll(wm) - 1;
             uint32_t base = 0;
-            if (lane == leader) base = atomicAdd(next_read, (uint32_t)__popcll(wm));
+            if (lane == leader) base = atomicAdd(as_global(next_read), (uint32_t)__popcll(wm));
             base = __shfl(base, leader);
             if (want) {
                 const uint32_t rr = base + (uint32_t)__popcll(wm & ((1ULL << lane) - 1));
@@ -1849,7 +1874,7 @@ __device__ __forceinline__ void persistent_body(const DevIndex &ix, const Params
                     if (sb < c.best) c.best = sb;
                     const int score = s_score(cur);
                     if (score < c.best) c.best = score;
-                    const uint2 kl = state_kl(ix, strand, cur);
+                    const u2 kl = state_kl(ix, strand, cur);
                     const int rc = record(c, P,
                                           make_hit(strand, kl.x, kl.y, s_len(cur), score, s_nmm(cur), s_ngo(cur),
                                                    s_nge(cur)),
@@ -1928,15 +1953,15 @@ __device__ __forceinline__ void persistent_body(const DevIndex &ix, const Params
         uint32_t lo[4] = {0, 0, 0, 0}, hi[4] = {0, 0, 0, 0};
         const DevDir qd = pick_dir(ix, qdir);
         if (O.work) w_query += query || tent;
-        uint4 ta = make_uint4(0, 0, 0, 0), tb = ta;
+        u4 ta = mk4(0, 0, 0, 0), tb = ta;
         if (tent) {
-            const uint4 *e = reinterpret_cast<const uint4 *>(qd.kt) + (tent >> 1);
+            const u4 *e = reinterpret_cast<const u4 *>(qd.kt) + (tent >> 1);
             ta = e[0];
             if (q == 0) tb = e[1];
         }
         if (query) rank_children<LW>(ix, qd, q1, q2, lo, hi, true);
         if (tent && q == 0) kt_pick(ta, tb, lo, hi);
-        const uint2 tkl = (tent & 1) ? make_uint2(ta.z, ta.w) : make_uint2(ta.x, ta.y);
+        const u2 tkl = (tent & 1) ? mk2(ta.z, ta.w) : mk2(ta.x, ta.y);
 
         // consume
         if (!DP && (act == ACT_DSTEP || act == ACT_DRUN)) {
@@ -2075,8 +2100,11 @@ __global__ void k_set_task_args(TaskArgs *dst, TaskArgs a) {
 constexpr uint32_t DRAIN_MIN = 256;
 constexpr int TASK_REFILL = 32;  // idle lanes of a wave that make it take new tasks
 template <int LW>
-__global__ __launch_bounds__(BLOCK) void k_align_tasks(DevIndex ix, Params P, const TaskArgs *A, uint32_t g,
+__global__ __launch_bounds__(BLOCK) void k_align_tasks(DevIndex ix, Params P, const TaskArgs *Aarg, uint32_t g,
                                                        uint32_t drain) {
+    using GlobalArgs = const __attribute__((address_space(1))) TaskArgs;
+    GlobalArgs *Ag = (GlobalArgs *)Aarg;
+    const TaskArgs *A = (const TaskArgs *)Ag;
     const uint32_t ntask = min(ld_agent(&A->X.ctl[1 + g]), A->X.task_cap);
     if (ntask == 0) return;  // the whole grid: nothing was split
     const int lane = threadIdx.x & 63;
@@ -2089,10 +2117,11 @@ __global__ __launch_bounds__(BLOCK) void k_align_tasks(DevIndex ix, Params P, co
     uint32_t s = 0, texp = 0, witer = 0;
     int strand = 0, m = 0, maxd = 0;
     bool has_n = false;
-    uint4 cur = make_uint4(0, 0, 0, 0);
+    u4 cur = mk4(0, 0, 0, 0);
     Seed S{0, 0, 0};
     for (;;) {
-        asm volatile("" : "+s"(A));
+        asm volatile("" : "+s"(Ag));
+        A = (const TaskArgs *)Ag;
         const SplitBufs &X = A->X;
         witer++;
         // a wave learns that the round's tasks are all taken when one of
@@ -2124,24 +2153,24 @@ __global__ __launch_bounds__(BLOCK) void k_align_tasks(DevIndex ix, Params P, co
             if (want && t >= ntask) exhausted = true;
         }
         if (want && !exhausted) {
-            const uint32_t ref = X.task_ref[g & 1][t];
+            const uint32_t ref = as_global(X.task_ref[g & 1])[t];
             // unused entries and the parts of failed reads are skipped (a
             // stale flag only costs the work)
-            if (ref != TASK_EMPTY && !X.slot_fail[ref & 0x7fffffffu]) {
+            if (ref != TASK_EMPTY && !as_global(X.slot_fail)[ref & 0x7fffffffu]) {
                 s = ref & 0x7fffffffu;
                 strand = (int)(ref >> 31);
-                const uint32_t meta = X.slot_meta[s];
+                const uint32_t meta = as_global(X.slot_meta)[s];
                 m = (int)(meta & 1023);
                 maxd = (int)((meta >> 10) & 15);
                 has_n = (meta >> 14) != 0;
                 // the slot's row, read in place: the tasks of one read share
                 // it in the caches
-                c.pd = X.slot_rows + ((size_t)s * 2 + (size_t)strand) * X.dstride;
-                cur = X.tasks[g & 1][t];
+                c.pd = as_global(X.slot_rows + ((size_t)s * 2 + (size_t)strand) * X.dstride);
+                cur = as_global(X.tasks[g & 1])[t];
                 valid = true;
                 c.sp = c.sbase = 0;
                 c.ncand = 0;
-                c.best = X.slot_best[s];  // a stale value only prunes less
+                c.best = as_global(X.slot_best)[s];  // a stale value only prunes less
                 c.expand = 0;
                 texp = 0;
                 S = seed_of(P, m);
@@ -2164,8 +2193,8 @@ __global__ __launch_bounds__(BLOCK) void k_align_tasks(DevIndex ix, Params P, co
                     c.best = score;
                     atomicMin(&X.slot_best[s], score);
                 }
-                const uint2 kl = state_kl(ix, strand, cur);
-                const uint4 h = make_hit(strand, kl.x, kl.y, s_len(cur), score, s_nmm(cur), s_ngo(cur), s_nge(cur));
+                const u2 kl = state_kl(ix, strand, cur);
+                const u4 h = make_hit(strand, kl.x, kl.y, s_len(cur), score, s_nmm(cur), s_ngo(cur), s_nge(cur));
                 if (record(c, P, h, PH_FAST)) {
                     flush_slot(X, P, s, c);
                     if (record(c, P, h, PH_FAST)) {
@@ -2193,19 +2222,19 @@ __global__ __launch_bounds__(BLOCK) void k_align_tasks(DevIndex ix, Params P, co
         int q = 0;
         uint32_t tent = 0;
         uint32_t lo[4] = {0, 0, 0, 0}, hi[4] = {0, 0, 0, 0};
-        uint4 ta = make_uint4(0, 0, 0, 0), tb = ta;
+        u4 ta = mk4(0, 0, 0, 0), tb = ta;
         if (query && (uint32_t)s_len(cur) < ix.kt_levels) {
             const int bound = (P.mode == BWFM_MODE_BEST && c.best != INF_SCORE) ? c.best + P.s_mm : INF_SCORE;
             q = run_steps(ix, cur, c.pd, maxd, bound, has_n, S, P);
             tent = q ? run_entry(ix, cur, c.pd, q) : kt_children(s_len(cur), cur.x);
-            const uint4 *e = reinterpret_cast<const uint4 *>(qd.kt) + (tent >> 1);
+            const u4 *e = reinterpret_cast<const u4 *>(qd.kt) + (tent >> 1);
             ta = e[0];
             if (q == 0) tb = e[1];
         }
         if (query && tent == 0) rank_children<LW>(ix, qd, cur.x, cur.y + 1, lo, hi, true);
         if (q) {
             const uint32_t n =
-                run_take(cur, valid, (tent & 1) ? make_uint2(ta.z, ta.w) : make_uint2(ta.x, ta.y), c.pd, q, P);
+                run_take(cur, valid, (tent & 1) ? mk2(ta.z, ta.w) : mk2(ta.x, ta.y), c.pd, q, P);
             c.expand += n;
             texp += n;
         } else if (query) {
@@ -2291,14 +2320,14 @@ __global__ __launch_bounds__(BLOCK) void k_align_slow(DevIndex ix, ReadsView rd,
 
 // Copy each read's reported hits from the staging arena to the CSR output.
 // Launched only when the output holds them all.
-__global__ void k_compact(uint32_t n, const uint64_t *hoff, const uint4 *stage, const uint64_t *stage_off,
-                          uint4 *hits, const uint64_t *n_dev, const uint32_t *err) {
+__global__ void k_compact(uint32_t n, const uint64_t *hoff, const u4 *stage, const uint64_t *stage_off,
+                          u4 *hits, const uint64_t *n_dev, const uint32_t *err) {
     const uint32_t r = blockIdx.x * blockDim.x + threadIdx.x;
     if (err && *err) return;  // the output cannot hold the hits
     if (r >= count_of(n, n_dev)) return;
     const uint64_t o = hoff[r], e = hoff[r + 1];
     if (e == o) return;
-    const uint4 *src = stage + stage_off[r];
+    const u4 *src = stage + stage_off[r];
     for (uint64_t j = 0; j < e - o; j++) hits[o + j] = src[j];
 }
 
@@ -2380,18 +2409,18 @@ __global__ __launch_bounds__(SCAN_BLOCK) void k_scan_apply(const uint32_t *in, u
 // ------------------------------------------------------------------ locate
 
 // per hit: number of positions to locate (width if <= max_occ, else 0)
-__global__ void k_loc_count(uint64_t n_hits, const uint4 *hits, uint32_t max_occ, uint32_t *cnt,
+__global__ void k_loc_count(uint64_t n_hits, const u4 *hits, uint32_t max_occ, uint32_t *cnt,
                             const uint64_t *n_dev) {
     uint64_t h = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (h >= count_of(n_hits, n_dev)) return;
-    uint4 x = hits[h];
+    u4 x = hits[h];
     uint64_t w = (uint64_t)x.y - x.x + 1;
     cnt[h] = (x.x <= x.y && w <= max_occ) ? (uint32_t)w : 0;
 }
 
 // position p of the located hits: its hit is the last h with poff[h] <= p
 template <int LW>
-__device__ void locate_one(const DevIndex &ix, uint64_t n_hits, const uint4 *hits, const uint64_t *poff, uint64_t p,
+__device__ void locate_one(const DevIndex &ix, uint64_t n_hits, const u4 *hits, const uint64_t *poff, uint64_t p,
                            uint32_t *pos) {
     uint64_t lo = 0, hi = n_hits;
     while (hi - lo > 1) {
@@ -2399,7 +2428,7 @@ __device__ void locate_one(const DevIndex &ix, uint64_t n_hits, const uint4 *hit
         if (poff[mid] <= p) lo = mid;
         else hi = mid;
     }
-    uint4 x = hits[lo];
+    u4 x = hits[lo];
     int strand = h_strand(x);
     const DevDir d = pick_dir(ix, strand == 0 ? 1 : 0);
     uint32_t j = x.x + (uint32_t)(p - poff[lo]);
@@ -2417,7 +2446,7 @@ __device__ void locate_one(const DevIndex &ix, uint64_t n_hits, const uint4 *hit
 
 // one lane per position (grid-stride): find its hit, walk LF to a sampled row
 template <int LW>
-__global__ void k_loc_rows(DevIndex ix, uint64_t n_hits, const uint4 *hits, const uint64_t *poff, uint64_t total,
+__global__ void k_loc_rows(DevIndex ix, uint64_t n_hits, const u4 *hits, const uint64_t *poff, uint64_t total,
                            uint32_t *pos, const uint64_t *n_hits_dev, const uint64_t *total_dev) {
     n_hits = count_of(n_hits, n_hits_dev);
     total = count_of(total, total_dev);
@@ -2484,7 +2513,7 @@ __global__ __launch_bounds__(256) void k_sort_big(const uint64_t *poff, uint32_t
 
 struct EndView {
     const uint64_t *hoff;
-    const uint4 *hits;
+    const u4 *hits;
     const uint64_t *poff;  // per hit, indexed by (hit index - hbase)
     const uint32_t *pos;
     uint64_t hbase;        // hoff[0]
@@ -2501,13 +2530,13 @@ __device__ __forceinline__ uint64_t lower_bound(const uint32_t *a, uint64_t n, u
 }
 
 // single-end primary: smallest (score, diffs, strand, pos, len)
-__device__ bool se_primary(const EndView &e, uint32_t q, uint32_t &pos, uint4 &hit, bool &rep) {
+__device__ bool se_primary(const EndView &e, uint32_t q, uint32_t &pos, u4 &hit, bool &rep) {
     bool found = false;
     rep = false;
     for (uint64_t i = e.hoff[q]; i < e.hoff[q + 1]; i++) {
         uint64_t o = e.poff[i - e.hbase], w = e.poff[i - e.hbase + 1] - o;
         if (w == 0) { rep = true; continue; }
-        uint4 h = e.hits[i];
+        u4 h = e.hits[i];
         uint32_t p = e.pos[o];  // sorted: the first is the smallest
         bool b;
         if (!found) b = true;
@@ -2540,11 +2569,11 @@ __global__ void k_pair(uint32_t n_pairs, EndView e1, EndView e2, int paired, int
     int64_t bs = 0, bd = 0, bpf = 0;
     if (paired) {
         for (uint64_t i = e1.hoff[q]; i < e1.hoff[q + 1]; i++) {
-            uint4 h1 = e1.hits[i];
+            u4 h1 = e1.hits[i];
             const uint32_t *P1 = e1.pos + e1.poff[i - e1.hbase];
             uint64_t n1 = e1.poff[i - e1.hbase + 1] - e1.poff[i - e1.hbase];
             for (uint64_t j = e2.hoff[q]; j < e2.hoff[q + 1]; j++) {
-                uint4 h2 = e2.hits[j];
+                u4 h2 = e2.hits[j];
                 if (h_strand(h1) == h_strand(h2)) continue;
                 const uint32_t *P2 = e2.pos + e2.poff[j - e2.hbase];
                 uint64_t n2 = e2.poff[j - e2.hbase + 1] - e2.poff[j - e2.hbase];
@@ -2602,7 +2631,7 @@ __global__ void k_pair(uint32_t n_pairs, EndView e1, EndView e2, int paired, int
         }
     }
     uint32_t pp;
-    uint4 hp;
+    u4 hp;
     bool rep1 = false, rep2 = false;
     bool f1 = se_primary(e1, q, pp, hp, rep1);
     if (found) {
@@ -2644,7 +2673,7 @@ __global__ __launch_bounds__(256) void k_kt_level(DevIndex ix, int which, int d,
     if (p >= ((uint64_t)1 << (2 * (d - 1)))) return;
     const DevDir dd = pick_dir(ix, which);
     const uint64_t pe = kt_level_start(d - 1) + p;
-    const uint2 kl = reinterpret_cast<const uint2 *>(kt)[pe];
+    const u2 kl = reinterpret_cast<const u2 *>(kt)[pe];
     uint32_t lo[4], hi[4];
     if (mark && kl.y == 0) {
 #pragma unroll
@@ -2663,9 +2692,9 @@ __global__ __launch_bounds__(256) void k_kt_level(DevIndex ix, int which, int d,
                 }
         }
     }
-    uint4 *dst = reinterpret_cast<uint4 *>(kt + 2 * (size_t)kt_children(d - 1, (uint32_t)p));
-    dst[0] = make_uint4(lo[0], hi[0] - 1, lo[1], hi[1] - 1);
-    dst[1] = make_uint4(lo[2], hi[2] - 1, lo[3], hi[3] - 1);
+    u4 *dst = reinterpret_cast<u4 *>(kt + 2 * (size_t)kt_children(d - 1, (uint32_t)p));
+    dst[0] = mk4(lo[0], hi[0] - 1, lo[1], hi[1] - 1);
+    dst[1] = mk4(lo[2], hi[2] - 1, lo[3], hi[3] - 1);
 }
 
 // level 0: the empty string's interval (0, n)
@@ -2683,7 +2712,7 @@ __global__ void k_kt_root(uint32_t *kt, uint32_t n) {
 // as in the search's pointer chase.  Every index is reduced into
 // [0, n_lines), so any buffer contents are safe.
 template <int LW>
-__global__ __launch_bounds__(256) void k_probe_gather(const uint4 *buf, uint64_t n_lines, uint32_t iters,
+__global__ __launch_bounds__(256) void k_probe_gather(const u4 *buf, uint64_t n_lines, uint32_t iters,
                                                       uint32_t *sink) {
     const uint32_t t = blockIdx.x * blockDim.x + threadIdx.x;
     uint64_t x = 0x9E3779B97F4A7C15ULL * (t + 1);
@@ -2693,10 +2722,10 @@ __global__ __launch_bounds__(256) void k_probe_gather(const uint4 *buf, uint64_t
         x *= 0xBF58476D1CE4E5B9ULL;
         x ^= x >> 29;
         const uint64_t line = __umul64hi(x, n_lines);
-        const uint4 *L = buf + line * (LW / 4);
+        const u4 *L = buf + line * (LW / 4);
 #pragma unroll
         for (int q = 0; q < LW / 4; q++) {
-            uint4 v = L[q];
+            u4 v = L[q];
             acc += v.x ^ v.y ^ v.z ^ v.w;
         }
         x += acc;
@@ -2961,9 +2990,9 @@ inline SplitBufs carve_split(Carver &cv, const SplitShape &z, uint32_t budget, T
     X.slot_own = cv.take<uint32_t>(z.slot_cap);
     X.slot_obest = cv.take<int>(z.slot_cap);
     X.slot_rows = cv.take<uint8_t>((size_t)z.slot_cap * 2 * z.dstride);
-    X.slot_hits = cv.take<uint4>((size_t)z.slot_cap * SLOT_HITS);
+    X.slot_hits = cv.take<u4>((size_t)z.slot_cap * SLOT_HITS);
     for (int k = 0; k < 2; k++) {
-        X.tasks[k] = cv.take<uint4>(z.task_cap);
+        X.tasks[k] = cv.take<u4>(z.task_cap);
         X.task_ref[k] = cv.take<uint32_t>(z.task_cap);
     }
     X.ctl = cv.take<uint32_t>(SPLIT_CTL);
@@ -3051,14 +3080,14 @@ int align_impl(bwfm_index *ix, bwfm::Workspace &ws, const bwfm_reads *rd, const 
     int rc = ws_reserve(ws, need, st, &w);
     if (rc) return rc;
     Carver cv{(char *)w};
-    uint4 *lstack = cv.take<uint4>((size_t)blanes * stack_cap);
-    uint4 *lcand = cv.take<uint4>((size_t)blanes * FAST_CAND);
-    uint4 *sstack = cv.take<uint4>((size_t)slow_lanes * worst_stack);
-    uint4 *scand = cv.take<uint4>((size_t)slow_lanes * scap);
+    u4 *lstack = cv.take<u4>((size_t)blanes * stack_cap);
+    u4 *lcand = cv.take<u4>((size_t)blanes * FAST_CAND);
+    u4 *sstack = cv.take<u4>((size_t)slow_lanes * worst_stack);
+    u4 *scand = cv.take<u4>((size_t)slow_lanes * scap);
     uint32_t *n_rep = cv.take<uint32_t>(n);
     uint32_t *slow_list = cv.take<uint32_t>(n);
     uint64_t *stage_off = cv.take<uint64_t>(n);
-    uint4 *stage = cv.take<uint4>(stage_cap);
+    u4 *stage = cv.take<u4>(stage_cap);
     uint64_t *part = cv.take<uint64_t>(scan_part_elems(n));
     PersistentArgs *pargs = cv.take<PersistentArgs>(1);
     uint8_t *drows = dpre ? cv.take<uint8_t>((size_t)n * 2 * dstride) : nullptr;
@@ -3125,7 +3154,7 @@ int align_impl(bwfm_index *ix, bwfm::Workspace &ws, const bwfm_reads *rd, const 
     if (n && total) {
         int t = tm.begin("compact");
         k_compact<<<blocks(n, 256), 256, 0, st>>>(n, res->hit_offsets, stage, stage_off,
-                                                  reinterpret_cast<uint4 *>(res->hits), nullptr, nullptr);
+                                                  reinterpret_cast<u4 *>(res->hits), nullptr, nullptr);
         tm.end(t);
         HIPCHK(hipGetLastError());
     }
@@ -3135,7 +3164,7 @@ int align_impl(bwfm_index *ix, bwfm::Workspace &ws, const bwfm_reads *rd, const 
 
 // positions of all hits of one result; pos_off has n_hits + 1 entries
 template <int LW>
-int locate_impl(bwfm_index *ix, uint64_t n_hits, const uint4 *hits, uint32_t max_occ, uint64_t *pos_off,
+int locate_impl(bwfm_index *ix, uint64_t n_hits, const u4 *hits, uint32_t max_occ, uint64_t *pos_off,
                 uint32_t *pos, uint64_t cap, uint32_t *cnt, uint64_t *part, uint32_t *big, uint32_t *n_big,
                 hipStream_t st, uint64_t *total_out, bool timed = true) {
     const DevIndex D = dev_index(ix);
@@ -3404,7 +3433,7 @@ extern "C" int bwfm_locate(const bwfm_index *cix, uint32_t n_reads, const bwfm_a
     uint32_t *big = cv.take<uint32_t>(n_hits);
     uint32_t *n_big = cv.take<uint32_t>(1);
     uint64_t total = 0;
-    const uint4 *hits = (const uint4 *)res->hits + h0;
+    const u4 *hits = (const u4 *)res->hits + h0;
     rc = by_layout(ix, [&](auto lw) {
         return locate_impl<decltype(lw)::value>(ix, n_hits, hits, max_occ, pos_off, pos, cap, cnt, part, big, n_big,
                                                 st, &total);
@@ -3455,7 +3484,7 @@ int pair_impl(bwfm_index *ix, uint32_t n_pairs, const bwfm_aln_result *r1, const
     uint64_t total[2] = {0, 0};
     for (int e = 0; e < 2; e++) {
         if (!rr[e]) continue;
-        const uint4 *hits = (const uint4 *)rr[e]->hits + hb[e];
+        const u4 *hits = (const u4 *)rr[e]->hits + hb[e];
         // counting pass: capacity 0 reports the total
         int rc = by_layout(ix, [&](auto lw) {
             return locate_impl<decltype(lw)::value>(ix, nh[e], hits, pp->max_occ, poff[e], nullptr, 0, cnt, part, big,
@@ -3468,7 +3497,7 @@ int pair_impl(bwfm_index *ix, uint32_t n_pairs, const bwfm_aln_result *r1, const
     uint32_t *pos[2] = {(uint32_t *)pmem, (uint32_t *)pmem + total[0]};
     for (int e = 0; e < 2; e++) {
         if (!rr[e] || !total[e]) continue;
-        const uint4 *hits = (const uint4 *)rr[e]->hits + hb[e];
+        const u4 *hits = (const u4 *)rr[e]->hits + hb[e];
         uint64_t t2 = 0;
         int rc = by_layout(ix, [&](auto lw) {
             return locate_impl<decltype(lw)::value>(ix, nh[e], hits, pp->max_occ, poff[e], pos[e], total[e], cnt,
@@ -3477,9 +3506,9 @@ int pair_impl(bwfm_index *ix, uint32_t n_pairs, const bwfm_aln_result *r1, const
         if (rc) return rc;
     }
     if (n_pairs) {
-        EndView e1{r1->hit_offsets, (const uint4 *)r1->hits, poff[0], pos[0], hb[0]};
+        EndView e1{r1->hit_offsets, (const u4 *)r1->hits, poff[0], pos[0], hb[0]};
         EndView e2 = e1;
-        if (r2) e2 = EndView{r2->hit_offsets, (const uint4 *)r2->hits, poff[1], pos[1], hb[1]};
+        if (r2) e2 = EndView{r2->hit_offsets, (const u4 *)r2->hits, poff[1], pos[1], hb[1]};
         CallTimer tm(st, timed);
         int t = tm.begin("pair");
         k_pair<<<blocks(n_pairs, 256), 256, 0, st>>>(n_pairs, e1, e2, r2 ? 1 : 0, pp->lo, pp->hi, pp->mu, out, nullptr,
@@ -3664,11 +3693,11 @@ extern "C" int bwfm_probe_gather(const void *buf, uint64_t bytes, uint32_t line_
     HIPCHK(hipEventCreate(&b));
     HIPCHK(hipEventRecord(a, st));
     if (line_bytes == 128)
-        k_probe_gather<32><<<lanes / 256, 256, 0, st>>>((const uint4 *)buf, n_lines, iters, sink);
+        k_probe_gather<32><<<lanes / 256, 256, 0, st>>>((const u4 *)buf, n_lines, iters, sink);
     else if (line_bytes == 32)
-        k_probe_gather<8><<<lanes / 256, 256, 0, st>>>((const uint4 *)buf, n_lines, iters, sink);
+        k_probe_gather<8><<<lanes / 256, 256, 0, st>>>((const u4 *)buf, n_lines, iters, sink);
     else
-        k_probe_gather<16><<<lanes / 256, 256, 0, st>>>((const uint4 *)buf, n_lines, iters, sink);
+        k_probe_gather<16><<<lanes / 256, 256, 0, st>>>((const u4 *)buf, n_lines, iters, sink);
     hipError_t e = hipGetLastError();
     HIPCHK(hipEventRecord(b, st));
     HIPCHK(hipEventSynchronize(b));
@@ -3728,12 +3757,12 @@ struct bwfm_pipeline {
     uint64_t *offsets = nullptr;
     uint8_t *maxd = nullptr;
     // search buffers
-    uint4 *lstack = nullptr, *lcand = nullptr, *sstack = nullptr, *scand = nullptr, *stage = nullptr;
+    u4 *lstack = nullptr, *lcand = nullptr, *sstack = nullptr, *scand = nullptr, *stage = nullptr;
     uint32_t *n_rep = nullptr, *slow_list = nullptr;
     uint64_t *stage_off = nullptr, *part = nullptr;
     // outputs
     uint64_t *hoff = nullptr, *poff = nullptr;
-    uint4 *hits = nullptr;
+    u4 *hits = nullptr;
     uint32_t *c1 = nullptr, *c2 = nullptr, *cnt = nullptr, *big = nullptr, *pos = nullptr;
     uint8_t *status = nullptr;
     bwfm_pair *pairs = nullptr;
@@ -3917,17 +3946,17 @@ extern "C" int bwfm_pipeline_create(const bwfm_index *cix, const bwfm_aln_params
     pl->bases = cv.take<uint8_t>(q->max_bases);
     pl->offsets = cv.take<uint64_t>(nmax + 1);
     pl->maxd = cv.take<uint8_t>(nmax);
-    pl->lstack = cv.take<uint4>((size_t)blanes * pl->stack_cap);
-    pl->lcand = cv.take<uint4>((size_t)blanes * FAST_CAND);
-    pl->sstack = cv.take<uint4>((size_t)pl->slow_lanes * pl->worst_stack);
-    pl->scand = cv.take<uint4>((size_t)pl->slow_lanes * pl->scap);
+    pl->lstack = cv.take<u4>((size_t)blanes * pl->stack_cap);
+    pl->lcand = cv.take<u4>((size_t)blanes * FAST_CAND);
+    pl->sstack = cv.take<u4>((size_t)pl->slow_lanes * pl->worst_stack);
+    pl->scand = cv.take<u4>((size_t)pl->slow_lanes * pl->scap);
     pl->n_rep = cv.take<uint32_t>(nmax);
     pl->slow_list = cv.take<uint32_t>(nmax);
     pl->stage_off = cv.take<uint64_t>(nmax);
-    pl->stage = cv.take<uint4>(hcap);
+    pl->stage = cv.take<u4>(hcap);
     pl->part = cv.take<uint64_t>(scan_part_elems(std::max<uint64_t>(nmax, hcap)));
     pl->hoff = cv.take<uint64_t>(nmax + 1);
-    pl->hits = cv.take<uint4>(hcap);
+    pl->hits = cv.take<u4>(hcap);
     pl->c1 = cv.take<uint32_t>(nmax);
     pl->c2 = cv.take<uint32_t>(nmax);
     pl->status = cv.take<uint8_t>(nmax);
