@@ -1233,7 +1233,17 @@ constexpr uint32_t SLOT_HITS = 2 * FAST_CAND;
 // control words: [0] slots taken; [1 + g] task entries reserved in
 // generation g (0: by the first pass, k: by round k); [2 + SPLIT_ROUNDS + g]
 // entries of generation g taken by round g + 1
-constexpr uint32_t SPLIT_CTL = 2 * (SPLIT_ROUNDS + 1) + 2;
+// [SPLIT_DONE] waves of the first pass that have ended
+constexpr uint32_t SPLIT_DONE = 2 * (SPLIT_ROUNDS + 1) + 2;
+constexpr uint32_t SPLIT_CTL = SPLIT_DONE + 1;
+// Long reads (the builds with the D-array pre-pass): once DRAIN_EIGHTHS of
+// the first pass's waves have ended, the parts still running are split after
+// DRAIN_BUDGET expansions already: the few reads with the largest trees would
+// otherwise hold single waves until each part has reached the full budget
+// (150 k reads of 250 bases: 184 ms without, 47 at 4 eighths, 45 at 2, 58 at
+// 6).  On 100-base reads the endgame ends sooner by itself (30 k pairs: 7.0
+// ms without, 8.2-9.2 with).
+constexpr uint32_t DRAIN_EIGHTHS = 4, DRAIN_BUDGET = 256;
 
 struct SplitBufs {
     uint32_t *slot_read;    // the slot's read
@@ -1613,14 +1623,15 @@ __device__ __forceinline__ void persistent_body(const DevIndex &ix, const Params
     // 4096 waves, each 1.7 k iterations long.  (25 k reads of 36 bases, every
     // placement within 2 mismatches: 9.6 -> 2.3 ms; 30 k pairs of 100 bases,
     // aligned, paired and rescued: 16.0 -> 8.4 ms; batches of more reads than
-    // lanes take 64 at a time as before and keep their time.)  Long reads
-    // (DP) keep 64 to a wave: their trees are far larger than a wave and the
-    // split rounds spread them over the device.
+    // lanes take 64 at a time as before and keep their time.)  2000
+    // reads of 250 bases: 16.9 -> 9.4 ms.
     const uint32_t n_waves = gridDim.x * (blockDim.x >> 6);
-    const uint32_t cap = DP ? 64u : min((n_reads + n_waves - 1) / n_waves, 64u);
+    const uint32_t cap = min((n_reads + n_waves - 1) / n_waves, 64u);
     int phase = PZ_IDLE;
     bool exhausted = (uint32_t)lane >= cap;
     bool endgame = false;  // wave-uniform: the batch's reads are all taken
+    bool drain = false;    // wave-uniform: most of the grid has ended
+    uint32_t eg_iter = 0;
     int ow = lane;         // owner lane of the read this lane works on
     uint32_t r = 0;
     int m = 0, maxd = 0, strand = 0;
@@ -1777,8 +1788,13 @@ __device__ __forceinline__ void persistent_body(const DevIndex &ix, const Params
             // of the wave at a time (a read's slot is taken once); a part's
             // expansions count from the read's start for its owner and from
             // the hand-over for a helper
-            const uint32_t bud = A->X.budget;
+            uint32_t bud = A->X.budget;
             if (bud) {
+                if (DP) {
+                    if ((eg_iter++ & 15) == 15 && !drain)
+                        drain = (uint64_t)ld_agent(&A->X.ctl[SPLIT_DONE]) * 8 >= (uint64_t)n_waves * DRAIN_EIGHTHS;
+                    if (drain) bud = min(bud, DRAIN_BUDGET);
+                }
                 const bool want = (phase == PZ_SEARCH || phase == PZ_HELP) && c.sp > c.sbase && c.expand >= bud &&
                                   !(sh_ld(&ws.flags[ow]) & (SH_FAIL | SH_NOSPLIT));
                 unsigned long long sm = __ballot(want);
@@ -2042,6 +2058,7 @@ __device__ __forceinline__ void persistent_body(const DevIndex &ix, const Params
             }
         }
     }
+    if (DP && A->X.budget && lane == 0) atomicAdd(as_global(&A->X.ctl[SPLIT_DONE]), 1u);
     if (A->O.work) {
         if (lane == 0) atomicAdd(&A->O.work[0], (unsigned long long)w_iters);
         atomicAdd(&A->O.work[1], (unsigned long long)w_busy);
@@ -2926,10 +2943,9 @@ uint32_t persistent_lanes(uint32_t bs, size_t lds, int waves_per_simd, bool dp =
 }
 
 // Lanes of the batched form for n reads: the lanes that fit, but no more
-// than a wave per read (a wave's other lanes help its reads), or one per read
-// for long reads (dpre), which are not spread.
-inline uint32_t batched_lanes(uint32_t fit, uint32_t n, uint32_t bs, bool dpre) {
-    const uint64_t want = ((std::max<uint64_t>(n, 1) * (dpre ? 1 : 64) + bs - 1) / bs) * bs;
+// than a wave per read (a wave's other lanes help its reads).
+inline uint32_t batched_lanes(uint32_t fit, uint32_t n, uint32_t bs) {
+    const uint64_t want = ((std::max<uint64_t>(n, 1) * 64 + bs - 1) / bs) * bs;
     return (uint32_t)std::min<uint64_t>(fit, want);
 }
 
@@ -2958,17 +2974,20 @@ inline uint32_t split_budget_of(const bwfm_aln_params &p) {
 }
 
 // Room of the split searches for a batch of n reads of at most mlen bases:
-// a slot for one read in eight (at least 64, at most 2^26) and sixteen task entries a
-// read (at least 4096, at most 2^26) per generation.  A split hands out a
-// few hundred entries on long reads.  Running out is not an error: a read
-// or task that finds no room goes on alone.
+// a slot for one read in eight (at least 64, at most 2^26) and, per
+// generation, sixteen task entries a read, in smaller batches 4096 a read up
+// to 2^24 (at most 2^26 in all).  A split hands out a few hundred entries on
+// long reads.  Running out is not an error, but a read or task that finds no
+// room goes on alone, which can take seconds (2.2 s for 150 k reads of 250
+// bases whose splits outgrew sixteen entries a read).
 struct SplitShape {
     uint32_t slot_cap, task_cap, dstride;
 };
 inline SplitShape split_shape(uint32_t n, uint32_t mlen) {
     SplitShape z;
     z.slot_cap = std::min<uint32_t>(std::min<uint32_t>(std::max<uint32_t>(n, 1), std::max<uint32_t>(64, n / 8)), 1u << 26);
-    z.task_cap = (uint32_t)std::min<uint64_t>(std::max<uint64_t>(16ull * n, 4096), 1ull << 26);
+    z.task_cap = (uint32_t)std::min<uint64_t>(std::max<uint64_t>(16ull * n, 4096ull * std::min(std::max(n, 1u), 4096u)),
+                                              1ull << 26);
     z.dstride = ((mlen + 15) / 16) * 16;
     return z;
 }
@@ -3057,7 +3076,7 @@ int align_impl(bwfm_index *ix, bwfm::Workspace &ws, const bwfm_reads *rd, const 
     const size_t lds = (size_t)bs * lstride + (plain ? 0 : (bs / 64) * sizeof(WaveShare));
     const uint32_t nr_up = ((std::max<uint32_t>(n, 1) + bs - 1) / bs) * bs;
     const uint32_t lanes =
-        plain ? nr_up : batched_lanes(persistent_lanes<LW>(bs, lds, p->waves_per_simd, dpre), n, bs, dpre);
+        plain ? nr_up : batched_lanes(persistent_lanes<LW>(bs, lds, p->waves_per_simd, dpre), n, bs);
     const uint32_t stack_cap = plain ? std::min<uint32_t>(worst_stack, PLAIN_STACK) : worst_stack;
     // the task rounds' grid shares the lane buffers: room for the larger one
     const uint32_t tlanes = sbud ? task_lanes<LW>(nr_up, lanes) : 0u;
@@ -3914,7 +3933,7 @@ extern "C" int bwfm_pipeline_create(const bwfm_index *cix, const bwfm_aln_params
                                                     return persistent_lanes<decltype(lw)::value>(
                                                         pl->bs, pl->lds, ap->waves_per_simd, dpre);
                                                 }),
-                                      nmax, pl->bs, dpre);
+                                      nmax, pl->bs);
     pl->stack_cap = plain ? std::min<uint32_t>(pl->worst_stack, PLAIN_STACK) : pl->worst_stack;
     pl->tlanes = sbud ? by_layout(ix, [&](auto lw) { return task_lanes<decltype(lw)::value>(nr_up, pl->lanes); }) : 0u;
     const uint32_t blanes = std::max(pl->lanes, pl->tlanes);

@@ -41,3 +41,19 @@ def test_small_batches(setup, n, split):
     assert np.array_equal(hits.view(np.uint8), ores.hits[:h].view(np.uint8))
     assert np.array_equal(c1, ores.c1[:n]) and np.array_equal(c2, ores.c2[:n])
     assert np.array_equal(st & 7, ores.status[:n])
+
+
+@pytest.mark.parametrize("n", [1, 65, 700])
+def test_small_batches_of_long_reads(n):
+    """250 bp reads: few reads with large trees, whose parts are split early
+    once half of the waves have ended."""
+    g = configs.c2_genome(1_000_000, seed=311)
+    reads = configs.c5_reads(g, n, seed=312)
+    kw = configs.PARAMS["C5"]
+    ores = oracle.align(oracle.Index(g.seq), reads.bases, reads.offsets, oracle.Params(**kw), threads=8)
+    ix = bw.Index(g.seq, **configs.LAYOUT["C5"]).upload()
+    b = torch.from_numpy(reads.bases).cuda()
+    o = torch.from_numpy(reads.offsets.view(np.int64)).cuda()
+    ho, hits, c1, c2, st = bw.align_batch(ix, b, o, bw.Params(**kw), max_len=250).to_numpy()
+    assert np.array_equal(ho, ores.hit_off) and np.array_equal(hits.view(np.uint8), ores.hits.view(np.uint8))
+    assert np.array_equal(c1, ores.c1) and np.array_equal(c2, ores.c2) and np.array_equal(st & 7, ores.status)
