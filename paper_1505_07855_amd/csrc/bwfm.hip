@@ -2871,12 +2871,12 @@ int ws_grow(void *&ptr, size_t &have, size_t bytes, hipStream_t st) {
     if (have >= bytes && ptr) return BWFM_OK;
     if (ptr) {
         HIPCHK(hipStreamSynchronize(st));
-        (void)hipFree(ptr);
+        dev_free(ptr);
     }
     ptr = nullptr;
     have = 0;
     const size_t want = std::max<size_t>(bytes + bytes / 8, 4096);
-    if (hipMalloc(&ptr, want) != hipSuccess) {
+    if (dev_malloc(&ptr, want) != hipSuccess) {
         ptr = nullptr;
         (void)hipGetLastError();
         return fail(BWFM_E_NOMEM, "workspace allocation of " + std::to_string(want) + " bytes failed");
@@ -2943,9 +2943,13 @@ uint32_t persistent_lanes(uint32_t bs, size_t lds, int waves_per_simd, bool dp =
 }
 
 // Lanes of the batched form for n reads: the lanes that fit, but no more
-// than a wave per read (a wave's other lanes help its reads).
+// than a wave per read (a wave's other lanes help its reads) up to 1024
+// reads, 16 lanes per read from 4096 on (each lane needs its buffers: 17 KB
+// at 100 bases).  1000 pairs take 2.5 ms at a wave per read, 2.9 ms at 16
+// lanes; 5000 pairs 3.7 ms either way.
 inline uint32_t batched_lanes(uint32_t fit, uint32_t n, uint32_t bs) {
-    const uint64_t want = ((std::max<uint64_t>(n, 1) * 64 + bs - 1) / bs) * bs;
+    const uint64_t per = std::min<uint64_t>(64ull * std::max(n, 1u), std::max<uint64_t>(65536, 16ull * n));
+    const uint64_t want = ((per + bs - 1) / bs) * bs;
     return (uint32_t)std::min<uint64_t>(fit, want);
 }
 
@@ -2975,8 +2979,8 @@ inline uint32_t split_budget_of(const bwfm_aln_params &p) {
 
 // Room of the split searches for a batch of n reads of at most mlen bases:
 // a slot for one read in eight (at least 64, at most 2^26) and, per
-// generation, sixteen task entries a read, in smaller batches 4096 a read up
-// to 2^24 (at most 2^26 in all).  A split hands out a few hundred entries on
+// generation, sixteen task entries a read, in smaller batches 1024 a read up
+// to 2^23 (at most 2^26 in all).  A split hands out a few hundred entries on
 // long reads.  Running out is not an error, but a read or task that finds no
 // room goes on alone, which can take seconds (2.2 s for 150 k reads of 250
 // bases whose splits outgrew sixteen entries a read).
@@ -2986,7 +2990,7 @@ struct SplitShape {
 inline SplitShape split_shape(uint32_t n, uint32_t mlen) {
     SplitShape z;
     z.slot_cap = std::min<uint32_t>(std::min<uint32_t>(std::max<uint32_t>(n, 1), std::max<uint32_t>(64, n / 8)), 1u << 26);
-    z.task_cap = (uint32_t)std::min<uint64_t>(std::max<uint64_t>(16ull * n, 4096ull * std::min(std::max(n, 1u), 4096u)),
+    z.task_cap = (uint32_t)std::min<uint64_t>(std::max<uint64_t>(16ull * n, 1024ull * std::min(std::max(n, 1u), 8192u)),
                                               1ull << 26);
     z.dstride = ((mlen + 15) / 16) * 16;
     return z;
@@ -3257,8 +3261,8 @@ static void fill_table(const bwfm_index *ix, int d, uint32_t *kt, int levels, in
 // The search's interval table, made once the rank lines are on the device.
 // Depth: the least with 4^depth >= 2 n, at most 15, so that most of the
 // deepest strings are absent or unique and a run of exact matches ends in
-// its one entry: 100 Mbp: 14 levels, 2.9 GB per direction (a level less left
-// twice the rank queries after the runs).  It takes at most a quarter of the
+// its one entry: 100 Mbp: 14 levels, 2.9 GB per direction (its iterations per
+// read: 1031, with 13 levels 1223, with 12 1421).  It takes at most a quarter of the
 // free memory (less deep, or not made at all, where that is short: results
 // do not depend on it).
 int bwfm::build_search_tables(bwfm_index *ix, hipStream_t st) {
@@ -3266,12 +3270,13 @@ int bwfm::build_search_tables(bwfm_index *ix, hipStream_t st) {
     HIPCHK(hipMemGetInfo(&free_b, &total_b));
     int levels = 1;
     while (levels < 15 && ((uint64_t)1 << (2 * levels)) < 2 * ix->n) levels++;
+    free_b += dev_cached();
     while (levels > 0 && 2 * kt_bytes((uint32_t)levels) > free_b / 4) levels--;
     if (levels == 0) return BWFM_OK;
     const uint64_t bytes = kt_bytes((uint32_t)levels);
-    if (hipMalloc(&ix->d_jt[0], bytes) != hipSuccess || hipMalloc(&ix->d_jt[1], bytes) != hipSuccess) {
+    if (dev_malloc(&ix->d_jt[0], bytes) != hipSuccess || dev_malloc(&ix->d_jt[1], bytes) != hipSuccess) {
         (void)hipGetLastError();
-        if (ix->d_jt[0]) (void)hipFree(ix->d_jt[0]);
+        dev_free(ix->d_jt[0]);
         ix->d_jt[0] = ix->d_jt[1] = nullptr;
         return BWFM_OK;
     }
@@ -3293,14 +3298,14 @@ extern "C" int bwfm_index_upload(bwfm_index *ix, void *stream) {
     uint64_t bytes = 0;
     for (int d = 0; d < 2; d++) {
         size_t lb = ix->dir[d].lines.size() * 4, sb = ix->dir[d].sa.size() * 4;
-        if (hipMalloc(&ix->d_lines[d], lb) != hipSuccess || hipMalloc(&ix->d_sa[d], sb) != hipSuccess)
+        if (dev_malloc(&ix->d_lines[d], lb) != hipSuccess || dev_malloc(&ix->d_sa[d], sb) != hipSuccess)
             return fail(BWFM_E_NOMEM, "index upload: device allocation failed");
         HIPCHK(hipMemcpyAsync(ix->d_lines[d], ix->dir[d].lines.data(), lb, hipMemcpyHostToDevice, st));
         HIPCHK(hipMemcpyAsync(ix->d_sa[d], ix->dir[d].sa.data(), sb, hipMemcpyHostToDevice, st));
         bytes += lb + sb;
     }
     const size_t pb = std::max<size_t>(ix->pac.size(), 1) * 4;
-    if (hipMalloc(&ix->d_pac, pb) != hipSuccess) return fail(BWFM_E_NOMEM, "index upload: device allocation failed");
+    if (dev_malloc(&ix->d_pac, pb) != hipSuccess) return fail(BWFM_E_NOMEM, "index upload: device allocation failed");
     if (!ix->pac.empty())
         HIPCHK(hipMemcpyAsync(ix->d_pac, ix->pac.data(), ix->pac.size() * 4, hipMemcpyHostToDevice, st));
     bytes += pb;
@@ -3364,15 +3369,15 @@ extern "C" int bwfm_index_kmer_get(const bwfm_index *ix, int which, int level, u
 extern "C" void bwfm_index_free(bwfm_index *ix) {
     if (!ix) return;
     for (int d = 0; d < 2; d++) {
-        if (ix->d_lines[d]) (void)hipFree(ix->d_lines[d]);
-        if (ix->d_sa[d]) (void)hipFree(ix->d_sa[d]);
+        dev_free(ix->d_lines[d]);
+        dev_free(ix->d_sa[d]);
         if (ix->d_kt[d]) (void)hipFree(ix->d_kt[d]);
-        if (ix->d_jt[d]) (void)hipFree(ix->d_jt[d]);
+        dev_free(ix->d_jt[d]);
     }
-    if (ix->d_pac) (void)hipFree(ix->d_pac);
+    dev_free(ix->d_pac);
     for (auto &kv : ix->ws) {
-        if (kv.second->ptr) (void)hipFree(kv.second->ptr);
-        if (kv.second->pos) (void)hipFree(kv.second->pos);
+        dev_free(kv.second->ptr);
+        dev_free(kv.second->pos);
     }
     delete ix;
 }

@@ -86,6 +86,13 @@ void pack_ref(const uint8_t *text, uint64_t n, std::vector<uint32_t> &out);
 // 0 or a bwfm_err.  Without room for them the index works without.
 int build_search_tables(bwfm_index *ix, ihipStream_t *st);
 
+// Device blocks through the library's bounded pool (index_gpu.hip): as
+// hipMalloc (its error code, 0 = success) and hipFree on the current device.
+// dev_cached: bytes held.
+int dev_malloc(void **out, size_t bytes);
+void dev_free(void *p);
+size_t dev_cached();
+
 }  // namespace bwfm
 
 struct bwfm_index {

@@ -15,14 +15,133 @@
 
 #include <algorithm>
 #include <cstring>
+#include <deque>
 #include <memory>
 #include <rocprim/rocprim.hpp>
 #include <string>
+#include <unordered_map>
 #include <vector>
 
 #include "bwfm_internal.h"
 
 using namespace bwfm;
+
+// ------------------------------------------------------------------ device blocks
+
+namespace {
+
+// Device blocks that indexes, their workspaces and index builds give back are
+// kept for the next ones: giving memory back to the driver and taking it
+// again costs up to 28 ms per GB once it has to be cleared (a 16 Mbp
+// reference indexed and a first batch aligned, over and over: 31 ms a pass
+// with 288 GB of fresh memory ahead, 60-150 ms after that).  At most
+// POOL_BYTES are held, the oldest block goes first, and an allocation that
+// fails gives every held block back and tries again.
+constexpr size_t POOL_BYTES = (size_t)8 << 30;
+constexpr size_t POOL_MIN = (size_t)1 << 20;  // smaller blocks are not held
+
+struct DevPool {
+    struct Block {
+        void *p;
+        size_t bytes;
+        int dev;
+    };
+    std::mutex mu;
+    std::unordered_map<void *, Block> live;  // blocks handed out (of POOL_MIN and more)
+    std::deque<Block> held;                  // blocks given back, oldest first
+    size_t held_bytes = 0;
+};
+DevPool &pool() {
+    static DevPool *p = new DevPool;  // never destroyed: the runtime may be gone at exit
+    return *p;
+}
+
+}  // namespace
+
+int bwfm::dev_malloc(void **out, size_t bytes) {
+    *out = nullptr;
+    if (bytes < POOL_MIN) return hipMalloc(out, bytes);
+    int dev = 0;
+    if (hipError_t e = hipGetDevice(&dev)) return e;
+    DevPool &P = pool();
+    const size_t want = (bytes + ((size_t)2 << 20) - 1) & ~(((size_t)2 << 20) - 1);
+    std::vector<void *> drop;
+    {
+        // the smallest held block that fits and wastes at most a quarter
+        std::lock_guard<std::mutex> g(P.mu);
+        size_t best = P.held.size();
+        for (size_t i = 0; i < P.held.size(); i++) {
+            const auto &b = P.held[i];
+            if (b.dev == dev && b.bytes >= want && b.bytes - want <= want / 4 &&
+                (best == P.held.size() || b.bytes < P.held[best].bytes))
+                best = i;
+        }
+        if (best < P.held.size()) {
+            const auto b = P.held[best];
+            P.held.erase(P.held.begin() + (ptrdiff_t)best);
+            P.held_bytes -= b.bytes;
+            P.live[b.p] = b;
+            *out = b.p;
+            return hipSuccess;
+        }
+    }
+    hipError_t e = hipMalloc(out, want);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        {
+            std::lock_guard<std::mutex> g(P.mu);
+            for (const auto &b : P.held) drop.push_back(b.p);
+            P.held.clear();
+            P.held_bytes = 0;
+        }
+        if (drop.empty()) return e;
+        for (void *p : drop) (void)hipFree(p);
+        e = hipMalloc(out, want);
+        if (e != hipSuccess) return e;
+    }
+    std::lock_guard<std::mutex> g(P.mu);
+    P.live[*out] = DevPool::Block{*out, want, dev};
+    return hipSuccess;
+}
+
+// Waits for the device's work, as hipFree does, before the block may be
+// handed out again.
+void bwfm::dev_free(void *p) {
+    if (!p) return;
+    DevPool &P = pool();
+    DevPool::Block b{};
+    {
+        std::lock_guard<std::mutex> g(P.mu);
+        auto it = P.live.find(p);
+        if (it != P.live.end()) {
+            b = it->second;
+            P.live.erase(it);
+        }
+    }
+    int dev = -1;
+    if (!b.p || b.bytes > POOL_BYTES / 2 || hipGetDevice(&dev) != hipSuccess || dev != b.dev ||
+        hipDeviceSynchronize() != hipSuccess) {
+        (void)hipFree(p);
+        return;
+    }
+    std::vector<void *> drop;
+    {
+        std::lock_guard<std::mutex> g(P.mu);
+        P.held.push_back(b);
+        P.held_bytes += b.bytes;
+        while (P.held_bytes > POOL_BYTES) {
+            drop.push_back(P.held.front().p);
+            P.held_bytes -= P.held.front().bytes;
+            P.held.pop_front();
+        }
+    }
+    for (void *q : drop) (void)hipFree(q);
+}
+
+size_t bwfm::dev_cached() {
+    std::lock_guard<std::mutex> g(pool().mu);
+    return pool().held_bytes;
+}
 
 namespace {
 
@@ -213,11 +332,11 @@ __global__ void k_ix_heads(const uint64_t *off, uint64_t n_lines, uint32_t lw, u
 struct DevScratch {
     std::vector<void *> ptrs;
     ~DevScratch() {
-        for (void *p : ptrs) (void)hipFree(p);
+        for (void *p : ptrs) dev_free(p);
     }
     template <class T> T *alloc(size_t n) {
         void *p = nullptr;
-        if (hipMalloc(&p, std::max<size_t>(n, 1) * sizeof(T)) != hipSuccess) return nullptr;
+        if (dev_malloc(&p, std::max<size_t>(n, 1) * sizeof(T)) != hipSuccess) return nullptr;
         ptrs.push_back(p);
         return static_cast<T *>(p);
     }
@@ -279,7 +398,7 @@ int build_dir_device(const uint8_t *t, uint64_t n, uint32_t line_bytes, uint32_t
     uint32_t *sa = s.alloc<uint32_t>(N);
     if (!sa) return fail(BWFM_E_NOMEM, "index build: device suffix array");
     if (int rc = suffix_sort(t, n, sa, st)) return rc;
-    if (hipMalloc(&d_lines, n_lines * lw * 4) != hipSuccess || hipMalloc(&d_sa, n_samples * 4) != hipSuccess)
+    if (dev_malloc(&d_lines, n_lines * lw * 4) != hipSuccess || dev_malloc(&d_sa, n_samples * 4) != hipSuccess)
         return fail(BWFM_E_NOMEM, "index build: device index");
     uint32_t *lines = static_cast<uint32_t *>(d_lines), *samp = static_cast<uint32_t *>(d_sa);
     uint32_t *gcnt = s.alloc<uint32_t>(4 * n_groups), *lc = s.alloc<uint32_t>(4 * n_lines);
@@ -348,13 +467,14 @@ extern "C" int bwfm_build_index_device(const uint8_t *ref, uint64_t n, const bwf
     hipStream_t st = (hipStream_t)stream;
     int dev = 0;
     DCHK(hipGetDevice(&dev));
-    uint8_t *t = nullptr, *r = nullptr;
-    if (hipMalloc(&t, n) != hipSuccess) return fail(BWFM_E_NOMEM, "index build: device text");
+    void *tp = nullptr, *rp = nullptr;
+    if (dev_malloc(&tp, n) != hipSuccess) return fail(BWFM_E_NOMEM, "index build: device text");
+    uint8_t *t = static_cast<uint8_t *>(tp);
     int rc = BWFM_OK;
     if (hipMemcpyAsync(t, ref, n, hipMemcpyHostToDevice, st) != hipSuccess)
         rc = fail(BWFM_E_DEVICE, "index build: text upload");
     const uint64_t pac_words = (n + 15) / 16;
-    if (!rc && hipMalloc(&ix->d_pac, pac_words * 4) != hipSuccess) rc = fail(BWFM_E_NOMEM, "index build: packed text");
+    if (!rc && dev_malloc(&ix->d_pac, pac_words * 4) != hipSuccess) rc = fail(BWFM_E_NOMEM, "index build: packed text");
     if (!rc) {
         k_pack_ref<<<grid_for(pac_words, 256), 256, 0, st>>>(t, n, (uint32_t *)ix->d_pac);
         try {
@@ -370,9 +490,10 @@ extern "C" int bwfm_build_index_device(const uint8_t *ref, uint64_t n, const bwf
                                    ix->d_sa[0], st);
     if (!rc) {
         // reverse(T) in place of T
-        if (hipMalloc(&r, n) != hipSuccess) {
+        if (dev_malloc(&rp, n) != hipSuccess) {
             rc = fail(BWFM_E_NOMEM, "index build: device text");
         } else {
+            uint8_t *r = static_cast<uint8_t *>(rp);
             k_reverse<<<grid_for(n, 256), 256, 0, st>>>(t, n, r);
             rc = build_dir_device(r, n, q.line_bytes, q.bases_per_line, q.sa_sample, q.rank_format, ix->dir[1],
                                   ix->d_lines[1],
@@ -380,18 +501,18 @@ extern "C" int bwfm_build_index_device(const uint8_t *ref, uint64_t n, const bwf
         }
     }
     (void)hipStreamSynchronize(st);
-    if (t) (void)hipFree(t);
-    if (r) (void)hipFree(r);
+    dev_free(tp);
+    dev_free(rp);
     if (!rc) rc = build_search_tables(ix.get(), st);
     if (rc) {
         for (int d = 0; d < 2; d++) {
-            if (ix->d_jt[d]) (void)hipFree(ix->d_jt[d]);
+            dev_free(ix->d_jt[d]);
             ix->d_jt[d] = nullptr;
-            if (ix->d_lines[d]) (void)hipFree(ix->d_lines[d]);
-            if (ix->d_sa[d]) (void)hipFree(ix->d_sa[d]);
+            dev_free(ix->d_lines[d]);
+            dev_free(ix->d_sa[d]);
             ix->d_lines[d] = ix->d_sa[d] = nullptr;
         }
-        if (ix->d_pac) (void)hipFree(ix->d_pac);
+        dev_free(ix->d_pac);
         ix->d_pac = nullptr;
         return rc;
     }
