@@ -201,6 +201,7 @@ __device__ __forceinline__ DevDir pick_dir(const DevIndex &ix, int which) {
     d.primary = which ? ix.dir[1].primary : ix.dir[0].primary;
     d.pad = 0;
     d.kt = which ? ix.dir[1].kt : ix.dir[0].kt;
+    d.full = which ? ix.dir[1].full : ix.dir[0].full;
     return d;
 }
 
@@ -224,18 +225,27 @@ constexpr int LW_SUB128 = 33;
 template <int LW> constexpr int line_words() { return LW == LW_SUB ? 16 : (LW == LW_SUB128 ? 32 : LW); }
 constexpr uint32_t SUB128_ROWS = 384;
 
-// The four intervals of a string's one-base extensions, read from the
-// interval table as two 16-byte words (p: A and C, q: G and T), as [lo, hi):
-// lo = k, hi = l + 1.  An extension that does not occur has lo >= hi.
-__device__ __forceinline__ void kt_pick(u4 p, u4 q, uint32_t lo[4], uint32_t hi[4]) {
-    lo[0] = p.x;
-    hi[0] = p.y + 1;
-    lo[1] = p.z;
-    hi[1] = p.w + 1;
-    lo[2] = q.x;
-    hi[2] = q.y + 1;
-    lo[3] = q.z;
-    hi[3] = q.w + 1;
+// The one-base extensions of a string, as the search takes them: per base a
+// the interval (x, y) = (k, l), or (text position, SINGLE) for a string that
+// occurs once and is followed in the text; bit a of mask: it occurs.
+struct Kids {
+    uint32_t x[4], y[4], mask;
+};
+constexpr uint32_t SINGLE = 0xffffffffu;  // above every l
+
+// from the interval table's two 16-byte words (p: A and C, q: G and T); a
+// string that does not occur has y = 0 (one that does has l >= 1, since row 0
+// is the empty suffix's)
+__device__ __forceinline__ void kt_pick(u4 p, u4 q, Kids &k) {
+    k.x[0] = p.x;
+    k.y[0] = p.y;
+    k.x[1] = p.z;
+    k.y[1] = p.w;
+    k.x[2] = q.x;
+    k.y[2] = q.y;
+    k.x[3] = q.z;
+    k.y[3] = q.w;
+    k.mask = (p.y ? 1u : 0u) | (p.w ? 2u : 0u) | (q.y ? 4u : 0u) | (q.w ? 8u : 0u);
 }
 // first entry of level d <= 15, which fits 32 bits
 __device__ __forceinline__ uint32_t kt_start32(int d) { return d == 0 ? 0u : ((1u << (2 * d)) + 8u) / 3u; }
@@ -522,21 +532,24 @@ __device__ __forceinline__ void occ4_pair(const DevIndex &ix, const DevDir &d, u
     count(B, i2, l2, o2);
 }
 
-// The intervals [lo, hi) of a string's four extensions from the rank counts
-// at its k (i1) and l + 1 (i2); pair: rows in one line fetch it once.
+// A string's four extensions from the rank counts at its k (i1) and l + 1
+// (i2); pair: rows in one line fetch it once.
 template <int LW>
-__device__ __forceinline__ void rank_children(const DevIndex &ix, const DevDir &d, uint32_t i1, uint32_t i2,
-                                              uint32_t lo[4], uint32_t hi[4], bool pair) {
+__device__ __forceinline__ void rank_children(const DevIndex &ix, const DevDir &d, uint32_t i1, uint32_t i2, Kids &k,
+                                              bool pair) {
+    uint32_t lo[4], hi[4];
     if (pair) {
         occ4_pair<LW>(ix, d, i1, i2, lo, hi);
     } else {
         occ4<LW>(ix, d, i1, lo);
         occ4<LW>(ix, d, i2, hi);
     }
+    k.mask = 0;
 #pragma unroll
     for (int a = 0; a < 4; a++) {
-        lo[a] += d.C[a];
-        hi[a] += d.C[a];
+        k.x[a] = lo[a] + d.C[a];
+        k.y[a] = hi[a] + d.C[a] - 1;
+        k.mask |= lo[a] < hi[a] ? 1u << a : 0u;
     }
 }
 
@@ -737,14 +750,22 @@ __device__ __forceinline__ int s_sd(u4 s) { return (s.z >> 24) & 15; }
 __device__ __forceinline__ int s_score(u4 s) { return s.w & 1023; }
 __device__ __forceinline__ int s_len(u4 s) { return (s.w >> 10) & 1023; }
 
-// Interval of a completed state: (x, y) itself, or, while X is shorter than
-// the interval table's levels (x holds the code of X), X's table entry on
-// the strand's search index.
+// Interval of a completed state: (x, y) itself; while X is shorter than the
+// interval table's levels (x holds the code of X), X's table entry on the
+// strand's search index; for a string that occurs once (x its position in
+// that direction's text), the row of the suffix there.
 __device__ __forceinline__ u2 state_kl(const DevIndex &ix, int strand, u4 s) {
     const int len = s_len(s);
-    if (len >= (int)ix.kt_levels) return mk2(s.x, s.y);
-    const u2 *kt = reinterpret_cast<const u2 *>(strand == 0 ? ix.dir[1].kt : ix.dir[0].kt);
-    return kt[kt_start32(len) + s.x];
+    if (len < (int)ix.kt_levels) {
+        const u2 *kt = reinterpret_cast<const u2 *>(strand == 0 ? ix.dir[1].kt : ix.dir[0].kt);
+        return kt[kt_start32(len) + s.x];
+    }
+    if (s.y == SINGLE) {
+        const uint32_t *isa = (strand == 0 ? ix.dir[1].full : ix.dir[0].full) + (size_t)ix.n + 1;
+        const uint32_t k = isa[s.x];
+        return mk2(k, k);
+    }
+    return mk2(s.x, s.y);
 }
 
 // ---- runs of exact matches through the interval table
@@ -757,7 +778,7 @@ __device__ __forceinline__ u2 state_kl(const DevIndex &ix, int strand, u4 s) {
 // occur.  On the benchmark batch three quarters of the expansions are steps
 // of such runs, 4 of them to a run.
 
-// Two bits per base of row[at, at + q), q <= 15, base j in bits 2 j: the row
+// Two bits per base of row[at, at + q), q <= 16, base j in bits 2 j: the row
 // is read as whole dwords (it starts dword-aligned; at most 3 bytes past its
 // last base are touched, inside the row's last dword).
 __device__ __forceinline__ uint32_t row_code(const uint8_t *row, int at, int q) {
@@ -774,13 +795,15 @@ __device__ __forceinline__ uint32_t row_code(const uint8_t *row, int at, int q) 
     }
     const uint32_t lo = v[0] | (v[1] << 8) | (v[2] << 16) | (v[3] << 24);
     const uint64_t w = ((uint64_t)v[4] << 32) | lo;
-    return (uint32_t)(w >> (2 * sh)) & ((1u << (2 * q)) - 1u);
+    return (uint32_t)(w >> (2 * sh)) & (uint32_t)((1ull << (2 * q)) - 1ull);
 }
-// the q two-bit digits of c in the opposite order
-__device__ __forceinline__ uint32_t rev_digits(uint32_t c, int q) {
+// sixteen two-bit digits in the opposite order
+__device__ __forceinline__ uint32_t rev16(uint32_t c) {
     const uint32_t r = __brev(c);
-    return q ? (((r >> 1) & 0x55555555u) | ((r & 0x55555555u) << 1)) >> (32 - 2 * q) : 0u;
+    return ((r >> 1) & 0x55555555u) | ((r & 0x55555555u) << 1);
 }
+// the q <= 15 two-bit digits of c in the opposite order
+__device__ __forceinline__ uint32_t rev_digits(uint32_t c, int q) { return q ? rev16(c) >> (32 - 2 * q) : 0u; }
 
 // Steps of the exact run from state cur (i >= 0, |X| < the table's levels)
 // to the deepest level, or 0 when a difference may still be taken on the
@@ -801,6 +824,15 @@ __device__ __forceinline__ int run_steps(const DevIndex &ix, u4 cur, const uint8
 __device__ __forceinline__ uint32_t run_entry(const DevIndex &ix, u4 cur, const uint8_t *pd, int q) {
     return kt_start32((int)ix.kt_levels) + ((cur.x << (2 * q)) | row_code(pd, s_i(cur) + 1 - q, q));
 }
+// cur, t matches on: x and y are the caller's
+__device__ __forceinline__ void step_matches(u4 &cur, int t, const uint8_t *pd, const Params &P) {
+    const int e = s_i(cur) - t;
+    const int De = e >= 0 ? pd[e] >> 3 : 0;
+    cur.z = (cur.z & ~(3u << 10)) - (uint32_t)t;
+    cur.w = (cur.w & 0xfffffu) + ((uint32_t)t << 10);
+    cur.w |= (uint32_t)(s_score(cur) + P.minc * De) << 20;
+}
+
 // cur after its run: the state q steps on, or dropped (valid cleared) when
 // its string stops occurring.  Returns the states the run expanded.
 __device__ __forceinline__ uint32_t run_take(u4 &cur, bool &valid, u2 kl, const uint8_t *pd, int q,
@@ -809,14 +841,117 @@ __device__ __forceinline__ uint32_t run_take(u4 &cur, bool &valid, u2 kl, const 
         valid = false;
         return kl.x - (uint32_t)s_len(cur);
     }
-    const int e = s_i(cur) - q;
-    const int De = e >= 0 ? pd[e] >> 3 : 0;
+    step_matches(cur, q, pd, P);
     cur.x = kl.x;
     cur.y = kl.y;
-    cur.z = (cur.z & ~(3u << 10)) - (uint32_t)q;
-    cur.w = (cur.w & 0xfffffu) + ((uint32_t)q << 10);
-    cur.w |= (uint32_t)(s_score(cur) + P.minc * De) << 20;
     return (uint32_t)q;
+}
+
+// ---- strings that occur once
+//
+// The deepest level's entry of a string that occurs once holds its position
+// p in the direction's text (y = SINGLE).  Its extensions are then read from
+// the packed reference: sixteen bases in one load, the same line for the
+// whole read, where the rank lines took a random line fill per base.  The
+// row of a completed hit comes from the inverse suffix array.
+
+// two words at any word boundary
+typedef uint32_t u2w __attribute__((ext_vector_type(2), aligned(4)));
+// first of the two words of the packed reference holding the 16 bases next to
+// be prepended at position p > 0 of direction dir's text: T[p - 16, p), or,
+// for reverse(T), T[n - p, n - p + 16) (the copy has a word of padding)
+__device__ __forceinline__ uint32_t text_word(const DevIndex &ix, int dir, uint32_t p) {
+    return dir == 0 ? (p >= 16 ? (p - 16) >> 4 : 0u) : (ix.n - p) >> 4;
+}
+// those bases from the two words: T[p - 1], T[p - 2], ... from the highest
+// digit down (dir 0), or T[n - p], T[n - p + 1], ... from the lowest up (dir
+// 1); digits past the text's end are arbitrary
+__device__ __forceinline__ uint32_t text_bases(const DevIndex &ix, int dir, uint32_t p, uint32_t w0, uint32_t w1) {
+    if (dir == 0) {
+        const bool head = p < 16;
+        return __builtin_amdgcn_alignbit(head ? w0 : w1, head ? 0u : w0, 2 * (p & 15));
+    }
+    return __builtin_amdgcn_alignbit(w1, w0, 2 * ((ix.n - p) & 15));
+}
+
+// One step of a state whose string occurs once at p > 0, win its next bases
+// from the highest digit down.  A run of matches is taken at once: its
+// positions have no mismatch children, and their gaps, where one may still
+// open, go on the stack as one run entry (gap state GAP_RUN, y = the run's
+// length, x, i and the rest as at its start, lb that of its cheapest gap),
+// which is dropped whole once the bound passes it.  Returns true when the run
+// was taken; else k receives the one child.
+constexpr int GAP_RUN = 3;
+__device__ bool text_step(u4 &cur, uint32_t win, int maxd, int bound, bool has_n, const Params &P, LaneCtx &c,
+                          Kids &k) {
+    const int i = s_i(cur);
+    const uint32_t p = cur.x;
+    if (!has_n && s_gs(cur) == 0 && p) {
+        const int r = min(16, i + 1);
+        const uint32_t pc = row_code(c.pd, i + 1 - r, r) << (32 - 2 * r);
+        const uint32_t df = win ^ pc;
+        int t = df ? __clz(df) >> 1 : 16;
+        t = min(t, r);
+        t = (int)min((uint32_t)t, p);
+        if (t) {
+            const int e = i - t;
+            const int De = e >= 0 ? c.pd[e] >> 3 : 0;
+            const int ngo = s_ngo(cur), lbg = s_score(cur) + P.s_gapo + P.minc * De;
+            const bool gap = ngo < P.max_gapo && s_nmm(cur) + ngo + s_nge(cur) + 1 + De <= maxd && lbg <= bound;
+            if (!gap || c.sp + 8 <= c.stack_cap) {
+                if (gap) {
+                    c.stack[(size_t)c.sp * c.sstride] =
+                        mk4(p, (uint32_t)t, cur.z | ((uint32_t)GAP_RUN << 10), (cur.w & 0xfffffu) | ((uint32_t)lbg << 20));
+                    c.sp++;
+                }
+                step_matches(cur, t, c.pd, P);
+                cur.x = p - (uint32_t)t;
+                c.expand += (uint32_t)t;
+                return true;
+            }
+        }
+    }
+    const uint32_t a = win >> 30;
+    k.mask = p ? 1u << a : 0u;
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+        k.x[q] = p - 1;
+        k.y[q] = SINGLE;
+    }
+    c.expand++;
+    return false;
+}
+
+// A run entry taken from the stack: its deepest position's gaps come next (k
+// holds the deletion's child, cur the state there; the caller takes gaps
+// only), the rest of the run goes back on the stack.
+__device__ __forceinline__ void unroll_run(u4 &cur, const Params &P, LaneCtx &c, Kids &k) {
+    const int t = (int)cur.y, i = s_i(cur);
+    const int lb0 = s_score(cur) + P.s_gapo;
+    const int j = i - t + 1;  // the position taken now
+    if (t > 1) {
+        const int De = c.pd[j] >> 3;  // the rest ends one position before j
+        c.stack[(size_t)c.sp * c.sstride] =
+            mk4(cur.x, (uint32_t)(t - 1), cur.z, (cur.w & 0xfffffu) | ((uint32_t)(lb0 + P.minc * De) << 20));
+        c.sp++;
+    }
+    cur.x -= (uint32_t)(t - 1);
+    cur.y = SINGLE;
+    cur.z = (cur.z & ~(3u << 10)) - (uint32_t)(t - 1);
+    cur.w = (cur.w & 0xfffffu) + ((uint32_t)(t - 1) << 10);
+    k.mask = 1u << (c.pd[j] & 3);
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+        k.x[q] = cur.x - 1;
+        k.y[q] = SINGLE;
+    }
+}
+
+// Whether a state with one row left (k = l, |X| = len) is better followed in
+// the text: past the table's depth by a few bases it is mostly the read's own
+// place, while most states that get there by chance are gone.
+__device__ __forceinline__ bool to_text(const DevIndex &ix, u4 cur) {
+    return cur.x == cur.y && ix.kt_levels && s_len(cur) >= (int)ix.kt_levels + 3;
 }
 
 // the empty string's interval, nothing consumed, lower bound minc * D[m - 1]
@@ -862,13 +997,13 @@ __device__ int resolve(u4 &cur, bool &valid, int strand, const Params &P, LaneCt
     }
 }
 
-// Children of an expanded state, from the intervals [lo, hi) of its
-// string's four extensions, built directly in packed form: each differs
-// from the parent by a few field increments.  They are taken in reverse of
+// Children of an expanded state, from its string's four extensions, built
+// directly in packed form: each differs from the parent by a few field
+// increments.  gaps_only: a run's position, whose match was taken before.  They are taken in reverse of
 // the fixed order (match, mismatches by base, insertion, deletions by base);
 // the first surviving one becomes cur, the others are pushed with their
 // lower bounds.  Returns R_OK or R_STACK.
-__device__ int expand_children(u4 &cur, bool &valid, const uint32_t (&lo)[4], const uint32_t (&hi)[4], int b, int m, int maxd, int Di, int Dn, const Seed &S,
+__device__ int expand_children(u4 &cur, bool &valid, const Kids &k, bool gaps_only, int b, int m, int maxd, int Di, int Dn, const Seed &S,
                                const Params &P, LaneCtx &c, uint32_t K) {
     const int i = s_i(cur), gs = s_gs(cur), ngo = s_ngo(cur), nge = s_nge(cur), sd = s_sd(cur);
     const int score = s_score(cur), len = s_len(cur);
@@ -877,7 +1012,7 @@ __device__ int expand_children(u4 &cur, bool &valid, const uint32_t (&lo)[4], co
     const bool coded = (uint32_t)(len + 1) < K;
     uint32_t kx[4];
 #pragma unroll
-    for (int a = 0; a < 4; a++) kx[a] = coded ? (cur.x << 2) | (uint32_t)a : lo[a];
+    for (int a = 0; a < 4; a++) kx[a] = coded ? (cur.x << 2) | (uint32_t)a : k.x[a];
     const int diffs = s_nmm(cur) + ngo + nge;
     const int bound = (P.mode == BWFM_MODE_BEST && c.best != INF_SCORE) ? c.best + P.s_mm : INF_SCORE;
     const uint32_t z0 = cur.z & ~(3u << 10);  // gap state cleared
@@ -919,7 +1054,7 @@ __device__ int expand_children(u4 &cur, bool &valid, const uint32_t (&lo)[4], co
             const uint32_t w = (uint32_t)nsc | ((uint32_t)(len + 1) << 10) | ((uint32_t)lb << 20);
 #pragma unroll
             for (int a = 3; a >= 0; a--)
-                if (lo[a] < hi[a]) offer(kx[a], hi[a] - 1, z, w);
+                if (k.mask & (1u << a)) offer(kx[a], k.y[a], z, w);
         }
     }
     const int in_i = (i >= S.lo && i < S.hi) ? 1 : 0;
@@ -937,7 +1072,7 @@ __device__ int expand_children(u4 &cur, bool &valid, const uint32_t (&lo)[4], co
         }
     }
     // mismatches, then the match (offered last, so it becomes current)
-    {
+    if (!gaps_only) {
         const int nsc = score + P.s_mm;
         const int lb = nsc + P.minc * Dn;
         if (diffs + 1 <= maxd && (S.sl == 0 || sd + in_i <= P.seed_diff) && diffs + 1 + Dn <= maxd && lb <= bound) {
@@ -945,11 +1080,11 @@ __device__ int expand_children(u4 &cur, bool &valid, const uint32_t (&lo)[4], co
             const uint32_t w = (uint32_t)nsc | ((uint32_t)(len + 1) << 10) | ((uint32_t)lb << 20);
 #pragma unroll
             for (int a = 3; a >= 0; a--)
-                if (a != b && lo[a] < hi[a]) offer(kx[a], hi[a] - 1, z, w);
+                if (a != b && (k.mask & (1u << a))) offer(kx[a], k.y[a], z, w);
         }
         const int lbm = score + P.minc * Dn;
-        if (b < 4 && sel4(lo, b) < sel4(hi, b) && diffs + Dn <= maxd && lbm <= bound)
-            offer(sel4(kx, b), sel4(hi, b) - 1, z0 - 1u,
+        if (b < 4 && ((k.mask >> b) & 1u) && diffs + Dn <= maxd && lbm <= bound)
+            offer(sel4(kx, b), sel4(k.y, b), z0 - 1u,
                   (uint32_t)score | ((uint32_t)(len + 1) << 10) | ((uint32_t)lbm << 20));
     }
     if (have) cur = pend;
@@ -977,6 +1112,20 @@ __device__ __forceinline__ void row_fill(uint8_t *row, int at, int cnt, int z, i
     }
 }
 
+// Matches of row[di, di + q) with the text bases next to be prepended at
+// position p > 0 (words w0, w1) in the D-array scan's direction (0 for strand
+// +, 1 for strand -), where the pattern is taken from its start.
+__device__ __forceinline__ int dtext_matches(const DevIndex &ix, int strand, uint32_t p, uint32_t w0, uint32_t w1,
+                                             const uint8_t *row, int di, int q) {
+    uint32_t win = text_bases(ix, strand, p, w0, w1);
+    if (strand == 0) win = rev16(win);
+    uint32_t pc = row_code(row, di, q);
+    if (strand) pc = ~pc;
+    const uint32_t df = win ^ pc;
+    const int t = df ? (__ffs((int)df) - 1) >> 1 : 16;
+    return (int)min((uint32_t)min(t, q), p);
+}
+
 // D-array of one strand on the other index, in place over the staged
 // pattern (strand 0: row holds reverse(read), strand 1: its complement is
 // taken here).  Returns false when the bound already exceeds the budget at
@@ -999,6 +1148,29 @@ __device__ bool build_d(const DevIndex &ix, const DevDir &od, int m, int strand,
                 l = kl.y;
                 i += r;
                 fresh = false;
+                if (l == SINGLE && i < m) {
+                    // followed in the text to the first base that differs
+                    for (;;) {
+                        const int q = min(16, m - i);
+                        int t = 0;
+                        if (k) {
+                            const u2w w = *reinterpret_cast<const u2w *>(ix.pac + text_word(ix, strand, k));
+                            t = dtext_matches(ix, strand, k, w.x, w.y, c.pd, i, q);
+                        }
+                        row_fill(c.pd, i, t, z, strand);
+                        i += t;
+                        k -= (uint32_t)t;
+                        if (t < q || i == m) break;
+                    }
+                    if (i < m) {
+                        if (++z > maxd) return false;
+                        row_fill(c.pd, i, 1, z, strand);
+                        i++;
+                        k = 0;
+                        l = ix.n;
+                        fresh = true;
+                    }
+                }
             } else {
                 const int d = (int)kl.x - 1;  // bases that occur; the next one ends the segment
                 row_fill(c.pd, i, d, z, strand);
@@ -1044,9 +1216,13 @@ __device__ int search_strand(const DevIndex &ix, const DevDir &sd_, int m, int s
         int rr = resolve(cur, valid, strand, P, c, phase, 0x7fffffff, ix);
         if (rr == 0) return R_OK;
         if (rr < 0) return -rr;
-        uint32_t lo[4], hi[4];
-        if ((uint32_t)s_len(cur) < ix.kt_levels) {
-            const int bound = (P.mode == BWFM_MODE_BEST && c.best != INF_SCORE) ? c.best + P.s_mm : INF_SCORE;
+        Kids k;
+        bool gaps_only = false;
+        const int bound = (P.mode == BWFM_MODE_BEST && c.best != INF_SCORE) ? c.best + P.s_mm : INF_SCORE;
+        if (s_gs(cur) == GAP_RUN) {
+            unroll_run(cur, P, c, k);
+            gaps_only = true;
+        } else if ((uint32_t)s_len(cur) < ix.kt_levels) {
             const int q = run_steps(ix, cur, c.pd, maxd, bound, has_n, S, P);
             if (q) {
                 const u2 kl = reinterpret_cast<const u2 *>(sd_.kt)[run_entry(ix, cur, c.pd, q)];
@@ -1054,15 +1230,29 @@ __device__ int search_strand(const DevIndex &ix, const DevDir &sd_, int m, int s
                 continue;
             }
             const u4 *e = reinterpret_cast<const u4 *>(sd_.kt + 2 * (size_t)kt_children(s_len(cur), cur.x));
-            kt_pick(e[0], e[1], lo, hi);
+            kt_pick(e[0], e[1], k);
+            c.expand++;
+        } else if (cur.y == SINGLE || to_text(ix, cur)) {
+            if (cur.y != SINGLE) {
+                cur.x = sd_.full[cur.x];
+                cur.y = SINGLE;
+            }
+            const int dir = strand == 0 ? 1 : 0;
+            uint32_t win = 0;
+            if (cur.x) {
+                const u2w w = *reinterpret_cast<const u2w *>(ix.pac + text_word(ix, dir, cur.x));
+                win = text_bases(ix, dir, cur.x, w.x, w.y);
+                if (dir) win = rev16(win);
+            }
+            if (text_step(cur, win, maxd, bound, has_n, P, c, k)) continue;
         } else {
-            rank_children<LW>(ix, sd_, cur.x, cur.y + 1, lo, hi, false);
+            rank_children<LW>(ix, sd_, cur.x, cur.y + 1, k, false);
+            c.expand++;
         }
-        c.expand++;
         const int i = s_i(cur);
         const int b = pd_base(c, i);
         const int Di = pd_d(c, i), Dn = pd_d(c, i - 1);
-        int rc = expand_children(cur, valid, lo, hi, b, m, maxd, Di, Dn, S, P, c, ix.kt_levels);
+        int rc = expand_children(cur, valid, k, gaps_only, b, m, maxd, Di, Dn, S, P, c, ix.kt_levels);
         if (rc) return rc;
     }
 }
@@ -1470,7 +1660,8 @@ __global__ __launch_bounds__(BLOCK) void k_align_plain(DevIndex ix, ReadsView rd
 }
 
 enum { PZ_IDLE = 0, PZ_DSCAN = 1, PZ_SEARCH = 2, PZ_HELP = 3, PZ_WAIT = 4 };
-enum { ACT_NONE = 0, ACT_DSTEP = 1, ACT_EXPAND = 2, ACT_RUN = 3, ACT_DRUN = 4 };
+enum { ACT_NONE = 0, ACT_DSTEP = 1, ACT_EXPAND = 2, ACT_RUN = 3, ACT_DRUN = 4, ACT_TEXT = 5, ACT_DTEXT = 6,
+       ACT_UNROLL = 7 };
 
 // Per-wave block in LDS through which the lanes of a wave share one read's
 // search once the batch's reads are all taken: an idle lane receives the
@@ -1821,6 +2012,8 @@ __device__ __forceinline__ void persistent_body(const DevIndex &ix, const Params
         int act = ACT_NONE;
         int q = 0;           // bases the table entry covers: a run's steps, or a D-array segment's start
         uint32_t tent = 0;   // the entry
+        uint32_t tpos = 0;   // text position whose next bases are read
+        bool conv = false;   // the one row left becomes a text position
         bool query = false;  // rank query at q1, q2
         bool hit = false;
         int qdir = 0;  // index queried: 0 = T, 1 = reverse(T)
@@ -1837,6 +2030,9 @@ __device__ __forceinline__ void persistent_body(const DevIndex &ix, const Params
                 uint32_t code = rev_digits(row_code(own_pd, di, q), q);
                 if (strand) code ^= (1u << (2 * q)) - 1u;
                 tent = kt_start32(q) + code;
+            } else if (!dfresh && dl == SINGLE) {
+                act = ACT_DTEXT;
+                tpos = dk;
             } else {
                 const int b = own_pd[di] & 7;  // the staged base (strand +)
                 da = (strand == 0 || b > 3) ? b : 3 - b;
@@ -1861,11 +2057,19 @@ __device__ __forceinline__ void persistent_body(const DevIndex &ix, const Params
             if (rr == 1) {
                 act = ACT_EXPAND;
                 qdir = strand == 0 ? 1 : 0;
-                if ((uint32_t)s_len(cur) < ix.kt_levels) {
+                if (s_gs(cur) == GAP_RUN) {
+                    act = ACT_UNROLL;
+                } else if ((uint32_t)s_len(cur) < ix.kt_levels) {
                     const int bound = (P.mode == BWFM_MODE_BEST && c.best != INF_SCORE) ? c.best + P.s_mm : INF_SCORE;
                     q = run_steps(ix, cur, c.pd, maxd, bound, has_n, S, P);
                     if (q) act = ACT_RUN;
                     tent = q ? run_entry(ix, cur, c.pd, q) : kt_children(s_len(cur), cur.x);
+                } else if (cur.y == SINGLE) {
+                    act = ACT_TEXT;
+                    tpos = cur.x;
+                } else if (to_text(ix, cur)) {
+                    act = ACT_NONE;
+                    conv = true;
                 } else {
                     query = true;
                     q1 = cur.x;
@@ -1966,34 +2170,51 @@ __device__ __forceinline__ void persistent_body(const DevIndex &ix, const Params
         // the shared part: a table entry (the load issued first, so that its
         // latency overlaps the rank query's in other lanes), or the rank
         // counts at q1 and q2, on one index
-        uint32_t lo[4] = {0, 0, 0, 0}, hi[4] = {0, 0, 0, 0};
+        Kids kids;
+        kids.mask = 0;
+#pragma unroll
+        for (int a = 0; a < 4; a++) kids.x[a] = kids.y[a] = 0;
         const DevDir qd = pick_dir(ix, qdir);
-        if (O.work) w_query += query || tent;
+        if (O.work) w_query += query || tent || tpos || conv;
         u4 ta = mk4(0, 0, 0, 0), tb = ta;
+        uint32_t w0 = 0, w1 = 0;
         if (tent) {
             const u4 *e = reinterpret_cast<const u4 *>(qd.kt) + (tent >> 1);
             ta = e[0];
             if (q == 0) tb = e[1];
         }
-        if (query) rank_children<LW>(ix, qd, q1, q2, lo, hi, true);
-        if (tent && q == 0) kt_pick(ta, tb, lo, hi);
+        if (tpos) {
+            const u2w w = *reinterpret_cast<const u2w *>(ix.pac + text_word(ix, qdir, tpos));
+            w0 = w.x;
+            w1 = w.y;
+        }
+        if (conv) w0 = qd.full[cur.x];
+        if (query) rank_children<LW>(ix, qd, q1, q2, kids, true);
+        if (tent && q == 0) kt_pick(ta, tb, kids);
         const u2 tkl = (tent & 1) ? mk2(ta.z, ta.w) : mk2(ta.x, ta.y);
 
         // consume
-        if (!DP && (act == ACT_DSTEP || act == ACT_DRUN)) {
+        if (!DP && (act == ACT_DSTEP || act == ACT_DRUN || act == ACT_DTEXT)) {
             bool empty = true;
             if (act == ACT_DSTEP && da < 4) {
-                dk = sel4(lo, da);
-                const uint32_t h = sel4(hi, da);
-                empty = dk >= h;
-                dl = h - 1;
+                dk = sel4(kids.x, da);
+                dl = sel4(kids.y, da);
+                empty = !((kids.mask >> da) & 1u);
             }
             bool skip = false;
-            if (act == ACT_DRUN) {
-                empty = tkl.y == 0;
-                dk = tkl.x;
-                dl = tkl.y;
-                const int d = empty ? (int)tkl.x - 1 : q;  // bases that occur
+            if (act != ACT_DSTEP) {
+                int d;  // bases that occur
+                if (act == ACT_DRUN) {
+                    empty = tkl.y == 0;
+                    dk = tkl.x;
+                    dl = tkl.y;
+                    d = empty ? (int)tkl.x - 1 : q;
+                } else {
+                    const int r = min(16, m - di);
+                    d = tpos ? dtext_matches(ix, strand, tpos, w0, w1, own_pd, di, r) : 0;
+                    empty = d < r;
+                    dk = tpos - (uint32_t)d;
+                }
                 row_fill(own_pd, di, d, dz, strand);
                 di += d;
                 const int b = own_pd[empty ? di : 0] & 7;
@@ -2040,12 +2261,24 @@ __device__ __forceinline__ void persistent_body(const DevIndex &ix, const Params
             }
         } else if (act == ACT_RUN) {
             c.expand += run_take(cur, valid, tkl, c.pd, q, P);
-        } else if (act == ACT_EXPAND) {
-            c.expand++;
+        } else if (conv) {
+            cur.x = w0;
+            cur.y = SINGLE;
+        }
+        bool grow = act == ACT_EXPAND || act == ACT_UNROLL;
+        if (act == ACT_EXPAND) c.expand++;
+        if (act == ACT_UNROLL) unroll_run(cur, P, c, kids);
+        if (act == ACT_TEXT) {
+            uint32_t win = text_bases(ix, qdir, tpos, w0, w1);
+            if (qdir) win = rev16(win);
+            const int bound = (P.mode == BWFM_MODE_BEST && c.best != INF_SCORE) ? c.best + P.s_mm : INF_SCORE;
+            grow = !text_step(cur, win, maxd, bound, has_n, P, c, kids);
+        }
+        if (grow) {
             const int i = s_i(cur);
             const int b = pd_base(c, i);
             const int Di = pd_d(c, i), Dn = pd_d(c, i - 1);
-            int rc = expand_children(cur, valid, lo, hi, b, m, maxd, Di, Dn, S, P, c, ix.kt_levels);
+            int rc = expand_children(cur, valid, kids, act == ACT_UNROLL, b, m, maxd, Di, Dn, S, P, c, ix.kt_levels);
             if (rc) {
                 // cannot happen with worst-case stacks; kept as a guard
                 if (endgame) {
@@ -2237,29 +2470,53 @@ __global__ __launch_bounds__(BLOCK) void k_align_tasks(DevIndex ix, Params P, co
         }
         const DevDir qd = pick_dir(ix, strand == 0 ? 1 : 0);
         int q = 0;
-        uint32_t tent = 0;
-        uint32_t lo[4] = {0, 0, 0, 0}, hi[4] = {0, 0, 0, 0};
+        uint32_t tent = 0, w0 = 0, w1 = 0;
+        Kids kids;
+        kids.mask = 0;
+#pragma unroll
+        for (int a = 0; a < 4; a++) kids.x[a] = kids.y[a] = 0;
         u4 ta = mk4(0, 0, 0, 0), tb = ta;
-        if (query && (uint32_t)s_len(cur) < ix.kt_levels) {
-            const int bound = (P.mode == BWFM_MODE_BEST && c.best != INF_SCORE) ? c.best + P.s_mm : INF_SCORE;
+        const int qdir = strand == 0 ? 1 : 0;
+        const int bound = (P.mode == BWFM_MODE_BEST && c.best != INF_SCORE) ? c.best + P.s_mm : INF_SCORE;
+        const bool unroll = query && s_gs(cur) == GAP_RUN;
+        const bool shallow = query && !unroll && (uint32_t)s_len(cur) < ix.kt_levels;
+        const bool text = query && !unroll && !shallow && cur.y == SINGLE;
+        const bool conv = query && !unroll && !shallow && !text && to_text(ix, cur);
+        if (shallow) {
             q = run_steps(ix, cur, c.pd, maxd, bound, has_n, S, P);
             tent = q ? run_entry(ix, cur, c.pd, q) : kt_children(s_len(cur), cur.x);
             const u4 *e = reinterpret_cast<const u4 *>(qd.kt) + (tent >> 1);
             ta = e[0];
             if (q == 0) tb = e[1];
         }
-        if (query && tent == 0) rank_children<LW>(ix, qd, cur.x, cur.y + 1, lo, hi, true);
+        if (text && cur.x) {
+            const u2w w = *reinterpret_cast<const u2w *>(ix.pac + text_word(ix, qdir, cur.x));
+            w0 = w.x;
+            w1 = w.y;
+        }
+        if (conv) w0 = qd.full[cur.x];
+        const bool rank = query && !unroll && !shallow && !text && !conv;
+        if (rank) rank_children<LW>(ix, qd, cur.x, cur.y + 1, kids, true);
+        const uint32_t e0 = c.expand;
+        bool grow = unroll || rank || (shallow && q == 0);
+        if (rank || (shallow && q == 0)) c.expand++;
         if (q) {
-            const uint32_t n =
-                run_take(cur, valid, (tent & 1) ? mk2(ta.z, ta.w) : mk2(ta.x, ta.y), c.pd, q, P);
-            c.expand += n;
-            texp += n;
-        } else if (query) {
-            if (tent) kt_pick(ta, tb, lo, hi);
-            c.expand++;
-            texp++;
+            c.expand += run_take(cur, valid, (tent & 1) ? mk2(ta.z, ta.w) : mk2(ta.x, ta.y), c.pd, q, P);
+        } else if (conv) {
+            cur.x = w0;
+            cur.y = SINGLE;
+        } else if (text) {
+            uint32_t win = text_bases(ix, qdir, cur.x, w0, w1);
+            if (qdir) win = rev16(win);
+            grow = !text_step(cur, win, maxd, bound, has_n, P, c, kids);
+        } else if (unroll) {
+            unroll_run(cur, P, c, kids);
+        }
+        texp += c.expand - e0;
+        if (grow) {
+            if (shallow) kt_pick(ta, tb, kids);
             const int i = s_i(cur);
-            if (expand_children(cur, valid, lo, hi, pd_base(c, i), m, maxd, pd_d(c, i), pd_d(c, i - 1), S, P, c,
+            if (expand_children(cur, valid, kids, unroll, pd_base(c, i), m, maxd, pd_d(c, i), pd_d(c, i - 1), S, P, c,
                                 ix.kt_levels)) {
                 atomicOr(&X.slot_fail[s], 1u);  // cannot happen with worst-case stacks; kept as a guard
                 done = true;
@@ -2691,27 +2948,66 @@ __global__ __launch_bounds__(256) void k_kt_level(DevIndex ix, int which, int d,
     const DevDir dd = pick_dir(ix, which);
     const uint64_t pe = kt_level_start(d - 1) + p;
     const u2 kl = reinterpret_cast<const u2 *>(kt)[pe];
-    uint32_t lo[4], hi[4];
+    Kids k;
     if (mark && kl.y == 0) {
 #pragma unroll
         for (int a = 0; a < 4; a++) {
-            lo[a] = kl.x;
-            hi[a] = 1;
+            k.x[a] = kl.x;
+            k.y[a] = 0;
         }
     } else {
-        rank_children<LW>(ix, dd, kl.x, kl.y + 1, lo, hi, false);
+        rank_children<LW>(ix, dd, kl.x, kl.y + 1, k, false);
         if (mark) {
 #pragma unroll
             for (int a = 0; a < 4; a++)
-                if (lo[a] >= hi[a]) {
-                    lo[a] = (uint32_t)d;
-                    hi[a] = 1;
+                if (!(k.mask & (1u << a))) {
+                    k.x[a] = (uint32_t)d;
+                    k.y[a] = 0;
                 }
         }
     }
     u4 *dst = reinterpret_cast<u4 *>(kt + 2 * (size_t)kt_children(d - 1, (uint32_t)p));
-    dst[0] = mk4(lo[0], hi[0] - 1, lo[1], hi[1] - 1);
-    dst[1] = mk4(lo[2], hi[2] - 1, lo[3], hi[3] - 1);
+    dst[0] = mk4(k.x[0], k.y[0], k.x[1], k.y[1]);
+    dst[1] = mk4(k.x[2], k.y[2], k.x[3], k.y[3]);
+}
+
+// Strings of the deepest level that occur once get their position in the
+// direction's text: one thread per position of the text.
+__global__ __launch_bounds__(256) void k_kt_single(DevIndex ix, int which, int levels, uint32_t *kt) {
+    u2 *lv = reinterpret_cast<u2 *>(kt) + kt_level_start(levels);
+    for (uint64_t p = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; p + levels <= ix.n;
+         p += (uint64_t)gridDim.x * blockDim.x) {
+        // the string at p: T[p, p + levels), or T[n - p - levels, n - p) backwards
+        const uint32_t t0 = which == 0 ? (uint32_t)p : ix.n - (uint32_t)p - (uint32_t)levels;
+        const u2w w = *reinterpret_cast<const u2w *>(ix.pac + (t0 >> 4));
+        uint32_t code = __builtin_amdgcn_alignbit(w.y, w.x, 2 * (t0 & 15)) & ((1u << (2 * levels)) - 1u);
+        if (which) code = rev_digits(code, levels);
+        const u2 kl = lv[code];
+        if (kl.x == kl.y) lv[code] = mk2((uint32_t)p, SINGLE);
+    }
+}
+
+// The whole suffix array and its inverse from the sampled rows: one thread
+// per sampled row walks back through the text until the next sampled row (or
+// the text's start), so that every row is visited once.
+template <int LW>
+__global__ __launch_bounds__(256) void k_full_sa(DevIndex ix, int which, uint64_t n_samples, uint32_t *sa,
+                                                 uint32_t *isa) {
+    const DevDir d = pick_dir(ix, which);
+    const uint32_t mask = (1u << ix.sa_shift) - 1u;
+    for (uint64_t s = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; s < n_samples;
+         s += (uint64_t)gridDim.x * blockDim.x) {
+        uint32_t j = (uint32_t)(s << ix.sa_shift);
+        uint32_t q = d.sa[s];
+        for (;;) {
+            sa[j] = q;
+            isa[q] = j;
+            if (q == 0) break;
+            j = lf_step<LW>(ix, d, j);
+            q--;
+            if ((j & mask) == 0) break;
+        }
+    }
 }
 
 // level 0: the empty string's interval (0, n)
@@ -2825,7 +3121,9 @@ DevIndex dev_index(const bwfm_index *ix) {
         for (int a = 0; a < 4; a++) d.dir[k].C[a] = (uint32_t)ix->dir[k].C[a];
         d.dir[k].primary = (uint32_t)ix->dir[k].primary;
         d.dir[k].kt = (const uint32_t *)ix->d_jt[k];
+        d.dir[k].full = (const uint32_t *)ix->d_full[k];
     }
+    d.pac = (const uint32_t *)ix->d_pac;
     d.kt_levels = ix->jt_levels;
     d.magic = (uint64_t)(((unsigned __int128)1 << 64) / ix->bpl) + 1;
     d.n = (uint32_t)ix->n;
@@ -3262,30 +3560,51 @@ static void fill_table(const bwfm_index *ix, int d, uint32_t *kt, int levels, in
 // Depth: the least with 4^depth >= 2 n, at most 15, so that most of the
 // deepest strings are absent or unique and a run of exact matches ends in
 // its one entry: 100 Mbp: 14 levels, 2.9 GB per direction (its iterations per
-// read: 1031, with 13 levels 1223, with 12 1421).  It takes at most a quarter of the
-// free memory (less deep, or not made at all, where that is short: results
-// do not depend on it).
+// read: 1031, with 13 levels 1223, with 12 1421).  With it come the
+// whole suffix array and its inverse, 8 bytes a base and direction, which
+// turn rows into text positions and back.  All of it takes at most half of
+// the free memory (less deep, or not made at all, where that is short:
+// results do not depend on it).
 int bwfm::build_search_tables(bwfm_index *ix, hipStream_t st) {
     size_t free_b = 0, total_b = 0;
     HIPCHK(hipMemGetInfo(&free_b, &total_b));
     int levels = 1;
     while (levels < 15 && ((uint64_t)1 << (2 * levels)) < 2 * ix->n) levels++;
     free_b += dev_cached();
-    while (levels > 0 && 2 * kt_bytes((uint32_t)levels) > free_b / 4) levels--;
+    while (levels > 0 && 2 * (kt_bytes((uint32_t)levels) + 2 * (ix->n + 1) * 4) > free_b / 2) levels--;
     if (levels == 0) return BWFM_OK;
-    const uint64_t bytes = kt_bytes((uint32_t)levels);
-    if (dev_malloc(&ix->d_jt[0], bytes) != hipSuccess || dev_malloc(&ix->d_jt[1], bytes) != hipSuccess) {
-        (void)hipGetLastError();
-        dev_free(ix->d_jt[0]);
-        ix->d_jt[0] = ix->d_jt[1] = nullptr;
-        return BWFM_OK;
+    const uint64_t bytes = kt_bytes((uint32_t)levels), full = 2 * (ix->n + 1) * 4;
+    for (int d = 0; d < 2; d++)
+        if (dev_malloc(&ix->d_jt[d], bytes) || dev_malloc(&ix->d_full[d], full)) {
+            (void)hipGetLastError();
+            free_search_tables(ix);
+            return BWFM_OK;
+        }
+    DevIndex D = dev_index(ix);  // no levels yet: the builders read rank lines
+    for (int d = 0; d < 2; d++) {
+        uint32_t *kt = (uint32_t *)ix->d_jt[d], *sa = (uint32_t *)ix->d_full[d];
+        fill_table(ix, d, kt, levels, 1, st);
+        k_kt_single<<<(uint32_t)std::min<uint64_t>(blocks(ix->n, 256), 1u << 16), 256, 0, st>>>(D, d, levels, kt);
+        by_layout(ix, [&](auto t) {
+            k_full_sa<decltype(t)::value><<<(uint32_t)std::min<uint64_t>(blocks(ix->n_samples, 256), 1u << 16), 256, 0,
+                                            st>>>(D, d, ix->n_samples, sa, sa + ix->n + 1);
+            return 0;
+        });
     }
-    for (int d = 0; d < 2; d++) fill_table(ix, d, (uint32_t *)ix->d_jt[d], levels, 1, st);
     HIPCHK(hipGetLastError());
     HIPCHK(hipStreamSynchronize(st));
     ix->jt_levels = (uint32_t)levels;
-    ix->device_bytes += 2 * bytes;
+    ix->device_bytes += 2 * (bytes + full);
     return BWFM_OK;
+}
+
+void bwfm::free_search_tables(bwfm_index *ix) {
+    for (int d = 0; d < 2; d++) {
+        dev_free(ix->d_jt[d]);
+        dev_free(ix->d_full[d]);
+        ix->d_jt[d] = ix->d_full[d] = nullptr;
+    }
+    ix->jt_levels = 0;
 }
 
 extern "C" int bwfm_index_upload(bwfm_index *ix, void *stream) {
@@ -3304,7 +3623,7 @@ extern "C" int bwfm_index_upload(bwfm_index *ix, void *stream) {
         HIPCHK(hipMemcpyAsync(ix->d_sa[d], ix->dir[d].sa.data(), sb, hipMemcpyHostToDevice, st));
         bytes += lb + sb;
     }
-    const size_t pb = std::max<size_t>(ix->pac.size(), 1) * 4;
+    const size_t pb = (ix->pac.size() + 2) * 4;  // two words of padding (text_word)
     if (dev_malloc(&ix->d_pac, pb) != hipSuccess) return fail(BWFM_E_NOMEM, "index upload: device allocation failed");
     if (!ix->pac.empty())
         HIPCHK(hipMemcpyAsync(ix->d_pac, ix->pac.data(), ix->pac.size() * 4, hipMemcpyHostToDevice, st));
@@ -3372,8 +3691,8 @@ extern "C" void bwfm_index_free(bwfm_index *ix) {
         dev_free(ix->d_lines[d]);
         dev_free(ix->d_sa[d]);
         if (ix->d_kt[d]) (void)hipFree(ix->d_kt[d]);
-        dev_free(ix->d_jt[d]);
     }
+    free_search_tables(ix);
     dev_free(ix->d_pac);
     for (auto &kv : ix->ws) {
         dev_free(kv.second->ptr);

@@ -31,11 +31,13 @@ struct DevDir {
     uint32_t C[4];
     uint32_t primary;
     uint32_t pad;
+    const uint32_t *full;  // SA[0, n] then its inverse, with the interval table
     const uint32_t *kt;  // the search's interval table, (k, l) word pairs (kt_level_start), or null
 };
 
 struct DevIndex {
     DevDir dir[2];
+    const uint32_t *pac;  // the reference, two bits per base
     uint64_t magic;       // floor(2^64 / bases_per_line) + 1: row / bpl = mulhi(row, magic)
     uint32_t n;           // text length (n + 1 < 2^32)
     uint32_t bpl;         // rows per rank line
@@ -85,6 +87,7 @@ void pack_ref(const uint8_t *text, uint64_t n, std::vector<uint32_t> &out);
 // Device structures the search derives from the uploaded index (bwfm.hip):
 // 0 or a bwfm_err.  Without room for them the index works without.
 int build_search_tables(bwfm_index *ix, ihipStream_t *st);
+void free_search_tables(bwfm_index *ix);
 
 // Device blocks through the library's bounded pool (index_gpu.hip): as
 // hipMalloc (its error code, 0 = success) and hipFree on the current device.
@@ -108,6 +111,7 @@ struct bwfm_index {
     void *d_pac = nullptr;
     void *d_jt[2] = {nullptr, nullptr};  // the search's interval tables, made at upload
     uint32_t jt_levels = 0;              // their depth (0: none)
+    void *d_full[2] = {nullptr, nullptr};  // per direction SA[0, n], then its inverse (with the tables)
     void *d_kt[2] = {nullptr, nullptr};  // the caller's short-string tables (bwfm_index_kmer_table)
     uint32_t kt_levels = 0;
     uint64_t device_bytes = 0;

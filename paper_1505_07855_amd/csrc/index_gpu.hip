@@ -474,7 +474,7 @@ extern "C" int bwfm_build_index_device(const uint8_t *ref, uint64_t n, const bwf
     if (hipMemcpyAsync(t, ref, n, hipMemcpyHostToDevice, st) != hipSuccess)
         rc = fail(BWFM_E_DEVICE, "index build: text upload");
     const uint64_t pac_words = (n + 15) / 16;
-    if (!rc && dev_malloc(&ix->d_pac, pac_words * 4) != hipSuccess) rc = fail(BWFM_E_NOMEM, "index build: packed text");
+    if (!rc && dev_malloc(&ix->d_pac, (pac_words + 2) * 4) != hipSuccess) rc = fail(BWFM_E_NOMEM, "index build: packed text");
     if (!rc) {
         k_pack_ref<<<grid_for(pac_words, 256), 256, 0, st>>>(t, n, (uint32_t *)ix->d_pac);
         try {
@@ -505,9 +505,9 @@ extern "C" int bwfm_build_index_device(const uint8_t *ref, uint64_t n, const bwf
     dev_free(rp);
     if (!rc) rc = build_search_tables(ix.get(), st);
     if (rc) {
+        free_search_tables(ix.get());
         for (int d = 0; d < 2; d++) {
-            dev_free(ix->d_jt[d]);
-            ix->d_jt[d] = nullptr;
+
             dev_free(ix->d_lines[d]);
             dev_free(ix->d_sa[d]);
             ix->d_lines[d] = ix->d_sa[d] = nullptr;
