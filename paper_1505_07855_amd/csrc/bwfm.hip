@@ -81,8 +81,6 @@ constexpr uint32_t PLAIN_STACK = 320;  // stack entries per lane, plain form fir
 //             one 64-bit shift (1).
 //   PAIRLINE: the paired rank query of planar lines shares a line that
 //             holds both rows (0) or always fetches two (1).
-//   REFILL:   idle lanes take new reads every iteration (0) or only once a
-//             quarter of the wave is idle or no lane is busy (1).
 //   SUBHDR:   with SUBLOAD 0, a 128-byte sub-counted query reads the
 //             boundary words only for rows past 128 (0) or always (1).
 #ifndef BWFM_GENE_ROWMASK
@@ -91,24 +89,17 @@ constexpr uint32_t PLAIN_STACK = 320;  // stack entries per lane, plain form fir
 #ifndef BWFM_GENE_PAIRLINE
 #define BWFM_GENE_PAIRLINE 0
 #endif
-#ifndef BWFM_GENE_REFILL
-#define BWFM_GENE_REFILL 0
-#endif
 #ifndef BWFM_GENE_SUBHDR
 #define BWFM_GENE_SUBHDR 0
 #endif
-//   DPREPASS: the batched form scans each read's D-arrays inside the
-//             persistent loop, one rank query per iteration, unless its
-//             reads may be DPRE_MIN_LEN bases or longer (0), or always (1)
-//             in a pre-pass kernel of its own, one lane per read, so the
-//             loop only searches.
-#ifndef BWFM_GENE_DPREPASS
-#define BWFM_GENE_DPREPASS 0
+// Reads of a batch are long when max_len reaches this: their few largest
+// trees are split early (DRAIN_EIGHTHS).
+constexpr uint32_t LONG_READ = 200;
+// Lanes of a wave that must wait for a strand or read change before the wave
+// makes them (BWFM_TURN_MIN may override it).
+#ifndef BWFM_TURN_MIN
+#define BWFM_TURN_MIN 8
 #endif
-// Batches whose max_len reaches this scan their D-arrays in the pre-pass:
-// on 250 bp reads the pre-pass and a loop that only searches take 5-6% less
-// time than the loop's own scans, on 100 bp reads 7% more.
-constexpr uint32_t DPRE_MIN_LEN = 200;
 //   SUBLOAD:  a 128-byte sub-counted query loads the line's first 16 bytes
 //             and, past row 128, its next 16 (0), or 12 bytes of counts and
 //             the one boundary word its row needs (1, shipped: fewer
@@ -1426,7 +1417,7 @@ constexpr uint32_t SLOT_HITS = 2 * FAST_CAND;
 // [SPLIT_DONE] waves of the first pass that have ended
 constexpr uint32_t SPLIT_DONE = 2 * (SPLIT_ROUNDS + 1) + 2;
 constexpr uint32_t SPLIT_CTL = SPLIT_DONE + 1;
-// Long reads (the builds with the D-array pre-pass): once DRAIN_EIGHTHS of
+// Batches of long reads (LONG_READ): once DRAIN_EIGHTHS of
 // the first pass's waves have ended, the parts still running are split after
 // DRAIN_BUDGET expansions already: the few reads with the largest trees would
 // otherwise hold single waves until each part has reached the full budget
@@ -1454,6 +1445,7 @@ struct SplitBufs {
     uint32_t slot_cap, task_cap, dstride;
     uint32_t budget;  // expansions of a lane's part of a read before it is split (endgame); 0: off
     uint32_t count;   // nonzero: the parts' expansions are summed (per-read work counters)
+    uint32_t drain;   // nonzero: a batch of long reads, split early at the end (DRAIN_EIGHTHS)
 };
 
 __device__ __forceinline__ uint32_t ld_agent(const uint32_t *p) {
@@ -1659,9 +1651,8 @@ __global__ __launch_bounds__(BLOCK) void k_align_plain(DevIndex ix, ReadsView rd
     publish(c, P, O, r);
 }
 
-enum { PZ_IDLE = 0, PZ_DSCAN = 1, PZ_SEARCH = 2, PZ_HELP = 3, PZ_WAIT = 4 };
-enum { ACT_NONE = 0, ACT_DSTEP = 1, ACT_EXPAND = 2, ACT_RUN = 3, ACT_DRUN = 4, ACT_TEXT = 5, ACT_DTEXT = 6,
-       ACT_UNROLL = 7 };
+enum { PZ_IDLE = 0, PZ_TURN = 1, PZ_SEARCH = 2, PZ_HELP = 3, PZ_WAIT = 4 };
+enum { ACT_NONE = 0, ACT_EXPAND = 1, ACT_RUN = 2, ACT_TEXT = 3, ACT_UNROLL = 4 };
 
 // Per-wave block in LDS through which the lanes of a wave share one read's
 // search once the batch's reads are all taken: an idle lane receives the
@@ -1693,10 +1684,11 @@ __device__ __forceinline__ void wave_fence() {
 }
 
 // Batched form: a persistent grid whose lanes pull reads from a shared
-// counter.  Each loop iteration performs one rank-query pair per busy lane --
-// a D-array step or a search expansion -- so lanes at different stages of
-// different reads still share the expensive part, and a lane whose read is
-// done takes the next one at once (wave-wide ballot, one atomic per wave).
+// counter.  Each loop iteration performs one search expansion per busy lane,
+// so lanes at different stages of different reads still share its memory
+// round trips.  Lanes whose strand or read has ended wait until BWFM_TURN_MIN
+// of the wave do; they then publish, take the next reads (one atomic per
+// wave) and copy their rows together, sharing those round trips too.
 // When the counter runs past the batch, idle lanes help the busy lanes of
 // their wave through WaveShare instead of waiting for the slowest one.
 // Arguments of the batched kernel that are used only at read boundaries:
@@ -1727,9 +1719,11 @@ __device__ __forceinline__ const uint8_t *drow_of(const uint8_t *drows, uint32_t
 }
 
 // D-array pre-pass of the batched form: one lane per read, both strands in
-// turn on the other index (the same scan as the plain form's, with the
-// short-string table when the index has one), each strand's row staged in
-// LDS and then copied out whole.
+// turn on the other index, each strand's row staged in LDS and then copied
+// out whole.  (In the search loop the same scan cost every wave its
+// instructions in every iteration, though 4% of the lanes were at it: 2M
+// reads of 100 bases searched in 72.7 ms with the scan in the loop, in 59.2
+// with this pass's 3.3 ms before it and the grouped read changes.)
 template <int LW>
 __global__ __launch_bounds__(BLOCK) void k_dscan(DevIndex ix, ReadsView rd, Params P, uint8_t *drows, uint8_t *dflag,
                                                  uint32_t dstride, uint32_t lstride) {
@@ -1786,9 +1780,7 @@ __global__ void k_set_args(PersistentArgs *dst, PersistentArgs a) {
     if (threadIdx.x == 0) *dst = a;
 }
 
-// DP: the D-arrays come from the pre-pass (k_dscan); otherwise the loop
-// scans them itself.
-template <int LW, bool DP>
+template <int LW>
 __device__ __forceinline__ void persistent_body(const DevIndex &ix, const Params &P, const PersistentArgs *Aarg) {
     // the argument block, through an address space the compiler sees
     using GlobalArgs = const __attribute__((address_space(1))) PersistentArgs;
@@ -1826,11 +1818,8 @@ __device__ __forceinline__ void persistent_body(const DevIndex &ix, const Params
     int ow = lane;         // owner lane of the read this lane works on
     uint32_t r = 0;
     int m = 0, maxd = 0, strand = 0;
-    bool has_n = false;  // the read holds an N
-    // D scan state
-    int di = 0, dz = 0;
-    uint32_t dk = 0, dl = 0;
-    bool dfresh = true;  // at the start of a segment
+    bool has_n = false;   // the read holds an N
+    bool two = false;     // strand - is searched too
     // search state
     u4 cur = mk4(0, 0, 0, 0);
     bool valid = false;
@@ -1846,70 +1835,85 @@ __device__ __forceinline__ void persistent_body(const DevIndex &ix, const Params
         const ReadsView &rd = A->rd;
         const ReadOut &O = A->O;
         uint32_t *const next_read = A->next_read;
-        // refill idle lanes, one atomic per wave
-        const bool want = phase == PZ_IDLE && !exhausted;
-        const unsigned long long wm = __ballot(want);
-#if BWFM_GENE_REFILL == 1
-        // refill in bulk: a quarter of the wave idle, or nothing left running
-        if (wm && (__popcll(wm) >= 16 || __ballot(phase != PZ_IDLE) == 0)) {
-#else
-        if (wm) {
-#endif
-            const int leader = __ffsll(wm) - 1;
-            uint32_t base = 0;
-            if (lane == leader) base = atomicAdd(as_global(next_read), (uint32_t)__popcll(wm));
-            base = __shfl(base, leader);
-            if (want) {
-                const uint32_t rr = base + (uint32_t)__popcll(wm & ((1ULL << lane) - 1));
-                if (rr >= n_reads) {
-                    exhausted = true;
+        // lanes whose strand or read has ended, and idle ones while reads are
+        // left, once enough of them wait (in the endgame, at once)
+        const bool turn = phase == PZ_TURN || (phase == PZ_IDLE && !exhausted);
+        const unsigned long long tm = __ballot(turn);
+        if (tm && (endgame || __popcll(tm) >= BWFM_TURN_MIN || __ballot(phase >= PZ_SEARCH) == 0)) {
+            bool load = false;
+            if (phase == PZ_TURN) {
+                const int fl = sh_ld(&ws.flags[lane]);
+                if (fl & SH_FAIL) {
+                    if (fl >> SH_SLOT_SHIFT)
+                        end_split_read(A->X, c, fl);
+                    else
+                        send_to_second_pass(O, r);
+                    if (O.expand) O.expand[r] = c.expand + (uint32_t)sh_ld(&ws.hexp[lane]);
+                    phase = PZ_IDLE;
+                } else if (strand == 0 && two) {
+                    strand = 1;
+                    load = true;
                 } else {
-                    r = rr;
-                    uint64_t o0;
-                    if (!check_read(rd, P, O, r, m, maxd, o0)) {
-                        ow = lane;
-                        c.pd = own_pd;
-                        c.cand = own_cand;
-                        c.ncand = 0;
-                        c.best = INF_SCORE;
-                        c.expand = 0;
-                        if (DP) {
+                    c.ncand = (uint32_t)sh_ld(&ws.ncand[lane]);
+                    const int sb = sh_ld(&ws.best[lane]);
+                    if (sb < c.best) c.best = sb;
+                    c.cand = own_cand;
+                    c.expand += (uint32_t)sh_ld(&ws.hexp[lane]);
+                    if (fl >> SH_SLOT_SHIFT)
+                        end_split_read(A->X, c, fl);
+                    else
+                        publish(c, P, O, r, (fl & SH_HELPED) ? (uint8_t)BWFM_ST_SHARED : (uint8_t)0);
+                    phase = PZ_IDLE;
+                }
+            }
+            const bool want = phase == PZ_IDLE && !exhausted;
+            const unsigned long long wm = __ballot(want);
+            if (wm) {
+                const int leader = __ffsll(wm) - 1;
+                uint32_t base = 0;
+                if (lane == leader) base = atomicAdd(as_global(next_read), (uint32_t)__popcll(wm));
+                base = __shfl(base, leader);
+                if (want) {
+                    const uint32_t rr = base + (uint32_t)__popcll(wm & ((1ULL << lane) - 1));
+                    if (rr >= n_reads) {
+                        exhausted = true;
+                    } else {
+                        r = rr;
+                        uint64_t o0;
+                        if (!check_read(rd, P, O, r, m, maxd, o0)) {
+                            ow = lane;
+                            c.pd = own_pd;
+                            c.cand = own_cand;
+                            c.ncand = 0;
+                            c.best = INF_SCORE;
+                            c.expand = 0;
                             // the first strand the pre-pass left searchable,
                             // or nothing to search
-                            const int dfl = A->dflag[r];
+                            const int dfl = as_global(A->dflag)[r];
                             has_n = (dfl & 4) != 0;
+                            two = (dfl & 2) == 0;
                             strand = (dfl & 1) ? 1 : 0;
-                            if ((dfl & 3) == 3) {
-                                publish(c, P, O, r);
-                                phase = PZ_IDLE;
-                            } else {
-                                load_drow(own_pd, drow_of(A->drows, A->dstride, r, strand), m);
-                                phase = PZ_SEARCH;
-                                cur = root_state(ix, m, P.minc * pd_d(c, m - 1));
-                                valid = true;
-                                c.sp = c.sbase = 0;
-                            }
-                        } else {
-                            has_n = stage_read(own_pd, rd.bases + o0, m);
-                            strand = 0;
-                            phase = PZ_DSCAN;
-                            di = 0;
-                            dz = 0;
-                            dk = 0;
-                            dl = ix.n;
-                            dfresh = true;
+                            load = (dfl & 3) != 3;
+                            if (!load) publish(c, P, O, r);
+                            S = seed_of(P, m);
+                            sh_st(&ws.best[lane], INF_SCORE);
+                            sh_st(&ws.ncand[lane], 0);
+                            sh_st(&ws.pending[lane], 0);
+                            sh_st(&ws.flags[lane], 0);
+                            sh_st(&ws.hexp[lane], 0);
+                            if (A->X.budget) A->lane_read[gl] = r;
                         }
-                        S = seed_of(P, m);
-                        sh_st(&ws.best[lane], INF_SCORE);
-                        sh_st(&ws.ncand[lane], 0);
-                        sh_st(&ws.pending[lane], 0);
-                        sh_st(&ws.flags[lane], 0);
-                        sh_st(&ws.hexp[lane], 0);
-                        if (A->X.budget) A->lane_read[gl] = r;
                     }
                 }
             }
             if (cap < 64) exhausted = true;
+            if (load) {
+                load_drow(own_pd, drow_of(A->drows, A->dstride, r, strand), m);
+                phase = PZ_SEARCH;
+                cur = root_state(ix, m, P.minc * pd_d(c, m - 1));
+                valid = true;
+                c.sp = c.sbase = 0;
+            }
         }
         if (__ballot(phase != PZ_IDLE) == 0) {
             if (__ballot(!exhausted) == 0) break;
@@ -1918,7 +1922,7 @@ __device__ __forceinline__ void persistent_body(const DevIndex &ix, const Params
         endgame = endgame || __ballot(exhausted) != 0;
         if (O.work) {
             w_iters++;
-            w_busy += phase != PZ_IDLE && phase != PZ_WAIT;
+            w_busy += phase == PZ_SEARCH || phase == PZ_HELP;
         }
 
         if (endgame) {
@@ -1981,7 +1985,7 @@ __device__ __forceinline__ void persistent_body(const DevIndex &ix, const Params
             // the hand-over for a helper
             uint32_t bud = A->X.budget;
             if (bud) {
-                if (DP) {
+                if (A->X.drain) {
                     if ((eg_iter++ & 15) == 15 && !drain)
                         drain = (uint64_t)ld_agent(&A->X.ctl[SPLIT_DONE]) * 8 >= (uint64_t)n_waves * DRAIN_EIGHTHS;
                     if (drain) bud = min(bud, DRAIN_BUDGET);
@@ -2010,7 +2014,7 @@ __device__ __forceinline__ void persistent_body(const DevIndex &ix, const Params
         // decide this lane's action and rank queries; a lane that changes
         // phase here acts in its new phase from the next iteration on
         int act = ACT_NONE;
-        int q = 0;           // bases the table entry covers: a run's steps, or a D-array segment's start
+        int q = 0;           // steps of the run the table entry covers
         uint32_t tent = 0;   // the entry
         uint32_t tpos = 0;   // text position whose next bases are read
         bool conv = false;   // the one row left becomes a text position
@@ -2018,29 +2022,8 @@ __device__ __forceinline__ void persistent_body(const DevIndex &ix, const Params
         bool hit = false;
         int qdir = 0;  // index queried: 0 = T, 1 = reverse(T)
         uint32_t q1 = 0, q2 = 0;
-        int da = 4;
         bool part_done = false;  // this lane's part of the strand's search is over
-        if (!DP && phase == PZ_DSCAN) {
-            act = ACT_DSTEP;
-            qdir = strand == 0 ? 0 : 1;
-            if (dfresh && ix.kt_levels && !has_n) {
-                // a segment's first bases in one table entry
-                act = ACT_DRUN;
-                q = min((int)ix.kt_levels, m - di);
-                uint32_t code = rev_digits(row_code(own_pd, di, q), q);
-                if (strand) code ^= (1u << (2 * q)) - 1u;
-                tent = kt_start32(q) + code;
-            } else if (!dfresh && dl == SINGLE) {
-                act = ACT_DTEXT;
-                tpos = dk;
-            } else {
-                const int b = own_pd[di] & 7;  // the staged base (strand +)
-                da = (strand == 0 || b > 3) ? b : 3 - b;
-                query = da < 4;
-                q1 = dk;
-                q2 = dl + 1;
-            }
-        } else if (phase == PZ_SEARCH || phase == PZ_HELP) {
+        if (phase == PZ_SEARCH || phase == PZ_HELP) {
             int rr = resolve(cur, valid, strand, P, c, PH_FAST, POPS_PER_STEP, ix, endgame);
             if (rr == 2) {
                 // pop limit reached: keep popping next iteration
@@ -2129,42 +2112,7 @@ __device__ __forceinline__ void persistent_body(const DevIndex &ix, const Params
         }
         if (phase == PZ_WAIT && sh_ld(&ws.pending[lane]) == 0) {
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-            const int fl = sh_ld(&ws.flags[lane]);
-            if (fl & SH_FAIL) {
-                if (fl >> SH_SLOT_SHIFT)
-                    end_split_read(A->X, c, fl);
-                else
-                    send_to_second_pass(O, r);
-                if (O.expand) O.expand[r] = c.expand + (uint32_t)sh_ld(&ws.hexp[lane]);
-                phase = PZ_IDLE;
-            } else if (strand == 0 && (!DP || !(A->dflag[r] & 2))) {
-                strand = 1;
-                if (DP) {
-                    load_drow(own_pd, drow_of(A->drows, A->dstride, r, 1), m);
-                    phase = PZ_SEARCH;
-                    cur = root_state(ix, m, P.minc * pd_d(c, m - 1));
-                    valid = true;
-                    c.sp = c.sbase = 0;
-                } else {
-                    phase = PZ_DSCAN;
-                    di = 0;
-                    dz = 0;
-                    dk = 0;
-                    dl = ix.n;
-                    dfresh = true;
-                }
-            } else {
-                c.ncand = (uint32_t)sh_ld(&ws.ncand[lane]);
-                const int sb = sh_ld(&ws.best[lane]);
-                if (sb < c.best) c.best = sb;
-                c.cand = own_cand;
-                c.expand += (uint32_t)sh_ld(&ws.hexp[lane]);
-                if (fl >> SH_SLOT_SHIFT)
-                    end_split_read(A->X, c, fl);
-                else
-                    publish(c, P, O, r, (fl & SH_HELPED) ? (uint8_t)BWFM_ST_SHARED : (uint8_t)0);
-                phase = PZ_IDLE;
-            }
+            phase = PZ_TURN;
         }
 
         // the shared part: a table entry (the load issued first, so that its
@@ -2194,72 +2142,7 @@ __device__ __forceinline__ void persistent_body(const DevIndex &ix, const Params
         const u2 tkl = (tent & 1) ? mk2(ta.z, ta.w) : mk2(ta.x, ta.y);
 
         // consume
-        if (!DP && (act == ACT_DSTEP || act == ACT_DRUN || act == ACT_DTEXT)) {
-            bool empty = true;
-            if (act == ACT_DSTEP && da < 4) {
-                dk = sel4(kids.x, da);
-                dl = sel4(kids.y, da);
-                empty = !((kids.mask >> da) & 1u);
-            }
-            bool skip = false;
-            if (act != ACT_DSTEP) {
-                int d;  // bases that occur
-                if (act == ACT_DRUN) {
-                    empty = tkl.y == 0;
-                    dk = tkl.x;
-                    dl = tkl.y;
-                    d = empty ? (int)tkl.x - 1 : q;
-                } else {
-                    const int r = min(16, m - di);
-                    d = tpos ? dtext_matches(ix, strand, tpos, w0, w1, own_pd, di, r) : 0;
-                    empty = d < r;
-                    dk = tpos - (uint32_t)d;
-                }
-                row_fill(own_pd, di, d, dz, strand);
-                di += d;
-                const int b = own_pd[empty ? di : 0] & 7;
-                da = strand ? 3 - b : b;
-            }
-            dfresh = empty;
-            if (empty) {
-                dz++;
-                dk = 0;
-                dl = ix.n;
-                skip = dz > maxd;
-            }
-            if (!skip && (empty || act == ACT_DSTEP)) {
-                own_pd[di] = (uint8_t)(da | (dz << 3));
-                di++;
-            }
-            if (skip || di == m) {
-                if (!skip) {
-                    phase = PZ_SEARCH;
-                    cur = root_state(ix, m, P.minc * dz);
-                    valid = true;
-                    c.sp = c.sbase = 0;
-                } else if (strand == 0) {
-                    strand = 1;
-                    di = 0;
-                    dz = 0;
-                    dk = 0;
-                    dl = ix.n;
-                    dfresh = true;
-                } else {
-                    // strand - cannot match; the read's helpers, if any,
-                    // were all done before this D scan began
-                    c.ncand = (uint32_t)sh_ld(&ws.ncand[lane]);
-                    const int sb = sh_ld(&ws.best[lane]);
-                    if (sb < c.best) c.best = sb;
-                    c.expand += (uint32_t)sh_ld(&ws.hexp[lane]);
-                    const int fl = sh_ld(&ws.flags[lane]);
-                    if (fl >> SH_SLOT_SHIFT)
-                        end_split_read(A->X, c, fl);
-                    else
-                        publish(c, P, O, r, (fl & SH_HELPED) ? (uint8_t)BWFM_ST_SHARED : (uint8_t)0);
-                    phase = PZ_IDLE;
-                }
-            }
-        } else if (act == ACT_RUN) {
+        if (act == ACT_RUN) {
             c.expand += run_take(cur, valid, tkl, c.pd, q, P);
         } else if (conv) {
             cur.x = w0;
@@ -2291,7 +2174,7 @@ __device__ __forceinline__ void persistent_body(const DevIndex &ix, const Params
             }
         }
     }
-    if (DP && A->X.budget && lane == 0) atomicAdd(as_global(&A->X.ctl[SPLIT_DONE]), 1u);
+    if (A->X.budget && lane == 0) atomicAdd(as_global(&A->X.ctl[SPLIT_DONE]), 1u);
     if (A->O.work) {
         if (lane == 0) atomicAdd(&A->O.work[0], (unsigned long long)w_iters);
         atomicAdd(&A->O.work[1], (unsigned long long)w_busy);
@@ -2304,24 +2187,21 @@ __device__ __forceinline__ void persistent_body(const DevIndex &ix, const Params
 // waves stay resident per SIMD.  The search is latency-bound, so the second
 // is faster on the benchmark batch (122 ms against 134); a build held to 96
 // VGPRs spills to scratch and is slower still (205 ms).  The autotuner picks.
-template <int LW, bool DP = false>
+template <int LW>
 __global__ __launch_bounds__(BLOCK) void k_align_persistent(DevIndex ix, Params P, const PersistentArgs *A) {
-    persistent_body<LW, DP>(ix, P, A);
+    persistent_body<LW>(ix, P, A);
 }
-template <int LW, bool DP = false>
+template <int LW>
 __global__ __launch_bounds__(BLOCK, 4) void k_align_persistent4(DevIndex ix, Params P, const PersistentArgs *A) {
-    persistent_body<LW, DP>(ix, P, A);
+    persistent_body<LW>(ix, P, A);
 }
 
 using PersistentKernel = void (*)(DevIndex, Params, const PersistentArgs *);
 
 // the build serving a waves_per_simd setting: 0 and >= 4 take the 4-wave
-// build, 1-3 the compiler's own; dp: D-arrays from the pre-pass
+// build, 1-3 the compiler's own
 template <int LW>
-PersistentKernel persistent_kernel(int waves_per_simd, bool dp = false) {
-    if (dp)
-        return (waves_per_simd == 0 || waves_per_simd >= 4) ? k_align_persistent4<LW, true>
-                                                              : k_align_persistent<LW, true>;
+PersistentKernel persistent_kernel(int waves_per_simd) {
     return (waves_per_simd == 0 || waves_per_simd >= 4) ? k_align_persistent4<LW> : k_align_persistent<LW>;
 }
 
@@ -3224,12 +3104,12 @@ size_t scan_part_elems(uint64_t n) { return (n + SCAN_BLOCK - 1) / SCAN_BLOCK + 
 // size and its dynamic LDS, at most waves_per_simd waves per SIMD (0 = no
 // cap; a CU has 4 SIMDs).
 template <int LW>
-uint32_t persistent_lanes(uint32_t bs, size_t lds, int waves_per_simd, bool dp = false) {
+uint32_t persistent_lanes(uint32_t bs, size_t lds, int waves_per_simd) {
     int dev = 0, cus = 0, per_cu = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
         cus = 256;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, persistent_kernel<LW>(waves_per_simd, dp), (int)bs, lds) !=
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, persistent_kernel<LW>(waves_per_simd), (int)bs, lds) !=
             hipSuccess ||
         per_cu < 1)
         per_cu = 1;
@@ -3372,13 +3252,11 @@ int align_impl(bwfm_index *ix, bwfm::Workspace &ws, const bwfm_reads *rd, const 
     const uint32_t lstride = lds_stride_for(mlen);
     const bool plain = p->form == BWFM_FORM_PLAIN;
     const uint32_t sbud = plain ? 0u : split_budget_of(*p);  // split searches (batched form)
-    // the D-array pre-pass (batched form, long reads or when that gene is on)
-    const bool dpre = !plain && (BWFM_GENE_DPREPASS == 1 || mlen >= DPRE_MIN_LEN);
     const uint32_t bs = block_for(lstride);
     const size_t lds = (size_t)bs * lstride + (plain ? 0 : (bs / 64) * sizeof(WaveShare));
     const uint32_t nr_up = ((std::max<uint32_t>(n, 1) + bs - 1) / bs) * bs;
     const uint32_t lanes =
-        plain ? nr_up : batched_lanes(persistent_lanes<LW>(bs, lds, p->waves_per_simd, dpre), n, bs);
+        plain ? nr_up : batched_lanes(persistent_lanes<LW>(bs, lds, p->waves_per_simd), n, bs);
     const uint32_t stack_cap = plain ? std::min<uint32_t>(worst_stack, PLAIN_STACK) : worst_stack;
     // the task rounds' grid shares the lane buffers: room for the larger one
     const uint32_t tlanes = sbud ? task_lanes<LW>(nr_up, lanes) : 0u;
@@ -3394,7 +3272,7 @@ int align_impl(bwfm_index *ix, bwfm::Workspace &ws, const bwfm_reads *rd, const 
     need += sizeof(PersistentArgs) + 256;
     // the D-array pre-pass's rows
     const uint32_t dstride = ((mlen + 15) / 16) * 16;
-    if (dpre) need += (size_t)n * 2 * dstride + n + 2 * 256;
+    if (!plain) need += (size_t)n * 2 * dstride + n + 2 * 256;
     const SplitShape zs = split_shape(n, mlen);
     if (sbud) need += split_bytes(zs) + (size_t)lanes * 4 + 256;
     void *w;
@@ -3411,11 +3289,12 @@ int align_impl(bwfm_index *ix, bwfm::Workspace &ws, const bwfm_reads *rd, const 
     u4 *stage = cv.take<u4>(stage_cap);
     uint64_t *part = cv.take<uint64_t>(scan_part_elems(n));
     PersistentArgs *pargs = cv.take<PersistentArgs>(1);
-    uint8_t *drows = dpre ? cv.take<uint8_t>((size_t)n * 2 * dstride) : nullptr;
-    uint8_t *dflag = dpre ? cv.take<uint8_t>(n) : nullptr;
+    uint8_t *drows = plain ? nullptr : cv.take<uint8_t>((size_t)n * 2 * dstride);
+    uint8_t *dflag = plain ? nullptr : cv.take<uint8_t>(n);
     TaskArgs *targs = nullptr;
     SplitBufs X = sbud ? carve_split(cv, zs, sbud, &targs) : SplitBufs{};
     X.count = expand != nullptr;
+    X.drain = mlen >= LONG_READ;
     uint32_t *lane_read = sbud ? cv.take<uint32_t>(lanes) : nullptr;
     uint32_t *ctl = cv.take<uint32_t>(16);  // n_slow, next_read, stage_used (64-bit), slow_next
     uint32_t *n_slow = ctl, *next_read = ctl + 1, *slow_next = ctl + 4;
@@ -3437,15 +3316,13 @@ int align_impl(bwfm_index *ix, bwfm::Workspace &ws, const bwfm_reads *rd, const 
             k_align_plain<LW><<<nr_up / bs, bs, lds, st>>>(D, rv, P, lb, O);
             tm.end(t);
         } else {
-            if (dpre) {
-                int td = tm.begin("dscan");
-                k_dscan<LW><<<nr_up / bs, bs, (size_t)bs * lstride, st>>>(D, rv, P, drows, dflag, dstride, lstride);
-                tm.end(td);
-            }
+            int td = tm.begin("dscan");
+            k_dscan<LW><<<nr_up / bs, bs, (size_t)bs * lstride, st>>>(D, rv, P, drows, dflag, dstride, lstride);
+            tm.end(td);
             k_set_args<<<1, 64, 0, st>>>(pargs, PersistentArgs{rv, lb, O, next_read, drows, dflag, dstride, X, lane_read});
             int ts = tm.begin("align_search");
             int t = tm.begin("align_persistent");
-            hipLaunchKernelGGL(persistent_kernel<LW>(p->waves_per_simd, dpre), dim3(lanes / bs), dim3(bs), lds, st, D, P,
+            hipLaunchKernelGGL(persistent_kernel<LW>(p->waves_per_simd), dim3(lanes / bs), dim3(bs), lds, st, D, P,
                                (const PersistentArgs *)pargs);
             tm.end(t);
             if (sbud) {
@@ -4111,7 +3988,7 @@ struct bwfm_pipeline {
     bwfm_pair *pairs = nullptr;
     uint64_t *ctl = nullptr;
     PersistentArgs *pargs = nullptr;
-    uint8_t *drows = nullptr, *dflag = nullptr;  // D-array pre-pass output (gene DPREPASS)
+    uint8_t *drows = nullptr, *dflag = nullptr;  // D-array pre-pass output
     uint32_t dstride = 0;
     SplitBufs X{};               // split searches (X.budget 0: off)
     TaskArgs *targs = nullptr;
@@ -4156,7 +4033,7 @@ int pipe_enqueue(bwfm_pipeline *pl, hipStream_t st, bool timed, bool capture) {
     auto mark = [&](hipEvent_t e) {
         return capture ? hipEventRecordWithFlags(e, st, hipEventRecordExternal) : hipEventRecord(e, st);
     };
-    if (!plain && pl->drows) {
+    if (!plain) {
         const uint32_t nr_up = ((nmax + pl->bs - 1) / pl->bs) * pl->bs;
         k_dscan<LW><<<nr_up / pl->bs, pl->bs, (size_t)pl->bs * pl->lstride, st>>>(D, rv, P, pl->drows, pl->dflag,
                                                                                pl->dstride, pl->lstride);
@@ -4170,7 +4047,7 @@ int pipe_enqueue(bwfm_pipeline *pl, hipStream_t st, bool timed, bool capture) {
     if (plain)
         k_align_plain<LW><<<pl->lanes / pl->bs, pl->bs, pl->lds, st>>>(D, rv, P, lb, O);
     else
-        hipLaunchKernelGGL(persistent_kernel<LW>(pl->ap.waves_per_simd, pl->drows != nullptr), dim3(pl->lanes / pl->bs),
+        hipLaunchKernelGGL(persistent_kernel<LW>(pl->ap.waves_per_simd), dim3(pl->lanes / pl->bs),
                            dim3(pl->bs),
                            pl->lds, st, D, P, (const PersistentArgs *)pl->pargs);
     if (timed) HIPCHK(mark(pl->ev[1]));
@@ -4247,7 +4124,6 @@ extern "C" int bwfm_pipeline_create(const bwfm_index *cix, const bwfm_aln_params
     pl->lstride = lds_stride_for(mlen);
     const bool plain = ap->form == BWFM_FORM_PLAIN;
     const uint32_t sbud = plain ? 0u : split_budget_of(*ap);
-    const bool dpre = !plain && (BWFM_GENE_DPREPASS == 1 || mlen >= DPRE_MIN_LEN);
     pl->bs = block_for(pl->lstride);
     pl->lds = (size_t)pl->bs * pl->lstride + (plain ? 0 : (pl->bs / 64) * sizeof(WaveShare));
     const uint32_t nr_up = ((nmax + pl->bs - 1) / pl->bs) * pl->bs;
@@ -4255,7 +4131,7 @@ extern "C" int bwfm_pipeline_create(const bwfm_index *cix, const bwfm_aln_params
                       : batched_lanes(by_layout(ix,
                                                 [&](auto lw) {
                                                     return persistent_lanes<decltype(lw)::value>(
-                                                        pl->bs, pl->lds, ap->waves_per_simd, dpre);
+                                                        pl->bs, pl->lds, ap->waves_per_simd);
                                                 }),
                                       nmax, pl->bs);
     pl->stack_cap = plain ? std::min<uint32_t>(pl->worst_stack, PLAIN_STACK) : pl->worst_stack;
@@ -4277,7 +4153,7 @@ extern "C" int bwfm_pipeline_create(const bwfm_index *cix, const bwfm_aln_params
     add(PC_WORDS * 8);
     add(sizeof(PersistentArgs));
     pl->dstride = ((mlen + 15) / 16) * 16;
-    if (dpre) {
+    if (!plain) {
         add((size_t)nmax * 2 * pl->dstride);
         add(nmax);
     }
@@ -4310,12 +4186,13 @@ extern "C" int bwfm_pipeline_create(const bwfm_index *cix, const bwfm_aln_params
     pl->pairs = cv.take<bwfm_pair>(q->max_pairs);
     pl->ctl = cv.take<uint64_t>(PC_WORDS);
     pl->pargs = cv.take<PersistentArgs>(1);
-    if (dpre) {
+    if (!plain) {
         pl->drows = cv.take<uint8_t>((size_t)nmax * 2 * pl->dstride);
         pl->dflag = cv.take<uint8_t>(nmax);
     }
     if (sbud) {
         pl->X = carve_split(cv, zs, sbud, &pl->targs);
+        pl->X.drain = mlen >= LONG_READ;
         pl->lane_read = cv.take<uint32_t>(pl->lanes);
     }
     if (hipEventCreate(&pl->ev[0]) != hipSuccess || hipEventCreate(&pl->ev[1]) != hipSuccess ||
