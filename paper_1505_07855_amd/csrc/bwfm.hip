@@ -79,15 +79,10 @@ constexpr uint32_t PLAIN_STACK = 320;  // stack entries per lane, plain form fir
 // searches over them.
 //   ROWMASK:  row masks of a 32-row group by compare and select (0) or by
 //             one 64-bit shift (1).
-//   PAIRLINE: the paired rank query of planar lines shares a line that
-//             holds both rows (0) or always fetches two (1).
 //   SUBHDR:   with SUBLOAD 0, a 128-byte sub-counted query reads the
 //             boundary words only for rows past 128 (0) or always (1).
 #ifndef BWFM_GENE_ROWMASK
 #define BWFM_GENE_ROWMASK 0
-#endif
-#ifndef BWFM_GENE_PAIRLINE
-#define BWFM_GENE_PAIRLINE 0
 #endif
 #ifndef BWFM_GENE_SUBHDR
 #define BWFM_GENE_SUBHDR 0
@@ -222,7 +217,11 @@ constexpr uint32_t SUB128_ROWS = 384;
 struct Kids {
     uint32_t x[4], y[4], mask;
 };
-constexpr uint32_t SINGLE = 0xffffffffu;  // above every l
+// y of such a string: SINGLE0 and more, above every l (texts have the tables
+// only below SINGLE0 bases): SINGLE0 + the code of the next NEXT bases to be
+// prepended, the first in the lowest digit, or SINGLE where they are not known
+constexpr uint32_t SINGLE = 0xffffffffu, SINGLE0 = 0xfffff800u;
+constexpr int NEXT = 5;
 
 // from the interval table's two 16-byte words (p: A and C, q: G and T); a
 // string that does not occur has y = 0 (one that does has l >= 1, since row 0
@@ -269,47 +268,6 @@ __device__ __forceinline__ void occ4_sub(const DevIndex &ix, const DevDir &d, ui
     o[2] = h.y + cG;
     o[3] = h.z + cT;
     o[0] = i - o[1] - o[2] - o[3] - (i > d.primary ? 1u : 0u);
-}
-
-// Occ at rows i1 and i2 of sub-counted lines, for the search loop, where
-// line requests cost more than bit counting: whole lines are fetched (four
-// 16-byte loads, once when both rows fall in one line) and each row's
-// group is picked from registers.
-__device__ __forceinline__ void occ4_sub_pair(const DevIndex &ix, const DevDir &d, uint32_t i1, uint32_t i2,
-                                              uint32_t o1[4], uint32_t o2[4]) {
-    const uint32_t l1 = line_of(ix, i1), l2 = line_of(ix, i2);
-    const u4 *L1 = reinterpret_cast<const u4 *>(d.lines) + (size_t)l1 * 4;
-    const u4 *L2 = reinterpret_cast<const u4 *>(d.lines) + (size_t)l2 * 4;
-    u4 a[4], b[4];
-#pragma unroll
-    for (int q = 0; q < 4; q++) a[q] = L1[q];
-    if (l1 != l2) {
-#pragma unroll
-        for (int q = 0; q < 4; q++) b[q] = L2[q];
-    } else {
-#pragma unroll
-        for (int q = 0; q < 4; q++) b[q] = a[q];
-    }
-    auto count = [&](const u4(&v)[4], uint32_t i, uint32_t line, uint32_t o[4]) {
-        const uint32_t r = i - line * 160u, g = r >> 5;
-        // the group's two plane words: words 6 + 2 g and 7 + 2 g of the line
-        const uint32_t hi = g == 0 ? v[1].z : g == 1 ? v[2].x : g == 2 ? v[2].z : g == 3 ? v[3].x : v[3].z;
-        const uint32_t lo = g == 0 ? v[1].w : g == 1 ? v[2].y : g == 2 ? v[2].w : g == 3 ? v[3].y : v[3].w;
-        const uint32_t m = (1u << (r & 31)) - 1u;
-        uint32_t cC = __popc(~hi & lo & m), cG = __popc(hi & ~lo & m), cT = __popc(hi & lo & m);
-        if (g) {
-            const uint32_t sh = 8 * (g - 1);
-            cC += (v[0].w >> sh) & 255u;
-            cG += (v[1].x >> sh) & 255u;
-            cT += (v[1].y >> sh) & 255u;
-        }
-        o[1] = v[0].x + cC;
-        o[2] = v[0].y + cG;
-        o[3] = v[0].z + cT;
-        o[0] = i - o[1] - o[2] - o[3] - (i > d.primary ? 1u : 0u);
-    };
-    count(a, i1, l1, o1);
-    count(b, i2, l2, o2);
 }
 
 // Occ of all four bases at row i from the pieces of its 128-byte
@@ -470,67 +428,17 @@ __device__ __forceinline__ void occ4(const DevIndex &ix, const DevDir &d, uint32
     o[3] = h.w + cT;
 }
 
-// Occ(., i1) and Occ(., i2) on one direction, as occ4 twice, except that a
-// lane whose two rows fall in one rank line (k and l + 1 of a narrow
-// interval: two thirds of the expansions on the benchmark) fetches that
-// line once.  The search is bound by line requests more than by their
-// bytes, so the skipped request is the saving.
-template <int LW>
-__device__ __forceinline__ void occ4_pair(const DevIndex &ix, const DevDir &d, uint32_t i1, uint32_t i2, uint32_t o1[4],
-                                          uint32_t o2[4]) {
-    if constexpr (LW == LW_SUB) {
-        occ4_sub_pair(ix, d, i1, i2, o1, o2);
-        return;
-    }
-    if constexpr (LW == LW_SUB128) {
-        occ4_sub128_pair(ix, d, i1, i2, o1, o2);
-        return;
-    }
-    const uint32_t l1 = line_of(ix, i1), l2 = line_of(ix, i2);
-    const u4 *L1 = reinterpret_cast<const u4 *>(d.lines) + (size_t)l1 * (LW / 4);
-    const u4 *L2 = reinterpret_cast<const u4 *>(d.lines) + (size_t)l2 * (LW / 4);
-    const bool same = BWFM_GENE_PAIRLINE == 0 && l1 == l2;
-    u4 a[LW / 4], b[LW / 4];
-#pragma unroll
-    for (int q = 0; q < LW / 4; q++) a[q] = L1[q];
-    if (!same) {
-#pragma unroll
-        for (int q = 0; q < LW / 4; q++) b[q] = L2[q];
-    } else {
-#pragma unroll
-        for (int q = 0; q < LW / 4; q++) b[q] = a[q];
-    }
-    const u4(&A)[LW / 4] = a;
-    const u4(&B)[LW / 4] = b;
-    auto count = [&](const u4(&v)[LW / 4], uint32_t i, uint32_t line, uint32_t o[4]) {
-        const int r = (int)(i - line * ix.bpl);
-        uint32_t cC = 0, cG = 0, cT = 0;
-#pragma unroll
-        for (int q = 0; q < LW / 4 - 1; q++) {
-            const u4 w = v[1 + q];
-            const uint32_t m0 = rows_mask(r - q * 64), m1 = rows_mask(r - q * 64 - 32);
-            cT += __popc(w.x & w.y & m0) + __popc(w.z & w.w & m1);
-            cG += __popc(w.x & ~w.y & m0) + __popc(w.z & ~w.w & m1);
-            cC += __popc(~w.x & w.y & m0) + __popc(~w.z & w.w & m1);
-        }
-        const uint32_t cA = (uint32_t)r - cC - cG - cT;
-        o[0] = v[0].x + cA - (i > d.primary ? 1u : 0u);
-        o[1] = v[0].y + cC;
-        o[2] = v[0].z + cG;
-        o[3] = v[0].w + cT;
-    };
-    count(A, i1, l1, o1);
-    count(B, i2, l2, o2);
-}
-
 // A string's four extensions from the rank counts at its k (i1) and l + 1
-// (i2); pair: rows in one line fetch it once.
+// (i2).  On 128-byte sub-counted lines the two rows share what one line gives
+// both; on the others they are counted one after the other, since holding two
+// whole lines made the 4-wave build of the batched kernel spill (up to 81
+// registers; rank queries are the rarer step now that short strings come from
+// the table and unique ones from the text).
 template <int LW>
-__device__ __forceinline__ void rank_children(const DevIndex &ix, const DevDir &d, uint32_t i1, uint32_t i2, Kids &k,
-                                              bool pair) {
+__device__ __forceinline__ void rank_children(const DevIndex &ix, const DevDir &d, uint32_t i1, uint32_t i2, Kids &k) {
     uint32_t lo[4], hi[4];
-    if (pair) {
-        occ4_pair<LW>(ix, d, i1, i2, lo, hi);
+    if constexpr (LW == LW_SUB128) {
+        occ4_sub128_pair(ix, d, i1, i2, lo, hi);
     } else {
         occ4<LW>(ix, d, i1, lo);
         occ4<LW>(ix, d, i2, hi);
@@ -598,7 +506,7 @@ __device__ __forceinline__ uint32_t lf_step(const DevIndex &ix, const DevDir &d,
 
 // Search states are packed in 16 bytes: x = k (or, while |X| is below the
 // index's short-string levels, the code of X: see state_k), y = l,
-// z = (i + 1) | gap state << 10 | n_mm << 12 | n_gapo << 16 | n_gape << 20 | seed diffs << 24,
+// z = (i + 1) | gap state << 10 | n_mm << 12 | n_gapo << 16 | n_gape << 20 | seed diffs << 24 | family << 28,
 // w = score | |X| << 10 | lb << 20, where lb = score + minc * D[i] is the
 // state's lower bound on its final score, fixed once the D-array is built.
 // Every field fits: diffs <= 15, score <= 15 * 63, |X| <= 512 + 15.
@@ -751,7 +659,7 @@ __device__ __forceinline__ u2 state_kl(const DevIndex &ix, int strand, u4 s) {
         const u2 *kt = reinterpret_cast<const u2 *>(strand == 0 ? ix.dir[1].kt : ix.dir[0].kt);
         return kt[kt_start32(len) + s.x];
     }
-    if (s.y == SINGLE) {
+    if (s.y >= SINGLE0) {
         const uint32_t *isa = (strand == 0 ? ix.dir[1].full : ix.dir[0].full) + (size_t)ix.n + 1;
         const uint32_t k = isa[s.x];
         return mk2(k, k);
@@ -769,24 +677,24 @@ __device__ __forceinline__ u2 state_kl(const DevIndex &ix, int strand, u4 s) {
 // occur.  On the benchmark batch three quarters of the expansions are steps
 // of such runs, 4 of them to a run.
 
-// Two bits per base of row[at, at + q), q <= 16, base j in bits 2 j: the row
+// Two bits per base of row[at, at + q), q <= 20, base j in bits 2 j: the row
 // is read as whole dwords (it starts dword-aligned; at most 3 bytes past its
 // last base are touched, inside the row's last dword).
-__device__ __forceinline__ uint32_t row_code(const uint8_t *row, int at, int q) {
+template <int ND = 5>  // dwords read: 5 for q <= 17, 6 for q <= 20
+__device__ __forceinline__ uint64_t row_code(const uint8_t *row, int at, int q) {
     const uint32_t *A = reinterpret_cast<const uint32_t *>(row) + (at >> 2);
     const int sh = at & 3, nd = (sh + q + 3) >> 2;
-    uint32_t v[5];
+    uint32_t v[ND];
 #pragma unroll
-    for (int t = 0; t < 5; t++) v[t] = t < nd ? A[t] : 0u;
+    for (int t = 0; t < ND; t++) v[t] = t < nd ? A[t] : 0u;
+    uint64_t w = 0;
 #pragma unroll
-    for (int t = 0; t < 5; t++) {
+    for (int t = 0; t < ND; t++) {
         uint32_t u = v[t] & 0x03030303u;
         u |= u >> 6;
-        v[t] = (u & 0x0fu) | ((u >> 12) & 0xf0u);
+        w |= (uint64_t)((u & 0x0fu) | ((u >> 12) & 0xf0u)) << (8 * t);
     }
-    const uint32_t lo = v[0] | (v[1] << 8) | (v[2] << 16) | (v[3] << 24);
-    const uint64_t w = ((uint64_t)v[4] << 32) | lo;
-    return (uint32_t)(w >> (2 * sh)) & (uint32_t)((1ull << (2 * q)) - 1ull);
+    return (w >> (2 * sh)) & ((1ull << (2 * q)) - 1ull);
 }
 // sixteen two-bit digits in the opposite order
 __device__ __forceinline__ uint32_t rev16(uint32_t c) {
@@ -796,10 +704,17 @@ __device__ __forceinline__ uint32_t rev16(uint32_t c) {
 // the q <= 15 two-bit digits of c in the opposite order
 __device__ __forceinline__ uint32_t rev_digits(uint32_t c, int q) { return q ? rev16(c) >> (32 - 2 * q) : 0u; }
 
-// Steps of the exact run from state cur (i >= 0, |X| < the table's levels)
-// to the deepest level, or 0 when a difference may still be taken on the
-// way: D falls towards the pattern's start, so no difference fits anywhere
-// in the run when none fits with the D of its end.
+// The children of a state shorter than the table's levels that are not taken
+// at once are one stack entry, its family: the state itself with the family
+// field set, in y the children left (bits 0-3 mismatch by base, bit 4 the
+// insertion, bits 8-11 deletion by base), lb their lowest.
+constexpr uint32_t FAMILY = 1u << 28;
+constexpr uint32_t FAM_MM = 15u, FAM_INS = 16u, FAM_DEL = 15u << 8;
+
+// Steps of the exact run from state cur (i >= 0, |X| at most the table's
+// levels) to the deepest level, or 0 when a difference may still be taken on
+// the way: D falls towards the pattern's start, so no difference fits
+// anywhere in the run when none fits with the D of its end.
 __device__ __forceinline__ int run_steps(const DevIndex &ix, u4 cur, const uint8_t *pd, int maxd, int bound,
                                          bool has_n, const Seed &S, const Params &P) {
     const int q = (int)ix.kt_levels - s_len(cur);
@@ -811,31 +726,15 @@ __device__ __forceinline__ int run_steps(const DevIndex &ix, u4 cur, const uint8
                       (S.sl != 0 && !has_n && s_sd(cur) >= P.seed_diff && e + 1 >= S.lo);
     return none ? q : 0;
 }
-// Table entry of the run of q steps from cur.
-__device__ __forceinline__ uint32_t run_entry(const DevIndex &ix, u4 cur, const uint8_t *pd, int q) {
-    return kt_start32((int)ix.kt_levels) + ((cur.x << (2 * q)) | row_code(pd, s_i(cur) + 1 - q, q));
-}
+
 // cur, t matches on: x and y are the caller's
 __device__ __forceinline__ void step_matches(u4 &cur, int t, const uint8_t *pd, const Params &P) {
     const int e = s_i(cur) - t;
     const int De = e >= 0 ? pd[e] >> 3 : 0;
-    cur.z = (cur.z & ~(3u << 10)) - (uint32_t)t;
+    if (t) cur.z &= ~(3u << 10);
+    cur.z -= (uint32_t)t;
     cur.w = (cur.w & 0xfffffu) + ((uint32_t)t << 10);
     cur.w |= (uint32_t)(s_score(cur) + P.minc * De) << 20;
-}
-
-// cur after its run: the state q steps on, or dropped (valid cleared) when
-// its string stops occurring.  Returns the states the run expanded.
-__device__ __forceinline__ uint32_t run_take(u4 &cur, bool &valid, u2 kl, const uint8_t *pd, int q,
-                                             const Params &P) {
-    if (kl.y == 0) {  // absent: kl.x - 1 of the bases occur
-        valid = false;
-        return kl.x - (uint32_t)s_len(cur);
-    }
-    step_matches(cur, q, pd, P);
-    cur.x = kl.x;
-    cur.y = kl.y;
-    return (uint32_t)q;
 }
 
 // ---- strings that occur once
@@ -865,22 +764,21 @@ __device__ __forceinline__ uint32_t text_bases(const DevIndex &ix, int dir, uint
     return __builtin_amdgcn_alignbit(w1, w0, 2 * ((ix.n - p) & 15));
 }
 
-// One step of a state whose string occurs once at p > 0, win its next bases
-// from the highest digit down.  A run of matches is taken at once: its
+// One step of a state whose string occurs once at p, win its next bases from
+// the highest digit down, pc the r <= 16 pattern bases it meets (r = 0: one
+// base at a time).  A run of matches is taken at once: its
 // positions have no mismatch children, and their gaps, where one may still
 // open, go on the stack as one run entry (gap state GAP_RUN, y = the run's
 // length, x, i and the rest as at its start, lb that of its cheapest gap),
 // which is dropped whole once the bound passes it.  Returns true when the run
 // was taken; else k receives the one child.
 constexpr int GAP_RUN = 3;
-__device__ bool text_step(u4 &cur, uint32_t win, int maxd, int bound, bool has_n, const Params &P, LaneCtx &c,
-                          Kids &k) {
+__device__ __forceinline__ bool text_step(u4 &cur, uint32_t win, uint32_t pc, int r, int maxd, int bound,
+                                          const Params &P, LaneCtx &c, Kids &k) {
     const int i = s_i(cur);
     const uint32_t p = cur.x;
-    if (!has_n && s_gs(cur) == 0 && p) {
-        const int r = min(16, i + 1);
-        const uint32_t pc = row_code(c.pd, i + 1 - r, r) << (32 - 2 * r);
-        const uint32_t df = win ^ pc;
+    if (r) {
+        const uint32_t df = win ^ (pc << (32 - 2 * r));
         int t = df ? __clz(df) >> 1 : 16;
         t = min(t, r);
         t = (int)min((uint32_t)t, p);
@@ -998,15 +896,11 @@ __device__ int expand_children(u4 &cur, bool &valid, const Kids &k, bool gaps_on
                                const Params &P, LaneCtx &c, uint32_t K) {
     const int i = s_i(cur), gs = s_gs(cur), ngo = s_ngo(cur), nge = s_nge(cur), sd = s_sd(cur);
     const int score = s_score(cur), len = s_len(cur);
-    // x of the children that consume a base: k, or their code while
-    // shorter than the short-string levels
-    const bool coded = (uint32_t)(len + 1) < K;
-    uint32_t kx[4];
-#pragma unroll
-    for (int a = 0; a < 4; a++) kx[a] = coded ? (cur.x << 2) | (uint32_t)a : k.x[a];
+    const bool coded = (uint32_t)len < K;  // the children not taken are then one entry
     const int diffs = s_nmm(cur) + ngo + nge;
     const int bound = (P.mode == BWFM_MODE_BEST && c.best != INF_SCORE) ? c.best + P.s_mm : INF_SCORE;
     const uint32_t z0 = cur.z & ~(3u << 10);  // gap state cleared
+    const uint32_t len1 = (uint32_t)(len + 1) << 10;
     // room for the at most 8 states pushed below: checked once per
     // expansion.  Entries below sbase were handed to other lanes; sliding
     // the pending ones down makes room when the top of the stack is reached.
@@ -1020,16 +914,21 @@ __device__ int expand_children(u4 &cur, bool &valid, const Kids &k, bool gaps_on
         valid = false;
         return R_STACK;
     }
-    u4 pend = cur;
-    bool have = false;
-    const int rc = R_OK;
-    auto offer = [&](uint32_t k, uint32_t l, uint32_t z, uint32_t w) {
-        if (have) {
-            c.stack[(size_t)c.sp * c.sstride] = pend;
-            c.sp++;
+    const uint32_t sp0 = c.sp;
+    u4 last = cur;
+    auto push = [&](u4 v) {
+        c.stack[(size_t)c.sp * c.sstride] = v;
+        c.sp++;
+        last = v;
+    };
+    uint32_t fam = 0;
+    int fam_lb = INF_SCORE;
+    auto push_set = [&](uint32_t set, uint32_t z, uint32_t w) {
+        while (set) {  // highest base first, so that the lowest is taken first
+            const int a = 31 - __clz((int)set);
+            set &= ~(1u << a);
+            push(mk4(sel4(k.x, a), sel4(k.y, a), z, w));
         }
-        pend = mk4(k, l, z, w);
-        have = true;
     };
     // deletions: reference base a between read bases i and i + 1 (same i)
     {
@@ -1041,11 +940,12 @@ __device__ int expand_children(u4 &cur, bool &valid, const Kids &k, bool gaps_on
         const int lb = nsc + P.minc * Di;
         if (bd >= P.s1 && bd <= m - P.s1 && nd <= maxd && ngo2 <= P.max_gapo && (P.max_gape < 0 || nge2 <= P.max_gape) &&
             (S.sl == 0 || sd + in <= P.seed_diff) && nd + Di <= maxd && lb <= bound) {
-            const uint32_t z = (z0 | ((uint32_t)GAP_DEL << 10)) + (ext ? (1u << 20) : (1u << 16)) + ((uint32_t)in << 24);
-            const uint32_t w = (uint32_t)nsc | ((uint32_t)(len + 1) << 10) | ((uint32_t)lb << 20);
-#pragma unroll
-            for (int a = 3; a >= 0; a--)
-                if (k.mask & (1u << a)) offer(kx[a], k.y[a], z, w);
+            if (coded) {
+                fam |= k.mask << 8;
+                if (k.mask) fam_lb = lb;
+            } else
+            push_set(k.mask, (z0 | ((uint32_t)GAP_DEL << 10)) + (ext ? (1u << 20) : (1u << 16)) + ((uint32_t)in << 24),
+                     (uint32_t)nsc | len1 | ((uint32_t)lb << 20));
         }
     }
     const int in_i = (i >= S.lo && i < S.hi) ? 1 : 0;
@@ -1057,29 +957,238 @@ __device__ int expand_children(u4 &cur, bool &valid, const Kids &k, bool gaps_on
         const int lb = nsc + P.minc * Dn;
         if (nd <= maxd && ngo2 <= P.max_gapo && (P.max_gape < 0 || nge2 <= P.max_gape) &&
             (S.sl == 0 || sd + in_i <= P.seed_diff) && nd + Dn <= maxd && lb <= bound) {
-            const uint32_t z =
-                (z0 | ((uint32_t)GAP_INS << 10)) - 1u + (ext ? (1u << 20) : (1u << 16)) + ((uint32_t)in_i << 24);
-            offer(cur.x, cur.y, z, (uint32_t)nsc | ((uint32_t)len << 10) | ((uint32_t)lb << 20));
+            if (coded) {
+                fam |= FAM_INS;
+                fam_lb = min(fam_lb, lb);
+            } else
+                push(mk4(cur.x, cur.y,
+                         (z0 | ((uint32_t)GAP_INS << 10)) - 1u + (ext ? (1u << 20) : (1u << 16)) +
+                             ((uint32_t)in_i << 24),
+                         (uint32_t)nsc | ((uint32_t)len << 10) | ((uint32_t)lb << 20)));
         }
     }
-    // mismatches, then the match (offered last, so it becomes current)
+    // mismatches, then the match, which becomes current
+    bool match = false;
     if (!gaps_only) {
         const int nsc = score + P.s_mm;
         const int lb = nsc + P.minc * Dn;
         if (diffs + 1 <= maxd && (S.sl == 0 || sd + in_i <= P.seed_diff) && diffs + 1 + Dn <= maxd && lb <= bound) {
-            const uint32_t z = z0 - 1u + (1u << 12) + ((uint32_t)in_i << 24);
-            const uint32_t w = (uint32_t)nsc | ((uint32_t)(len + 1) << 10) | ((uint32_t)lb << 20);
-#pragma unroll
-            for (int a = 3; a >= 0; a--)
-                if (a != b && (k.mask & (1u << a))) offer(kx[a], k.y[a], z, w);
+            const uint32_t set = k.mask & ~(b < 4 ? 1u << b : 0u);
+            if (coded) {
+                fam |= set;
+                if (set) fam_lb = min(fam_lb, lb);
+            } else
+                push_set(set, z0 - 1u + (1u << 12) + ((uint32_t)in_i << 24),
+                         (uint32_t)nsc | len1 | ((uint32_t)lb << 20));
         }
+        if (fam) push(mk4(cur.x, fam, cur.z | FAMILY, (cur.w & 0xfffffu) | ((uint32_t)fam_lb << 20)));
         const int lbm = score + P.minc * Dn;
-        if (b < 4 && ((k.mask >> b) & 1u) && diffs + Dn <= maxd && lbm <= bound)
-            offer(sel4(kx, b), sel4(k.y, b), z0 - 1u,
-                  (uint32_t)score | ((uint32_t)(len + 1) << 10) | ((uint32_t)lbm << 20));
+        match = b < 4 && ((k.mask >> b) & 1u) && diffs + Dn <= maxd && lbm <= bound;
+        if (match) {
+            const bool code = (uint32_t)(len + 1) < K;
+            cur = mk4(code ? (cur.x << 2) | (uint32_t)b : sel4(k.x, b), sel4(k.y, b), z0 - 1u,
+                      (uint32_t)score | len1 | ((uint32_t)lbm << 20));
+        }
     }
-    if (have) cur = pend;
-    valid = have;
+    valid = match || c.sp > sp0;
+    if (!match && c.sp > sp0) {
+        c.sp--;
+        cur = last;
+    }
+    return R_OK;
+}
+
+// One step of the search from cur, for the lanes that go: the next of a
+// family, a run of matches or the children through the interval table, the
+// text, or the rank lines of the search index qd (direction qdir).  Loads of
+// all kinds are issued before any is used, so lanes that take different ways
+// share one round trip.  Returns R_OK or R_STACK.
+template <int LW>
+__device__ __forceinline__ int search_step(const DevIndex &ix, const DevDir &qd, int qdir, bool go, u4 &cur, bool &valid,
+                                           int m, int maxd, bool has_n, const Seed &S, const Params &P, LaneCtx &c) {
+    const int K = (int)ix.kt_levels;
+    const int bound = (P.mode == BWFM_MODE_BEST && c.best != INF_SCORE) ? c.best + P.s_mm : INF_SCORE;
+    const bool unroll = go && s_gs(cur) == GAP_RUN;
+    const bool fam = go && (cur.z & FAMILY) != 0;
+    bool shallow = go && !unroll && s_len(cur) < K;
+    const bool deep = go && !unroll && !shallow;
+    // a family: the children that the bound leaves, of them one kind now --
+    // cur becomes its children's common state (x still the parent's code),
+    // sib their bases (0: the insertion, whose code is the parent's)
+    const uint32_t pz = cur.z, pw = cur.w;
+    uint32_t sib = 0, left = 0;  // left: the family's other kinds
+    if (fam) {
+        const int i = s_i(cur), gs = s_gs(cur), score = s_score(cur), len = s_len(cur);
+        const int Di = c.pd[i] >> 3, Dn = i > 0 ? c.pd[i - 1] >> 3 : 0;
+        const bool xi = gs == GAP_INS, xd = gs == GAP_DEL;
+        const int sm = score + P.s_mm, si = score + (xi ? P.s_gape : P.s_gapo), sd = score + (xd ? P.s_gape : P.s_gapo);
+        const int lbm = sm + P.minc * Dn, lbi = si + P.minc * Dn, lbd = sd + P.minc * Di;
+        left = (lbm <= bound ? cur.y & FAM_MM : 0u) | (lbi <= bound ? cur.y & FAM_INS : 0u) |
+               (lbd <= bound ? cur.y & FAM_DEL : 0u);
+        const uint32_t z0 = cur.z & ~(FAMILY | (3u << 10));
+        const uint32_t in_i = (i >= S.lo && i < S.hi) ? 1u << 24 : 0u;
+        if (left & FAM_MM) {
+            sib = left & FAM_MM;
+            left &= ~FAM_MM;
+            cur.z = z0 - 1u + (1u << 12) + in_i;
+            cur.w = (uint32_t)sm | ((uint32_t)(len + 1) << 10) | ((uint32_t)lbm << 20);
+        } else if (left & FAM_INS) {
+            left &= ~FAM_INS;
+            cur.z = (z0 | ((uint32_t)GAP_INS << 10)) - 1u + (xi ? 1u << 20 : 1u << 16) + in_i;
+            cur.w = (uint32_t)si | ((uint32_t)len << 10) | ((uint32_t)lbi << 20);
+        } else if (left) {
+            sib = left >> 8;
+            left = 0;
+            cur.z = (z0 | ((uint32_t)GAP_DEL << 10)) + (xd ? 1u << 20 : 1u << 16) +
+                    ((i + 1 > S.lo && i + 1 < S.hi) ? 1u << 24 : 0u);
+            cur.w = (uint32_t)sd | ((uint32_t)(len + 1) << 10) | ((uint32_t)lbd << 20);
+        } else {
+            shallow = false;  // nothing the bound leaves
+            valid = false;
+        }
+    }
+    // the family entry of what is left with `rest` of the kind taken (lb stays
+    // the lowest of the whole family's)
+    auto family = [&](uint32_t rest) {
+        return mk4(cur.x, left | (s_gs(cur) == GAP_DEL ? rest << 8 : rest), pz, pw);
+    };
+    const int len = s_len(cur), i = s_i(cur);
+    const bool text = deep && cur.y >= SINGLE0;
+    const bool conv = deep && !text && to_text(ix, cur);
+    const bool rank = deep && !text && !conv;
+    int q = 0;
+    bool run = false, sure = false;  // sure: no difference fits in the NEXT bases after the run either
+    if (shallow) {
+        q = run_steps(ix, cur, c.pd, maxd, bound, has_n, S, P);
+        run = q > 0 || len == K;
+        if (q > 0) {
+            const int e = i - q - NEXT;
+            const int De = e >= 0 ? c.pd[e] >> 3 : 0;
+            sure = s_nmm(cur) + s_ngo(cur) + s_nge(cur) + 1 + De > maxd ||
+                   s_score(cur) + P.minc + P.minc * De > bound;
+        }
+    }
+    // the pattern bases of a run and the next ones, or of a text step
+    const int nx = run ? min(NEXT, i + 1 - q) : 0;
+    const int w = run ? q : (text && !has_n && s_gs(cur) == 0 && cur.x ? min(16, i + 1) : 0);
+    uint32_t code = 0, next = 0;
+    if (w + nx) {
+        const uint64_t cw = row_code<6>(c.pd, i + 1 - w - nx, w + nx);
+        next = (uint32_t)cw & ((1u << (2 * nx)) - 1u);
+        code = (uint32_t)(cw >> (2 * nx));
+    }
+    const uint32_t sib1 = sib & (sib - 1), sib2 = sib1 & (sib1 - 1);
+    u4 ta = mk4(0, 0, 0, 0), tb = ta;
+    const bool kids = shallow && !run && i >= 0;
+    if (run) {
+        // up to three siblings' runs at once
+        const u2 *e = reinterpret_cast<const u2 *>(qd.kt) + kt_start32(K) + code;
+        const uint32_t x0 = sib ? (cur.x << 2) | (uint32_t)(__ffs((int)sib) - 1) : cur.x;
+        const u2 v = e[x0 << (2 * q)];
+        ta.x = v.x;
+        ta.y = v.y;
+        if (sib1) {
+            const u2 v1 = e[((cur.x << 2) | (uint32_t)(__ffs((int)sib1) - 1)) << (2 * q)];
+            ta.z = v1.x;
+            ta.w = v1.y;
+        }
+        if (sib2) {
+            const u2 v2 = e[((cur.x << 2) | (uint32_t)(__ffs((int)sib2) - 1)) << (2 * q)];
+            tb.x = v2.x;
+            tb.y = v2.y;
+        }
+    } else if (shallow) {
+        // the first child on its own, the rest of the family back on the stack
+        if (left | sib1) {
+            c.stack[(size_t)c.sp * c.sstride] = family(sib1);
+            c.sp++;
+        }
+        if (sib) cur.x = (cur.x << 2) | (uint32_t)(__ffs((int)sib) - 1);
+        if (kids) {
+            const u4 *e = reinterpret_cast<const u4 *>(qd.kt) + (kt_children(len, cur.x) >> 1);
+            ta = e[0];
+            tb = e[1];
+        }
+    }
+    if (text && cur.x) {
+        const u2w v = *reinterpret_cast<const u2w *>(ix.pac + text_word(ix, qdir, cur.x));
+        ta.x = v.x;
+        ta.y = v.y;
+    }
+    if (conv) ta.x = qd.full[cur.x];
+    Kids k;
+    k.mask = 0;
+#pragma unroll
+    for (int a = 0; a < 4; a++) k.x[a] = k.y[a] = 0;
+    if (rank) rank_children<LW>(ix, qd, cur.x, cur.y + 1, k);
+
+    bool grow = rank || unroll || kids;
+    if (run) {
+        uint32_t n = 0;  // states expanded by the runs that end
+        // whether the run of entry kl ends: its string is absent (kl.x - 1
+        // of its bases occur), or occurs once and is not followed by the
+        // pattern's next bases
+        next = rev_digits(next, nx);  // the first to come in the lowest digit
+        auto ends = [&](u2 kl) {
+            if (kl.y == 0) {
+                n += kl.x - (uint32_t)len;
+                return true;
+            }
+            if (!sure || kl.y < SINGLE0 || kl.y == SINGLE) return false;
+            const uint32_t df = (kl.y ^ next) & ((1u << (2 * nx)) - 1u);
+            if (!df) return false;
+            n += (uint32_t)q + ((uint32_t)(__ffs((int)df) - 1) >> 1) + 1u;
+            return true;
+        };
+        u2 kl = mk2(ta.x, ta.y);
+        uint32_t rest = sib1;
+        bool over = ends(kl);
+        if (over && sib1) {
+            kl = mk2(ta.z, ta.w);
+            rest = sib2;
+            over = ends(kl);
+            if (over && sib2) {
+                kl = mk2(tb.x, tb.y);
+                rest = sib2 & (sib2 - 1);
+                over = ends(kl);
+            }
+        }
+        const bool more = (left | rest) != 0;
+        const u4 f = family(rest);
+        if (over) {
+            cur = f;
+            valid = more;
+        } else {
+            if (more) {
+                c.stack[(size_t)c.sp * c.sstride] = f;
+                c.sp++;
+            }
+            step_matches(cur, q, c.pd, P);
+            cur.x = kl.x;
+            cur.y = kl.y;
+            n += (uint32_t)q;
+        }
+        c.expand += n;
+    } else if (kids) {
+        kt_pick(ta, tb, k);
+    }
+    if (conv) {
+        cur.x = ta.x;
+        cur.y = SINGLE;
+    }
+    if (text) {
+        uint32_t win = text_bases(ix, qdir, cur.x, ta.x, ta.y);
+        if (qdir) win = rev16(win);
+        grow = !text_step(cur, win, code, w, maxd, bound, P, c, k);
+    }
+    if (unroll) unroll_run(cur, P, c, k);
+    int rc = R_OK;
+    if (grow) {
+        if (!unroll && !text) c.expand++;
+        const int j = s_i(cur);
+        rc = expand_children(cur, valid, k, unroll, pd_base(c, j), m, maxd, pd_d(c, j), pd_d(c, j - 1), S, P, c,
+                             (uint32_t)K);
+    }
     return rc;
 }
 
@@ -1110,7 +1219,7 @@ __device__ __forceinline__ int dtext_matches(const DevIndex &ix, int strand, uin
                                              const uint8_t *row, int di, int q) {
     uint32_t win = text_bases(ix, strand, p, w0, w1);
     if (strand == 0) win = rev16(win);
-    uint32_t pc = row_code(row, di, q);
+    uint32_t pc = (uint32_t)row_code(row, di, q);
     if (strand) pc = ~pc;
     const uint32_t df = win ^ pc;
     const int t = df ? (__ffs((int)df) - 1) >> 1 : 16;
@@ -1126,71 +1235,64 @@ __device__ bool build_d(const DevIndex &ix, const DevDir &od, int m, int strand,
     uint32_t k = 0, l = ix.n;
     bool fresh = true;  // at the start of a segment
     int z = 0;
+    // bases from position i on, at most r, before an N
+    auto to_n = [&](int i, int r) {
+        int q = 0;
+        while (q < r && !(c.pd[i + q] & 4)) q++;
+        return q;
+    };
     for (int i = 0; i < m;) {
-        if (fresh && ix.kt_levels && !has_n) {
+        int d = 0;           // bases that occur from i on
+        bool empty = true;   // and the next one ends the segment
+        if (fresh && ix.kt_levels) {
             // the segment's first bases in one table entry
-            const int r = min((int)ix.kt_levels, m - i);
-            uint32_t code = rev_digits(row_code(c.pd, i, r), r);
-            if (strand) code ^= (1u << (2 * r)) - 1u;
-            const u2 kl = reinterpret_cast<const u2 *>(od.kt)[kt_start32(r) + code];
-            if (kl.y) {
-                row_fill(c.pd, i, r, z, strand);
+            int r = min((int)ix.kt_levels, m - i);
+            if (has_n) r = to_n(i, r);
+            if (r) {
+                uint32_t code = rev_digits((uint32_t)row_code(c.pd, i, r), r);
+                if (strand) code ^= (1u << (2 * r)) - 1u;
+                const u2 kl = reinterpret_cast<const u2 *>(od.kt)[kt_start32(r) + code];
+                empty = kl.y == 0;
+                d = empty ? (int)kl.x - 1 : r;
                 k = kl.x;
                 l = kl.y;
-                i += r;
-                fresh = false;
-                if (l == SINGLE && i < m) {
-                    // followed in the text to the first base that differs
-                    for (;;) {
-                        const int q = min(16, m - i);
-                        int t = 0;
-                        if (k) {
-                            const u2w w = *reinterpret_cast<const u2w *>(ix.pac + text_word(ix, strand, k));
-                            t = dtext_matches(ix, strand, k, w.x, w.y, c.pd, i, q);
-                        }
-                        row_fill(c.pd, i, t, z, strand);
-                        i += t;
-                        k -= (uint32_t)t;
-                        if (t < q || i == m) break;
-                    }
-                    if (i < m) {
-                        if (++z > maxd) return false;
-                        row_fill(c.pd, i, 1, z, strand);
-                        i++;
-                        k = 0;
-                        l = ix.n;
-                        fresh = true;
-                    }
-                }
-            } else {
-                const int d = (int)kl.x - 1;  // bases that occur; the next one ends the segment
-                row_fill(c.pd, i, d, z, strand);
-                if (++z > maxd) return false;
-                row_fill(c.pd, i + d, 1, z, strand);
-                i += d + 1;
-                k = 0;
-                l = ix.n;
             }
-            continue;
+        } else if (l >= SINGLE0) {
+            // followed in the text to the first base that differs
+            int r = min(16, m - i);
+            if (has_n) r = to_n(i, r);
+            if (k && r) {
+                const u2w w = *reinterpret_cast<const u2w *>(ix.pac + text_word(ix, strand, k));
+                d = dtext_matches(ix, strand, k, w.x, w.y, c.pd, i, r);
+                k -= (uint32_t)d;
+            }
+            empty = d < r || r == 0;
+        } else {
+            const int b = c.pd[i] & 7;
+            const int a = (strand == 0 || b > 3) ? b : 3 - b;
+            if (a < 4) {
+                const uint32_t ok = occ1<LW>(ix, od, a, k), ol = occ1<LW>(ix, od, a, l + 1);
+                empty = ok >= ol;
+                d = empty ? 0 : 1;
+                k = sel4(od.C, a) + ok;
+                l = sel4(od.C, a) + ol - 1;
+                if (k == l && !empty && ix.kt_levels) {
+                    k = od.full[k];
+                    l = SINGLE;
+                }
+            }
         }
-        const int b = c.pd[i] & 7;
-        const int a = (strand == 0 || b > 3) ? b : 3 - b;
-        bool empty = true;
-        if (a < 4) {
-            uint32_t ok = occ1<LW>(ix, od, a, k), ol = occ1<LW>(ix, od, a, l + 1);
-            empty = ok >= ol;
-            k = sel4(od.C, a) + ok;
-            l = sel4(od.C, a) + ol - 1;
-        }
+        row_fill(c.pd, i, d, z, strand);
+        i += d;
         fresh = empty;
         if (empty) {
-            z++;
+            if (++z > maxd) return false;
+            // (an N keeps its code on both strands)
+            row_fill(c.pd, i, 1, z, strand && !(c.pd[i] & 4));
+            i++;
             k = 0;
             l = ix.n;
-            if (z > maxd) return false;
         }
-        c.pd[i] = (uint8_t)(a | (z << 3));
-        i++;
     }
     return true;
 }
@@ -1207,43 +1309,7 @@ __device__ int search_strand(const DevIndex &ix, const DevDir &sd_, int m, int s
         int rr = resolve(cur, valid, strand, P, c, phase, 0x7fffffff, ix);
         if (rr == 0) return R_OK;
         if (rr < 0) return -rr;
-        Kids k;
-        bool gaps_only = false;
-        const int bound = (P.mode == BWFM_MODE_BEST && c.best != INF_SCORE) ? c.best + P.s_mm : INF_SCORE;
-        if (s_gs(cur) == GAP_RUN) {
-            unroll_run(cur, P, c, k);
-            gaps_only = true;
-        } else if ((uint32_t)s_len(cur) < ix.kt_levels) {
-            const int q = run_steps(ix, cur, c.pd, maxd, bound, has_n, S, P);
-            if (q) {
-                const u2 kl = reinterpret_cast<const u2 *>(sd_.kt)[run_entry(ix, cur, c.pd, q)];
-                c.expand += run_take(cur, valid, kl, c.pd, q, P);
-                continue;
-            }
-            const u4 *e = reinterpret_cast<const u4 *>(sd_.kt + 2 * (size_t)kt_children(s_len(cur), cur.x));
-            kt_pick(e[0], e[1], k);
-            c.expand++;
-        } else if (cur.y == SINGLE || to_text(ix, cur)) {
-            if (cur.y != SINGLE) {
-                cur.x = sd_.full[cur.x];
-                cur.y = SINGLE;
-            }
-            const int dir = strand == 0 ? 1 : 0;
-            uint32_t win = 0;
-            if (cur.x) {
-                const u2w w = *reinterpret_cast<const u2w *>(ix.pac + text_word(ix, dir, cur.x));
-                win = text_bases(ix, dir, cur.x, w.x, w.y);
-                if (dir) win = rev16(win);
-            }
-            if (text_step(cur, win, maxd, bound, has_n, P, c, k)) continue;
-        } else {
-            rank_children<LW>(ix, sd_, cur.x, cur.y + 1, k, false);
-            c.expand++;
-        }
-        const int i = s_i(cur);
-        const int b = pd_base(c, i);
-        const int Di = pd_d(c, i), Dn = pd_d(c, i - 1);
-        int rc = expand_children(cur, valid, k, gaps_only, b, m, maxd, Di, Dn, S, P, c, ix.kt_levels);
+        const int rc = search_step<LW>(ix, sd_, strand == 0 ? 1 : 0, true, cur, valid, m, maxd, has_n, S, P, c);
         if (rc) return rc;
     }
 }
@@ -1464,21 +1530,30 @@ __device__ bool take_tasks(const SplitBufs &X, uint32_t g, uint32_t cnt, uint32_
     return false;
 }
 
+// Task entries a pending state takes: one, or a family's children one each.
+__device__ __forceinline__ uint32_t task_count(u4 v) { return (v.z & FAMILY) ? (uint32_t)__popc(v.y) : 1u; }
+__device__ uint32_t task_count(const LaneCtx &c, u4 cur, bool has_cur) {
+    uint32_t n = has_cur ? task_count(cur) : 0u;
+    for (uint32_t j = c.sbase; j < c.sp; j++) n += task_count(c.stack[(size_t)j * c.sstride]);
+    return n;
+}
+
 // Write cur when has_cur, then the lane's pending stack entries, to the
 // entries reserved at off in generation g; the lane's stack is left empty.
 __device__ void put_tasks(const SplitBufs &X, uint32_t g, uint32_t off, uint32_t ref, LaneCtx &c, u4 cur,
                           bool has_cur) {
     u4 *T = as_global(X.tasks[g & 1]);
     uint32_t *R = as_global(X.task_ref[g & 1]);
-    if (has_cur) {
-        T[off] = cur;
-        R[off] = ref;
-        off++;
-    }
-    for (uint32_t j = c.sbase; j < c.sp; j++, off++) {
-        T[off] = c.stack[(size_t)j * c.sstride];
-        R[off] = ref;
-    }
+    auto put = [&](u4 v) {
+        uint32_t set = (v.z & FAMILY) ? v.y : 1u;
+        for (; set; set &= set - 1, off++) {
+            if (v.z & FAMILY) v.y = set & (0u - set);
+            T[off] = v;
+            R[off] = ref;
+        }
+    };
+    if (has_cur) put(cur);
+    for (uint32_t j = c.sbase; j < c.sp; j++) put(c.stack[(size_t)j * c.sstride]);
     c.sp = c.sbase = 0;
 }
 
@@ -1535,7 +1610,7 @@ constexpr int SH_SLOT_SHIFT = 5;
 // is left.
 __device__ bool split_part(const SplitBufs &X, uint32_t r, uint32_t owner, int strand, int m, int maxd, bool has_n,
                            int best, LaneCtx &c, u4 cur, bool valid, int &fl) {
-    const uint32_t cnt = (valid ? 1u : 0u) + (c.sp - c.sbase);
+    const uint32_t cnt = task_count(c, cur, valid);
     const bool had = (fl >> SH_SLOT_SHIFT) != 0;
     if (!had && ld_agent(&X.ctl[0]) >= X.slot_cap) return false;
     uint32_t off = 0;
@@ -1652,7 +1727,6 @@ __global__ __launch_bounds__(BLOCK) void k_align_plain(DevIndex ix, ReadsView rd
 }
 
 enum { PZ_IDLE = 0, PZ_TURN = 1, PZ_SEARCH = 2, PZ_HELP = 3, PZ_WAIT = 4 };
-enum { ACT_NONE = 0, ACT_EXPAND = 1, ACT_RUN = 2, ACT_TEXT = 3, ACT_UNROLL = 4 };
 
 // Per-wave block in LDS through which the lanes of a wave share one read's
 // search once the batch's reads are all taken: an idle lane receives the
@@ -2013,15 +2087,8 @@ __device__ __forceinline__ void persistent_body(const DevIndex &ix, const Params
 
         // decide this lane's action and rank queries; a lane that changes
         // phase here acts in its new phase from the next iteration on
-        int act = ACT_NONE;
-        int q = 0;           // steps of the run the table entry covers
-        uint32_t tent = 0;   // the entry
-        uint32_t tpos = 0;   // text position whose next bases are read
-        bool conv = false;   // the one row left becomes a text position
-        bool query = false;  // rank query at q1, q2
+        bool go = false;  // cur takes a step
         bool hit = false;
-        int qdir = 0;  // index queried: 0 = T, 1 = reverse(T)
-        uint32_t q1 = 0, q2 = 0;
         bool part_done = false;  // this lane's part of the strand's search is over
         if (phase == PZ_SEARCH || phase == PZ_HELP) {
             int rr = resolve(cur, valid, strand, P, c, PH_FAST, POPS_PER_STEP, ix, endgame);
@@ -2037,28 +2104,7 @@ __device__ __forceinline__ void persistent_body(const DevIndex &ix, const Params
             } else if (rr == 0) {
                 part_done = true;
             }
-            if (rr == 1) {
-                act = ACT_EXPAND;
-                qdir = strand == 0 ? 1 : 0;
-                if (s_gs(cur) == GAP_RUN) {
-                    act = ACT_UNROLL;
-                } else if ((uint32_t)s_len(cur) < ix.kt_levels) {
-                    const int bound = (P.mode == BWFM_MODE_BEST && c.best != INF_SCORE) ? c.best + P.s_mm : INF_SCORE;
-                    q = run_steps(ix, cur, c.pd, maxd, bound, has_n, S, P);
-                    if (q) act = ACT_RUN;
-                    tent = q ? run_entry(ix, cur, c.pd, q) : kt_children(s_len(cur), cur.x);
-                } else if (cur.y == SINGLE) {
-                    act = ACT_TEXT;
-                    tpos = cur.x;
-                } else if (to_text(ix, cur)) {
-                    act = ACT_NONE;
-                    conv = true;
-                } else {
-                    query = true;
-                    q1 = cur.x;
-                    q2 = cur.y + 1;
-                }
-            }
+            go = rr == 1;
             if (!endgame && phase == PZ_SEARCH) {
                 sh_st(&ws.best[lane], c.best);
                 sh_st(&ws.ncand[lane], (int)c.ncand);
@@ -2115,62 +2161,16 @@ __device__ __forceinline__ void persistent_body(const DevIndex &ix, const Params
             phase = PZ_TURN;
         }
 
-        // the shared part: a table entry (the load issued first, so that its
-        // latency overlaps the rank query's in other lanes), or the rank
-        // counts at q1 and q2, on one index
-        Kids kids;
-        kids.mask = 0;
-#pragma unroll
-        for (int a = 0; a < 4; a++) kids.x[a] = kids.y[a] = 0;
-        const DevDir qd = pick_dir(ix, qdir);
-        if (O.work) w_query += query || tent || tpos || conv;
-        u4 ta = mk4(0, 0, 0, 0), tb = ta;
-        uint32_t w0 = 0, w1 = 0;
-        if (tent) {
-            const u4 *e = reinterpret_cast<const u4 *>(qd.kt) + (tent >> 1);
-            ta = e[0];
-            if (q == 0) tb = e[1];
-        }
-        if (tpos) {
-            const u2w w = *reinterpret_cast<const u2w *>(ix.pac + text_word(ix, qdir, tpos));
-            w0 = w.x;
-            w1 = w.y;
-        }
-        if (conv) w0 = qd.full[cur.x];
-        if (query) rank_children<LW>(ix, qd, q1, q2, kids, true);
-        if (tent && q == 0) kt_pick(ta, tb, kids);
-        const u2 tkl = (tent & 1) ? mk2(ta.z, ta.w) : mk2(ta.x, ta.y);
-
-        // consume
-        if (act == ACT_RUN) {
-            c.expand += run_take(cur, valid, tkl, c.pd, q, P);
-        } else if (conv) {
-            cur.x = w0;
-            cur.y = SINGLE;
-        }
-        bool grow = act == ACT_EXPAND || act == ACT_UNROLL;
-        if (act == ACT_EXPAND) c.expand++;
-        if (act == ACT_UNROLL) unroll_run(cur, P, c, kids);
-        if (act == ACT_TEXT) {
-            uint32_t win = text_bases(ix, qdir, tpos, w0, w1);
-            if (qdir) win = rev16(win);
-            const int bound = (P.mode == BWFM_MODE_BEST && c.best != INF_SCORE) ? c.best + P.s_mm : INF_SCORE;
-            grow = !text_step(cur, win, maxd, bound, has_n, P, c, kids);
-        }
-        if (grow) {
-            const int i = s_i(cur);
-            const int b = pd_base(c, i);
-            const int Di = pd_d(c, i), Dn = pd_d(c, i - 1);
-            int rc = expand_children(cur, valid, kids, act == ACT_UNROLL, b, m, maxd, Di, Dn, S, P, c, ix.kt_levels);
-            if (rc) {
-                // cannot happen with worst-case stacks; kept as a guard
-                if (endgame) {
-                    atomicOr(&ws.flags[ow], SH_FAIL);  // every lane of the read drops out
-                } else {
-                    send_to_second_pass(O, r);
-                    if (O.expand) O.expand[r] = c.expand;
-                    phase = PZ_IDLE;
-                }
+        const DevDir qd = pick_dir(ix, strand == 0 ? 1 : 0);
+        if (O.work) w_query += go;
+        if (search_step<LW>(ix, qd, strand == 0 ? 1 : 0, go, cur, valid, m, maxd, has_n, S, P, c)) {
+            // cannot happen with worst-case stacks; kept as a guard
+            if (endgame) {
+                atomicOr(&ws.flags[ow], SH_FAIL);  // every lane of the read drops out
+            } else {
+                send_to_second_pass(O, r);
+                if (O.expand) O.expand[r] = c.expand;
+                phase = PZ_IDLE;
             }
         }
     }
@@ -2338,7 +2338,7 @@ __global__ __launch_bounds__(BLOCK) void k_align_tasks(DevIndex ix, Params P, co
             } else if (rr == 1) {
                 if (drain && drained && texp >= DRAIN_MIN && c.sp > c.sbase) {
                     uint32_t off = 0;
-                    if (take_tasks(X, g + 1, 1 + (c.sp - c.sbase), off)) {
+                    if (take_tasks(X, g + 1, task_count(c, cur, true), off)) {
                         put_tasks(X, g + 1, off, s | ((uint32_t)strand << 31), c, cur, true);
                         valid = false;
                         done = true;
@@ -2349,59 +2349,12 @@ __global__ __launch_bounds__(BLOCK) void k_align_tasks(DevIndex ix, Params P, co
             // rr == 2: the pop limit; popping goes on next iteration
         }
         const DevDir qd = pick_dir(ix, strand == 0 ? 1 : 0);
-        int q = 0;
-        uint32_t tent = 0, w0 = 0, w1 = 0;
-        Kids kids;
-        kids.mask = 0;
-#pragma unroll
-        for (int a = 0; a < 4; a++) kids.x[a] = kids.y[a] = 0;
-        u4 ta = mk4(0, 0, 0, 0), tb = ta;
-        const int qdir = strand == 0 ? 1 : 0;
-        const int bound = (P.mode == BWFM_MODE_BEST && c.best != INF_SCORE) ? c.best + P.s_mm : INF_SCORE;
-        const bool unroll = query && s_gs(cur) == GAP_RUN;
-        const bool shallow = query && !unroll && (uint32_t)s_len(cur) < ix.kt_levels;
-        const bool text = query && !unroll && !shallow && cur.y == SINGLE;
-        const bool conv = query && !unroll && !shallow && !text && to_text(ix, cur);
-        if (shallow) {
-            q = run_steps(ix, cur, c.pd, maxd, bound, has_n, S, P);
-            tent = q ? run_entry(ix, cur, c.pd, q) : kt_children(s_len(cur), cur.x);
-            const u4 *e = reinterpret_cast<const u4 *>(qd.kt) + (tent >> 1);
-            ta = e[0];
-            if (q == 0) tb = e[1];
-        }
-        if (text && cur.x) {
-            const u2w w = *reinterpret_cast<const u2w *>(ix.pac + text_word(ix, qdir, cur.x));
-            w0 = w.x;
-            w1 = w.y;
-        }
-        if (conv) w0 = qd.full[cur.x];
-        const bool rank = query && !unroll && !shallow && !text && !conv;
-        if (rank) rank_children<LW>(ix, qd, cur.x, cur.y + 1, kids, true);
         const uint32_t e0 = c.expand;
-        bool grow = unroll || rank || (shallow && q == 0);
-        if (rank || (shallow && q == 0)) c.expand++;
-        if (q) {
-            c.expand += run_take(cur, valid, (tent & 1) ? mk2(ta.z, ta.w) : mk2(ta.x, ta.y), c.pd, q, P);
-        } else if (conv) {
-            cur.x = w0;
-            cur.y = SINGLE;
-        } else if (text) {
-            uint32_t win = text_bases(ix, qdir, cur.x, w0, w1);
-            if (qdir) win = rev16(win);
-            grow = !text_step(cur, win, maxd, bound, has_n, P, c, kids);
-        } else if (unroll) {
-            unroll_run(cur, P, c, kids);
+        if (search_step<LW>(ix, qd, strand == 0 ? 1 : 0, query, cur, valid, m, maxd, has_n, S, P, c)) {
+            atomicOr(&X.slot_fail[s], 1u);  // cannot happen with worst-case stacks; kept as a guard
+            done = true;
         }
         texp += c.expand - e0;
-        if (grow) {
-            if (shallow) kt_pick(ta, tb, kids);
-            const int i = s_i(cur);
-            if (expand_children(cur, valid, kids, unroll, pd_base(c, i), m, maxd, pd_d(c, i), pd_d(c, i - 1), S, P, c,
-                                ix.kt_levels)) {
-                atomicOr(&X.slot_fail[s], 1u);  // cannot happen with worst-case stacks; kept as a guard
-                done = true;
-            }
-        }
         if (done) {
             flush_slot(X, P, s, c);
             busy = false;
@@ -2836,7 +2789,7 @@ __global__ __launch_bounds__(256) void k_kt_level(DevIndex ix, int which, int d,
             k.y[a] = 0;
         }
     } else {
-        rank_children<LW>(ix, dd, kl.x, kl.y + 1, k, false);
+        rank_children<LW>(ix, dd, kl.x, kl.y + 1, k);
         if (mark) {
 #pragma unroll
             for (int a = 0; a < 4; a++)
@@ -2863,7 +2816,18 @@ __global__ __launch_bounds__(256) void k_kt_single(DevIndex ix, int which, int l
         uint32_t code = __builtin_amdgcn_alignbit(w.y, w.x, 2 * (t0 & 15)) & ((1u << (2 * levels)) - 1u);
         if (which) code = rev_digits(code, levels);
         const u2 kl = lv[code];
-        if (kl.x == kl.y) lv[code] = mk2((uint32_t)p, SINGLE);
+        if (kl.x == kl.y) {
+            uint32_t next = SINGLE;
+            if (p >= (uint32_t)NEXT) {
+                // the bases before p in the direction's text, the nearest first
+                const uint32_t t1 = which == 0 ? (uint32_t)p - NEXT : ix.n - (uint32_t)p;
+                const u2w v = *reinterpret_cast<const u2w *>(ix.pac + (t1 >> 4));
+                next = __builtin_amdgcn_alignbit(v.y, v.x, 2 * (t1 & 15)) & ((1u << (2 * NEXT)) - 1u);
+                if (which == 0) next = rev_digits(next, NEXT);
+                next |= SINGLE0;
+            }
+            lv[code] = mk2((uint32_t)p, next);
+        }
     }
 }
 
@@ -3448,6 +3412,7 @@ int bwfm::build_search_tables(bwfm_index *ix, hipStream_t st) {
     int levels = 1;
     while (levels < 15 && ((uint64_t)1 << (2 * levels)) < 2 * ix->n) levels++;
     free_b += dev_cached();
+    if (ix->n >= SINGLE0) return BWFM_OK;
     while (levels > 0 && 2 * (kt_bytes((uint32_t)levels) + 2 * (ix->n + 1) * 4) > free_b / 2) levels--;
     if (levels == 0) return BWFM_OK;
     const uint64_t bytes = kt_bytes((uint32_t)levels), full = 2 * (ix->n + 1) * 4;

@@ -5,8 +5,7 @@ The paper improves BarraCUDA by changing its kernel source and keeping a
 change only when the output stays the same and the kernel gets faster
 (sections 1, 3 and 5).  Here the kernel source (csrc/bwfm.hip) carries
 alternative implementations of single code sites ("genes", macros
-BWFM_GENE_*: row masks, the paired rank query, the sub-counted line's header
-loads, the loads of a sub-counted query) next to the tuning constants it
+BWFM_GENE_*: row masks, the sub-counted line's header loads, the loads of a sub-counted query) next to the tuning constants it
 exposes (stack pops per iteration, lanes that wait for a read change,
 first-pass hit slots, second-pass lanes).  A variant is one value per gene; each variant is its own library
 build.  The search is a (1+1) evolution strategy in generations:
@@ -45,7 +44,6 @@ OUT = os.path.join(HERE, "_variants")
 # gene -> (reference value, alternatives)
 GENES = {
     "BWFM_GENE_ROWMASK": (0, (1,)),
-    "BWFM_GENE_PAIRLINE": (0, (1,)),
     "BWFM_GENE_SUBHDR": (0, (1,)),
     "BWFM_GENE_SUBLOAD": (1, (0,)),
     "BWFM_POPS_PER_STEP": (1, (2,)),
@@ -57,7 +55,7 @@ GENES = {
 
 # two variants the package build compiles for the GPU tests: every gene
 # away from the shipped value in one of them
-TEST_VARIANTS = [{"BWFM_GENE_ROWMASK": 1, "BWFM_GENE_PAIRLINE": 1, "BWFM_GENE_SUBLOAD": 0, "BWFM_GENE_SUBHDR": 1},
+TEST_VARIANTS = [{"BWFM_GENE_ROWMASK": 1, "BWFM_GENE_SUBLOAD": 0, "BWFM_GENE_SUBHDR": 1},
                  {"BWFM_TURN_MIN": 1, "BWFM_POPS_PER_STEP": 2}]
 
 
