@@ -3,10 +3,9 @@
 // bounds allow around its mate's primary (section 3.7 closes the pipeline
 // with BWA's pairing step, of which this is the rescue part).
 //
-// One wave per rescued pair (a wave takes a few pair records and works
-// through those that need a rescue, one after another).  The mate's m bases
+// A group of 16, 32 or 64 lanes works on a pair.  The mate's m bases
 // are the rows of the dynamic-programming matrices, R consecutive rows per
-// lane; the window's reference bases are its columns.  The wave sweeps the
+// lane; the window's reference bases are its columns.  The group sweeps the
 // columns in skewed order -- lane l works on column t - l at step t -- so
 // each lane receives the row above its first row (the previous lane's last
 // row) one step after it was made, through a one-lane DPP shift.  Every cell
@@ -16,6 +15,19 @@
 // the start along at no extra cost.  The window is decoded from the packed
 // reference into LDS first.  Work per pair is m x window cells, a few
 // hundred steps: the kernel is bound by integer ALU work, not memory.
+//
+// Groups of 16 lanes with many rows each, four pairs a wave, are the rule: a
+// step's fixed work (the shift, the window base, loop and range checks) is
+// then spread over up to 16 cells a lane instead of 2, the rows of a mate
+// leave at most one lane's worth idle, and the skew is 15 columns instead of
+// 63.  A wave with fewer pairs at hand gives each of them more lanes.  Pairs
+// are listed by block and its four waves take from the list, longest mates
+// first.  Bound by VALU issue: 89 instructions a step of a wave, 13 a cell
+// (four of them for each gap matrix), issued 82% of the time.  Against
+// one wave a pair with 1, 2, 4 or 8 rows a lane and a check of every cell
+// against the best: 300 k pairs of 36-150 bases, a sixth to rescue, 2.17 ->
+// 1.38 ms; of 250 bases 6.6 -> 5.6; 30 k of 150 bases 0.88 -> 0.41; 1 k of
+// mixed lengths 0.33 -> 0.12 (a wave there worked off four records in turn).
 
 #include <hip/hip_runtime.h>
 
@@ -29,8 +41,8 @@ using namespace bwfm;
 
 namespace {
 
-constexpr int RB = 64;   // threads per block: one wave, so the hardware hands out work one wave at a time
-constexpr int PPW = 4;   // pair records a wave takes (lanes 0 .. PPW - 1): few, so waves end evenly
+constexpr int RB = 256, WAVES = RB / 64;  // threads of a block, waves
+constexpr uint32_t TAKE_MAX = 128;          // pair records a block takes at most
 // cell keys: score * KS + preference * KP + start column
 constexpr int KS = 1 << 15, KP = 1 << 13;
 constexpr int NEGK = -(1 << 30);  // no alignment can end here (score -32768)
@@ -61,56 +73,59 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_wave_barrier();
 }
 
-// v from the previous lane of the wave (a DPP shift right by one lane);
-// lane 0, which has no previous lane, gets 0
-__device__ __forceinline__ int row_above(int v) {
-    return __builtin_amdgcn_mov_dpp(v, 0x138 /* wave_shr:1 */, 0xF, 0xF, true);
+// v from the previous lane of the group of G lanes (a DPP shift right by one
+// lane); a group's first lane, which has no previous lane, gets 0
+template <int G> __device__ __forceinline__ int row_above(int v) {
+    if constexpr (G == 16) return __builtin_amdgcn_mov_dpp(v, 0x111 /* row_shr:1 */, 0xF, 0xF, true);
+    const int up = __builtin_amdgcn_mov_dpp(v, 0x138 /* wave_shr:1 */, 0xF, 0xF, true);
+    return G == 64 || (threadIdx.x & (G - 1)) ? up : 0;
 }
 
-// Rescue one pair with the whole wave (all arguments wave-uniform).
-template <int R>
-__device__ void rescue_one(const uint32_t *pac, uint64_t n, const EndView &ev, uint32_t pair, uint64_t o0, int m,
-                           int mate, uint32_t pa, int la, int sa, int lo, int hi, int max_len, const Scores &S,
-                           uint8_t *win,
-                           bwfm_rescue *out) {
-    const int lane = threadIdx.x & 63;
+// One pair record that needs a rescue, as the lane that read it found it.
+struct Mate {
+    const uint8_t *q;  // the mate's bases
+    uint32_t pair, pa;    // the record; where the anchor lies
+    int end, m, la, sa;
+};
+
+// Rescue a pair per group of G lanes (c: the group's pair, the same in all its
+// lanes; on: it has one).  m <= G * R.
+template <int G, int R>
+__device__ __forceinline__ void rescue_groups(const uint32_t *pac, uint64_t n, const Mate &c, bool on, int lo, int hi,
+                              const Scores &S, uint8_t *win, bwfm_rescue *out) {
+    int lane = threadIdx.x & (G - 1);
+    asm volatile("" : "+v"(lane));  // (keeps the builds' code from being merged, which held the registers of all: 167 instead of 87)
+    const int m = on ? c.m : 0;
     int64_t w0, w1;
-    if (sa == 0) {
-        w0 = pa;
-        w1 = std::min<int64_t>((int64_t)pa + hi, (int64_t)n);
+    if (c.sa == 0) {
+        w0 = c.pa;
+        w1 = std::min<int64_t>((int64_t)c.pa + hi, (int64_t)n);
     } else {
-        w1 = std::min<int64_t>((int64_t)pa + la, (int64_t)n);
+        w1 = std::min<int64_t>((int64_t)c.pa + c.la, (int64_t)n);
         w0 = std::max<int64_t>(w1 - hi, 0);
     }
-    const int w = (int)std::max<int64_t>(w1 - w0, 0);
-    bwfm_rescue res;
-    std::memset(&res, 0, sizeof res);
-    if (m <= 0 || m > max_len || m > 64 * R || w <= 0) {
-        if (lane == 0) out[pair] = res;
-        return;
-    }
+    const int w = on ? (int)std::max<int64_t>(w1 - w0, 0) : 0;
     // the window, in the orientation the query reads it: forward after a +
     // anchor, reversed (from pr + lr - 1 down) after a - anchor
     // (each base stored times 8: the bit offset of its score in a row's profile)
-    for (int j = lane; j < w; j += 64) {
-        const uint64_t p = sa == 0 ? (uint64_t)(w0 + j) : (uint64_t)(w1 - 1 - j);
+    for (int j = lane; j < w; j += G) {
+        const uint64_t p = c.sa == 0 ? (uint64_t)(w0 + j) : (uint64_t)(w1 - 1 - j);
         win[j] = (uint8_t)(8 * ((pac[p >> 4] >> (2 * (p & 15))) & 3));
     }
     // this lane's rows: query base i is mate base m - 1 - i, complemented
     // after a + anchor (the mate then lies on -).  Each row keeps its
     // substitution scores against A, C, G, T as four signed bytes.
     int prof[R];
+    const uint8_t *q = c.q + (m - 1 - lane * R);
+    const uint32_t miss = (uint8_t)(int8_t)-S.b * 0x01010101u, flip = (uint8_t)(S.a ^ -S.b);
 #pragma unroll
     for (int r = 0; r < R; r++) {
-        const int i = lane * R + r;
-        int c = 5;  // rows past the mate: match nothing, never reported
-        if (i < m) {
-            c = ev.bases[o0 + (uint64_t)(m - 1 - i)];
-            if (sa == 0 && c < 4) c = 3 - c;
+        int b = 5;  // rows past the mate: match nothing, never reported
+        if (lane * R + r < m) {
+            b = q[-r];
+            if (c.sa == 0 && b < 4) b = 3 - b;
         }
-        uint32_t pk = 0;
-        for (int b = 0; b < 4; b++) pk |= (uint32_t)(uint8_t)(int8_t)(c == b ? S.a : -S.b) << (8 * b);
-        prof[r] = (int)pk;
+        prof[r] = (int)(b < 4 ? miss ^ flip << (8 * b) : miss);
     }
     wave_sync();
     const int used = (m + R - 1) / R;        // lanes holding rows
@@ -122,147 +137,187 @@ __device__ void rescue_one(const uint32_t *pac, uint64_t n, const EndView &ev, u
     // alignment 0), carrying the start column along.  H keys are kept with
     // preference 3, so a gap opened from H arrives with preference 3 and
     // beats the extension of a gap (E kept at 2, F at 1) on equal scores;
-    // clearing one bit then brings E back to 2 and F back to 1.  The edge
-    // row and column are key 0; cells of score 0 or below never pass their
-    // start column on to a cell of positive score, so their keys' low bits
-    // do not matter.
+    // clearing one bit then brings E back to 2 and F back to 1.  A cell of
+    // score 0 in column j is kept as preference 3 and start j + 1, the
+    // highest key of score 0 that column can have: a cell one step down the
+    // diagonal extends it or starts at its own column, by the same addition.
+    // Ho is H less the cost of a gap's first base, which the next column's E
+    // and the next row's F both start from.
     const int oek = (S.o + S.e) * KS, ek = S.e * KS;
-    int Hp[R], Ep[R];
+    int Hp[R], Ho[R], Ep[R];
 #pragma unroll
     for (int r = 0; r < R; r++) {
         Hp[r] = 3 * KP;
+        Ho[r] = 3 * KP - oek;
         Ep[r] = NEGK;
     }
     int outH = 0, outF = 0;  // last row of this lane, current column
-    int prevH = 0;           // row above, previous column
+    int j = -lane;
+    int prevH = 3 * KP + max(j, 0);  // row above, previous column (edge row: score 0)
     int bestK = 0, bj = -1, bi = 0;
     int bestT = KS;  // a cell reports when its key reaches this: a score above the best
-    const int steps = w + used - 1;
-    const bool holds = lane < used;
-    int j = -lane;
+    int steps = m > 0 && w > 0 ? w + used - 1 : 0;
+#pragma unroll
+    for (int k = G; k < 64; k <<= 1) steps = max(steps, __shfl_xor(steps, k));
+    steps = __builtin_amdgcn_readfirstlane(steps);
+    const int wl = lane < used ? w : 0;  // columns of this lane
     for (int t = 0; t < steps; t++, j++) {
         // the row above this lane's first row, from the previous lane
-        const int upH = row_above(outH), upF = row_above(outF);
-        if (holds && (unsigned)j < (unsigned)w) {
+        const int upH = row_above<G>(outH), upF = row_above<G>(outF);
+        const int z = 3 * KP + min(j + 1, KP - 1);
+        if ((unsigned)j < (unsigned)wl) {
             const int sh = win[j];
-            const bool elig = j >= e_min;
-            int Hd = prevH, Hu = upH, F = upF;
-            const int j3 = j + 3 * KP;
+            int Hd = prevH, Huo = upH - oek, F = upF, top = 0;
 #pragma unroll
             for (int r = 0; r < R; r++) {
-                const int E = max(Hp[r] - oek, Ep[r] - ek) & ~KP;
-                F = max(Hu - oek, F - ek) & ~(2 * KP);
-                const int base = Hd >= KS ? Hd : j3;  // extend a positive cell, or start here
-                const int dg = base + __builtin_amdgcn_sbfe(prof[r], sh, 8) * KS;
-                const int H = max(max(dg, E), max(F, 0)) | (3 * KP);
+                const int E = max(Ho[r], Ep[r] - ek) & ~KP;
+                F = max(Huo, F - ek) & ~(2 * KP);
+                const int dg = Hd + __builtin_amdgcn_sbfe(prof[r], sh, 8) * KS;
+                const int H = max(max(max(dg, E), F), z) | (3 * KP);
                 Hd = Hp[r];
                 Hp[r] = H;
                 Ep[r] = E;
-                Hu = H;
-                if (elig && H >= bestT && lane * R + r < m) {
-                    bestK = H;
-                    bestT = (H & ~(KS - 1)) + KS;
-                    bj = j;
-                    bi = lane * R + r + 1;
-                }
+                Ho[r] = Huo = H - oek;
+                top = max(top, H);
             }
-            outH = Hu;
+            outH = Hp[R - 1];
             outF = F;
+            if (top >= bestT && j >= e_min) {
+#pragma unroll
+                for (int r = 0; r < R; r++)
+                    if (Hp[r] >= bestT && lane * R + r < m) {
+                        bestK = Hp[r];
+                        bestT = (bestK & ~(KS - 1)) + KS;
+                        bj = j;
+                        bi = lane * R + r + 1;
+                    }
+            }
         }
-        prevH = upH;
+        prevH = max(upH, z);  // (a group's first lane: score 0)
     }
     // the first best cell in column order: highest score, then smallest
     // column, then smallest row (each cell lives in exactly one lane)
     const int best = bestK >> 15;
-    uint64_t key = best > 0 ? ((uint64_t)(uint32_t)best << 32) | ((uint64_t)(0xFFFFu - (uint32_t)bj) << 16) |
-                                  (uint64_t)(0xFFFFu - (uint32_t)bi)
-                            : 0;
+    const uint64_t key = best >= S.min_score ? ((uint64_t)(uint32_t)best << 32) |
+                                                   ((uint64_t)(0xFFFFu - (uint32_t)bj) << 16) |
+                                                   (uint64_t)(0xFFFFu - (uint32_t)bi)
+                                             : 0;
     uint64_t top = key;
-    for (int k = 32; k > 0; k >>= 1) {
+    for (int k = G / 2; k > 0; k >>= 1) {
         const uint64_t o = __shfl_xor(top, k);
         top = o > top ? o : top;
     }
-    const unsigned long long who = __ballot(key == top && top != 0);
-    if (who) {
-        const int src = __ffsll((long long)who) - 1;
-        const int sbest = __shfl(best, src);
-        const int sbj = __shfl(bj, src);
-        const int sbO = __shfl(bestK & (KP - 1), src);
-        if (sbest >= S.min_score) {
-            res.end = (uint8_t)mate;
-            res.score = (int16_t)sbest;
-            res.len = (uint16_t)(sbj - sbO + 1);
-            res.insert = sbj + 1;
-            if (sa == 0) {
+    if (on && (top ? key == top : lane == 0)) {
+        bwfm_rescue res;
+        std::memset(&res, 0, sizeof res);
+        if (top) {
+            const int start = bestK & (KP - 1);
+            res.end = (uint8_t)c.end;
+            res.score = (int16_t)best;
+            res.len = (uint16_t)(bj - start + 1);
+            res.insert = bj + 1;
+            if (c.sa == 0) {
                 res.strand = 1;
-                res.pos = (uint32_t)(w0 + sbO);
+                res.pos = (uint32_t)(w0 + start);
             } else {
                 res.strand = 0;
-                res.pos = (uint32_t)(w1 - 1 - sbj);
+                res.pos = (uint32_t)(w1 - 1 - bj);
             }
         }
+        out[c.pair] = res;
     }
-    if (lane == 0) out[pair] = res;
+    wave_sync();  // the windows are rewritten for the next pairs
 }
 
-// RMAX: rows per lane that hold the batch's longest mate; each mate is
-// rescued by the build of the fewest rows per lane that hold it, so short
-// mates of a mixed batch keep more lanes busy and the sweep shorter.
-template <int RMAX>
-__global__ __launch_bounds__(RB) void k_rescue(const uint32_t *pac, uint64_t n, EndView e1, EndView e2,
-                                               const bwfm_pair *pairs, uint32_t n_pairs, int lo, int hi, int max_len,
-                                               Scores S, int win_stride, bwfm_rescue *out) {
+// the build of the fewest rows per lane that hold m rows (at most ML)
+template <int G, int ML>
+__device__ __forceinline__ void rescue_by_rows(const uint32_t *pac, uint64_t n, const Mate &c, bool on, int m, int lo,
+                                               int hi, const Scores &S, uint8_t *win, bwfm_rescue *out) {
+    const int need = (m + G - 1) / G;
+#define BWFM_ROWS(R)                                                                \
+    if constexpr (G * (R) <= ML)                                                    \
+        if (need <= (R)) return rescue_groups<G, (R)>(pac, n, c, on, lo, hi, S, win, out);
+    BWFM_ROWS(1) BWFM_ROWS(2) BWFM_ROWS(3) BWFM_ROWS(4) BWFM_ROWS(5) BWFM_ROWS(6) BWFM_ROWS(7) BWFM_ROWS(8)
+    BWFM_ROWS(10) BWFM_ROWS(12) BWFM_ROWS(14) BWFM_ROWS(16)
+#undef BWFM_ROWS
+}
+
+// ML: bound of the mates' lengths (up to 128 the registers leave 5 waves per
+// SIMD and more; above, 4 are held to).  A block takes `take` (<= RB) pair
+// records, a thread each, and lists those that need a rescue, long mates
+// first, so that the mates a wave works on together are of like lengths.  Its
+// waves take from the list, each at most `most` (1, 2 or 4) mates at a time,
+// fewer where the list holds fewer for each wave.
+template <int ML>
+__global__ __launch_bounds__(RB, ML <= 128 ? 1 : 4) void k_rescue(const uint32_t *pac, uint64_t n, EndView e1,
+                                                                  EndView e2, const bwfm_pair *pairs,
+                                                                  uint32_t n_pairs, int lo, int hi, int max_len,
+                                                                  Scores S, uint32_t take, int most, int win_stride,
+                                                                  bwfm_rescue *out) {
     extern __shared__ uint8_t lds[];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    uint8_t *win = lds + (size_t)wv * win_stride;
-    // the wave's first pair (uniform across the wave; said so, so that the
-    // per-pair values derived from it live in scalar registers)
-    const uint32_t base = __builtin_amdgcn_readfirstlane(((uint32_t)blockIdx.x * (RB / 64) + (uint32_t)wv) * PPW);
-    const uint32_t p = base + (uint32_t)lane;
+    __shared__ Mate list[RB];
+    __shared__ int len[RB];  // 0: no rescue
+    __shared__ int count, next;
+    const int tid = threadIdx.x;
+    const uint32_t p = blockIdx.x * take + (uint32_t)tid;
+    Mate c{};
     bool cand = false;
-    int mate = 0, la = 0, sa = 0;
-    uint32_t pa = 0;
-    if (lane < PPW && p < n_pairs) {
+    if ((uint32_t)tid < take && p < n_pairs) {
         const bwfm_pair pr = pairs[p];
         const bool m1 = (pr.flags & BWFM_PF_MAPPED1) != 0, m2 = (pr.flags & BWFM_PF_MAPPED2) != 0;
-        cand = !(pr.flags & BWFM_PF_PAIRED) && (m1 || m2);
         // the anchor: the mapped end, or of two the lower search score (end 1 on ties)
         const int anchor = (m1 && m2) ? (pr.score1 <= pr.score2 ? 1 : 2) : (m1 ? 1 : 2);
-        mate = 3 - anchor;
-        pa = anchor == 1 ? pr.pos1 : pr.pos2;
-        la = anchor == 1 ? pr.len1 : pr.len2;
-        sa = anchor == 1 ? pr.strand1 : pr.strand2;
+        c.pair = p;
+        c.end = 3 - anchor;
+        c.pa = anchor == 1 ? pr.pos1 : pr.pos2;
+        c.la = anchor == 1 ? pr.len1 : pr.len2;
+        c.sa = anchor == 1 ? pr.strand1 : pr.strand2;
+        if (!(pr.flags & BWFM_PF_PAIRED) && (m1 || m2)) {
+            const EndView &ev = c.end == 1 ? e1 : e2;
+            uint64_t o0;
+            end_span(ev, p, o0, c.m);
+            c.q = ev.bases + o0;
+            cand = c.m > 0 && c.m <= max_len;
+        }
         if (!cand) {
             bwfm_rescue z;
             std::memset(&z, 0, sizeof z);
             out[p] = z;
         }
     }
-    unsigned long long todo = __ballot(cand);
-    while (todo) {
-        const int src = __ffsll((long long)todo) - 1;
-        todo &= todo - 1;
-        const int c_mate = __builtin_amdgcn_readlane(mate, src), c_la = __builtin_amdgcn_readlane(la, src),
-                  c_sa = __builtin_amdgcn_readlane(sa, src);
-        const uint32_t c_pa = (uint32_t)__builtin_amdgcn_readlane((int)pa, src);
-        const EndView &ev = c_mate == 1 ? e1 : e2;
-        const uint32_t pair = base + (uint32_t)src;
-        uint64_t o0;
-        int m;
-        end_span(ev, pair, o0, m);
-        const int need = m <= 64 ? 1 : m <= 128 ? 2 : m <= 256 ? 4 : 8;
-        if (RMAX >= 8 && need == 8)
-            rescue_one<(RMAX >= 8 ? 8 : 1)>(pac, n, ev, pair, o0, m, c_mate, c_pa, c_la, c_sa, lo, hi, max_len, S, win,
-                                           out);
-        else if (RMAX >= 4 && need == 4)
-            rescue_one<(RMAX >= 4 ? 4 : 1)>(pac, n, ev, pair, o0, m, c_mate, c_pa, c_la, c_sa, lo, hi, max_len, S, win,
-                                           out);
-        else if (RMAX >= 2 && need == 2)
-            rescue_one<(RMAX >= 2 ? 2 : 1)>(pac, n, ev, pair, o0, m, c_mate, c_pa, c_la, c_sa, lo, hi, max_len, S, win,
-                                           out);
-        else  // one row per lane; a mate longer than the batch's bound is reported unrescued there
-            rescue_one<1>(pac, n, ev, pair, o0, m, c_mate, c_pa, c_la, c_sa, lo, hi, max_len, S, win, out);
-        wave_sync();  // the window is rewritten for the next pair
+    len[tid] = cand ? c.m : 0;
+    if (tid == 0) count = next = 0;
+    __syncthreads();
+    if (cand) {
+        int place = 0;
+        for (int i = 0; i < (int)take; i++) place += len[i] > c.m || (len[i] == c.m && i < tid);
+        list[place] = c;
+        atomicAdd(&count, 1);
+    }
+    __syncthreads();
+    const int all = __builtin_amdgcn_readfirstlane(count), wv = tid >> 6;
+    const int share = (all + WAVES - 1) / WAVES;
+    most = min(most, share >= 3 ? 4 : share);
+    uint8_t *wins = lds + (size_t)wv * most * win_stride;
+    for (;;) {
+        int i = 0;
+        if ((tid & 63) == 0) i = atomicAdd(&next, most);
+        i = __builtin_amdgcn_readfirstlane(i);
+        if (i >= all) break;
+        const int left = min(all - i, most);
+        const int at_once = left >= 3 ? 4 : left;
+        const int g = (tid & 63) / (64 / at_once);
+        const bool on = g < left;
+        const Mate x = list[on ? i + g : i];
+        const int m0 = __builtin_amdgcn_readfirstlane(list[i].m);  // the longest
+        uint8_t *win = wins + (size_t)g * win_stride;
+        if (at_once == 4) {
+            if constexpr (ML <= 256) rescue_by_rows<16, ML>(pac, n, x, on, m0, lo, hi, S, win, out);
+        } else if (at_once == 2) {
+            rescue_by_rows<32, ML>(pac, n, x, on, m0, lo, hi, S, win, out);
+        } else {
+            rescue_by_rows<64, ML>(pac, n, x, on, m0, lo, hi, S, win, out);
+        }
     }
 }
 
@@ -292,19 +347,28 @@ extern "C" int bwfm_rescue_mates(const bwfm_index *ix, const bwfm_reads *end1, c
     const Scores S{q.match, q.mismatch, q.gap_open, q.gap_extend, q.min_score};
     const int hi = std::max(pp->hi, 0);
     const int win_stride = std::max((hi + 15) & ~15, 16);
-    const uint64_t per_block = (uint64_t)(RB / 64) * PPW;
-    const uint32_t grid = (uint32_t)(((uint64_t)n_pairs + per_block - 1) / per_block);
-    const size_t lds = (size_t)(RB / 64) * win_stride;
+    // records a block takes: as many as it has waves while all blocks run at
+    // once (eight a CU), more of a larger batch so that its waves find four
+    // mates at a time, but at most 128: larger blocks end less evenly (300 k
+    // pairs of 36-150 bases at 64 / 128 / 256: 1.45 / 1.38 / 1.55 ms)
+    uint32_t take = WAVES;
+    while (take < TAKE_MAX && (uint64_t)take * 2048 < n_pairs) take *= 2;
+    const uint32_t grid = (n_pairs - 1) / take + 1;
+    // mates a wave works on at once: as many as its lanes hold the rows of
+    // and 48 KB of LDS hold the windows of
+    int most = max_len <= 256 ? 4 : 2;
+    while (most > 1 && (size_t)WAVES * most * win_stride > 48 * 1024) most /= 2;
+    const size_t lds = (size_t)WAVES * most * win_stride;
     const uint32_t *pac = (const uint32_t *)ix->d_pac;
     const int ml = (int)max_len;
     if (max_len <= 64)
-        k_rescue<1><<<grid, RB, lds, st>>>(pac, ix->n, e1, e2, pairs, n_pairs, pp->lo, hi, ml, S, win_stride, out);
+        k_rescue<64><<<grid, RB, lds, st>>>(pac, ix->n, e1, e2, pairs, n_pairs, pp->lo, hi, ml, S, take, most, win_stride, out);
     else if (max_len <= 128)
-        k_rescue<2><<<grid, RB, lds, st>>>(pac, ix->n, e1, e2, pairs, n_pairs, pp->lo, hi, ml, S, win_stride, out);
+        k_rescue<128><<<grid, RB, lds, st>>>(pac, ix->n, e1, e2, pairs, n_pairs, pp->lo, hi, ml, S, take, most, win_stride, out);
     else if (max_len <= 256)
-        k_rescue<4><<<grid, RB, lds, st>>>(pac, ix->n, e1, e2, pairs, n_pairs, pp->lo, hi, ml, S, win_stride, out);
+        k_rescue<256><<<grid, RB, lds, st>>>(pac, ix->n, e1, e2, pairs, n_pairs, pp->lo, hi, ml, S, take, most, win_stride, out);
     else
-        k_rescue<8><<<grid, RB, lds, st>>>(pac, ix->n, e1, e2, pairs, n_pairs, pp->lo, hi, ml, S, win_stride, out);
+        k_rescue<512><<<grid, RB, lds, st>>>(pac, ix->n, e1, e2, pairs, n_pairs, pp->lo, hi, ml, S, take, most, win_stride, out);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(BWFM_E_DEVICE, std::string("rescue_mates: launch: ") + hipGetErrorString(e));
     return BWFM_OK;
