@@ -42,7 +42,6 @@ using namespace bwfm;
 namespace {
 
 constexpr int RB = 256, WAVES = RB / 64;  // threads of a block, waves
-constexpr uint32_t TAKE_MAX = 128;          // pair records a block takes at most
 // cell keys: score * KS + preference * KP + start column
 constexpr int KS = 1 << 15, KP = 1 << 13;
 constexpr int NEGK = -(1 << 30);  // no alignment can end here (score -32768)
@@ -349,10 +348,11 @@ extern "C" int bwfm_rescue_mates(const bwfm_index *ix, const bwfm_reads *end1, c
     const int win_stride = std::max((hi + 15) & ~15, 16);
     // records a block takes: as many as it has waves while all blocks run at
     // once (eight a CU), more of a larger batch so that its waves find four
-    // mates at a time, but at most 128: larger blocks end less evenly (300 k
-    // pairs of 36-150 bases at 64 / 128 / 256: 1.45 / 1.38 / 1.55 ms)
+    // mates at a time.  Blocks of 256 records end less evenly than of 128 unless
+    // there are many (300 k pairs of 36-150 bases at 64 / 128 / 256: 1.45 /
+    // 1.38 / 1.55 ms; 1 M of 100 bases, 6% to rescue: 1.54 at 128, 1.46 at 256)
     uint32_t take = WAVES;
-    while (take < TAKE_MAX && (uint64_t)take * 2048 < n_pairs) take *= 2;
+    while (take < RB && (uint64_t)take * 2048 < n_pairs && (take < 128 || (uint64_t)take * 4096 <= n_pairs)) take *= 2;
     const uint32_t grid = (n_pairs - 1) / take + 1;
     // mates a wave works on at once: as many as its lanes hold the rows of
     // and 48 KB of LDS hold the windows of
