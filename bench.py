@@ -13,9 +13,10 @@ residency is picked first by the autotuner on the same batch.
 
 Prints one JSON line.  The roofline entry is for the dominant kernel (the
 persistent search), timed with HIP events around it on its stream (events
-captured into the graph); its algorithmic bytes per launch are the oracle's
-index-line touches per read (same traversal order) x line size x reads per
-launch.  The CPU baseline is the oracle itself on a bounded sample of the
+captured into the graph); its bytes per launch are counter-measured
+(profiles/), since the search takes most of the rank lines that the oracle's
+backward search touches (reported beside it) from interval tables and the
+text instead.  The CPU baseline is the oracle itself on a bounded sample of the
 same pairs.
 """
 from __future__ import annotations
@@ -273,8 +274,9 @@ def main_se(args):
     step aligns the whole batch and locates every reported hit; the plain
     form (one lane per read) and the batched form (one persistent launch)
     are timed and must agree (the plain form on C5 over a leading part of
-    the batch only: its waves wait for their slowest reads).  The roofline uses the oracle's line touches
-    per read over a leading sample, which is also the CPU baseline."""
+    the batch only: its waves wait for their slowest reads).  The roofline is
+    counter-measured; the oracle's line touches per read over a leading
+    sample, which is also the CPU baseline, stand beside it."""
     import torch
 
     import oracle
@@ -408,18 +410,14 @@ def main_se(args):
                "host_cpus_visible": len(os.sched_getaffinity(0)),
                "sample": f"first {sample} reads of the same batch, {rounds} time(s): align, locate; {cpu_s:.1f} s"}
         touches = (orr.counts["touch_s"] + orr.counts["touch_d"]).astype(np.float64)
-        bytes_per_read = float(touches.mean()) * ix.info()["line_bytes"]
         kms = out[best]["kernel_ms"]
         if kms:
-            achieved = bytes_per_read * n / (kms / 1e3) / 1e9
-            roofline = {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                        "frac": achieved / HBM_PEAK_GBS, "traffic": None,
+            roofline = {"bound": "hbm", "achieved": None, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": None,
+                        "traffic": None,
                         "kernel": ("k_align_plain" if best == "plain" else
-                                   "k_dscan + k_align_persistent + k_align_tasks" if max_len >= 200 else
-                                   "k_align_persistent + k_align_tasks"),
-                        "bytes_per_read": bytes_per_read, "reads_per_launch": n, "avg_launch_ms": kms,
-                        "note": "index resident in the Infinity Cache at this size; algorithmic bytes per step "
-                                "over the search's HIP-event time, against HBM's peak"}
+                                   "k_dscan + k_align_persistent + k_align_tasks"),
+                        "reads_per_launch": n, "avg_launch_ms": kms, "line_touches_per_read": float(touches.mean()),
+                        "basis": "counter-measured HBM-side bytes per step of the search"}
             if best == "batched" and cfg == "C5":
                 # counter-measured bytes of the same kernels at the same split
                 # budget (the budget moves work between the first pass and the
@@ -428,8 +426,8 @@ def main_se(args):
                 roofline["traffic"] = traffic
                 if traffic:
                     rate = traffic / (kms / 1e3) / 1e9
-                    roofline["traffic_rate"] = rate
-                    roofline["traffic_frac"] = rate / HBM_PEAK_GBS
+                    roofline["achieved"] = rate
+                    roofline["frac"] = rate / HBM_PEAK_GBS
     ms_step = out[best]["ms_per_step"]
     line = {
         "metric": f"aligned reads/s ({cfg} single-end) on 1 MI355X", "value": out[best]["aligned_reads_per_s"],
@@ -558,7 +556,8 @@ def main():
                     help="0: counts + bit planes; 1: sub-counted 64-byte lines of 160 rows; "
                          "2: sub-counted 128-byte lines of 384 rows")
     ap.add_argument("--kmer-levels", type=int, default=0,
-                    help="short-string interval table levels (0: none, -1: automatic)")
+                    help="levels of the caller's short-string interval table (0: none, -1: automatic); "
+                         "the search has its own")
     ap.add_argument("--waves-per-simd", type=int, default=0, help="batched-form residency (0 = autotuned)")
     ap.add_argument("--no-tune", dest="tune", action="store_false", help="skip the autotuner (most waves that fit)")
     ap.add_argument("--no-rescue", action="store_true", help="skip the mate-rescue measurement")
@@ -789,47 +788,39 @@ def main():
                "host_cpus_visible": len(os.sched_getaffinity(0)),
                "sample": f"first {ns} pairs of the same batch ({2 * ns} reads): align both ends, locate, pair; "
                          f"{cpu_s:.1f} s"}
-        # algorithmic bytes of the first-pass search kernel: rank lines the
-        # method touches per read (D-array scans + search), same order as the kernel
+        # rank lines a read touches in plain backward search (D-array scans +
+        # search), same order as the kernel
         touches = np.concatenate([r.counts["touch_s"] + r.counts["touch_d"] for r in ores]).astype(np.float64)
-        bytes_per_read = float(touches.mean()) * ix.info()["line_bytes"]
         kf, timed_in = kernel_ms.get("align_persistent"), "batched (graph replays)"
         if not kf:
             kf, timed_in = eager["kernel_ms"].get("align_persistent"), "batched-eager (same kernel and batch)"
         # the achievable rate of dependent random line fetches on a buffer
-        # the size of the index's rank lines (the same access pattern with
+        # the size of the index with its tables (the same access pattern with
         # no search around it), measured here, for a second fraction
         probe = None
         try:
-            lb = ix.info()["line_bytes"]
-            buf = torch.zeros(2 * ix.info()["lines"] * lb, dtype=torch.uint8, device="cuda")
-            bw.probe_gather(buf, lb, iters=16)
-            probe_lps = bw.probe_gather(buf, lb)
+            mib = min(ix.info()["device_bytes"] >> 20, 8192)
+            buf = torch.zeros(mib << 20, dtype=torch.uint8, device="cuda")
+            bw.probe_gather(buf, 128, iters=16)
+            probe = {"probe_lines_per_s": bw.probe_gather(buf, 128), "probe_buffer_mib": mib, "probe_line_bytes": 128}
             del buf
-            probe = {"lines_per_s": probe_lps, "line_bytes": lb}
         except Exception as e:  # the probe is context; the bench line stands without it
             log(f"gather probe skipped: {e}")
         if kf:
-            per_launch = bytes_per_read * n_reads
-            achieved = per_launch / (kf["avg_ms"] / 1e3) / 1e9
             traffic = traffic_from_profiles("k_align_persistent")
-            roofline = {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                        "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
-                        "kernel": "k_align_persistent", "bytes_per_read": bytes_per_read,
-                        "reads_per_launch": n_reads, "avg_launch_ms": kf["avg_ms"], "timed_in": timed_in}
-            if traffic:
-                # each 64-byte line access fills a 128-byte L2 line: the measured
-                # traffic rate, against the same peak
-                rate = traffic / (kf["avg_ms"] / 1e3) / 1e9
-                roofline["traffic_rate"] = rate
-                roofline["traffic_frac"] = rate / HBM_PEAK_GBS
+            rate = traffic / (kf["avg_ms"] / 1e3) / 1e9 if traffic else None
+            roofline = {"bound": "hbm", "achieved": rate, "peak": HBM_PEAK_GBS, "unit": "GB/s",
+                        "frac": rate / HBM_PEAK_GBS if rate else None, "traffic": traffic,
+                        "kernel": "k_align_persistent", "reads_per_launch": n_reads, "avg_launch_ms": kf["avg_ms"],
+                        "timed_in": timed_in, "basis": "counter-measured HBM-side bytes per launch",
+                        "line_touches_per_read": float(touches.mean())}
             if probe:
-                lines_ps = per_launch / ix.info()["line_bytes"] / (kf["avg_ms"] / 1e3)
-                roofline["random_line_ceiling"] = {
-                    "probe_lines_per_s": probe["lines_per_s"], "kernel_lines_per_s": lines_ps,
-                    "frac": lines_ps / probe["lines_per_s"],
-                    "note": "algorithmic rank-line fetches/s against a dependent random-line gather on an "
-                            "index-sized buffer (paper_1505_07855_amd.probes)"}
+                fills_ps = rate * 1e9 / 128 if rate else None
+                roofline["random_line_ceiling"] = dict(
+                    probe, kernel_fills_per_s=fills_ps,
+                    frac=fills_ps / probe["probe_lines_per_s"] if fills_ps else None,
+                    note="128-byte fills and writes/s against a gather of dependent random lines on a buffer the "
+                         "size of the index (paper_1505_07855_amd.probes)")
 
     out = {
         "metric": METRIC, "value": value, "unit": "aligned reads/s", "n_gpus": 1, "steps": args.steps,

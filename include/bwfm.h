@@ -27,7 +27,10 @@
  *  - The caller owns every buffer it passes in.  The library owns the
  *    index (host and device copies) and, per index, one grow-only device
  *    workspace for each stream it has been called on, all released by
- *    bwfm_index_free.
+ *    bwfm_index_free.  Device blocks of 1 MB and more that indexes, their
+ *    workspaces and builds release stay with the process, at most 8 GB a
+ *    device, for the next ones, and go back to the driver when an allocation
+ *    of the library fails without them.
  *  - Concurrency.  The index is read-only after upload: bwfm_align_batch,
  *    bwfm_locate and bwfm_pair_reads calls on different streams may run at
  *    the same time from different host threads, and their kernels overlap
@@ -130,22 +133,25 @@ int bwfm_build_index_device(const uint8_t *ref, uint64_t n, const bwfm_index_par
                             bwfm_index **out);
 
 /* Copy the index to the current device's memory (once; later calls are
- * no-ops).  Synchronises hip_stream.  Errors: E_INVAL, E_NOMEM, E_DEVICE. */
+ * no-ops) and make the search's tables there (bwfm_build_index_device makes
+ * them too): per direction the SA intervals of all strings of up to K bases,
+ * K the least with 4^K >= 2n, at most 15, and the whole suffix array and its
+ * inverse (8 bytes a base).  They take at most half of the device memory that
+ * is free: with less there are fewer levels, or none of them, and the
+ * results are the same.  Synchronises hip_stream.  Errors: E_INVAL, E_NOMEM,
+ * E_DEVICE. */
 int bwfm_index_upload(bwfm_index *idx, void *hip_stream);
 
-/* Short-string interval table (a device-side accelerator of the search in
- * section 2; it changes no result).  For each direction and each string S
+/* Short-string interval table for the caller's own use (it changes no
+ * result; the search reads its own tables, bwfm_index_upload).  For each
+ * direction and each string S
  * of d <= levels bases (2 bits per base, the base prepended last in the
  * low bits: code(aS) = 4 code(S) + a), the table holds the SA interval
  * (k, l) of S on that direction's index, exactly as backward search steps
  * reach it (k > l when S does not occur).  Level d starts at entry
  * 4 + (4^d - 4) / 3 (level 0, entry 0, is the empty string's (0, n)), so
  * the four one-base extensions of a string are 32 contiguous,
- * 32-byte-aligned bytes.  The plain form's search and D-array scan, and
- * the batched form's second pass, take the children of a state whose
- * matched string is shorter than `levels` bases from there: one access in
- * place of two rank-line fetches.  The batched form's persistent first
- * pass does not: there it measured slower.  Built on the device from the
+ * 32-byte-aligned bytes.  Built on the device from the
  * uploaded rank lines; replaces an existing table (no call that uses the
  * index may run meanwhile; captured pipeline steps are captured again on
  * their next run).  levels: 0 releases the table, -1 picks the smallest d
@@ -257,7 +263,10 @@ typedef struct {
                                take (rounds of one launch each); the lanes
                                of a wave share the rest of their reads in
                                flight either way.  0 = the library's default
-                               (16384), -1 = no splitting, else 16 .. 2^24.
+                               (16384; batches whose max_len is 200 or
+                               more drop to 256 once half of the first
+                               pass's waves have ended), -1 = no splitting,
+                               else 16 .. 2^24.
                                A tuning knob: results do not depend on it. */
 } bwfm_aln_params;
 
@@ -323,11 +332,12 @@ int bwfm_align_batch(const bwfm_index *idx, const bwfm_reads *reads, const bwfm_
                      bwfm_aln_result *res, void *hip_stream);
 
 /* As bwfm_align_batch, also writing each read's search work -- the number
- * of search states expanded (each expansion issues the two rank queries at
- * k and l + 1), summed over both passes -- to expand (device, n_reads).
+ * of search states expanded (a state counts once, whether its children come
+ * from rank queries at k and l + 1, a table or the text, and whether it is
+ * taken by itself or in a run), summed over both passes -- to expand (device, n_reads).
  * work (device, 14 uint64, or NULL; batched form only) receives the first
  * pass's loop iterations summed over waves, lane iterations spent on a read,
- * and lane iterations that issued a rank query, then the reads whose search
+ * and lane iterations that took a search step, then the reads whose search
  * was split, the tasks handed out over all rounds, the split reads that went
  * on to the second pass, and for each of the eight task generations (the
  * first pass's, then each round's but the last) the task entries asked for

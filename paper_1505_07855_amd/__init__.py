@@ -314,8 +314,9 @@ class Index:
         return self
 
     def kmer_table(self, levels: int = -1, stream=None) -> "Index":
-        """(Re)build the device short-string interval table with `levels`
-        levels (0 releases it)."""
+        """(Re)build the caller's device short-string interval table with
+        `levels` levels (0 releases it); the search has its own, made by
+        upload and build_device."""
         _check(lib().bwfm_index_kmer_table(self._h, levels, _stream_ptr(stream)))
         return self
 

@@ -11,16 +11,22 @@
 // 128 bytes): four uint32 counts of A, C, G, T before the line ($ counted as
 // A), then the line's BWT rows as bit planes -- per 32 rows a word of the
 // codes' high bits and a word of their low bits -- so one rank query is one
-// line fetch plus three popcounts per 32 rows.  Row-sampled suffix array values
-// serve locate.
+// line fetch plus three popcounts per 32 rows.  Beside them, made at upload:
+// the intervals of all strings of up to K bases, and the whole suffix array
+// and its inverse; with the packed reference they let a search take the
+// shallow part of its tree from one table entry a state, and the part below a
+// string that occurs once from the text (build_search_tables).  Row-sampled
+// suffix array values serve locate where these do not fit.
 //
 // Search.  One lane per read, both strands in turn, each strand 5' end
 // first (strand +: reverse(read) on the index of reverse(T); strand -:
-// revcomp(read) on the index of T).  Per strand the lane first builds the
-// D-array lower bound on the other index, then runs a depth-first search
+// revcomp(read) on the index of T).  Per strand the D-array lower bound is
+// built on the other index, then a depth-first search runs
 // whose current state lives in registers; the first surviving child becomes
 // the next current state and its siblings go to a lane-private stack in
-// device memory, so the common one-child step touches no stack.  Children are
+// device memory, so the common one-child step touches no stack; a shallow
+// state's siblings are one entry there, and a run of exact matches is one
+// step.  Children are
 // taken in a fixed order (match, mismatches by base, insertion, deletions by
 // base), and in BEST mode a state is dropped when its score plus the least
 // cost of its remaining D[i] differences exceeds best + s_mm.  Distinct hits
@@ -46,7 +52,8 @@ namespace {
 
 // 16- and 8-byte words as native vectors: a search state then lives in
 // registers (HIP's vector classes kept the current state of the batched
-// kernel in scratch memory, a store and a load every iteration).
+// kernel in scratch memory, a store and a load every iteration: with these
+// and as_global below 2M reads of 100 bases went from 99 to 77 ms).
 typedef uint32_t u4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ u4 mk4(uint32_t x, uint32_t y, uint32_t z, uint32_t w) { return u4{x, y, z, w}; }
@@ -2183,10 +2190,15 @@ __device__ __forceinline__ void persistent_body(const DevIndex &ix, const Params
 }
 
 // Two builds of the batched kernel: the compiler's own register budget
-// (about 144 VGPRs: 3 waves per SIMD) and one held to 128 VGPRs so that 4
-// waves stay resident per SIMD.  The search is latency-bound, so the second
-// is faster on the benchmark batch (122 ms against 134); a build held to 96
-// VGPRs spills to scratch and is slower still (205 ms).  The autotuner picks.
+// and one held to 128 VGPRs so that 4 waves stay resident per SIMD.  What
+// bounds the search is how many random 128-byte fills are in flight, and
+// the waves are what keeps them there: 2M reads of 100 bases on 100 Mbp take
+// 57 ms at 4 waves per SIMD, 65 at 3, 82 at 2 and 139 at 1.  A wave
+// then waits in each iteration for the slowest of 64 lanes' chains of one to
+// three dependent loads.  At 4 waves the device fills 36 G lines/s out of
+// tables, suffix arrays and stacks that together span gigabytes (the probe
+// of independent random lines: 57 G/s at 256 MB, 48 at 4 GB, 38 at 16 GB).
+// The autotuner picks.
 template <int LW>
 __global__ __launch_bounds__(BLOCK) void k_align_persistent(DevIndex ix, Params P, const PersistentArgs *A) {
     persistent_body<LW>(ix, P, A);
