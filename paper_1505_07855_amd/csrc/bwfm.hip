@@ -2240,7 +2240,13 @@ __global__ void k_set_task_args(TaskArgs *dst, TaskArgs a) {
 // them over the grid; the last round has no drain.  At a task's end its
 // hits go to the slot.
 constexpr uint32_t DRAIN_MIN = 256;
-constexpr int TASK_REFILL = 32;  // idle lanes of a wave that make it take new tasks
+// Idle lanes of a wave that make it take new tasks: few while a round holds
+// TASK_MANY and more tasks for each lane of its grid, when the idle lanes cost
+// most (2M reads of 250 bases at 10 / 32: 377 / 397 ms at the default split
+// budget, 294 / 331 at 512), else half, so that a short round's tasks do not
+// end up on few waves (150 k reads: 57 / 52 ms)
+constexpr int TASK_REFILL_MANY = 10, TASK_REFILL = 32;
+constexpr uint32_t TASK_MANY = 8;
 template <int LW>
 __global__ __launch_bounds__(BLOCK) void k_align_tasks(DevIndex ix, Params P, const TaskArgs *Aarg, uint32_t g,
                                                        uint32_t drain) {
@@ -2250,6 +2256,7 @@ __global__ __launch_bounds__(BLOCK) void k_align_tasks(DevIndex ix, Params P, co
     const uint32_t ntask = min(ld_agent(&A->X.ctl[1 + g]), A->X.task_cap);
     if (ntask == 0) return;  // the whole grid: nothing was split
     const int lane = threadIdx.x & 63;
+    const int refill = ntask / TASK_MANY >= gridDim.x * BLOCK ? TASK_REFILL_MANY : TASK_REFILL;
     LaneCtx c;
     init_ctx(c, A->B, blockIdx.x * blockDim.x + threadIdx.x);
     c.sstride = 1;
@@ -2277,12 +2284,12 @@ __global__ __launch_bounds__(BLOCK) void k_align_tasks(DevIndex ix, Params P, co
             if (sb < c.best) c.best = sb;
         }
         // idle lanes take the next tasks, one atomic per wave, once
-        // TASK_REFILL lanes of the wave are idle (or none is busy): tasks
+        // `refill` lanes of the wave are idle (or none is busy): tasks
         // end every few hundred expansions, and one counter taken by every
         // wave at that rate held the rounds to half their speed
         const bool idle = !busy && !exhausted;
         const unsigned long long im = __ballot(idle);
-        const bool bulk = __popcll(im) >= TASK_REFILL || __ballot(busy) == 0;
+        const bool bulk = __popcll(im) >= refill || __ballot(busy) == 0;
         const bool want = idle && bulk;
         const unsigned long long wm = bulk ? im : 0ull;
         uint32_t t = 0;
