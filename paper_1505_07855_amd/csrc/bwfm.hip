@@ -2635,10 +2635,13 @@ __global__ __launch_bounds__(256) void k_loc_wide(DevIndex ix, const u4 *hits, c
 }
 
 // sort each hit's positions: short segments by one lane, long ones by a
-// workgroup running a bitonic network (pairs past the end count as +inf)
+// workgroup running a bitonic network (pairs past the end count as +inf).
+// A total of 0 means that the positions do not fit, as above: poff then
+// reaches past pos, and nothing is sorted (n_big stays 0).
 __global__ void k_sort_small(uint64_t n_hits, const uint64_t *poff, uint32_t *pos, uint32_t *big, uint32_t *n_big,
-                             const uint64_t *n_dev) {
+                             const uint64_t *n_dev, const uint64_t *total_dev) {
     uint64_t h = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (total_dev && *total_dev == 0) return;
     if (h >= count_of(n_hits, n_dev)) return;
     uint64_t o = poff[h], w = poff[h + 1] - o;
     if (w <= 1) return;
@@ -3462,7 +3465,8 @@ int locate_rows(const bwfm_index *ix, uint64_t n_hits, const u4 *hits, const uin
     tm.end(t);
     if (rc) return rc;
     t = tm.begin("sort");
-    k_sort_small<<<blocks(n_hits, 256), 256, 0, st>>>(n_hits, pos_off, pos, big, n_big, nullptr);
+    k_sort_small<<<blocks(n_hits, 256), 256, 0, st>>>(n_hits, pos_off, pos, big, n_big, nullptr,
+                                                    nullptr);
     k_sort_big<<<1024, 256, 0, st>>>(pos_off, pos, big, n_big);
     tm.end(t);
     HIPCHK(hipGetLastError());
@@ -4126,7 +4130,8 @@ int pipe_enqueue(bwfm_pipeline *pl, hipStream_t st, bool timed, bool capture) {
     rc = locate_fill<LW>(D, hcap, pl->hits, pl->poff, pl->q.pos_capacity, pl->pos, pl->big, n_big, ctl + PC_HITS,
                          ctl + PC_POS, st);
     if (rc) return rc;
-    k_sort_small<<<blocks(hcap, 256), 256, 0, st>>>(hcap, pl->poff, pl->pos, pl->big, n_big, ctl + PC_HITS);
+    k_sort_small<<<blocks(hcap, 256), 256, 0, st>>>(hcap, pl->poff, pl->pos, pl->big, n_big, ctl + PC_HITS,
+                                                  ctl + PC_POS);
     k_sort_big<<<1024, 256, 0, st>>>(pl->poff, pl->pos, pl->big, n_big);
     EndView e1{pl->hoff, pl->hits, pl->poff, pl->pos, 0};
     EndView e2{pl->hoff, pl->hits, pl->poff, pl->pos, 0};  // offsets moved by n on the device
