@@ -2735,11 +2735,12 @@ __device__ bool se_primary(const EndView &e, uint32_t q, uint32_t &pos, u4 &hit,
 
 // One lane per pair.  With n_dev, the pair count is read on the device and
 // end 2's reads follow end 1's in one batch (its offsets start at
-// e1.hoff + n); a nonzero *err (an output was too small) writes nothing.
+// e1.hoff + n); a nonzero *err (an output was too small) makes every record
+// that of an unplaced pair, which mate rescue and MAPQ launched after it
+// leave alone (the hit offsets may then reach past the hits).
 __global__ void k_pair(uint32_t n_pairs, EndView e1, EndView e2, int paired, int32_t lo, int32_t hi, int32_t mu,
                        bwfm_pair *out, const uint64_t *n_dev, const uint32_t *err) {
     uint32_t q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (err && *err) return;
     if (n_dev) {
         n_pairs = (uint32_t)count_of(n_pairs, n_dev);
         e2.hoff = e1.hoff + n_pairs;
@@ -2748,6 +2749,10 @@ __global__ void k_pair(uint32_t n_pairs, EndView e1, EndView e2, int paired, int
     bwfm_pair o;
     memset(&o, 0, sizeof(o));
     o.pos1 = o.pos2 = 0xffffffffu;
+    if (err && *err) {
+        out[q] = o;
+        return;
+    }
     bool found = false;
     int64_t bs = 0, bd = 0, bpf = 0;
     if (paired) {

@@ -1,6 +1,7 @@
 """A captured step whose hits or positions outgrow their capacities by far:
-nothing past the arrays is touched, the need is reported, and the next batch
-that fits equals the oracle's."""
+nothing past the arrays is touched, the need is reported, every pair record
+is an unplaced pair's (so that rescue and MAPQ enqueued behind the step leave
+it alone), and the next batch that fits equals the oracle's."""
 from __future__ import annotations
 
 import numpy as np
@@ -64,16 +65,23 @@ def test_step_over_its_capacities(setup, short, graph):
     p = bw.Params(max_diff=2)
     caps = dict(pos_capacity=2_000) if short == "positions" else dict(hit_capacity=8)
     pl = bw.Pipeline(ix, p, LO, HI, MU, MAX_OCC, max_pairs=N, max_len=L, **caps)
+    ends = [(runs["wide"]["b"][e * N * L:(e + 1) * N * L].contiguous(), runs["wide"]["o"][:N + 1]) for e in (0, 1)]
     for _ in range(2):
         w = runs["wide"]
         pl.set_reads(w["b"], w["o"], N, max_len=L)
         pl.run(graph=graph)
+        r1, r2, prs, _, _ = pl.results()
+        resc = bw.rescue_mates(ix, ends[0], ends[1], prs, LO, HI, max_len=L)
+        q = bw.mapq(r1, r2, prs, rescue=resc, max_diff=2).cpu().numpy()
         st = pl.finish()
         if short == "positions":
             assert st["error"] == bw.PIPE_E_POSITIONS
             assert (st["n_hits"], st["n_positions"]) == (w["hits"], w["pos"])
         else:
             assert st["error"] & bw.PIPE_E_HITS and st["n_hits"] == w["hits"]
+        got = bw.pairs_numpy(prs)[:N]
+        assert (got["flags"] == 0).all() and (got["pos1"] == 0xFFFFFFFF).all() and (got["pos2"] == 0xFFFFFFFF).all()
+        assert not bw.rescue_numpy(resc)[:N].view(np.uint8).any() and not q.any()
         if short == "positions":  # a batch that fits
             s = runs["single"]
             pl.set_reads(s["b"], s["o"], N, max_len=L)
@@ -90,7 +98,7 @@ def test_served_steps_over_their_capacities(setup):
     text, runs = setup
     ix = bw.Index(text, line_bytes=64).upload()
     srv = bw.Server(ix, bw.Params(max_diff=2), LO, HI, MU, MAX_OCC, arena_bytes=4 << 20, step_pairs=64, max_len=L,
-                    budget_rule=False)
+                    budget_rule=False, rescue_mapq=True)
     tickets = []
     for name in ("wide", "single", "wide"):
         b, o = runs[name]["host"]
