@@ -3595,15 +3595,15 @@ extern "C" int bwfm_index_kmer_table(bwfm_index *ix, int levels, void *stream) {
     ix->device_bytes -= 2 * kt_bytes(ix->kt_levels);
     ix->kt_levels = 0;
     for (int d = 0; d < 2; d++) {
-        if (ix->d_kt[d]) (void)hipFree(ix->d_kt[d]);
+        dev_free(ix->d_kt[d]);
         ix->d_kt[d] = nullptr;
     }
     if (levels == 0) return BWFM_OK;
     const uint64_t bytes = kt_bytes((uint32_t)levels);
     for (int d = 0; d < 2; d++)
-        if (hipMalloc(&ix->d_kt[d], bytes) != hipSuccess) {
+        if (dev_malloc(&ix->d_kt[d], bytes) != hipSuccess) {
             for (int e = 0; e < 2; e++) {
-                if (ix->d_kt[e]) (void)hipFree(ix->d_kt[e]);
+                dev_free(ix->d_kt[e]);
                 ix->d_kt[e] = nullptr;
             }
             (void)hipGetLastError();
@@ -3635,7 +3635,7 @@ extern "C" void bwfm_index_free(bwfm_index *ix) {
     for (int d = 0; d < 2; d++) {
         dev_free(ix->d_lines[d]);
         dev_free(ix->d_sa[d]);
-        if (ix->d_kt[d]) (void)hipFree(ix->d_kt[d]);
+        dev_free(ix->d_kt[d]);
     }
     free_search_tables(ix);
     dev_free(ix->d_pac);
@@ -4224,7 +4224,7 @@ extern "C" int bwfm_pipeline_create(const bwfm_index *cix, const bwfm_aln_params
     const SplitShape zs = split_shape(nmax, mlen);
     if (sbud) need += split_bytes(zs) + (size_t)pl->lanes * 4 + 256;
     need += 4096;
-    if (hipMalloc(&pl->mem, need) != hipSuccess) return fail(BWFM_E_NOMEM, "pipeline: device allocation failed");
+    if (dev_malloc(&pl->mem, need) != hipSuccess) return fail(BWFM_E_NOMEM, "pipeline: device allocation failed");
     Carver cv{(char *)pl->mem};
     pl->bases = cv.take<uint8_t>(q->max_bases);
     pl->offsets = cv.take<uint64_t>(nmax + 1);
@@ -4429,7 +4429,7 @@ extern "C" void bwfm_pipeline_destroy(bwfm_pipeline *pl) {
     for (auto &e : pl->ev)
         if (e) (void)hipEventDestroy(e);
     if (pl->cap) (void)hipStreamDestroy(pl->cap);
-    if (pl->mem) (void)hipFree(pl->mem);
+    dev_free(pl->mem);
     delete pl;
 }
 

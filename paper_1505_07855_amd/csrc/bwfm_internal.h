@@ -89,12 +89,18 @@ void pack_ref(const uint8_t *text, uint64_t n, std::vector<uint32_t> &out);
 int build_search_tables(bwfm_index *ix, ihipStream_t *st);
 void free_search_tables(bwfm_index *ix);
 
-// Device blocks through the library's bounded pool (index_gpu.hip): as
+// The library's device memory, through its bounded pool (devpool.cpp): as
 // hipMalloc (its error code, 0 = success) and hipFree on the current device.
 // dev_cached: bytes held.
 int dev_malloc(void **out, size_t bytes);
 void dev_free(void *p);
 size_t dev_cached();
+template <class T> int dev_malloc(T **out, size_t bytes) {
+    void *p = nullptr;
+    const int e = dev_malloc(&p, bytes);
+    *out = static_cast<T *>(p);
+    return e;
+}
 
 }  // namespace bwfm
 

@@ -15,133 +15,14 @@
 
 #include <algorithm>
 #include <cstring>
-#include <deque>
 #include <memory>
 #include <rocprim/rocprim.hpp>
 #include <string>
-#include <unordered_map>
 #include <vector>
 
 #include "bwfm_internal.h"
 
 using namespace bwfm;
-
-// ------------------------------------------------------------------ device blocks
-
-namespace {
-
-// Device blocks that indexes, their workspaces and index builds give back are
-// kept for the next ones: giving memory back to the driver and taking it
-// again costs up to 28 ms per GB once it has to be cleared (a 16 Mbp
-// reference indexed and a first batch aligned, over and over: 31 ms a pass
-// with 288 GB of fresh memory ahead, 60-150 ms after that).  At most
-// POOL_BYTES are held, the oldest block goes first, and an allocation that
-// fails gives every held block back and tries again.
-constexpr size_t POOL_BYTES = (size_t)8 << 30;
-constexpr size_t POOL_MIN = (size_t)1 << 20;  // smaller blocks are not held
-
-struct DevPool {
-    struct Block {
-        void *p;
-        size_t bytes;
-        int dev;
-    };
-    std::mutex mu;
-    std::unordered_map<void *, Block> live;  // blocks handed out (of POOL_MIN and more)
-    std::deque<Block> held;                  // blocks given back, oldest first
-    size_t held_bytes = 0;
-};
-DevPool &pool() {
-    static DevPool *p = new DevPool;  // never destroyed: the runtime may be gone at exit
-    return *p;
-}
-
-}  // namespace
-
-int bwfm::dev_malloc(void **out, size_t bytes) {
-    *out = nullptr;
-    if (bytes < POOL_MIN) return hipMalloc(out, bytes);
-    int dev = 0;
-    if (hipError_t e = hipGetDevice(&dev)) return e;
-    DevPool &P = pool();
-    const size_t want = (bytes + ((size_t)2 << 20) - 1) & ~(((size_t)2 << 20) - 1);
-    std::vector<void *> drop;
-    {
-        // the smallest held block that fits and wastes at most a quarter
-        std::lock_guard<std::mutex> g(P.mu);
-        size_t best = P.held.size();
-        for (size_t i = 0; i < P.held.size(); i++) {
-            const auto &b = P.held[i];
-            if (b.dev == dev && b.bytes >= want && b.bytes - want <= want / 4 &&
-                (best == P.held.size() || b.bytes < P.held[best].bytes))
-                best = i;
-        }
-        if (best < P.held.size()) {
-            const auto b = P.held[best];
-            P.held.erase(P.held.begin() + (ptrdiff_t)best);
-            P.held_bytes -= b.bytes;
-            P.live[b.p] = b;
-            *out = b.p;
-            return hipSuccess;
-        }
-    }
-    hipError_t e = hipMalloc(out, want);
-    if (e != hipSuccess) {
-        (void)hipGetLastError();
-        {
-            std::lock_guard<std::mutex> g(P.mu);
-            for (const auto &b : P.held) drop.push_back(b.p);
-            P.held.clear();
-            P.held_bytes = 0;
-        }
-        if (drop.empty()) return e;
-        for (void *p : drop) (void)hipFree(p);
-        e = hipMalloc(out, want);
-        if (e != hipSuccess) return e;
-    }
-    std::lock_guard<std::mutex> g(P.mu);
-    P.live[*out] = DevPool::Block{*out, want, dev};
-    return hipSuccess;
-}
-
-// Waits for the device's work, as hipFree does, before the block may be
-// handed out again.
-void bwfm::dev_free(void *p) {
-    if (!p) return;
-    DevPool &P = pool();
-    DevPool::Block b{};
-    {
-        std::lock_guard<std::mutex> g(P.mu);
-        auto it = P.live.find(p);
-        if (it != P.live.end()) {
-            b = it->second;
-            P.live.erase(it);
-        }
-    }
-    int dev = -1;
-    if (!b.p || b.bytes > POOL_BYTES / 2 || hipGetDevice(&dev) != hipSuccess || dev != b.dev ||
-        hipDeviceSynchronize() != hipSuccess) {
-        (void)hipFree(p);
-        return;
-    }
-    std::vector<void *> drop;
-    {
-        std::lock_guard<std::mutex> g(P.mu);
-        P.held.push_back(b);
-        P.held_bytes += b.bytes;
-        while (P.held_bytes > POOL_BYTES) {
-            drop.push_back(P.held.front().p);
-            P.held_bytes -= P.held.front().bytes;
-            P.held.pop_front();
-        }
-    }
-    for (void *q : drop) (void)hipFree(q);
-}
-
-size_t bwfm::dev_cached() {
-    std::lock_guard<std::mutex> g(pool().mu);
-    return pool().held_bytes;
-}
 
 namespace {
 

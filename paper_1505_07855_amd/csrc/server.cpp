@@ -185,7 +185,7 @@ void release_slot(StepSlot &k) {
     void *ptrs[] = {k.d_off, k.d_len, k.d_md, k.d_hoff, k.d_hits, k.d_c1, k.d_c2, k.d_status, k.d_pairs, k.d_resc,
                     k.d_mapq};
     for (void *p : ptrs)
-        if (p) (void)hipFree(p);
+        dev_free(p);
     void *hptrs[] = {k.h_off, k.h_len, k.h_md, k.h_pairs, k.h_resc, k.h_mapq};
     for (void *p : hptrs)
         if (p) (void)hipHostFree(p);
@@ -196,7 +196,7 @@ void release_slot(StepSlot &k) {
 
 void release_device(bwfm_server *s) {
     for (auto &k : s->slot) release_slot(k);
-    if (s->arena_mem) (void)hipFree(s->arena_mem);
+    dev_free(s->arena_mem);
     s->arena_mem = nullptr;
 }
 
@@ -208,13 +208,13 @@ int make_slot(bwfm_server *s, StepSlot &k) {
     if (hipStreamCreateWithFlags(&k.stream, hipStreamNonBlocking) != hipSuccess ||
         hipEventCreateWithFlags(&k.done, hipEventDisableTiming) != hipSuccess)
         return fail(BWFM_E_DEVICE, "server_create: stream or event creation failed");
-    if (hipMalloc(&k.d_off, 8 * R) != hipSuccess || hipMalloc(&k.d_len, 4 * R) != hipSuccess ||
-        hipMalloc(&k.d_md, R) != hipSuccess || hipMalloc(&k.d_hoff, 8 * (R + 1)) != hipSuccess ||
-        hipMalloc(&k.d_hits, 16 * k.hit_cap) != hipSuccess || hipMalloc(&k.d_c1, 4 * R) != hipSuccess ||
-        hipMalloc(&k.d_c2, 4 * R) != hipSuccess || hipMalloc(&k.d_status, R) != hipSuccess ||
-        hipMalloc(&k.d_pairs, sizeof(bwfm_pair) * SP) != hipSuccess ||
-        (s->sp.rescue_mapq && (hipMalloc(&k.d_resc, sizeof(bwfm_rescue) * SP) != hipSuccess ||
-                               hipMalloc(&k.d_mapq, 2 * SP) != hipSuccess)))
+    if (dev_malloc(&k.d_off, 8 * R) != hipSuccess || dev_malloc(&k.d_len, 4 * R) != hipSuccess ||
+        dev_malloc(&k.d_md, R) != hipSuccess || dev_malloc(&k.d_hoff, 8 * (R + 1)) != hipSuccess ||
+        dev_malloc(&k.d_hits, 16 * k.hit_cap) != hipSuccess || dev_malloc(&k.d_c1, 4 * R) != hipSuccess ||
+        dev_malloc(&k.d_c2, 4 * R) != hipSuccess || dev_malloc(&k.d_status, R) != hipSuccess ||
+        dev_malloc(&k.d_pairs, sizeof(bwfm_pair) * SP) != hipSuccess ||
+        (s->sp.rescue_mapq && (dev_malloc(&k.d_resc, sizeof(bwfm_rescue) * SP) != hipSuccess ||
+                               dev_malloc(&k.d_mapq, 2 * SP) != hipSuccess)))
         return fail(BWFM_E_NOMEM, "server_create: device allocation failed");
     if (hipHostMalloc(&k.h_off, 8 * R) != hipSuccess || hipHostMalloc(&k.h_len, 4 * R) != hipSuccess ||
         hipHostMalloc(&k.h_md, R) != hipSuccess || hipHostMalloc(&k.h_pairs, sizeof(bwfm_pair) * SP) != hipSuccess ||
@@ -283,10 +283,10 @@ int run_step_eager(bwfm_server *s, StepSlot &k) {
         uint64_t need = 0;
         if (hipMemcpy(&need, k.d_hoff + n, 8, hipMemcpyDeviceToHost) != hipSuccess)
             return fail(BWFM_E_DEVICE, "server: reading hit need failed");
-        (void)hipFree(k.d_hits);
+        dev_free(k.d_hits);
         k.d_hits = nullptr;
         k.hit_cap = need + need / 4 + 1024;
-        if (hipMalloc(&k.d_hits, k.hit_cap * 16) != hipSuccess) return fail(BWFM_E_NOMEM, "server: hit buffer");
+        if (dev_malloc(&k.d_hits, k.hit_cap * 16) != hipSuccess) return fail(BWFM_E_NOMEM, "server: hit buffer");
         res.hits = reinterpret_cast<bwfm_hit *>(k.d_hits);
         res.hit_capacity = k.hit_cap;
         rc = bwfm_align_batch(s->ix, &rd, &s->ap, &res, k.stream);
@@ -525,7 +525,7 @@ extern "C" int bwfm_server_create(const bwfm_index *ix, const bwfm_aln_params *a
     for (uint32_t L = 0; L <= BWFM_MAX_READ; L++)
         s->rule[L] = (uint8_t)std::min(bwfm_max_diff_rule(L, 0.02, 0.04), BWFM_MAX_DIFF);
     if (hipSetDevice(s->device) != hipSuccess) return fail(BWFM_E_DEVICE, "server_create: device not available");
-    if (hipMalloc(&s->arena_mem, sp->arena_bytes) != hipSuccess) {
+    if (dev_malloc(&s->arena_mem, sp->arena_bytes) != hipSuccess) {
         s->arena_mem = nullptr;
         return fail(BWFM_E_NOMEM, "server_create: arena allocation failed");
     }

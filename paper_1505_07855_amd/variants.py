@@ -97,7 +97,7 @@ def build_one(defs: dict) -> str:
     obj = os.path.join(d, "bwfm.o")
     flags = [f"-D{k}={v}" for k, v in sorted(defs.items())]
     B._run([B.HIPCC, *B.HIP_FLAGS, *flags, "-c", os.path.join(B.CSRC, "bwfm.hip"), "-o", obj])
-    others = [os.path.join(B.OUT, f) for f in ("index_host.o", "index_gpu.o", "rescue.o", "mapq.o", "server.o")]
+    others = [os.path.join(B.OUT, f) for f in ("index_host.o", "index_gpu.o", "rescue.o", "mapq.o", "server.o", "devpool.o")]
     missing = [f for f in others if not os.path.exists(f)]
     if missing:
         raise RuntimeError(f"build the library first (missing {missing})")
