@@ -91,7 +91,7 @@ void free_search_tables(bwfm_index *ix);
 
 // The library's device memory, through its bounded pool (devpool.cpp): as
 // hipMalloc (its error code, 0 = success) and hipFree on the current device.
-// dev_cached: bytes held.
+// dev_cached: bytes held of the current device.
 int dev_malloc(void **out, size_t bytes);
 void dev_free(void *p);
 size_t dev_cached();

@@ -5,9 +5,9 @@
 // ones: giving memory back to the driver and taking it again costs up to
 // 28 ms per GB once it has to be cleared (a 16 Mbp reference indexed and a
 // first batch aligned, over and over: 31 ms a pass with 288 GB of fresh memory
-// ahead, 60-150 ms after that).  At most POOL_BYTES are held, the oldest
-// block goes first, and any allocation that fails, of whatever size,
-// gives every held block back and tries again.
+// ahead, 60-150 ms after that).  At most POOL_BYTES a device are held, the
+// oldest block goes first, and any allocation that fails, of whatever size,
+// gives the device's held blocks back and tries again.
 
 #include <hip/hip_runtime_api.h>
 
@@ -34,17 +34,20 @@ struct DevPool {
     std::mutex mu;
     std::unordered_map<void *, Block> live;  // blocks handed out (of POOL_MIN and more)
     std::deque<Block> held;                  // blocks given back, oldest first
-    size_t bytes() const {
+    size_t bytes_of(int dev) const {
         size_t n = 0;
-        for (const auto &b : held) n += b.bytes;
+        for (const auto &b : held) n += b.dev == dev ? b.bytes : 0;
         return n;
     }
-    // take the oldest held block
-    bool pop(Block &out) {
-        if (held.empty()) return false;
-        out = held.front();
-        held.pop_front();
-        return true;
+    // take the oldest held block of dev
+    bool pop(int dev, Block &out) {
+        for (auto it = held.begin(); it != held.end(); ++it)
+            if (it->dev == dev) {
+                out = *it;
+                held.erase(it);
+                return true;
+            }
+        return false;
     }
 };
 DevPool &pool() {
@@ -52,15 +55,15 @@ DevPool &pool() {
     return *p;
 }
 
-// Give the held blocks back to the driver.
-bool give_back() {
+// Give the held blocks of dev back to the driver.
+bool give_back(int dev) {
     DevPool &P = pool();
     bool any = false;
     for (;;) {
         Block b;
         {
             std::lock_guard<std::mutex> g(P.mu);
-            if (!P.pop(b)) return any;
+            if (!P.pop(dev, b)) return any;
         }
         (void)hipFree(b.p);
         any = true;
@@ -68,11 +71,11 @@ bool give_back() {
 }
 
 // hipMalloc, once more without the held blocks when it fails
-hipError_t take(void **out, size_t bytes) {
+hipError_t take(void **out, size_t bytes, int dev) {
     hipError_t e = hipMalloc(out, bytes);
     if (e == hipSuccess) return e;
     (void)hipGetLastError();
-    if (!give_back()) return e;
+    if (!give_back(dev)) return e;
     e = hipMalloc(out, bytes);
     if (e != hipSuccess) (void)hipGetLastError();
     return e;
@@ -84,7 +87,7 @@ int bwfm::dev_malloc(void **out, size_t bytes) {
     *out = nullptr;
     int dev = 0;
     if (hipError_t e = hipGetDevice(&dev)) return e;
-    if (bytes < POOL_MIN) return take(out, bytes);
+    if (bytes < POOL_MIN) return take(out, bytes, dev);
     DevPool &P = pool();
     const size_t want = (bytes + POOL_STEP - 1) / POOL_STEP * POOL_STEP;
     try {
@@ -107,7 +110,7 @@ int bwfm::dev_malloc(void **out, size_t bytes) {
     } catch (const std::bad_alloc &) {
         return hipErrorOutOfMemory;
     }
-    if (hipError_t e = take(out, want)) {
+    if (hipError_t e = take(out, want, dev)) {
         *out = nullptr;
         return e;
     }
@@ -151,13 +154,15 @@ void bwfm::dev_free(void *p) {
         Block old;
         {
             std::lock_guard<std::mutex> g(P.mu);
-            if (P.bytes() <= POOL_BYTES || !P.pop(old)) return;
+            if (P.bytes_of(dev) <= POOL_BYTES || !P.pop(dev, old)) return;
         }
         (void)hipFree(old.p);
     }
 }
 
 size_t bwfm::dev_cached() {
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess) return 0;
     std::lock_guard<std::mutex> g(pool().mu);
-    return pool().bytes();
+    return pool().bytes_of(dev);
 }

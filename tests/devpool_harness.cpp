@@ -72,6 +72,19 @@ int main() {
     bwfm::dev_free(big);
     bwfm::dev_free(d);
     check(used(0) == 0, "blocks of more than half the bound and small ones are not held");
+
+    // devices are counted apart
+    void *e = get(4 * GB), *f = get(4 * GB);
+    bwfm::dev_free(e);
+    bwfm::dev_free(f);
+    cur = 1;
+    check(bwfm::dev_cached() == 0, "another device's held blocks are not this one's");
+    void *g = get(3 * GB);
+    bwfm::dev_free(g);
+    check(used(0) == 8 * GB && used(1) == 3 * GB, "the bound is a device's own");
+    check(get(18 * GB) && used(0) == 8 * GB && used(1) == 18 * GB, "a failing device has its own blocks back");
+    cur = 0;
+    check(bwfm::dev_cached() == 8 * GB, "the first device still holds its blocks");
     std::printf("all checks passed\n");
     return 0;
 }
