@@ -27,10 +27,11 @@
  *  - The caller owns every buffer it passes in.  The library owns the
  *    index (host and device copies) and, per index, one grow-only device
  *    workspace for each stream it has been called on, all released by
- *    bwfm_index_free.  Device blocks of 1 MB and more that indexes, their
- *    workspaces and builds release stay with the process, at most 8 GB a
- *    device, for the next ones, and go back to the driver when an allocation
- *    of the library fails without them.
+ *    bwfm_index_free.  Device blocks of 1 MB to 4 GB that indexes, their
+ *    workspaces, builds, captured steps and servers release stay with the
+ *    process, at most 8 GB a device, for the next ones; they go back to the
+ *    driver when an allocation of the library fails without them, and with
+ *    bwfm_release_cached.
  *  - Concurrency.  The index is read-only after upload: bwfm_align_batch,
  *    bwfm_locate and bwfm_pair_reads calls on different streams may run at
  *    the same time from different host threads, and their kernels overlap
@@ -170,6 +171,12 @@ int bwfm_index_kmer_get(const bwfm_index *idx, int which, int level, uint64_t fi
 
 /* Release host and device memory of the index and its workspace. */
 void bwfm_index_free(bwfm_index *idx);
+
+/* Give the device blocks that the library holds for later use (see the
+ * conventions above) back to the driver, on every device: for a caller whose
+ * own allocator needs the memory, and before hipDeviceReset, which would
+ * leave the library holding blocks that are gone.  Returns BWFM_OK. */
+int bwfm_release_cached(void);
 
 /* Write the host part of an index to path (created or truncated): a
  * little-endian header (magic, version 2, layout, n), then per direction C,

@@ -123,7 +123,7 @@ SYMBOLS = ("bwfm_build_index", "bwfm_index_upload", "bwfm_index_free", "bwfm_ind
            "bwfm_pipeline_set_reads", "bwfm_pipeline_run", "bwfm_pipeline_finish", "bwfm_pipeline_outputs",
            "bwfm_pipeline_destroy", "bwfm_pipeline_bind_reads", "bwfm_pipeline_set_count",
            "bwfm_build_index_device", "bwfm_index_get_ref", "bwfm_rescue_mates", "bwfm_mapq",
-           "bwfm_index_kmer_table", "bwfm_index_kmer_get")
+           "bwfm_index_kmer_table", "bwfm_index_kmer_get", "bwfm_release_cached")
 
 
 def lib():
@@ -169,6 +169,7 @@ def lib():
             "bwfm_last_error": ([], ctypes.c_char_p),
             "bwfm_timing_enable": ([c_int], c_int),
             "bwfm_timing_reset": ([], c_int),
+            "bwfm_release_cached": ([], c_int),
             "bwfm_timing_get": ([ctypes.c_char_p, P, P], c_int),
             "bwfm_probe_gather": ([P, u64, u32, u32, u32, P, P, P], c_int),
             "bwfm_server_create": ([P, P, P, P, ctypes.POINTER(P)], c_int),
@@ -547,6 +548,12 @@ def rescue_numpy(t) -> np.ndarray:
 
 def pairs_numpy(t) -> np.ndarray:
     return t.cpu().numpy().view(PAIR_DTYPE).reshape(-1)
+
+
+def release_cached():
+    """Give the device blocks the library holds for later use back to the
+    driver (bwfm_release_cached)."""
+    _check(lib().bwfm_release_cached())
 
 
 def timing_enable(on: bool = True):

@@ -39,10 +39,10 @@ struct DevPool {
         for (const auto &b : held) n += b.dev == dev ? b.bytes : 0;
         return n;
     }
-    // take the oldest held block of dev
+    // take the oldest held block of dev (dev < 0: of any device)
     bool pop(int dev, Block &out) {
         for (auto it = held.begin(); it != held.end(); ++it)
-            if (it->dev == dev) {
+            if (dev < 0 || it->dev == dev) {
                 out = *it;
                 held.erase(it);
                 return true;
@@ -55,7 +55,7 @@ DevPool &pool() {
     return *p;
 }
 
-// Give the held blocks of dev back to the driver.
+// Give the held blocks of dev (< 0: of every device) back to the driver.
 bool give_back(int dev) {
     DevPool &P = pool();
     bool any = false;
@@ -165,4 +165,9 @@ size_t bwfm::dev_cached() {
     if (hipGetDevice(&dev) != hipSuccess) return 0;
     std::lock_guard<std::mutex> g(pool().mu);
     return pool().bytes_of(dev);
+}
+
+extern "C" int bwfm_release_cached(void) {
+    give_back(-1);
+    return BWFM_OK;
 }

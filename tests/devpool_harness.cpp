@@ -85,6 +85,8 @@ int main() {
     check(get(18 * GB) && used(0) == 8 * GB && used(1) == 18 * GB, "a failing device has its own blocks back");
     cur = 0;
     check(bwfm::dev_cached() == 8 * GB, "the first device still holds its blocks");
+    // the caller may have all of them back
+    check(bwfm_release_cached() == BWFM_OK && used(0) == 0 && bwfm::dev_cached() == 0, "released");
     std::printf("all checks passed\n");
     return 0;
 }
