@@ -36,9 +36,10 @@
  *    bwfm_locate and bwfm_pair_reads calls on different streams may run at
  *    the same time from different host threads, and their kernels overlap
  *    on the device; each uses its own stream's workspace.  Calls on one
- *    stream from several threads take turns.  bwfm_index_upload and
- *    bwfm_index_kmer_table change the index and wait for the calls in
- *    flight; bwfm_index_free must not overlap any other call on the index.
+ *    stream from several threads take turns.  bwfm_index_upload,
+ *    bwfm_index_search_tables and bwfm_index_kmer_table change the index and
+ *    wait for the calls in flight; bwfm_index_free must not overlap any
+ *    other call on the index.
  *  - The three calls above block the calling thread until their own stream
  *    has finished the call's work (the number of hits decides the output
  *    size, which they check); the captured step (bwfm_pipeline_*) is the
@@ -143,6 +144,17 @@ int bwfm_build_index_device(const uint8_t *ref, uint64_t n, const bwfm_index_par
  * E_DEVICE. */
 int bwfm_index_upload(bwfm_index *idx, void *hip_stream);
 
+/* Depth of the search's tables: -1 = the rule above (the default), 0 = none
+ * of them (the search and locate then read rank lines and SA samples only, and
+ * the index takes the least memory), 1..15 = that many levels, fewer where
+ * memory is short.  Results are the same with every depth.  Before the upload
+ * it takes effect there; on an uploaded index (its device current) the tables
+ * are made anew: the call waits for the calls in flight and for the device,
+ * and captured pipeline steps are captured again on their next run.
+ * Synchronises hip_stream.  Errors: E_INVAL (NULL, levels out of range,
+ * another device), E_DEVICE (the index is left without tables). */
+int bwfm_index_search_tables(bwfm_index *idx, int levels, void *hip_stream);
+
 /* Short-string interval table for the caller's own use (it changes no
  * result; the search reads its own tables, bwfm_index_upload).  For each
  * direction and each string S
@@ -153,9 +165,8 @@ int bwfm_index_upload(bwfm_index *idx, void *hip_stream);
  * 4 + (4^d - 4) / 3 (level 0, entry 0, is the empty string's (0, n)), so
  * the four one-base extensions of a string are 32 contiguous,
  * 32-byte-aligned bytes.  Built on the device from the
- * uploaded rank lines; replaces an existing table (no call that uses the
- * index may run meanwhile; captured pipeline steps are captured again on
- * their next run).  levels: 0 releases the table, -1 picks the smallest d
+ * uploaded rank lines; replaces an existing table (it waits for the calls in
+ * flight).  levels: 0 releases the table, -1 picks the smallest d
  * with 4^d >= n (at most 14: 2.9 GB per direction), 1..15 as given (15:
  * 11.5 GB per direction).  Synchronises hip_stream.  Errors: E_INVAL
  * (NULL, not uploaded, levels out of range; the index is left as it was),
@@ -203,7 +214,7 @@ typedef struct {
     uint64_t kmer_bytes;    /* device memory of that table, both directions (each padded to 256 bytes) */
     uint64_t ws_bytes;      /* device memory of the per-stream workspaces, summed */
     uint32_t ws_streams;    /* streams that have a workspace */
-    uint32_t pad;
+    uint32_t search_levels; /* levels of the search's own interval table (0: none) */
 } bwfm_index_info;
 
 int bwfm_index_get_info(const bwfm_index *idx, bwfm_index_info *out);

@@ -57,7 +57,7 @@ class _IndexInfo(ctypes.Structure):
                 ("line_bytes", ctypes.c_uint32), ("bases_per_line", ctypes.c_uint32),
                 ("sa_sample", ctypes.c_uint32), ("uploaded", ctypes.c_uint32), ("rank_format", ctypes.c_uint32),
                 ("kmer_levels", ctypes.c_uint32), ("kmer_bytes", ctypes.c_uint64), ("ws_bytes", ctypes.c_uint64),
-                ("ws_streams", ctypes.c_uint32), ("pad", ctypes.c_uint32)]
+                ("ws_streams", ctypes.c_uint32), ("search_levels", ctypes.c_uint32)]
 
 
 class _Reads(ctypes.Structure):
@@ -123,7 +123,8 @@ SYMBOLS = ("bwfm_build_index", "bwfm_index_upload", "bwfm_index_free", "bwfm_ind
            "bwfm_pipeline_set_reads", "bwfm_pipeline_run", "bwfm_pipeline_finish", "bwfm_pipeline_outputs",
            "bwfm_pipeline_destroy", "bwfm_pipeline_bind_reads", "bwfm_pipeline_set_count",
            "bwfm_build_index_device", "bwfm_index_get_ref", "bwfm_rescue_mates", "bwfm_mapq",
-           "bwfm_index_kmer_table", "bwfm_index_kmer_get", "bwfm_release_cached")
+           "bwfm_index_kmer_table", "bwfm_index_kmer_get", "bwfm_release_cached",
+           "bwfm_index_search_tables")
 
 
 def lib():
@@ -147,6 +148,7 @@ def lib():
             "bwfm_build_index": ([P, u64, P, ctypes.POINTER(P)], c_int),
             "bwfm_index_upload": ([P, P], c_int),
             "bwfm_index_kmer_table": ([P, c_int, P], c_int),
+            "bwfm_index_search_tables": ([P, c_int, P], c_int),
             "bwfm_index_kmer_get": ([P, c_int, c_int, u64, u64, P], c_int),
             "bwfm_build_index_device": ([P, u64, P, P, ctypes.POINTER(P)], c_int),
             "bwfm_index_save": ([P, ctypes.c_char_p], c_int),
@@ -321,6 +323,13 @@ class Index:
         _check(lib().bwfm_index_kmer_table(self._h, levels, _stream_ptr(stream)))
         return self
 
+    def search_tables(self, levels: int = -1, stream=None) -> "Index":
+        """Depth of the search's own tables (bwfm_index_search_tables): -1 the
+        library's rule, 0 none, else that many levels.  Results do not depend
+        on it; before upload() it takes effect there."""
+        _check(lib().bwfm_index_search_tables(self._h, levels, _stream_ptr(stream)))
+        return self
+
     def kmer_entries(self, which: int, level: int, first: int = 0, count: int | None = None) -> np.ndarray:
         """Entries of one table level as an (count, 2) array of (k, l)."""
         if count is None:
@@ -335,7 +344,8 @@ class Index:
         return dict(n=i.n, primary=list(i.primary), C=[list(c) for c in i.C], lines=i.lines, sa_samples=i.sa_samples,
                     device_bytes=i.device_bytes, line_bytes=i.line_bytes, bases_per_line=i.bases_per_line,
                     sa_sample=i.sa_sample, uploaded=bool(i.uploaded), rank_format=i.rank_format,
-                    kmer_levels=i.kmer_levels, kmer_bytes=i.kmer_bytes, ws_bytes=i.ws_bytes, ws_streams=i.ws_streams)
+                    kmer_levels=i.kmer_levels, kmer_bytes=i.kmer_bytes, ws_bytes=i.ws_bytes, ws_streams=i.ws_streams,
+                    search_levels=i.search_levels)
 
     def bwt(self, which: int = 0) -> np.ndarray:
         out = np.empty(self.n + 1, np.uint8)

@@ -3501,27 +3501,28 @@ static void fill_table(const bwfm_index *ix, int d, uint32_t *kt, int levels, in
 }
 
 // The search's interval table, made once the rank lines are on the device.
-// Depth: the least with 4^depth >= 2 n, at most 15, so that most of the
-// deepest strings are absent or unique and a run of exact matches ends in
-// its one entry: 100 Mbp: 14 levels, 2.9 GB per direction (its iterations per
-// read: 1031, with 13 levels 1223, with 12 1421).  With it come the
-// whole suffix array and its inverse, 8 bytes a base and direction, which
-// turn rows into text positions and back.  All of it takes at most half of
-// the free memory (less deep, or not made at all, where that is short:
+// Depth, unless the caller set one: the least with 4^depth >= 2 n, at most 15,
+// so that most of the deepest strings are absent or unique and a run of exact
+// matches ends in its one entry: 100 Mbp: 14 levels, 2.9 GB per direction (its
+// iterations per read: 1031, with 13 levels 1223, with 12 1421).  With it come
+// the whole suffix array and its inverse, 8 bytes a base and direction, which
+// turn rows into text positions and back (the deepest level names unique
+// strings by position, so neither is of use alone).  All of it takes at most
+// half of the free memory (less deep, or not made at all, where that is short:
 // results do not depend on it).
 int bwfm::build_search_tables(bwfm_index *ix, hipStream_t st) {
+    if (ix->jt_want == 0 || ix->n >= SINGLE0) return BWFM_OK;
     size_t free_b = 0, total_b = 0;
     HIPCHK(hipMemGetInfo(&free_b, &total_b));
-    int levels = 1;
-    while (levels < 15 && ((uint64_t)1 << (2 * levels)) < 2 * ix->n) levels++;
     free_b += dev_cached();
-    if (ix->n >= SINGLE0) return BWFM_OK;
+    int levels = ix->jt_want > 0 ? ix->jt_want : 1;
+    if (ix->jt_want < 0)
+        while (levels < 15 && ((uint64_t)1 << (2 * levels)) < 2 * ix->n) levels++;
     while (levels > 0 && 2 * (kt_bytes((uint32_t)levels) + 2 * (ix->n + 1) * 4) > free_b / 2) levels--;
     if (levels == 0) return BWFM_OK;
     const uint64_t bytes = kt_bytes((uint32_t)levels), full = 2 * (ix->n + 1) * 4;
     for (int d = 0; d < 2; d++)
         if (dev_malloc(&ix->d_jt[d], bytes) || dev_malloc(&ix->d_full[d], full)) {
-            (void)hipGetLastError();
             free_search_tables(ix);
             return BWFM_OK;
         }
@@ -3536,20 +3537,42 @@ int bwfm::build_search_tables(bwfm_index *ix, hipStream_t st) {
             return 0;
         });
     }
-    HIPCHK(hipGetLastError());
-    HIPCHK(hipStreamSynchronize(st));
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    if (e != hipSuccess) {
+        free_search_tables(ix);
+        return fail(BWFM_E_DEVICE, std::string("the search's tables: ") + hipGetErrorString(e));
+    }
     ix->jt_levels = (uint32_t)levels;
     ix->device_bytes += 2 * (bytes + full);
     return BWFM_OK;
 }
 
+// Drop the search's tables; the caller has waited for the work that reads them.
 void bwfm::free_search_tables(bwfm_index *ix) {
     for (int d = 0; d < 2; d++) {
         dev_free(ix->d_jt[d]);
         dev_free(ix->d_full[d]);
         ix->d_jt[d] = ix->d_full[d] = nullptr;
     }
+    if (ix->jt_levels) ix->device_bytes -= 2 * (kt_bytes(ix->jt_levels) + 2 * (ix->n + 1) * 4);
     ix->jt_levels = 0;
+    ix->jt_gen++;
+}
+
+extern "C" int bwfm_index_search_tables(bwfm_index *ix, int levels, void *stream) {
+    if (!ix) return fail(BWFM_E_INVAL, "search_tables: NULL index");
+    if (levels < -1 || levels > 15) return fail(BWFM_E_INVAL, "search_tables: levels must be -1, 0 or 1..15");
+    std::unique_lock<std::shared_mutex> g(ix->mu);
+    if (ix->device >= 0) {
+        int dev = -1;
+        HIPCHK(hipGetDevice(&dev));
+        if (dev != ix->device) return fail(BWFM_E_INVAL, "search_tables: the index's device must be current");
+        HIPCHK(hipDeviceSynchronize());  // captured steps on any stream may still read the tables
+        free_search_tables(ix);
+    }
+    ix->jt_want = levels;
+    return ix->device >= 0 ? build_search_tables(ix, (hipStream_t)stream) : (int)BWFM_OK;
 }
 
 extern "C" int bwfm_index_upload(bwfm_index *ix, void *stream) {
@@ -4068,6 +4091,7 @@ struct bwfm_pipeline {
     hipEvent_t ev[3] = {nullptr, nullptr, nullptr};  // first pass start, end; the search's end
     hipStream_t cap = nullptr;  // capture only: nothing runs on it
     bool timed_graph = false, timed_last = false;
+    uint64_t jt_gen = 0;        // the index's search tables that the graph was captured with
     bool timing_uncapturable = false;  // a capture with event nodes failed once
 };
 
@@ -4322,6 +4346,8 @@ extern "C" int bwfm_pipeline_set_count(bwfm_pipeline *pl, uint32_t n_pairs) {
 extern "C" int bwfm_pipeline_run(bwfm_pipeline *pl, int graph, void *stream) {
     if (!pl) return fail(BWFM_E_INVAL, "pipeline_run: NULL pipeline");
     hipStream_t st = (hipStream_t)stream;
+    // the search's tables stay as they are until the step is enqueued
+    std::shared_lock<std::shared_mutex> ig(pl->ix->mu);
     bool timed;
     {
         std::lock_guard<std::mutex> g(timing().mu);
@@ -4336,7 +4362,7 @@ extern "C" int bwfm_pipeline_run(bwfm_pipeline *pl, int graph, void *stream) {
         return pipe_enqueue_any(pl, st, timed, false);
     }
     if (pl->timing_uncapturable) timed = false;
-    if (pl->exec && pl->timed_graph != timed) drop_graph(pl);
+    if (pl->exec && (pl->timed_graph != timed || pl->jt_gen != pl->ix->jt_gen)) drop_graph(pl);
     if (!pl->exec) {
         // recorded on the pipeline's own stream (the caller's may be the
         // null stream, which cannot be captured); launched on the caller's
@@ -4367,6 +4393,7 @@ extern "C" int bwfm_pipeline_run(bwfm_pipeline *pl, int graph, void *stream) {
         pl->graph = gph;
         pl->exec = ex;
         pl->timed_graph = timed;
+        pl->jt_gen = pl->ix->jt_gen;
     }
     pl->timed_last = pl->timed_graph;
     HIPCHK(hipGraphLaunch(pl->exec, st));

@@ -117,13 +117,15 @@ struct bwfm_index {
     void *d_pac = nullptr;
     void *d_jt[2] = {nullptr, nullptr};  // the search's interval tables, made at upload
     uint32_t jt_levels = 0;              // their depth (0: none)
+    int jt_want = -1;                    // depth asked for (bwfm_index_search_tables; -1: the library's rule)
+    uint64_t jt_gen = 0;                 // bumped whenever they change (captured steps hold their addresses)
     void *d_full[2] = {nullptr, nullptr};  // per direction SA[0, n], then its inverse (with the tables)
     void *d_kt[2] = {nullptr, nullptr};  // the caller's short-string tables (bwfm_index_kmer_table)
     uint32_t kt_levels = 0;
     uint64_t device_bytes = 0;
     // held shared by calls that only read the index's device state (align,
-    // locate, pair), exclusively by calls that change it (upload, the
-    // short-string table)
+    // locate, pair, a captured step's run), exclusively by calls that change
+    // it (upload, the search's tables, the caller's short-string table)
     std::shared_mutex mu;
     std::mutex ws_mu;                                           // guards ws
     std::map<void *, std::unique_ptr<bwfm::Workspace>> ws;      // one per stream used

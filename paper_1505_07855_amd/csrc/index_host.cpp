@@ -386,6 +386,7 @@ extern "C" int bwfm_index_get_info(const bwfm_index *ix, bwfm_index_info *o) {
     o->rank_format = ix->rank_format;
     o->kmer_levels = ix->kt_levels;
     o->kmer_bytes = ix->kt_levels ? 2 * ((8 * bwfm::kt_level_start((int)ix->kt_levels + 1) + 255) / 256 * 256) : 0;
+    o->search_levels = ix->jt_levels;
     bwfm_index *mix = const_cast<bwfm_index *>(ix);
     std::lock_guard<std::mutex> g(mix->ws_mu);
     for (auto &kv : mix->ws) o->ws_bytes += kv.second->bytes + kv.second->pos_bytes;
