@@ -3427,8 +3427,9 @@ int locate_fill(const DevIndex &D, uint64_t n_hits, const u4 *hits, const uint64
                                                         total_dev);
         k_loc_wide<<<512, 256, 0, st>>>(D, hits, pos_off, pos, big, n_big + 1);
     } else {
-        k_loc_rows<LW><<<(uint32_t)std::min<uint64_t>(blocks(total, 256), total_dev ? 2048 : 65536), 256, 0, st>>>(
-            D, n_hits, hits, pos_off, total, pos, n_hits_dev, total_dev);
+        // (a captured step's bound may be 0, its grid not)
+        const uint64_t grid = std::min<uint64_t>(std::max(blocks(total, 256), 1u), total_dev ? 2048 : 65536);
+        k_loc_rows<LW><<<(uint32_t)grid, 256, 0, st>>>(D, n_hits, hits, pos_off, total, pos, n_hits_dev, total_dev);
     }
     HIPCHK(hipGetLastError());
     return BWFM_OK;

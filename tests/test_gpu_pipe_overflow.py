@@ -92,6 +92,26 @@ def test_step_over_its_capacities(setup, short, graph):
     pl.close()
 
 
+@pytest.mark.parametrize("levels", [0, -1])
+def test_no_room_for_positions(setup, levels):
+    """pos_capacity 0, with and without the search's tables: a batch without
+    hits runs, one with hits is reported."""
+    text, runs = setup
+    ix = bw.Index(text, line_bytes=64).search_tables(levels).upload()
+    pl = bw.Pipeline(ix, bw.Params(max_diff=2), LO, HI, MU, MAX_OCC, max_pairs=N, max_len=L, pos_capacity=0)
+    b = torch.full((2 * N * L,), 4, dtype=torch.uint8, device="cuda")
+    for graph in (False, True):
+        pl.set_reads(b, runs["single"]["o"], N, max_len=L)
+        pl.run(graph=graph)
+        st = pl.finish()
+        assert (st["error"], st["n_hits"], st["n_positions"]) == (0, 0, 0)
+        pl.set_reads(runs["single"]["b"], runs["single"]["o"], N, max_len=L)
+        pl.run(graph=graph)
+        st = pl.finish()
+        assert (st["error"], st["n_positions"]) == (bw.PIPE_E_POSITIONS, runs["single"]["pos"])
+    pl.close()
+
+
 def test_served_steps_over_their_capacities(setup):
     """A server whose steps outgrow the capacities it starts with redoes
     them: records equal the oracle's."""
