@@ -281,9 +281,10 @@ typedef struct {
                                take (rounds of one launch each); the lanes
                                of a wave share the rest of their reads in
                                flight either way.  0 = the library's default
-                               (16384; batches whose max_len is 200 or
-                               more drop to 256 once half of the first
-                               pass's waves have ended), -1 = no splitting,
+                               (16384).  Batches with an eighth of reads of
+                               200 bases and more, or with 64 reads split
+                               already, drop to 256 once half of the first
+                               pass's waves have ended.  -1 = no splitting,
                                else 16 .. 2^24.
                                A tuning knob: results do not depend on it. */
 } bwfm_aln_params;

@@ -94,8 +94,8 @@ constexpr uint32_t PLAIN_STACK = 320;  // stack entries per lane, plain form fir
 #ifndef BWFM_GENE_SUBHDR
 #define BWFM_GENE_SUBHDR 0
 #endif
-// Reads of a batch are long when max_len reaches this: their few largest
-// trees are split early (DRAIN_EIGHTHS).
+// Reads of this many bases and more are long: a batch of them has its few
+// largest trees split early (DRAIN_EIGHTHS).
 constexpr uint32_t LONG_READ = 200;
 // Lanes of a wave that must wait for a strand or read change before the wave
 // makes them (BWFM_TURN_MIN may override it).
@@ -1487,17 +1487,25 @@ constexpr uint32_t SLOT_HITS = 2 * FAST_CAND;
 // control words: [0] slots taken; [1 + g] task entries reserved in
 // generation g (0: by the first pass, k: by round k); [2 + SPLIT_ROUNDS + g]
 // entries of generation g taken by round g + 1
-// [SPLIT_DONE] waves of the first pass that have ended
+// [SPLIT_DONE] waves of the first pass that have ended, plus DRAIN_HEAVY once
+// DRAIN_SLOTS reads have been split; [SPLIT_LONG] long reads in every
+// sixteenth wave of the D-array pass
 constexpr uint32_t SPLIT_DONE = 2 * (SPLIT_ROUNDS + 1) + 2;
-constexpr uint32_t SPLIT_CTL = SPLIT_DONE + 1;
-// Batches of long reads (LONG_READ): once DRAIN_EIGHTHS of
-// the first pass's waves have ended, the parts still running are split after
-// DRAIN_BUDGET expansions already: the few reads with the largest trees would
+constexpr uint32_t SPLIT_LONG = SPLIT_DONE + 1;
+constexpr uint32_t SPLIT_CTL = SPLIT_LONG + 1;
+// Early splits: once DRAIN_EIGHTHS of the first pass's waves have ended, the
+// parts still running are split after DRAIN_BUDGET expansions already, in a
+// batch with an eighth of long reads or more (as the D-array pass sees them,
+// not as the caller declares them): the few reads with the largest trees would
 // otherwise hold single waves until each part has reached the full budget
-// (150 k reads of 250 bases: 184 ms without, 47 at 4 eighths, 45 at 2, 58 at
-// 6).  On 100-base reads the endgame ends sooner by itself (30 k pairs: 7.0
-// ms without, 8.2-9.2 with).
-constexpr uint32_t DRAIN_EIGHTHS = 4, DRAIN_BUDGET = 256;
+// (150 k reads of 250 bases: 184 ms without, 47 with; 45 at 2 eighths, 58 at
+// 6).  Batches of shorter reads mostly end sooner without (30 k reads of 150
+// bases, 4 differences: 4.5 ms, with it 6.2), unless their trees prove as
+// large: they wait for DRAIN_SLOTS reads that outgrew the full budget (50 k
+// reads of 150 bases, 6 differences: 400 ms without, 110 with).  And where the
+// declared length leaves the first pass a wave a SIMD or less, splitting is
+// the shorter way for any reads (60 k of 100 bases, declared 512: 9.4, 8.2).
+constexpr uint32_t DRAIN_EIGHTHS = 4, DRAIN_BUDGET = 256, DRAIN_SLOTS = 64, DRAIN_HEAVY = 1u << 24;
 
 struct SplitBufs {
     uint32_t *slot_read;    // the slot's read
@@ -1518,7 +1526,7 @@ struct SplitBufs {
     uint32_t slot_cap, task_cap, dstride;
     uint32_t budget;  // expansions of a lane's part of a read before it is split (endgame); 0: off
     uint32_t count;   // nonzero: the parts' expansions are summed (per-read work counters)
-    uint32_t drain;   // nonzero: a batch of long reads, split early at the end (DRAIN_EIGHTHS)
+    uint32_t drain;   // ctl[SPLIT_DONE] from which the parts are split early (DRAIN_EIGHTHS)
 };
 
 __device__ __forceinline__ uint32_t ld_agent(const uint32_t *p) {
@@ -1640,6 +1648,7 @@ __device__ bool split_part(const SplitBufs &X, uint32_t r, uint32_t owner, int s
         X.slot_owner[s] = owner;
         X.slot_own[s] = 0;
         X.slot_obest[s] = INF_SCORE;
+        if (s + 1 == DRAIN_SLOTS && X.drain >= DRAIN_HEAVY) atomicAdd(&X.ctl[SPLIT_DONE], DRAIN_HEAVY);
         fl |= (int)((s + 1) << SH_SLOT_SHIFT);
     }
     if (!(fl & (SH_ROW0 << strand))) {
@@ -1807,7 +1816,7 @@ __device__ __forceinline__ const uint8_t *drow_of(const uint8_t *drows, uint32_t
 // with this pass's 3.3 ms before it and the grouped read changes.)
 template <int LW>
 __global__ __launch_bounds__(BLOCK) void k_dscan(DevIndex ix, ReadsView rd, Params P, uint8_t *drows, uint8_t *dflag,
-                                                 uint32_t dstride, uint32_t lstride) {
+                                                 uint32_t dstride, uint32_t lstride, uint32_t *n_long) {
     const uint32_t r = blockIdx.x * blockDim.x + threadIdx.x;
     if (r >= reads_n(rd)) return;
     uint64_t o0, len;
@@ -1817,6 +1826,10 @@ __global__ __launch_bounds__(BLOCK) void k_dscan(DevIndex ix, ReadsView rd, Para
     // reads the search will not take (invalid or empty) get no rows
     if (bad || len == 0 || len > rd.max_len || len > BWFM_MAX_READ || maxd > BWFM_MAX_DIFF) return;
     const int m = (int)len;
+    if (n_long && ((r >> 6) & 15) == 0) {
+        const unsigned long long lm = __ballot(len >= LONG_READ);
+        if (lm && (r & 63) == (uint32_t)__ffsll((long long)lm) - 1) atomicAdd(n_long, (uint32_t)__popcll(lm));
+    }
     LaneCtx c;
     c.pd = lds_bytes + (size_t)threadIdx.x * lstride;
     const bool has_n = stage_read(c.pd, rd.bases + o0, m);
@@ -1857,8 +1870,14 @@ __device__ __forceinline__ void load_drow(uint8_t *pd, const uint8_t *row, int m
     }
 }
 
-__global__ void k_set_args(PersistentArgs *dst, PersistentArgs a) {
-    if (threadIdx.x == 0) *dst = a;
+// The batched kernel's argument block.  a.X.drain comes as the waves that must
+// have ended before parts are split early; unless that is to be at once or the
+// D-array pass has seen enough long reads, DRAIN_SLOTS reads must have been
+// split too (which adds DRAIN_HEAVY to the count).
+__global__ void k_set_args(PersistentArgs *dst, PersistentArgs a, uint32_t at_once) {
+    if (threadIdx.x) return;
+    if (a.X.budget && !at_once && (uint64_t)a.X.ctl[SPLIT_LONG] * 16 * 8 < reads_n(a.rd)) a.X.drain += DRAIN_HEAVY;
+    *dst = a;
 }
 
 template <int LW>
@@ -2066,11 +2085,8 @@ __device__ __forceinline__ void persistent_body(const DevIndex &ix, const Params
             // the hand-over for a helper
             uint32_t bud = A->X.budget;
             if (bud) {
-                if (A->X.drain) {
-                    if ((eg_iter++ & 15) == 15 && !drain)
-                        drain = (uint64_t)ld_agent(&A->X.ctl[SPLIT_DONE]) * 8 >= (uint64_t)n_waves * DRAIN_EIGHTHS;
-                    if (drain) bud = min(bud, DRAIN_BUDGET);
-                }
+                if ((eg_iter++ & 15) == 15 && !drain) drain = ld_agent(&A->X.ctl[SPLIT_DONE]) >= A->X.drain;
+                if (drain) bud = min(bud, DRAIN_BUDGET);
                 const bool want = (phase == PZ_SEARCH || phase == PZ_HELP) && c.sp > c.sbase && c.expand >= bud &&
                                   !(sh_ld(&ws.flags[ow]) & (SH_FAIL | SH_NOSPLIT));
                 unsigned long long sm = __ballot(want);
@@ -3190,6 +3206,13 @@ inline uint32_t block_for(uint32_t stride) {
     return bs;
 }
 
+// waves of a first pass of `lanes` that must have ended before its parts are
+// split early
+inline uint32_t drain_waves(uint32_t lanes) { return (lanes / 64 * DRAIN_EIGHTHS + 7) / 8; }
+// whether the declared read length leaves a CU of 160 KB so few of these
+// blocks (bs lanes, lds bytes) that they make a wave a SIMD or fewer
+inline uint32_t drain_at_once(uint32_t bs, size_t lds) { return 163840 / lds * (bs / 64) <= 4; }
+
 constexpr uint32_t SLOW_LANES = BWFM_SLOW_LANES;  // most lanes of the second pass
 constexpr uint32_t SPLIT_DEFAULT = 16384;         // split budget unless the caller sets one
 
@@ -3339,7 +3362,7 @@ int align_impl(bwfm_index *ix, bwfm::Workspace &ws, const bwfm_reads *rd, const 
     TaskArgs *targs = nullptr;
     SplitBufs X = sbud ? carve_split(cv, zs, sbud, &targs) : SplitBufs{};
     X.count = expand != nullptr;
-    X.drain = mlen >= LONG_READ;
+    X.drain = drain_waves(lanes);
     uint32_t *lane_read = sbud ? cv.take<uint32_t>(lanes) : nullptr;
     uint32_t *ctl = cv.take<uint32_t>(16);  // n_slow, next_read, stage_used (64-bit), slow_next
     uint32_t *n_slow = ctl, *next_read = ctl + 1, *slow_next = ctl + 4;
@@ -3362,9 +3385,11 @@ int align_impl(bwfm_index *ix, bwfm::Workspace &ws, const bwfm_reads *rd, const 
             tm.end(t);
         } else {
             int td = tm.begin("dscan");
-            k_dscan<LW><<<nr_up / bs, bs, (size_t)bs * lstride, st>>>(D, rv, P, drows, dflag, dstride, lstride);
+            k_dscan<LW><<<nr_up / bs, bs, (size_t)bs * lstride, st>>>(D, rv, P, drows, dflag, dstride, lstride,
+                                                                      sbud ? X.ctl + SPLIT_LONG : nullptr);
             tm.end(td);
-            k_set_args<<<1, 64, 0, st>>>(pargs, PersistentArgs{rv, lb, O, next_read, drows, dflag, dstride, X, lane_read});
+            k_set_args<<<1, 64, 0, st>>>(pargs, PersistentArgs{rv, lb, O, next_read, drows, dflag, dstride, X, lane_read},
+                                         drain_at_once(bs, lds));
             int ts = tm.begin("align_search");
             int t = tm.begin("align_persistent");
             hipLaunchKernelGGL(persistent_kernel<LW>(p->waves_per_simd), dim3(lanes / bs), dim3(bs), lds, st, D, P,
@@ -4120,16 +4145,16 @@ int pipe_enqueue(bwfm_pipeline *pl, hipStream_t st, bool timed, bool capture) {
     auto mark = [&](hipEvent_t e) {
         return capture ? hipEventRecordWithFlags(e, st, hipEventRecordExternal) : hipEventRecord(e, st);
     };
+    if (pl->X.budget) k_fill_u32<<<1, 64, 0, st>>>(pl->X.ctl, SPLIT_CTL, 0u);
     if (!plain) {
         const uint32_t nr_up = ((nmax + pl->bs - 1) / pl->bs) * pl->bs;
-        k_dscan<LW><<<nr_up / pl->bs, pl->bs, (size_t)pl->bs * pl->lstride, st>>>(D, rv, P, pl->drows, pl->dflag,
-                                                                               pl->dstride, pl->lstride);
-    }
-    if (pl->X.budget) k_fill_u32<<<1, 64, 0, st>>>(pl->X.ctl, SPLIT_CTL, 0u);
-    if (!plain)
+        k_dscan<LW><<<nr_up / pl->bs, pl->bs, (size_t)pl->bs * pl->lstride, st>>>(
+            D, rv, P, pl->drows, pl->dflag, pl->dstride, pl->lstride, pl->X.budget ? pl->X.ctl + SPLIT_LONG : nullptr);
         k_set_args<<<1, 64, 0, st>>>(pl->pargs,
                                      PersistentArgs{rv, lb, O, actl + 1, pl->drows, pl->dflag, pl->dstride, pl->X,
-                                                    pl->lane_read});
+                                                    pl->lane_read},
+                                     drain_at_once(pl->bs, pl->lds));
+    }
     if (timed) HIPCHK(mark(pl->ev[0]));
     if (plain)
         k_align_plain<LW><<<pl->lanes / pl->bs, pl->bs, pl->lds, st>>>(D, rv, P, lb, O);
@@ -4281,7 +4306,7 @@ extern "C" int bwfm_pipeline_create(const bwfm_index *cix, const bwfm_aln_params
     }
     if (sbud) {
         pl->X = carve_split(cv, zs, sbud, &pl->targs);
-        pl->X.drain = mlen >= LONG_READ;
+        pl->X.drain = drain_waves(pl->lanes);
         pl->lane_read = cv.take<uint32_t>(pl->lanes);
     }
     if (hipEventCreate(&pl->ev[0]) != hipSuccess || hipEventCreate(&pl->ev[1]) != hipSuccess ||
