@@ -2263,9 +2263,20 @@ constexpr uint32_t DRAIN_MIN = 256;
 // end up on few waves (150 k reads: 57 / 52 ms)
 constexpr int TASK_REFILL_MANY = 10, TASK_REFILL = 32;
 constexpr uint32_t TASK_MANY = 8;
+// Waves per SIMD of the rounds.  Five (96 registers; the planar formats of 64
+// and 128 bytes hold more and would spill) suit the long rounds of a batch of
+// many reads, whose random fills they keep in flight; in short rounds they only
+// cut the tasks finer, so a batch of fewer than TASK_READS reads a lane takes
+// the lanes of four (128-byte sub-counted lines, 250 bases, 4 / 5 waves: 2M at
+// a split budget of 512 293 / 273 ms, 1M 169 / 160, 600 k 150 / 150, 300 k 84 /
+// 86, 150 k 53.9 / 55.9).  At 64-byte sub-counted lines five take 100 k reads
+// as fast as four (40.3 / 41.5 ms).  The body as a function of its own takes 92
+// registers at 128-byte sub-counted lines, as the kernel itself 100.
+constexpr int TASK_WAVES = 5, TASK_WAVES_FEW = 4;
+constexpr uint32_t TASK_READS = 2;
 template <int LW>
-__global__ __launch_bounds__(BLOCK) void k_align_tasks(DevIndex ix, Params P, const TaskArgs *Aarg, uint32_t g,
-                                                       uint32_t drain) {
+__device__ __forceinline__ void tasks_body(const DevIndex &ix, const Params &P, const TaskArgs *Aarg, uint32_t g,
+                                           uint32_t drain) {
     using GlobalArgs = const __attribute__((address_space(1))) TaskArgs;
     GlobalArgs *Ag = (GlobalArgs *)Aarg;
     const TaskArgs *A = (const TaskArgs *)Ag;
@@ -2396,6 +2407,12 @@ __global__ __launch_bounds__(BLOCK) void k_align_tasks(DevIndex ix, Params P, co
             valid = false;
         }
     }
+}
+
+template <int LW>
+__global__ __launch_bounds__(BLOCK, LW == 16 || LW == 32 ? TASK_WAVES_FEW : TASK_WAVES) void k_align_tasks(
+    DevIndex ix, Params P, const TaskArgs *A, uint32_t g, uint32_t drain) {
+    tasks_body<LW>(ix, P, A, g, drain);
 }
 
 // Totals of the split searches for the work counters (work[3..5] start at
@@ -3286,6 +3303,8 @@ uint32_t task_lanes(uint32_t n_up, uint32_t lanes) {
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_align_tasks<LW>, (int)BLOCK, 0) != hipSuccess ||
         per_cu < 1)
         per_cu = 1;
+    if (LW != LW_SUB && (uint64_t)n_up < (uint64_t)cus * (uint64_t)per_cu * BLOCK * TASK_READS)
+        per_cu = std::min(per_cu, TASK_WAVES_FEW * 4 * 64 / BLOCK);
     const uint64_t fit = (uint64_t)cus * (uint64_t)per_cu * BLOCK;
     const uint64_t want = std::max<uint64_t>(lanes, ((16ull * n_up + BLOCK - 1) / BLOCK) * BLOCK);
     return (uint32_t)std::max<uint64_t>(std::min(fit, want), BLOCK);
