@@ -3241,18 +3241,21 @@ inline uint32_t split_budget_of(const bwfm_aln_params &p) {
 }
 
 // Room of the split searches for a batch of n reads of at most mlen bases:
-// a slot for one read in eight (at least 64, at most 2^26) and, per
-// generation, sixteen task entries a read, in smaller batches 1024 a read up
-// to 2^23 (at most 2^26 in all).  A split hands out a few hundred entries on
-// long reads.  Running out is not an error, but a read or task that finds no
-// room goes on alone, which can take seconds (2.2 s for 150 k reads of 250
-// bases whose splits outgrew sixteen entries a read).
+// in batches of long reads, which are split early, a slot for every read that
+// can be in flight when the batch runs dry (one a lane of the first pass); of
+// others a slot for one read in eight (at least 64, at most 2^26).  Per
+// generation sixteen task entries a read, in smaller batches 1024 a read up to
+// 2^23 (at most 2^26 in all): a split hands out a few hundred entries on long
+// reads.  Running out is not an error, but a read or task that finds no room
+// goes on alone, which can take seconds (2.2 s for 150 k reads of 250 bases
+// whose splits outgrew sixteen entries a read; 300 k / 600 k of them at a split
+// budget of 512 with a slot for one in eight 2.6 / 2.9 s, so 77 / 119 ms).
 struct SplitShape {
     uint32_t slot_cap, task_cap, dstride;
 };
-inline SplitShape split_shape(uint32_t n, uint32_t mlen) {
+inline SplitShape split_shape(uint32_t n, uint32_t mlen, uint32_t lanes) {
     SplitShape z;
-    z.slot_cap = std::min<uint32_t>(std::min<uint32_t>(std::max<uint32_t>(n, 1), std::max<uint32_t>(64, n / 8)), 1u << 26);
+    z.slot_cap = std::min(std::max(n, 1u), mlen >= LONG_READ ? lanes : std::min(std::max(64u, n / 8), 1u << 26));
     z.task_cap = (uint32_t)std::min<uint64_t>(std::max<uint64_t>(16ull * n, 1024ull * std::min(std::max(n, 1u), 8192u)),
                                               1ull << 26);
     z.dstride = ((mlen + 15) / 16) * 16;
@@ -3360,7 +3363,7 @@ int align_impl(bwfm_index *ix, bwfm::Workspace &ws, const bwfm_reads *rd, const 
     // the D-array pre-pass's rows
     const uint32_t dstride = ((mlen + 15) / 16) * 16;
     if (!plain) need += (size_t)n * 2 * dstride + n + 2 * 256;
-    const SplitShape zs = split_shape(n, mlen);
+    const SplitShape zs = split_shape(n, mlen, lanes);
     if (sbud) need += split_bytes(zs) + (size_t)lanes * 4 + 256;
     void *w;
     int rc = ws_reserve(ws, need, st, &w);
@@ -4290,7 +4293,7 @@ extern "C" int bwfm_pipeline_create(const bwfm_index *cix, const bwfm_aln_params
         add((size_t)nmax * 2 * pl->dstride);
         add(nmax);
     }
-    const SplitShape zs = split_shape(nmax, mlen);
+    const SplitShape zs = split_shape(nmax, mlen, pl->lanes);
     if (sbud) need += split_bytes(zs) + (size_t)pl->lanes * 4 + 256;
     need += 4096;
     if (dev_malloc(&pl->mem, need) != hipSuccess) return fail(BWFM_E_NOMEM, "pipeline: device allocation failed");

@@ -45,3 +45,16 @@ def test_long_reads_are_split_early_and_equal_the_oracle():
     o = oracle.align(oracle.Index(g.seq), r.bases, r.offsets, oracle.Params(**configs.PARAMS["C5"]), threads=8)
     want = [o.hit_off, o.hits.view(np.uint8), o.c1, o.c2, o.status]
     assert all(np.array_equal(a, b) for a, b in zip(want, got))
+
+
+def test_every_long_read_in_flight_finds_room():
+    """At the smallest split budget more of a batch is split than one read in
+    eight, the room that batches of short reads have."""
+    n = 3000
+    g = configs.c2_genome(2_000_000, seed=173)
+    r = configs.c5_reads(g, n, seed=174)
+    ix = bw.Index(g.seq, **configs.LAYOUT["C2"]).upload()
+    want, _ = _run(ix, r, bw.Params(**configs.PARAMS["C5"], split_budget=-1), 250)
+    got, split = _run(ix, r, bw.Params(**configs.PARAMS["C5"], split_budget=16), 250)
+    assert split > n // 8
+    assert all(np.array_equal(a, b) for a, b in zip(want, got))
