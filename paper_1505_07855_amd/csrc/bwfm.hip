@@ -3202,9 +3202,13 @@ uint32_t persistent_lanes(uint32_t bs, size_t lds, int waves_per_simd) {
 // than a wave per read (a wave's other lanes help its reads) up to 1024
 // reads, 16 lanes per read from 4096 on (each lane needs its buffers: 17 KB
 // at 100 bases).  1000 pairs take 2.5 ms at a wave per read, 2.9 ms at 16
-// lanes; 5000 pairs 3.7 ms either way.
-inline uint32_t batched_lanes(uint32_t fit, uint32_t n, uint32_t bs) {
-    const uint64_t per = std::min<uint64_t>(64ull * std::max(n, 1u), std::max<uint64_t>(65536, 16ull * n));
+// lanes; 5000 pairs 3.7 ms either way.  lean: a lane per read, where memory is
+// short (a call that finds no memory for its workspace is tried once more in
+// this shape, with the fewest task entries and slots too: 1000 reads of 512
+// bases 1.2 GB instead of 4.6).
+inline uint32_t batched_lanes(uint32_t fit, uint32_t n, uint32_t bs, bool lean) {
+    const uint64_t per = lean ? std::max(n, 1u)
+                              : std::min<uint64_t>(64ull * std::max(n, 1u), std::max<uint64_t>(65536, 16ull * n));
     const uint64_t want = ((per + bs - 1) / bs) * bs;
     return (uint32_t)std::min<uint64_t>(fit, want);
 }
@@ -3253,11 +3257,11 @@ inline uint32_t split_budget_of(const bwfm_aln_params &p) {
 struct SplitShape {
     uint32_t slot_cap, task_cap, dstride;
 };
-inline SplitShape split_shape(uint32_t n, uint32_t mlen, uint32_t lanes) {
+inline SplitShape split_shape(uint32_t n, uint32_t mlen, uint32_t lanes, bool lean) {
     SplitShape z;
-    z.slot_cap = std::min(std::max(n, 1u), mlen >= LONG_READ ? lanes : std::min(std::max(64u, n / 8), 1u << 26));
-    z.task_cap = (uint32_t)std::min<uint64_t>(std::max<uint64_t>(16ull * n, 1024ull * std::min(std::max(n, 1u), 8192u)),
-                                              1ull << 26);
+    const uint64_t least = lean ? 4096 : 1024ull * std::min(std::max(n, 1u), 8192u);
+    z.slot_cap = std::min(std::max(n, 1u), mlen >= LONG_READ && !lean ? lanes : std::min(std::max(64u, n / 8), 1u << 26));
+    z.task_cap = (uint32_t)std::min<uint64_t>(std::max<uint64_t>(16ull * n, least), 1ull << 26);
     z.dstride = ((mlen + 15) / 16) * 16;
     return z;
 }
@@ -3345,28 +3349,33 @@ int align_impl(bwfm_index *ix, bwfm::Workspace &ws, const bwfm_reads *rd, const 
     const uint32_t bs = block_for(lstride);
     const size_t lds = (size_t)bs * lstride + (plain ? 0 : (bs / 64) * sizeof(WaveShare));
     const uint32_t nr_up = ((std::max<uint32_t>(n, 1) + bs - 1) / bs) * bs;
-    const uint32_t lanes =
-        plain ? nr_up : batched_lanes(persistent_lanes<LW>(bs, lds, p->waves_per_simd), n, bs);
+    const uint32_t fit = plain ? 0 : persistent_lanes<LW>(bs, lds, p->waves_per_simd);
     const uint32_t stack_cap = plain ? std::min<uint32_t>(worst_stack, PLAIN_STACK) : worst_stack;
-    // the task rounds' grid shares the lane buffers: room for the larger one
-    const uint32_t tlanes = sbud ? task_lanes<LW>(nr_up, lanes) : 0u;
-    const uint32_t blanes = std::max(lanes, tlanes);
     // the staging arena holds the reported hits of every read: as many as
     // the output can take
     const uint64_t stage_cap = res->hit_capacity;
     const uint32_t slow_lanes = std::min<uint32_t>(nr_up, SLOW_LANES);
     const uint32_t scap = P.max_hits + 1;
-    size_t need = (size_t)blanes * stack_cap * 16 + (size_t)blanes * FAST_CAND * 16;
-    need += (size_t)slow_lanes * worst_stack * 16 + (size_t)slow_lanes * scap * 16;
-    need += (size_t)n * 4 * 2 + (size_t)n * 8 + stage_cap * 16 + scan_part_elems(n) * 8 + 16 * 256;
-    need += sizeof(PersistentArgs) + 256;
-    // the D-array pre-pass's rows
-    const uint32_t dstride = ((mlen + 15) / 16) * 16;
-    if (!plain) need += (size_t)n * 2 * dstride + n + 2 * 256;
-    const SplitShape zs = split_shape(n, mlen, lanes);
-    if (sbud) need += split_bytes(zs) + (size_t)lanes * 4 + 256;
+    const uint32_t dstride = ((mlen + 15) / 16) * 16;  // of the D-array pre-pass's rows
+    uint32_t lanes = 0, tlanes = 0, blanes = 0;
+    SplitShape zs{};
     void *w;
-    int rc = ws_reserve(ws, need, st, &w);
+    auto reserve = [&](bool lean) {
+        lanes = plain ? nr_up : batched_lanes(fit, n, bs, lean);
+        // the task rounds' grid shares the lane buffers: room for the larger one
+        tlanes = sbud ? task_lanes<LW>(nr_up, lanes) : 0u;
+        blanes = std::max(lanes, tlanes);
+        zs = split_shape(n, mlen, lanes, lean);
+        size_t need = (size_t)blanes * stack_cap * 16 + (size_t)blanes * FAST_CAND * 16;
+        need += (size_t)slow_lanes * worst_stack * 16 + (size_t)slow_lanes * scap * 16;
+        need += (size_t)n * 4 * 2 + (size_t)n * 8 + stage_cap * 16 + scan_part_elems(n) * 8 + 16 * 256;
+        need += sizeof(PersistentArgs) + 256;
+        if (!plain) need += (size_t)n * 2 * dstride + n + 2 * 256;
+        if (sbud) need += split_bytes(zs) + (size_t)lanes * 4 + 256;
+        return ws_reserve(ws, need, st, &w);
+    };
+    int rc = reserve(false);
+    if (rc == BWFM_E_NOMEM && !plain) rc = reserve(true);
     if (rc) return rc;
     Carver cv{(char *)w};
     u4 *lstack = cv.take<u4>((size_t)blanes * stack_cap);
@@ -4263,40 +4272,43 @@ extern "C" int bwfm_pipeline_create(const bwfm_index *cix, const bwfm_aln_params
     pl->bs = block_for(pl->lstride);
     pl->lds = (size_t)pl->bs * pl->lstride + (plain ? 0 : (pl->bs / 64) * sizeof(WaveShare));
     const uint32_t nr_up = ((nmax + pl->bs - 1) / pl->bs) * pl->bs;
-    pl->lanes = plain ? nr_up
-                      : batched_lanes(by_layout(ix,
-                                                [&](auto lw) {
-                                                    return persistent_lanes<decltype(lw)::value>(
-                                                        pl->bs, pl->lds, ap->waves_per_simd);
-                                                }),
-                                      nmax, pl->bs);
+    const uint32_t fit = plain ? 0 : by_layout(ix, [&](auto lw) {
+        return persistent_lanes<decltype(lw)::value>(pl->bs, pl->lds, ap->waves_per_simd);
+    });
     pl->stack_cap = plain ? std::min<uint32_t>(pl->worst_stack, PLAIN_STACK) : pl->worst_stack;
-    pl->tlanes = sbud ? by_layout(ix, [&](auto lw) { return task_lanes<decltype(lw)::value>(nr_up, pl->lanes); }) : 0u;
-    const uint32_t blanes = std::max(pl->lanes, pl->tlanes);
     pl->slow_lanes = std::min<uint32_t>(nr_up, SLOW_LANES);
     pl->scap = ap->max_hits + 1;
     const uint64_t hcap = std::max<uint64_t>(q->hit_capacity, 1);
     const uint64_t pcap = std::max<uint64_t>(q->pos_capacity, 1);
-    size_t need = 0;
-    auto add = [&](size_t b) { need += (b + 255) & ~size_t(255); };
-    add(q->max_bases); add((size_t)(nmax + 1) * 8); add(nmax);
-    add((size_t)blanes * pl->stack_cap * 16); add((size_t)blanes * FAST_CAND * 16);
-    add((size_t)pl->slow_lanes * pl->worst_stack * 16); add((size_t)pl->slow_lanes * pl->scap * 16);
-    add((size_t)nmax * 4); add((size_t)nmax * 4); add((size_t)nmax * 8); add(hcap * 16);
-    add(scan_part_elems(std::max<uint64_t>(nmax, hcap)) * 8);
-    add((size_t)(nmax + 1) * 8); add(hcap * 16); add((size_t)nmax * 4); add((size_t)nmax * 4); add(nmax);
-    add(hcap * 4); add(hcap * 4); add((hcap + 1) * 8); add(pcap * 4); add((size_t)q->max_pairs * sizeof(bwfm_pair));
-    add(PC_WORDS * 8);
-    add(sizeof(PersistentArgs));
     pl->dstride = ((mlen + 15) / 16) * 16;
-    if (!plain) {
-        add((size_t)nmax * 2 * pl->dstride);
-        add(nmax);
-    }
-    const SplitShape zs = split_shape(nmax, mlen, pl->lanes);
-    if (sbud) need += split_bytes(zs) + (size_t)pl->lanes * 4 + 256;
-    need += 4096;
-    if (dev_malloc(&pl->mem, need) != hipSuccess) return fail(BWFM_E_NOMEM, "pipeline: device allocation failed");
+    uint32_t blanes = 0;
+    SplitShape zs{};
+    auto reserve = [&](bool lean) {
+        pl->lanes = plain ? nr_up : batched_lanes(fit, nmax, pl->bs, lean);
+        pl->tlanes = sbud ? by_layout(ix, [&](auto lw) { return task_lanes<decltype(lw)::value>(nr_up, pl->lanes); }) : 0u;
+        blanes = std::max(pl->lanes, pl->tlanes);
+        zs = split_shape(nmax, mlen, pl->lanes, lean);
+        size_t need = 0;
+        auto add = [&](size_t b) { need += (b + 255) & ~size_t(255); };
+        add(q->max_bases); add((size_t)(nmax + 1) * 8); add(nmax);
+        add((size_t)blanes * pl->stack_cap * 16); add((size_t)blanes * FAST_CAND * 16);
+        add((size_t)pl->slow_lanes * pl->worst_stack * 16); add((size_t)pl->slow_lanes * pl->scap * 16);
+        add((size_t)nmax * 4); add((size_t)nmax * 4); add((size_t)nmax * 8); add(hcap * 16);
+        add(scan_part_elems(std::max<uint64_t>(nmax, hcap)) * 8);
+        add((size_t)(nmax + 1) * 8); add(hcap * 16); add((size_t)nmax * 4); add((size_t)nmax * 4); add(nmax);
+        add(hcap * 4); add(hcap * 4); add((hcap + 1) * 8); add(pcap * 4); add((size_t)q->max_pairs * sizeof(bwfm_pair));
+        add(PC_WORDS * 8);
+        add(sizeof(PersistentArgs));
+        if (!plain) {
+            add((size_t)nmax * 2 * pl->dstride);
+            add(nmax);
+        }
+        if (sbud) need += split_bytes(zs) + (size_t)pl->lanes * 4 + 256;
+        need += 4096;
+        return dev_malloc(&pl->mem, need);
+    };
+    if (reserve(false) != hipSuccess && (plain || reserve(true) != hipSuccess))
+        return fail(BWFM_E_NOMEM, "pipeline: device allocation failed");
     Carver cv{(char *)pl->mem};
     pl->bases = cv.take<uint8_t>(q->max_bases);
     pl->offsets = cv.take<uint64_t>(nmax + 1);
