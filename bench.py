@@ -449,11 +449,9 @@ def main_c3(args):
     """The uneven-length workload at full size (3.1 Gbp reference indexed on
     the device, 10M pairs of 36-150 bp with per-read budgets): the batched
     step (both ends in one persistent launch, locate, pair), timed as the
-    default workload is.  Its index lives in HBM, so its roofline compares
-    line fills with the gather probe on an index-sized buffer; the oracle
-    cannot index 3.1 Gbp within a bench run, so there is no CPU baseline and
-    no algorithmic byte count: the fills come from the committed FETCH_SIZE
-    summary of this workload."""
+    default workload is.  The oracle cannot index 3.1 Gbp within a bench run,
+    so there is no CPU baseline and no algorithmic byte count: the bytes come
+    from the committed FETCH_SIZE summary of this workload."""
     import torch
 
     import paper_1505_07855_amd as bw
@@ -508,22 +506,12 @@ def main_c3(args):
     value = aligned / (ms_step / 1e3)
     roofline = None
     traffic = traffic_from_profiles("k_align_persistent", "c3")
-    lb = ix.info()["line_bytes"]
-    buf = torch.zeros(2048 << 20, dtype=torch.uint8, device="cuda")
-    bw.probe_gather(buf, lb, iters=16)
-    probe_lps = bw.probe_gather(buf, lb)
-    del buf
     if k_ms:
-        fills_ps = traffic / 128 / (k_ms / 1e3) if traffic else None
         roofline = {"bound": "hbm", "achieved": traffic / (k_ms / 1e3) / 1e9 if traffic else None,
                     "peak": HBM_PEAK_GBS, "unit": "GB/s",
                     "frac": traffic / (k_ms / 1e3) / 1e9 / HBM_PEAK_GBS if traffic else None, "traffic": traffic,
                     "kernel": "k_align_persistent + k_align_tasks", "avg_launch_ms": k_ms, "reads_per_launch": 2 * n,
-                    "basis": "counter-measured HBM-side bytes per step of the search (no oracle count at 3.1 Gbp)",
-                    "random_line_ceiling": {"probe_lines_per_s": probe_lps, "probe_buffer_mib": 2048,
-                                            "probe_line_bytes": lb,
-                                            "kernel_fills_per_s": fills_ps,
-                                            "frac": fills_ps / probe_lps if fills_ps else None}}
+                    "basis": "counter-measured HBM-side bytes per step of the search (no oracle count at 3.1 Gbp)"}
     out = {
         "metric": METRIC, "value": value, "unit": "aligned reads/s", "n_gpus": 1, "steps": args.steps,
         "warmup": args.warmup, "ms_per_step": ms_step, "higher_is_better": True, "scaling": "weak",
@@ -794,18 +782,6 @@ def main():
         kf, timed_in = kernel_ms.get("align_persistent"), "batched (graph replays)"
         if not kf:
             kf, timed_in = eager["kernel_ms"].get("align_persistent"), "batched-eager (same kernel and batch)"
-        # the achievable rate of dependent random line fetches on a buffer
-        # the size of the index with its tables (the same access pattern with
-        # no search around it), measured here, for a second fraction
-        probe = None
-        try:
-            mib = min(ix.info()["device_bytes"] >> 20, 8192)
-            buf = torch.zeros(mib << 20, dtype=torch.uint8, device="cuda")
-            bw.probe_gather(buf, 128, iters=16)
-            probe = {"probe_lines_per_s": bw.probe_gather(buf, 128), "probe_buffer_mib": mib, "probe_line_bytes": 128}
-            del buf
-        except Exception as e:  # the probe is context; the bench line stands without it
-            log(f"gather probe skipped: {e}")
         if kf:
             traffic = traffic_from_profiles("k_align_persistent")
             rate = traffic / (kf["avg_ms"] / 1e3) / 1e9 if traffic else None
@@ -814,13 +790,6 @@ def main():
                         "kernel": "k_align_persistent", "reads_per_launch": n_reads, "avg_launch_ms": kf["avg_ms"],
                         "timed_in": timed_in, "basis": "counter-measured HBM-side bytes per launch",
                         "line_touches_per_read": float(touches.mean())}
-            if probe:
-                fills_ps = rate * 1e9 / 128 if rate else None
-                roofline["random_line_ceiling"] = dict(
-                    probe, kernel_fills_per_s=fills_ps,
-                    frac=fills_ps / probe["probe_lines_per_s"] if fills_ps else None,
-                    note="128-byte fills and writes/s against a gather of dependent random lines on a buffer the "
-                         "size of the index (paper_1505_07855_amd.probes)")
 
     out = {
         "metric": METRIC, "value": value, "unit": "aligned reads/s", "n_gpus": 1, "steps": args.steps,

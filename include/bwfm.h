@@ -736,9 +736,10 @@ int bwfm_timing_reset(void);
 int bwfm_timing_get(const char *kernel, double *total_ms, uint64_t *launches);
 
 /*
- * Random-line probe: the achievable rate of dependent random line fetches,
- * the access pattern of the search (each rank query is one line at an index
- * the previous query decided).  lanes (a multiple of 256) each perform iters
+ * Random-line probe: the rate of dependent random line fetches over one
+ * buffer (each fetch is one line at an index the previous one decided).  It
+ * measures the memory system alone and is no ceiling of the search, whose
+ * accesses are partly to neighbouring lines.  lanes (a multiple of 256) each perform iters
  * dependent fetches of whole line_bytes (32, 64 or 128) lines at pseudo-random
  * line indices within buf (device, bytes long; contents arbitrary).  sink:
  * device, lanes uint32 (defeats dead-code removal).  *ms_out receives the

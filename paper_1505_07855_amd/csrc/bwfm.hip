@@ -2207,14 +2207,12 @@ __device__ __forceinline__ void persistent_body(const DevIndex &ix, const Params
 
 // Two builds of the batched kernel: the compiler's own register budget
 // and one held to 128 VGPRs so that 4 waves stay resident per SIMD.  What
-// bounds the search is how many random 128-byte fills are in flight, and
-// the waves are what keeps them there: 2M reads of 100 bases on 100 Mbp take
-// 57 ms at 4 waves per SIMD, 65 at 3, 82 at 2 and 139 at 1.  A wave
-// then waits in each iteration for the slowest of 64 lanes' chains of one to
-// three dependent loads.  At 4 waves the device fills 36 G lines/s out of
-// tables, suffix arrays and stacks that together span gigabytes (the probe
-// of independent random lines: 57 G/s at 256 MB, 48 at 4 GB, 38 at 16 GB).
-// The autotuner picks.
+// bounds the search is the latency of its random accesses: a wave waits in
+// each iteration for the slowest of 64 lanes' chains of one to three dependent
+// loads out of tables, suffix arrays and stacks that together span gigabytes,
+// and only other waves' loads fill that time.  2M reads of 100 bases on 100
+// Mbp take 57 ms at 4 waves per SIMD, 65 at 3, 82 at 2 and 139 at 1.  The
+// autotuner picks.
 template <int LW>
 __global__ __launch_bounds__(BLOCK) void k_align_persistent(DevIndex ix, Params P, const PersistentArgs *A) {
     persistent_body<LW>(ix, P, A);
