@@ -627,7 +627,9 @@ int bwfm_pipeline_finish(bwfm_pipeline *pl, void *hip_stream, bwfm_pipeline_stat
  * valid until the next run): end 0 or 1 as an alignment result whose
  * hit_offsets index the shared hit array (see bwfm_locate on windows), the
  * per-hit position offsets (n_hits + 1, over both ends' hits in order) and
- * positions, and the n_pairs pair records. */
+ * positions, and the n_pairs pair records.  After a run over a capacity the
+ * records are those of unplaced pairs, which bwfm_rescue_mates and bwfm_mapq
+ * pass over; offsets may then reach past the hits and positions. */
 int bwfm_pipeline_outputs(bwfm_pipeline *pl, int end, bwfm_aln_result *res, uint64_t **pos_offsets,
                           uint32_t **positions, bwfm_pair **pairs);
 
@@ -726,8 +728,10 @@ int bwfm_max_diff_rule(uint32_t len, double err, double thres);
 /*
  * Kernel timing (off by default).  When on, the library brackets its
  * kernel launches with HIP events on the caller's stream and, when the
- * call completes, adds each launch's elapsed time under the kernel's name
- * ("align_fast", "align_slow", "compact", "locate_rows", "sort", "pair").
+ * call completes, adds each launch's elapsed time under its name
+ * ("align_plain"; "dscan", "align_persistent", "align_tasks", the last two
+ * together as "align_search"; "align_slow", "compact", "locate_rows", "sort",
+ * "pair").
  * Process-wide; for measurement, not for concurrent production use.
  *   timing_get: *total_ms and *launches for one name (0 if never run).
  */

@@ -796,8 +796,8 @@ __device__ __forceinline__ bool text_step(u4 &cur, uint32_t win, uint32_t pc, in
             const bool gap = ngo < P.max_gapo && s_nmm(cur) + ngo + s_nge(cur) + 1 + De <= maxd && lbg <= bound;
             if (!gap || c.sp + 8 <= c.stack_cap) {
                 if (gap) {
-                    c.stack[(size_t)c.sp * c.sstride] =
-                        mk4(p, (uint32_t)t, cur.z | ((uint32_t)GAP_RUN << 10), (cur.w & 0xfffffu) | ((uint32_t)lbg << 20));
+                    c.stack[(size_t)c.sp * c.sstride] = mk4(p, (uint32_t)t, cur.z | ((uint32_t)GAP_RUN << 10),
+                                                            (cur.w & 0xfffffu) | ((uint32_t)lbg << 20));
                     c.sp++;
                 }
                 step_matches(cur, t, c.pd, P);
@@ -895,12 +895,12 @@ __device__ int resolve(u4 &cur, bool &valid, int strand, const Params &P, LaneCt
 
 // Children of an expanded state, from its string's four extensions, built
 // directly in packed form: each differs from the parent by a few field
-// increments.  gaps_only: a run's position, whose match was taken before.  They are taken in reverse of
-// the fixed order (match, mismatches by base, insertion, deletions by base);
-// the first surviving one becomes cur, the others are pushed with their
-// lower bounds.  Returns R_OK or R_STACK.
-__device__ int expand_children(u4 &cur, bool &valid, const Kids &k, bool gaps_only, int b, int m, int maxd, int Di, int Dn, const Seed &S,
-                               const Params &P, LaneCtx &c, uint32_t K) {
+// increments.  gaps_only: a run's position, whose match was taken before.
+// They are taken in reverse of the fixed order (match, mismatches by base,
+// insertion, deletions by base); the first surviving one becomes cur, the
+// others are pushed with their lower bounds.  Returns R_OK or R_STACK.
+__device__ int expand_children(u4 &cur, bool &valid, const Kids &k, bool gaps_only, int b, int m, int maxd, int Di,
+                               int Dn, const Seed &S, const Params &P, LaneCtx &c, uint32_t K) {
     const int i = s_i(cur), gs = s_gs(cur), ngo = s_ngo(cur), nge = s_nge(cur), sd = s_sd(cur);
     const int score = s_score(cur), len = s_len(cur);
     const bool coded = (uint32_t)len < K;  // the children not taken are then one entry
@@ -945,14 +945,17 @@ __device__ int expand_children(u4 &cur, bool &valid, const Kids &k, bool gaps_on
         const int in = (bd > S.lo && bd < S.hi) ? 1 : 0;
         const int nsc = score + (ext ? P.s_gape : P.s_gapo);
         const int lb = nsc + P.minc * Di;
-        if (bd >= P.s1 && bd <= m - P.s1 && nd <= maxd && ngo2 <= P.max_gapo && (P.max_gape < 0 || nge2 <= P.max_gape) &&
-            (S.sl == 0 || sd + in <= P.seed_diff) && nd + Di <= maxd && lb <= bound) {
+        if (bd >= P.s1 && bd <= m - P.s1 && nd <= maxd && ngo2 <= P.max_gapo &&
+            (P.max_gape < 0 || nge2 <= P.max_gape) && (S.sl == 0 || sd + in <= P.seed_diff) && nd + Di <= maxd &&
+            lb <= bound) {
             if (coded) {
                 fam |= k.mask << 8;
                 if (k.mask) fam_lb = lb;
-            } else
-            push_set(k.mask, (z0 | ((uint32_t)GAP_DEL << 10)) + (ext ? (1u << 20) : (1u << 16)) + ((uint32_t)in << 24),
-                     (uint32_t)nsc | len1 | ((uint32_t)lb << 20));
+            } else {
+                push_set(k.mask,
+                         (z0 | ((uint32_t)GAP_DEL << 10)) + (ext ? (1u << 20) : (1u << 16)) + ((uint32_t)in << 24),
+                         (uint32_t)nsc | len1 | ((uint32_t)lb << 20));
+            }
         }
     }
     const int in_i = (i >= S.lo && i < S.hi) ? 1 : 0;
@@ -967,11 +970,12 @@ __device__ int expand_children(u4 &cur, bool &valid, const Kids &k, bool gaps_on
             if (coded) {
                 fam |= FAM_INS;
                 fam_lb = min(fam_lb, lb);
-            } else
+            } else {
                 push(mk4(cur.x, cur.y,
                          (z0 | ((uint32_t)GAP_INS << 10)) - 1u + (ext ? (1u << 20) : (1u << 16)) +
                              ((uint32_t)in_i << 24),
                          (uint32_t)nsc | ((uint32_t)len << 10) | ((uint32_t)lb << 20)));
+            }
         }
     }
     // mismatches, then the match, which becomes current
@@ -984,9 +988,10 @@ __device__ int expand_children(u4 &cur, bool &valid, const Kids &k, bool gaps_on
             if (coded) {
                 fam |= set;
                 if (set) fam_lb = min(fam_lb, lb);
-            } else
+            } else {
                 push_set(set, z0 - 1u + (1u << 12) + ((uint32_t)in_i << 24),
                          (uint32_t)nsc | len1 | ((uint32_t)lb << 20));
+            }
         }
         if (fam) push(mk4(cur.x, fam, cur.z | FAMILY, (cur.w & 0xfffffu) | ((uint32_t)fam_lb << 20)));
         const int lbm = score + P.minc * Dn;
@@ -1011,8 +1016,9 @@ __device__ int expand_children(u4 &cur, bool &valid, const Kids &k, bool gaps_on
 // all kinds are issued before any is used, so lanes that take different ways
 // share one round trip.  Returns R_OK or R_STACK.
 template <int LW>
-__device__ __forceinline__ int search_step(const DevIndex &ix, const DevDir &qd, int qdir, bool go, u4 &cur, bool &valid,
-                                           int m, int maxd, bool has_n, const Seed &S, const Params &P, LaneCtx &c) {
+__device__ __forceinline__ int search_step(const DevIndex &ix, const DevDir &qd, int qdir, bool go, u4 &cur,
+                                           bool &valid, int m, int maxd, bool has_n, const Seed &S, const Params &P,
+                                           LaneCtx &c) {
     const int K = (int)ix.kt_levels;
     const int bound = (P.mode == BWFM_MODE_BEST && c.best != INF_SCORE) ? c.best + P.s_mm : INF_SCORE;
     const bool unroll = go && s_gs(cur) == GAP_RUN;
@@ -1709,7 +1715,8 @@ __global__ void k_split_publish(Params P, SplitBufs X, ReadOut O) {
     for (uint32_t j = 0; j < nh; j++) {
         const u4 h = c.cand[j];
         uint32_t q = 0;
-        while (q < w && !(h_strand(c.cand[q]) == h_strand(h) && c.cand[q].x == h.x && h_len(c.cand[q]) == h_len(h))) q++;
+        while (q < w && !(h_strand(c.cand[q]) == h_strand(h) && c.cand[q].x == h.x && h_len(c.cand[q]) == h_len(h)))
+            q++;
         if (q == w)
             c.cand[w++] = h;
         else if (better(h, c.cand[q]))
@@ -2049,8 +2056,8 @@ __device__ __forceinline__ void persistent_body(const DevIndex &ix, const Params
                     const int gi = __popcll(G & lt);
                     if (gi < n) {
                         ws.box[gi] = c.stack[(size_t)c.sbase * c.sstride];
-                        ws.meta[gi] = (uint32_t)ow | ((uint32_t)strand << 6) | ((uint32_t)maxd << 7) | ((uint32_t)m << 11) |
-                                      ((uint32_t)has_n << 21);
+                        ws.meta[gi] = (uint32_t)ow | ((uint32_t)strand << 6) | ((uint32_t)maxd << 7) |
+                                      ((uint32_t)m << 11) | ((uint32_t)has_n << 21);
                         c.sbase++;
                         atomicAdd(&ws.pending[ow], 1);
                         atomicOr(&ws.flags[ow], SH_HELPED);
@@ -3258,7 +3265,8 @@ struct SplitShape {
 inline SplitShape split_shape(uint32_t n, uint32_t mlen, uint32_t lanes, bool lean) {
     SplitShape z;
     const uint64_t least = lean ? 4096 : 1024ull * std::min(std::max(n, 1u), 8192u);
-    z.slot_cap = std::min(std::max(n, 1u), mlen >= LONG_READ && !lean ? lanes : std::min(std::max(64u, n / 8), 1u << 26));
+    const uint32_t slots = mlen >= LONG_READ && !lean ? lanes : std::min(std::max(64u, n / 8), 1u << 26);
+    z.slot_cap = std::min(std::max(n, 1u), slots);
     z.task_cap = (uint32_t)std::min<uint64_t>(std::max<uint64_t>(16ull * n, least), 1ull << 26);
     z.dstride = ((mlen + 15) / 16) * 16;
     return z;
@@ -3318,8 +3326,8 @@ uint32_t task_lanes(uint32_t n_up, uint32_t lanes) {
 // After the first pass (split searches on): the collection of the split
 // reads' first-pass hits, the task rounds on their own grid of tlanes
 // lanes, on the first pass's lane buffers (allocated for both grids), the
-// last round without a drain, then the publication of the split reads.  Every launch reads its counts on the device, so the
-// sequence can be captured.
+// last round without a drain, then the publication of the split reads.  Every
+// launch reads its counts on the device, so the sequence can be captured.
 template <int LW>
 void enqueue_split(const DevIndex &D, const Params &P, const SplitBufs &X, TaskArgs *targs, const LaneBufs &lb,
                    const ReadOut &O, uint32_t tlanes, hipStream_t st) {
@@ -3417,8 +3425,9 @@ int align_impl(bwfm_index *ix, bwfm::Workspace &ws, const bwfm_reads *rd, const 
             k_dscan<LW><<<nr_up / bs, bs, (size_t)bs * lstride, st>>>(D, rv, P, drows, dflag, dstride, lstride,
                                                                       sbud ? X.ctl + SPLIT_LONG : nullptr);
             tm.end(td);
-            k_set_args<<<1, 64, 0, st>>>(pargs, PersistentArgs{rv, lb, O, next_read, drows, dflag, dstride, X, lane_read},
-                                         drain_at_once(bs, lds));
+            k_set_args<<<1, 64, 0, st>>>(
+                pargs, PersistentArgs{rv, lb, O, next_read, drows, dflag, dstride, X, lane_read},
+                drain_at_once(bs, lds));
             int ts = tm.begin("align_search");
             int t = tm.begin("align_persistent");
             hipLaunchKernelGGL(persistent_kernel<LW>(p->waves_per_simd), dim3(lanes / bs), dim3(bs), lds, st, D, P,
@@ -3447,7 +3456,8 @@ int align_impl(bwfm_index *ix, bwfm::Workspace &ws, const bwfm_reads *rd, const 
     HIPCHK(hipMemcpyAsync(&total, res->hit_offsets + n, 8, hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
     if (total > res->hit_capacity)
-        return fail(BWFM_E_CAPACITY, "hit capacity " + std::to_string(res->hit_capacity) + " < " + std::to_string(total));
+        return fail(BWFM_E_CAPACITY,
+                    "hit capacity " + std::to_string(res->hit_capacity) + " < " + std::to_string(total));
     if (n && total) {
         int t = tm.begin("compact");
         k_compact<<<blocks(n, 256), 256, 0, st>>>(n, res->hit_offsets, stage, stage_off,
@@ -3525,8 +3535,7 @@ int locate_rows(const bwfm_index *ix, uint64_t n_hits, const u4 *hits, const uin
     tm.end(t);
     if (rc) return rc;
     t = tm.begin("sort");
-    k_sort_small<<<blocks(n_hits, 256), 256, 0, st>>>(n_hits, pos_off, pos, big, n_big, nullptr,
-                                                    nullptr);
+    k_sort_small<<<blocks(n_hits, 256), 256, 0, st>>>(n_hits, pos_off, pos, big, n_big, nullptr, nullptr);
     k_sort_big<<<1024, 256, 0, st>>>(pos_off, pos, big, n_big);
     tm.end(t);
     HIPCHK(hipGetLastError());
@@ -3739,7 +3748,8 @@ static int check_aln_params(const bwfm_aln_params *p) {
 }
 
 // Argument checks shared by the align entry points; 0 or a bwfm_err.
-static int check_align_args(bwfm_index *ix, const bwfm_reads *rd, const bwfm_aln_params *p, const bwfm_aln_result *res) {
+static int check_align_args(bwfm_index *ix, const bwfm_reads *rd, const bwfm_aln_params *p,
+                            const bwfm_aln_result *res) {
     if (!ix || !rd || !p || !check_result(res, rd->n_reads)) return fail(BWFM_E_INVAL, "align_batch: NULL argument");
     if (!check_index(ix)) return fail(BWFM_E_STATE, "align_batch: index not uploaded");
     if (rd->n_reads && (!rd->bases || !rd->offsets)) return fail(BWFM_E_INVAL, "align_batch: NULL reads");
@@ -3777,7 +3787,8 @@ extern "C" int bwfm_align_batch_counted(const bwfm_index *cix, const bwfm_reads 
 extern "C" int bwfm_locate(const bwfm_index *cix, uint32_t n_reads, const bwfm_aln_result *res, uint32_t max_occ,
                            uint64_t *pos_off, uint32_t *pos, uint64_t cap, void *stream) {
     bwfm_index *ix = const_cast<bwfm_index *>(cix);
-    if (!ix || !check_result(res, n_reads) || !pos_off || (!pos && cap)) return fail(BWFM_E_INVAL, "locate: NULL argument");
+    if (!ix || !check_result(res, n_reads) || !pos_off || (!pos && cap))
+        return fail(BWFM_E_INVAL, "locate: NULL argument");
     if (!check_index(ix)) return fail(BWFM_E_STATE, "locate: index not uploaded");
     std::shared_lock<std::shared_mutex> g(ix->mu);
     hipStream_t st = (hipStream_t)stream;
@@ -4163,9 +4174,11 @@ int pipe_enqueue(bwfm_pipeline *pl, hipStream_t st, bool timed, bool capture) {
     uint32_t *err = reinterpret_cast<uint32_t *>(ctl + PC_ERR);
     ReadsView rv = pl->bound ? ReadsView{pl->in.bases, pl->in.offsets, pl->in.lengths, pl->in.max_diff, nmax,
                                          pl->in.max_len, ctl + PC_READS}
-                             : ReadsView{pl->bases, pl->offsets, nullptr, pl->maxd, nmax, pl->q.max_len, ctl + PC_READS};
+                             : ReadsView{pl->bases,      pl->offsets,    nullptr, pl->maxd, nmax,
+                                         pl->q.max_len, ctl + PC_READS};
     const bool plain = pl->ap.form == BWFM_FORM_PLAIN;
-    LaneBufs lb = plain ? LaneBufs{pl->lstack, pl->lcand, 1, pl->lanes, pl->stack_cap, 1, pl->lanes, FAST_CAND, pl->lstride}
+    LaneBufs lb = plain ? LaneBufs{pl->lstack, pl->lcand, 1, pl->lanes, pl->stack_cap, 1, pl->lanes, FAST_CAND,
+                                   pl->lstride}
                         : LaneBufs{pl->lstack, pl->lcand, pl->stack_cap, 1, pl->stack_cap, FAST_CAND, 1, FAST_CAND,
                                    pl->lstride};
     ReadOut O{pl->n_rep, pl->c1, pl->c2, pl->status, pl->slow_list, actl, pl->stage,
@@ -4283,7 +4296,8 @@ extern "C" int bwfm_pipeline_create(const bwfm_index *cix, const bwfm_aln_params
     SplitShape zs{};
     auto reserve = [&](bool lean) {
         pl->lanes = plain ? nr_up : batched_lanes(fit, nmax, pl->bs, lean);
-        pl->tlanes = sbud ? by_layout(ix, [&](auto lw) { return task_lanes<decltype(lw)::value>(nr_up, pl->lanes); }) : 0u;
+        pl->tlanes = 0;
+        if (sbud) pl->tlanes = by_layout(ix, [&](auto lw) { return task_lanes<decltype(lw)::value>(nr_up, pl->lanes); });
         blanes = std::max(pl->lanes, pl->tlanes);
         zs = split_shape(nmax, mlen, pl->lanes, lean);
         size_t need = 0;

@@ -128,7 +128,7 @@ __global__ void k_sa_init(const uint8_t *t, uint64_t n, uint64_t N, uint64_t *ke
 // groups.  Streaming: 12 bytes a row.  Each block adds its count once and the
 // grid is bounded (HEADS_BLOCKS): with an atomic per wave and 64 rows, 1.56 M
 // atomics on the one address set the time (100 Mbp: 18.8 ms a call; a 16 Mbp
-// reference indexed and a first batch aligned: 62.9 ms before, 38.0 ms now).
+// reference indexed and a first batch aligned: 62.9 ms with them, 38.0 without).
 constexpr uint32_t HEADS_BLOCKS = 2048;
 __global__ __launch_bounds__(256) void k_sa_heads(const uint64_t *key, uint64_t N, uint32_t *g,
                                                   unsigned long long *n_groups) {
@@ -355,7 +355,8 @@ extern "C" int bwfm_build_index_device(const uint8_t *ref, uint64_t n, const bwf
     if (hipMemcpyAsync(t, ref, n, hipMemcpyHostToDevice, st) != hipSuccess)
         rc = fail(BWFM_E_DEVICE, "index build: text upload");
     const uint64_t pac_words = (n + 15) / 16;
-    if (!rc && dev_malloc(&ix->d_pac, (pac_words + 2) * 4) != hipSuccess) rc = fail(BWFM_E_NOMEM, "index build: packed text");
+    if (!rc && dev_malloc(&ix->d_pac, (pac_words + 2) * 4) != hipSuccess)
+        rc = fail(BWFM_E_NOMEM, "index build: packed text");
     if (!rc) {
         k_pack_ref<<<grid_for(pac_words, 256), 256, 0, st>>>(t, n, (uint32_t *)ix->d_pac);
         try {
@@ -388,7 +389,6 @@ extern "C" int bwfm_build_index_device(const uint8_t *ref, uint64_t n, const bwf
     if (rc) {
         free_search_tables(ix.get());
         for (int d = 0; d < 2; d++) {
-
             dev_free(ix->d_lines[d]);
             dev_free(ix->d_sa[d]);
             ix->d_lines[d] = ix->d_sa[d] = nullptr;

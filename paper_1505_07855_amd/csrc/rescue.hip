@@ -93,7 +93,9 @@ template <int G, int R>
 __device__ __forceinline__ void rescue_groups(const uint32_t *pac, uint64_t n, const Mate &c, bool on, int lo, int hi,
                               const Scores &S, uint8_t *win, bwfm_rescue *out) {
     int lane = threadIdx.x & (G - 1);
-    asm volatile("" : "+v"(lane));  // (keeps the builds' code from being merged, which held the registers of all: 167 instead of 87)
+    // (keeps the builds' code from being merged, which held the registers of
+    // all: 167 instead of 87)
+    asm volatile("" : "+v"(lane));
     const int m = on ? c.m : 0;
     int64_t w0, w1;
     if (c.sa == 0) {
@@ -361,14 +363,10 @@ extern "C" int bwfm_rescue_mates(const bwfm_index *ix, const bwfm_reads *end1, c
     const size_t lds = (size_t)WAVES * most * win_stride;
     const uint32_t *pac = (const uint32_t *)ix->d_pac;
     const int ml = (int)max_len;
-    if (max_len <= 64)
-        k_rescue<64><<<grid, RB, lds, st>>>(pac, ix->n, e1, e2, pairs, n_pairs, pp->lo, hi, ml, S, take, most, win_stride, out);
-    else if (max_len <= 128)
-        k_rescue<128><<<grid, RB, lds, st>>>(pac, ix->n, e1, e2, pairs, n_pairs, pp->lo, hi, ml, S, take, most, win_stride, out);
-    else if (max_len <= 256)
-        k_rescue<256><<<grid, RB, lds, st>>>(pac, ix->n, e1, e2, pairs, n_pairs, pp->lo, hi, ml, S, take, most, win_stride, out);
-    else
-        k_rescue<512><<<grid, RB, lds, st>>>(pac, ix->n, e1, e2, pairs, n_pairs, pp->lo, hi, ml, S, take, most, win_stride, out);
+    const auto kernel = max_len <= 64 ? k_rescue<64> : max_len <= 128 ? k_rescue<128> : max_len <= 256 ? k_rescue<256>
+                                                                                                       : k_rescue<512>;
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(RB), lds, st, pac, ix->n, e1, e2, pairs, n_pairs, pp->lo, hi, ml, S,
+                       take, most, win_stride, out);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(BWFM_E_DEVICE, std::string("rescue_mates: launch: ") + hipGetErrorString(e));
     return BWFM_OK;

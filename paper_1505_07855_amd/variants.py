@@ -5,9 +5,10 @@ The paper improves BarraCUDA by changing its kernel source and keeping a
 change only when the output stays the same and the kernel gets faster
 (sections 1, 3 and 5).  Here the kernel source (csrc/bwfm.hip) carries
 alternative implementations of single code sites ("genes", macros
-BWFM_GENE_*: row masks, the sub-counted line's header loads, the loads of a sub-counted query) next to the tuning constants it
-exposes (stack pops per iteration, lanes that wait for a read change,
-first-pass hit slots, second-pass lanes).  A variant is one value per gene; each variant is its own library
+BWFM_GENE_*: row masks, the sub-counted line's header loads, the loads of a
+sub-counted query) next to the tuning constants it exposes (stack pops per
+iteration, lanes that wait for a read change, first-pass hit slots,
+second-pass lanes).  A variant is one value per gene; each variant is its own library
 build.  The search is a (1+1) evolution strategy in generations:
 
 * generation 1 mutates the reference in every single gene (each
@@ -97,7 +98,8 @@ def build_one(defs: dict) -> str:
     obj = os.path.join(d, "bwfm.o")
     flags = [f"-D{k}={v}" for k, v in sorted(defs.items())]
     B._run([B.HIPCC, *B.HIP_FLAGS, *flags, "-c", os.path.join(B.CSRC, "bwfm.hip"), "-o", obj])
-    others = [os.path.join(B.OUT, f) for f in ("index_host.o", "index_gpu.o", "rescue.o", "mapq.o", "server.o", "devpool.o")]
+    others = [os.path.join(B.OUT, f + ".o")
+              for f in ("index_host", "index_gpu", "rescue", "mapq", "server", "devpool")]
     missing = [f for f in others if not os.path.exists(f)]
     if missing:
         raise RuntimeError(f"build the library first (missing {missing})")
